@@ -1,4 +1,4 @@
-// bf16 MFMA contraction with direct global->LDS loads and a FOUR-stage ring of 32-deep K blocks.
+// MFMA contraction with direct global->LDS loads and a FOUR-stage ring of K blocks of 64 bytes (32 bf16 or 16 fp32).
 //
 // Same contract and data path as gemm_dma_kernel (gemm_dma.h), different pipeline depth.  What the main
 // loop of the two-stage kernel waits for is operand data: with one 64 KB stage in flight per compute unit
@@ -15,16 +15,43 @@
 //   fragment read is served 16 lanes (16 consecutive rows, one logical chunk) per clock, which must cover
 //   all 16 chunk positions of a 256-byte bank line: physical chunk = logical ^ ((row >> 2) & 3).
 //   KROW tile [32 k][rows]: as in gemm_dma.h (physical chunk = logical ^ (4 * (k & 3))).
+//
+// fp32 operands (K blocks of 16 in two steps of 8; ROWK fragments are one 16-byte read as above, KROW fragments four
+// 4-byte reads of 32 consecutive rows, the half-waves reading k and k + 4, whose rows start at the same bank: physical
+// chunk = logical ^ (8 * (k / 4 % 2)) moves one of them to the other 32 banks).  The fp32 matrix rate is a sixteenth of
+// the bf16 one, so the contraction is bound by the matrix cores alone if nothing delays them:
+//   - no staging registers: a register-staged 256 x 256 tile spilled 120-205 registers and ran at 69-73 TFLOP/s (64,000 x
+//     1280 outputs, depth 1024; the same product here: 136; a bare fp32 MFMA loop: 155);
+//   - few barriers per MFMA: 256 x 256 tiles on eight waves 140 TFLOP/s, 128 x 128 on four 136, 64 x 64 126 (the last for
+//     outputs with few tiles; five and two such workgroups share a compute unit).
 #pragma once
 #include "gemm_dma.h"
 
 namespace rnnlm_dev {
 
 __device__ inline int rowk32_swz(int row) { return (row >> 2) & 3; }
+__device__ inline int krow_swz_f32(int k) { return ((k >> 2) & 1) << 3; }
+
+// Fragments of one step and the update of a 32x32 block with them: 16 values of k for bf16 (mma16), 8 for fp32 (lane l
+// holds the 4 k values 4 * (l / 32) .. +3; the e-th 32x32x2 instruction contracts k = e and k = 4 + e).
+template <typename T>
+struct FragStep {
+  typedef bf16x8_t type;
+};
+template <>
+struct FragStep<float> {
+  typedef f32x4_t type;
+};
+__device__ inline void mma_step(f32x16_t &acc, const bf16x8_t &a, const bf16x8_t &b) { mma16(acc, a, b); }
+__device__ inline void mma_step(f32x16_t &acc, const f32x4_t &a, const f32x4_t &b) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
+}
 
 #if defined(__HIP_DEVICE_COMPILE__)
-template <int ROWS, int LAYOUT, int NT>
+template <typename T, int ROWS, int LAYOUT, int NT>
 struct DmaLoader32 {
+  static constexpr int ES = sizeof(T), BK = 64 / ES;
   static constexpr int BLOCKS = ROWS * 64 / 1024;  // kilobyte blocks per tile
   static constexpr int NW = NT / 64;
   static constexpr int PER = BLOCKS / NW;
@@ -33,6 +60,8 @@ struct DmaLoader32 {
   int off[PER];  // this lane's byte offset inside a k block for each of its kilobyte blocks
   i32x4_t rsrc;  // buffer resource: base, stride 0, extent in bytes, raw 32-bit addressing
   int kstep;     // bytes to advance per k block
+  unsigned long long base;  // fp32 K-major: the operand may exceed a resource's 32-bit offsets, which is then re-based
+  long left;                // at every k block (scalar arithmetic)
 
   __device__ inline void init(const char *op, long op_bytes, long ld_bytes, long row0, long k0, int tid) {
     const int wave = tid >> 6, lane = tid & 63;
@@ -43,16 +72,16 @@ struct DmaLoader32 {
         const int r = q >> 2, p = q & 3;
         off[i] = (int)(r * ld_bytes + ((p ^ rowk32_swz(r)) << 4));
       } else {
-        constexpr int CPR = ROWS / 8;
+        constexpr int CPR = ROWS * ES / 16;
         const int k = q / CPR, p = q % CPR;
-        off[i] = (int)(k * ld_bytes + ((p ^ krow_swz(k)) << 4));
+        off[i] = (int)(k * ld_bytes + ((p ^ (ES == 2 ? krow_swz(k) : krow_swz_f32(k))) << 4));
       }
     }
-    const long start = (LAYOUT == ROWK) ? row0 * ld_bytes + k0 * 2 : k0 * ld_bytes + row0 * 2;
-    kstep = (LAYOUT == ROWK) ? 64 : (int)(32 * ld_bytes);
-    const long left = op_bytes - start;
+    const long start = (LAYOUT == ROWK) ? row0 * ld_bytes + k0 * ES : k0 * ld_bytes + row0 * ES;
+    kstep = (LAYOUT == ROWK) ? 64 : (int)(BK * ld_bytes);
+    left = op_bytes - start;
     const unsigned records = left > 0xffffffffL ? 0xffffffffu : (unsigned)left;
-    const unsigned long long base = reinterpret_cast<unsigned long long>(op + start);
+    base = reinterpret_cast<unsigned long long>(op + start);
     // every word is uniform over the workgroup: keep the descriptor in scalar registers
     rsrc[0] = __builtin_amdgcn_readfirstlane((int)(unsigned)base);
     rsrc[1] = __builtin_amdgcn_readfirstlane((int)(unsigned)((base >> 32) & 0xffffu));
@@ -66,14 +95,22 @@ struct DmaLoader32 {
   // the LDS address of the kilobyte a wave instruction fills (64 lanes x 16 bytes, contiguous).
   __device__ inline void issue(char *tile, int kb, int tid) const {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int soff = kb * kstep;
+    int soff = kb * kstep;
+    i32x4_t rs = rsrc;
+    if constexpr (ES == 4 && LAYOUT == KROW) {
+      const long adv = (long)kb * kstep, rest = left - adv;
+      rs[0] = __builtin_amdgcn_readfirstlane((int)(unsigned)(base + adv));
+      rs[1] = __builtin_amdgcn_readfirstlane((int)(unsigned)(((base + adv) >> 32) & 0xffffu));
+      rs[2] = __builtin_amdgcn_readfirstlane((int)(rest > 0xffffffffL ? 0xffffffffu : (unsigned)rest));
+      soff = 0;
+    }
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const unsigned lds_addr =
           (unsigned)(unsigned long long)(lds_void_ptr)(tile + (wave + i * NW) * 1024);
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                    :
-                   : "s"(lds_addr), "v"(off[i]), "s"(rsrc), "s"(soff)
+                   : "s"(lds_addr), "v"(off[i]), "s"(rs), "s"(soff)
                    : "memory", "m0");
     }
   }
@@ -84,22 +121,42 @@ struct DmaLoader32 {
 //   ROWK: row r = r0 + 32 i: r*64 + (((2 st + h) ^ swz(r)) << 4), h = lane / 32; swz uses row bits 2..3, which
 //         do not depend on i: pre[st] = r0*64 + (((2 st + h) ^ swz) << 4), immediate = i * 2048.
 //   KROW: as DmaFragAddr<ROWS, KROW>, with two steps per tile.
-template <int ROWS, int LAYOUT>
+//   fp32: ROWK the same bytes seen as four values; KROW element (k, r) with k = 8 st + 4 h + e, so swz(k) = 8 h:
+//         pre[i] per 32-row block, immediate = (8 st + e) * ROWS * 4.
+template <typename T, int ROWS, int LAYOUT>
 struct DmaFragAddr32;
-template <int ROWS>
-struct DmaFragAddr32<ROWS, ROWK> {
+template <typename T, int ROWS>
+struct DmaFragAddr32<T, ROWS, ROWK> {
   int pre[2];
   __device__ inline void init(int r0, int lane) {
     const int h = lane >> 5, sw = rowk32_swz(r0);
 #pragma unroll
     for (int st = 0; st < 2; ++st) pre[st] = r0 * 64 + (((2 * st + h) ^ sw) << 4);
   }
-  __device__ inline bf16x8_t get(const char *tile, int i, int st) const {
-    return *reinterpret_cast<const bf16x8_t *>(tile + pre[st] + i * 2048);
+  __device__ inline typename FragStep<T>::type get(const char *tile, int i, int st) const {
+    return *reinterpret_cast<const typename FragStep<T>::type *>(tile + pre[st] + i * 2048);
   }
 };
 template <int ROWS>
-struct DmaFragAddr32<ROWS, KROW> : DmaFragAddr<ROWS, KROW> {};
+struct DmaFragAddr32<bf16_t, ROWS, KROW> : DmaFragAddr<ROWS, KROW> {};
+template <int ROWS>
+struct DmaFragAddr32<float, ROWS, KROW> {
+  int pre[4];
+  __device__ inline void init(int r0, int lane) {
+    const int h = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = r0 + 32 * i;
+      pre[i] = 4 * h * (ROWS * 4) + ((((r >> 2) ^ (h << 3)) << 4) | ((r & 3) << 2));
+    }
+  }
+  __device__ inline f32x4_t get(const char *tile, int i, int st) const {
+    f32x4_t f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f[e] = *reinterpret_cast<const float *>(tile + pre[i] + (8 * st + e) * (ROWS * 4));
+    return f;
+  }
+};
 
 template <int BM, int BN, class Epi>
 constexpr int dma4_stage_bytes() {
@@ -113,11 +170,12 @@ constexpr int dma4_stage_bytes() {
 // work items id, id + grid, ... (the grid is a multiple of 8, so a workgroup stays on the XCD whose chunk of
 // tiles it walks); the first three K blocks of the next tile are requested before the current tile's epilogue
 // starts, so the next main loop finds them in LDS instead of waiting a memory round trip per tile.
-template <int BM, int BN, int WGM, int WGN, int LA, int LB, class Epi, bool PERSIST = false>
+template <typename T, int BM, int BN, int WGM, int WGN, int LA, int LB, class Epi, bool PERSIST = false>
 __global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShape g, const Epi epi) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int NT = WGM * WGN * 64;
-  constexpr int BK = 32;
+  constexpr int ES = sizeof(T);
+  constexpr int BK = 64 / ES;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int TM = WTM / 32, TN = WTN / 32;
   constexpr int SBYTES = dma4_stage_bytes<BM, BN, Epi>();
@@ -131,13 +189,13 @@ __global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShap
   const int wm = wave % WGM, wn = wave / WGM;
   const int nwork = g.perXcd * NUM_XCD;
   const int stride = PERSIST ? (int)gridDim.x : nwork;
-  DmaLoader32<BM, LA, NT> la;
-  DmaLoader32<BN, LB, NT> lb;
+  DmaLoader32<T, BM, LA, NT> la;
+  DmaLoader32<T, BN, LB, NT> lb;
   bool prefetched = false;  // the loaders are set up for this tile and its first three blocks are in flight
   for (int wid = blockIdx.x; wid < nwork; wid += stride) {
   int tile_m, tile_n, split;
   if (!map_workgroup(g, wid, split, tile_m, tile_n)) continue;  // uniform for the workgroup (never after a prefetch)
-  // g.kBlocks counts 64-deep blocks; this kernel walks 32-deep ones
+  // g.kBlocks counts blocks of 128 bytes; this kernel walks blocks of 64
   const int kb0 = 2 * split * g.kBlocksPerSplit;
   const int kb1 = 2 * min((split + 1) * g.kBlocksPerSplit, g.kBlocks);
   const int nk = kb1 - kb0;
@@ -146,8 +204,8 @@ __global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShap
   epi.template init<TM, TN>(acc, tile_m * BM + wm * WTM, tile_n * BN + wn * WTN, lane, split);
 
   if (!prefetched) {
-    la.init(static_cast<const char *>(g.A), g.bytesA, g.lda * 2, (long)tile_m * BM, (long)kb0 * BK, tid);
-    lb.init(static_cast<const char *>(g.B), g.bytesB, g.ldb * 2, (long)tile_n * BN, (long)kb0 * BK, tid);
+    la.init(static_cast<const char *>(g.A), g.bytesA, g.lda * ES, (long)tile_m * BM, (long)kb0 * BK, tid);
+    lb.init(static_cast<const char *>(g.B), g.bytesB, g.ldb * ES, (long)tile_n * BN, (long)kb0 * BK, tid);
   }
   const int lr = lane & 31;
 
@@ -159,7 +217,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShap
     lb.issue(stage + BM * 64, kb, tid);
   };
   auto fetch = [&](char *stage, int kb) { fetch_of(stage, kb, nk); };
-  constexpr int LOADS_PER_BLOCK = DmaLoader32<BM, LA, NT>::PER + DmaLoader32<BN, LB, NT>::PER;
+  constexpr int LOADS_PER_BLOCK = DmaLoader32<T, BM, LA, NT>::PER + DmaLoader32<T, BN, LB, NT>::PER;
   static_assert(2 * LOADS_PER_BLOCK <= 15, "outstanding-load count must fit the low bits of vmcnt");
   // "this wave's loads of all but the two youngest blocks have landed, and its LDS reads have returned":
   // vmcnt = 2 * LOADS_PER_BLOCK, lgkmcnt = 0, expcnt left at its maximum (gfx9 encoding:
@@ -167,9 +225,9 @@ __global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShap
   constexpr int WAIT_TWO_BLOCKS = (2 * LOADS_PER_BLOCK) | (7 << 4);
 
   static_assert(TM <= 4 && TN <= 4, "fragment addressing covers up to four 32-row blocks per wave");
-  bf16x8_t fa[2][TM], fb[2][TN];
-  DmaFragAddr32<BM, LA> addr_a;
-  DmaFragAddr32<BN, LB> addr_b;
+  typename FragStep<T>::type fa[2][TM], fb[2][TN];
+  DmaFragAddr32<T, BM, LA> addr_a;
+  DmaFragAddr32<T, BN, LB> addr_b;
   addr_a.init(wm * WTM + lr, lane);
   addr_b.init(wn * WTN + lr, lane);
   auto read_frags = [&](const char *stage, int step, int buf) {
@@ -185,7 +243,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShap
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) mma16(acc[i][j], fa[buf][i], fb[buf][j]);
+      for (int j = 0; j < TN; ++j) mma_step(acc[i][j], fa[buf][i], fb[buf][j]);
     __builtin_amdgcn_s_setprio(0);
   };
   // One K block: `cur` holds the block being multiplied (its step-0 fragments are already in buffer 0),
@@ -236,8 +294,8 @@ __global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShap
       const int nkb0 = 2 * ns * g.kBlocksPerSplit;
       const int nnk = 2 * min((ns + 1) * g.kBlocksPerSplit, g.kBlocks) - nkb0;
       if (nnk > 0) {
-        la.init(static_cast<const char *>(g.A), g.bytesA, g.lda * 2, (long)nm * BM, (long)nkb0 * BK, tid);
-        lb.init(static_cast<const char *>(g.B), g.bytesB, g.ldb * 2, (long)nn * BN, (long)nkb0 * BK, tid);
+        la.init(static_cast<const char *>(g.A), g.bytesA, g.lda * ES, (long)nm * BM, (long)nkb0 * BK, tid);
+        lb.init(static_cast<const char *>(g.B), g.bytesB, g.ldb * ES, (long)nn * BN, (long)nkb0 * BK, tid);
         fetch_of(stage0, 0, nnk);
         fetch_of(stage1, 1, nnk);
         fetch_of(stage2, 2, nnk);
@@ -264,10 +322,10 @@ __global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShap
 #endif  // __HIP_DEVICE_COMPILE__
 }
 
-template <int BM, int BN, int WGM, int WGN, int LA, int LB, bool PERSIST = false, class Epi>
+template <typename T, int BM, int BN, int WGM, int WGN, int LA, int LB, bool PERSIST = false, class Epi>
 inline hipError_t launch_gemm_dma4(hipStream_t stream, const void *A, long lda, const void *B, long ldb, long Mg,
                                    long Ng, long K, int splits, const Epi &epi, int band = 4) {
-  constexpr int BK = 64;  // splits are made of 64-deep blocks, as in launch_gemm_dma
+  constexpr int ES = sizeof(T), BK = 128 / ES;  // splits are made of blocks of 128 bytes, as in launch_gemm_dma
   if (Mg <= 0 || Ng <= 0 || K < 0 || Mg % BM || Ng % BN || K % BK || splits < 1) return hipErrorInvalidValue;
   static_assert(4 * dma4_stage_bytes<BM, BN, Epi>() <= 160 * 1024, "tile does not fit the 160 KB of LDS");
   GemmShape g;
@@ -275,11 +333,12 @@ inline hipError_t launch_gemm_dma4(hipStream_t stream, const void *A, long lda, 
   g.B = B;
   g.lda = lda;
   g.ldb = ldb;
-  g.bytesA = 2 * lda * (LA == ROWK ? Mg : K);
-  g.bytesB = 2 * ldb * (LB == ROWK ? Ng : K);
-  // one k block of a K-major operand must stay within a 32-bit scalar offset
-  if ((LA == KROW && K * lda * 2 >= (1L << 31)) || (LB == KROW && K * ldb * 2 >= (1L << 31)) ||
-      lda * 2 * BM >= (1L << 31) || ldb * 2 * BN >= (1L << 31))
+  g.bytesA = ES * lda * (LA == ROWK ? Mg : K);
+  g.bytesB = ES * ldb * (LB == ROWK ? Ng : K);
+  // the k blocks of a K-major operand must stay within a 32-bit scalar offset (fp32: each block by itself)
+  const long reach = ES == 4 ? BK : K;
+  if ((LA == KROW && reach * lda * ES >= (1L << 31)) || (LB == KROW && reach * ldb * ES >= (1L << 31)) ||
+      lda * ES * BM >= (1L << 31) || ldb * ES * BN >= (1L << 31))
     return hipErrorInvalidValue;
   g.tilesM = (int)(Mg / BM);
   g.tilesN = (int)(Ng / BN);
@@ -293,7 +352,7 @@ inline hipError_t launch_gemm_dma4(hipStream_t stream, const void *A, long lda, 
   g.band = band < 0 ? -band : band;
   unsigned grid = (unsigned)(g.perXcd * NUM_XCD);
   if (PERSIST && grid > 256u) grid = 256u;  // one workgroup per compute unit
-  hipLaunchKernelGGL((gemm_dma4_kernel<BM, BN, WGM, WGN, LA, LB, Epi, PERSIST>), dim3(grid), dim3(WGM * WGN * 64), 0,
+  hipLaunchKernelGGL((gemm_dma4_kernel<T, BM, BN, WGM, WGN, LA, LB, Epi, PERSIST>), dim3(grid), dim3(WGM * WGN * 64), 0,
                      stream, g, epi);
   return hipGetLastError();
 }

@@ -77,14 +77,14 @@ __global__ void __launch_bounds__(WGM *WGN * 64) gemm_ring64_kernel(const GemmSh
   const int nwork = g.perXcd * NUM_XCD;
   const int stride = PERSIST ? (int)gridDim.x : nwork;
   DmaLoader64Asm<BM, NT> la;
-  DmaLoader32<BN, KROW, NT> lb;
-  constexpr int LOADS_TWO_ITERATIONS = DmaLoader64Asm<BM, NT>::PER + 2 * DmaLoader32<BN, KROW, NT>::PER;
+  DmaLoader32<bf16_t, BN, KROW, NT> lb;
+  constexpr int LOADS_TWO_ITERATIONS = DmaLoader64Asm<BM, NT>::PER + 2 * DmaLoader32<bf16_t, BN, KROW, NT>::PER;
   static_assert(LOADS_TWO_ITERATIONS <= 15, "outstanding-load count must fit the low bits of vmcnt");
   constexpr int WAIT_NEXT = LOADS_TWO_ITERATIONS | (7 << 4);  // vmcnt, expcnt at its maximum, lgkmcnt 0
   const int lr = lane & 31;
   static_assert(TM <= 4 && TN <= 4, "fragment addressing covers up to four 32-row blocks per wave");
   DmaFragAddr<BM, ROWK> addr_a;
-  DmaFragAddr32<BN, KROW> addr_b;
+  DmaFragAddr32<bf16_t, BN, KROW> addr_b;
   addr_a.init(wm * WTM + lr, lane);
   addr_b.init(wn * WTN + lr, lane);
 

@@ -120,41 +120,85 @@ namespace {
 // Tile shape of the three output-layer contractions and of the recurrent weight gradient: 256x256
 // output tile, 8 waves as 2 x 4 (wave tile 128 x 64).
 constexpr int BIG = 256;
-// The large contractions: bf16 operands take the direct global->LDS kernel (four-stage ring), fp32 the
-// register-staged one.
+
+// fp32 contractions: 256x256 output tiles on eight waves (one workgroup per compute unit), 128x128 or 64x64 on four (two
+// and five workgroups).  The tile and the number of splits of the contraction dimension minimise an estimate of the time.
+// A 64x64 tile's K block of 32 takes 1024 clocks (0.43 us) of a compute unit's matrix cores; workgroups that share a
+// compute unit share its rate, and a round of them ends together (the last, partly filled round fills compute units in
+// pairs: 640 workgroups of 128x128 took as long as 1024); measured against the rate of a bare MFMA loop (155 TFLOP/s),
+// whole rounds reach 92 % (256), 90 % (128) and 82 % (64); every split adds a pass over the output.
+struct F32Plan {
+  int tile, splits;
+};
+F32Plan f32_plan(long Mg, long Ng, long K, int max_splits) {
+  const long kb = (K + 31) / 32;
+  F32Plan best = {64, 1};
+  double best_us = 1e30;
+  for (int tile = 64; tile <= 256; tile *= 2) {
+    if (Mg % tile || Ng % tile) continue;
+    const double unit = (tile == 256 ? 16 / 0.92 : tile == 128 ? 4 / 0.90 : 1 / 0.82) * 0.43;
+    const int share = tile == 256 ? 1 : tile == 128 ? 2 : 5;
+    const long tiles = (Mg / tile) * (Ng / tile);
+    for (int S = 1; S <= max_splits && S <= kb; ++S) {
+      const long per = (kb + S - 1) / S, wgs = tiles * S;
+      const long rounds = wgs / (256 * share), rest = wgs % (256 * share);
+      // the rest: one per compute unit when it is all there is, otherwise packed
+      const long last = rest == 0 ? 0 : rounds == 0 ? (rest + 255) / 256 : share;
+      double us = (double)(rounds * share + last) * unit * per;
+      if (S > 1) us += 5.0 + (S + 1) * (double)Mg * Ng * 4.0 / 4e6;
+      if (us < best_us) {
+        best_us = us;
+        best = {tile, S};
+      }
+    }
+  }
+  return best;
+}
+template <int LA, int LB, class Epi>
+hipError_t f32_gemm(hipStream_t st, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
+                    const F32Plan &plan, const Epi &epi, int band = 4) {
+  if (plan.tile == 256) {
+    constexpr bool PERSIST = Epi::template lds_bytes<256, 256>() == 0;
+    return launch_gemm_dma4<float, 256, 256, 2, 4, LA, LB, PERSIST>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
+  }
+  if (plan.tile == 128)
+    return launch_gemm_dma4<float, 128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
+  return launch_gemm_dma4<float, 64, 64, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
+}
+
+// The large bf16 contractions take the direct global->LDS kernels.
 // RING4: the four-stage ring of 32-deep K blocks (deeper prefetch; pays when at least one operand is
 // K-major, whose 32-deep blocks are still made of full cache lines) instead of two stages of 64.
-template <typename T, int WGM, int WGN, int LA, int LB, bool RING4, class Epi>
+template <int WGM, int WGN, int LA, int LB, bool RING4, class Epi>
 hipError_t big_gemm(hipStream_t st, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
                     int splits, const Epi &epi, int band = 4) {
-  if constexpr (sizeof(T) == 2 && RING4) {
+  if constexpr (RING4) {
     // epilogues that leave the LDS alone run as one persistent workgroup per compute unit, which requests the
     // next tile's first K blocks before its epilogue
     constexpr bool PERSIST = Epi::template lds_bytes<BIG, BIG>() == 0;
-    return launch_gemm_dma4<BIG, BIG, WGM, WGN, LA, LB, PERSIST>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
-  } else if constexpr (sizeof(T) == 2) {
-    return launch_gemm_dma<BIG, BIG, WGM, WGN, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
+    return launch_gemm_dma4<bf16_t, BIG, BIG, WGM, WGN, LA, LB, PERSIST>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
   } else {
-    return launch_gemm<T, BIG, BIG, 2, 4, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
+    return launch_gemm_dma<BIG, BIG, WGM, WGN, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
   }
 }
 
 // The mid-sized contractions (128x128 output tiles: noise-panel products, the layers of the compressed
-// architecture): bf16 operands take the direct global->LDS kernels (the ring when an operand is K-major), fp32
-// the register-staged one.
+// architecture): bf16 operands take the direct global->LDS kernels (the ring when an operand is K-major).
 template <typename T, int LA, int LB, class Epi>
 hipError_t mid_gemm(hipStream_t st, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
                     int splits, const Epi &epi, int band = 4) {
-  // the direct-load kernels address a K-major operand's k blocks with a 32-bit scalar offset
+  // the direct-load kernels address a bf16 K-major operand's k blocks with a 32-bit scalar offset
   const bool fits = !((LA == KROW && K * lda * 2 >= (1L << 31)) || (LB == KROW && K * ldb * 2 >= (1L << 31)) ||
                       lda * 2 * 128 >= (1L << 31) || ldb * 2 * 128 >= (1L << 31));
-  if constexpr (sizeof(T) == 2 && (LA == KROW || LB == KROW)) {
-    if (fits) return launch_gemm_dma4<128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
-    return launch_gemm<T, 128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
-  } else if constexpr (sizeof(T) == 2) {
-    if (fits) return launch_gemm_dma<128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
+  if constexpr (sizeof(T) == 4) {
+    F32Plan plan = f32_plan(Mg, Ng, K, 1);
+    plan.splits = splits;
+    return f32_gemm<LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, plan, epi, band);
+  } else if constexpr (LA == KROW || LB == KROW) {
+    if (fits) return launch_gemm_dma4<bf16_t, 128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
     return launch_gemm<T, 128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
   } else {
+    if (fits) return launch_gemm_dma<128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
     return launch_gemm<T, 128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
   }
 }
@@ -173,10 +217,11 @@ bool cfg_ok(const rnnlm_config *c) {
   return true;
 }
 
+constexpr int MAX_SPLITS = 16;
 int desired_splits(long Mp, long Hp, long kBlocks) {
   const long tiles = (Mp / BIG) * (Hp / BIG);
   long s = 256 / tiles;  // one workgroup per compute unit: stay within one round
-  if (s > 16) s = 16;
+  if (s > MAX_SPLITS) s = MAX_SPLITS;
   if (s > kBlocks) s = kBlocks;
   if (s < 1) s = 1;
   return (int)s;
@@ -190,10 +235,14 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   Vp = (int)round_up(c.V, PAD_V);
   Bp = (int)round_up(c.B, PAD_B);
   MpMax = (int)round_up((long)c.T_max * Bp, PAD_M);
-  nPart = Vp / BIG;  // one softmax-statistics partial per tile row block
-  const int BK = (es == 4) ? 32 : 64;
-  const int S = desired_splits(MpMax, Dp, Vp / BK);
-  L.partElems = (long)S * MpMax * Dp;
+  nPart = Vp / (es == 4 ? 64 : BIG);  // one softmax-statistics partial per tile row block (fp32: of the smaller tile)
+  if (es == 4) {
+    L.partElems = (long)MpMax * Dp;
+    for (long M = PAD_M; M <= MpMax; M += PAD_M)
+      L.partElems = std::max(L.partElems, (long)f32_plan(M, Dp, Vp, MAX_SPLITS).splits * M * Dp);
+  } else {
+    L.partElems = (long)desired_splits(MpMax, Dp, Vp / 64) * MpMax * Dp;
+  }
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -560,6 +609,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     feat = at<T>(h, h->L.P_c);
   }
   if (!with_output) return RNNLM_OK;  // the scoring calls only wanted the layer above the states
+  int nPart = Vp / BIG;
   {
     StageTimer tm(h, RNNLM_STAGE_OUT_FWD, st);
     EpiOutFwd<T> epi;
@@ -574,15 +624,17 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
       // thousands of short tiles: one persistent workgroup per compute unit walks them, in bands of 8 vocabulary
       // row panels (the 32 tiles an XCD works on at a time then share 8 row panels and 4 position panels in its L2:
       // measured best of 1..16 on all three large configurations)
-      HIP_TRY((launch_gemm_dma<BIG, BIG, 4, 2, ROWK, ROWK, true>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp,
-                                                                 h->Dp, 1, epi, 8)));
+      HIP_TRY((launch_gemm_dma<BIG, BIG, 4, 2, ROWK, ROWK, true>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp,
+                                                                    Mp, h->Dp, 1, epi, 8)));
     } else {
-      HIP_TRY((big_gemm<T, 4, 2, ROWK, ROWK, false>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp, h->Dp, 1, epi)));
+      const F32Plan plan = f32_plan(Vp, Mp, h->D, 1);
+      HIP_TRY((f32_gemm<ROWK, ROWK>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp, round_up(h->D, 32), plan, epi, 8)));
+      nPart = Vp / plan.tile;
     }
   }
   StageTimer tm(h, RNNLM_STAGE_STATS, st);
   hipLaunchKernelGGL(merge_stats_kernel, dim3(blocks_for(Mrows, 64)), dim3(1024), 0, st, at<float2>(h, h->L.stat),
-                     Vp / BIG, ldz, Tn, c.B, Bp, zy, lse, at<float>(h, h->L.logp_int), logp_out);
+                     nPart, ldz, Tn, c.B, Bp, zy, lse, at<float>(h, h->L.logp_int), logp_out);
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
@@ -766,8 +818,9 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   {
     const int Dp = h->Dp;
     float *dF32 = c.P > 0 ? at<float>(h, h->L.dP32) : dHs32;
-    int S = desired_splits(Mp, Dp, Vp / BK);
     const long per = (long)Mp * Dp;
+    const F32Plan plan = f32_plan(Mp, Dp, Vp, (int)std::min<long>(MAX_SPLITS, std::max<long>(1, h->L.partElems / per)));
+    int S = sizeof(T) == 4 ? plan.splits : desired_splits(Mp, Dp, Vp / BK);
     if ((long)S * per > h->L.partElems) S = (int)(h->L.partElems / per);
     if (S < 1) S = 1;
     EpiPartial epi;
@@ -776,7 +829,11 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     epi.split_stride = per;
     {
       StageTimer tm(h, RNNLM_STAGE_OUT_BWD_H, st);
-      HIP_TRY((big_gemm<T, 2, 4, KROW, KROW, true>(st, ZT, ldz, Wo_c, Dp, Mp, Dp, Vp, S, epi)));
+      if constexpr (sizeof(T) == 4) {
+        HIP_TRY((f32_gemm<KROW, KROW>(st, ZT, ldz, Wo_c, Dp, Mp, Dp, round_up(c.V, 32), plan, epi)));
+      } else {
+        HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(st, ZT, ldz, Wo_c, Dp, Mp, Dp, Vp, S, epi)));
+      }
     }
     if (S > 1) {
       StageTimer tm(h, RNNLM_STAGE_REDUCE, st);
@@ -838,7 +895,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
       ep.split_stride = per;
       if (K > 0) {
         if constexpr (sizeof(T) == 2) {
-          HIP_TRY((launch_gemm_dma4<256, 128, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, K, S, ep)));
+          HIP_TRY((launch_gemm_dma4<bf16_t, 256, 128, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, K, S, ep)));
         } else {
           HIP_TRY((launch_gemm<T, 256, 64, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, K, S, ep)));
         }
@@ -891,8 +948,10 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     epi.C = c.H;
     epi.alpha = u.alpha;
     epi.lr = u.lr;
-    if (sizeof(T) == 2 && (long)(Hp / BIG) * (Hp / BIG) >= 64) {
-      HIP_TRY((big_gemm<T, 2, 4, KROW, KROW, true>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, 1, epi)));
+    if constexpr (sizeof(T) == 4) {
+      HIP_TRY((f32_gemm<KROW, KROW>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, f32_plan(Hp, Hp, Mp, 1), epi)));
+    } else if ((long)(Hp / BIG) * (Hp / BIG) >= 64) {
+      HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, 1, epi)));
     } else if (Hp <= 1024) {  // small matrix: 64x64 tiles give up to 256 workgroups
       HIP_TRY((launch_gemm<T, 64, 64, 2, 2, KROW, KROW>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, 1, epi)));
     } else {
@@ -935,8 +994,13 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
       epi.C = c.H;
       epi.alpha = u.alpha;
       epi.lr = u.lr;
-      HIP_TRY((launch_gemm<T, 64, 64, 2, 2, KROW, KROW>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.dP_c), h->Pp, Hp,
-                                                        h->Pp, Mp, 1, epi)));
+      if constexpr (sizeof(T) == 4) {
+        HIP_TRY((f32_gemm<KROW, KROW>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.dP_c), h->Pp, Hp, h->Pp, Mp,
+                                      f32_plan(Hp, h->Pp, Mp, 1), epi)));
+      } else {
+        HIP_TRY((launch_gemm<T, 64, 64, 2, 2, KROW, KROW>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.dP_c), h->Pp, Hp,
+                                                          h->Pp, Mp, 1, epi)));
+      }
     }
     {
     // Wo[v][j] -= lr * sum_m dz[v][m] Hs[m][j]: bf16 in the matrix's own orientation, fp32 and the compressed
@@ -963,7 +1027,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
         // blocks, gemm_ring64.h: 8-9 % faster at H = 1024 and 2048); the widest layer runs at the chip's power
         // limit, where the symmetric ring measured 0.5 % better
         if (Hp / BIG >= 16) {
-          HIP_TRY((big_gemm<T, 2, 4, ROWK, KROW, true>(st, ZT, ldz, Hs_c + (long)Bp * Hp, Hp, Vp, Hp, Mp, 1, e2, -8)));
+          HIP_TRY((big_gemm<2, 4, ROWK, KROW, true>(st, ZT, ldz, Hs_c + (long)Bp * Hp, Hp, Vp, Hp, Mp, 1, e2, -8)));
         } else {
           HIP_TRY((launch_gemm_ring64<BIG, BIG, 2, 4>(st, ZT, ldz, Hs_c + (long)Bp * Hp, Hp, Vp, Hp, Mp, 1, e2, -4)));
         }
@@ -980,14 +1044,13 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     epi.alpha = u.alpha;
     epi.lr = u.lr;
     const T *feat = c.P > 0 ? at<T>(h, h->L.P_c) : Hs_c + (long)Bp * Hp;
-    if ((long)(h->Dp / BIG) * (Vp / BIG) < 128) {  // a narrow layer above the state: smaller tiles fill the chip
-      if constexpr (sizeof(T) == 2) {
-        HIP_TRY((launch_gemm_dma4<128, BIG, 2, 4, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, epi, -4)));
-      } else {
-        HIP_TRY((launch_gemm<T, 128, 128, 2, 2, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, epi, -2)));
-      }
+    if constexpr (sizeof(T) == 4) {
+      HIP_TRY((f32_gemm<KROW, ROWK>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, round_up(Mrows, 32), f32_plan(h->Dp, Vp, Mrows, 1),
+                                    epi, -4)));
+    } else if ((long)(h->Dp / BIG) * (Vp / BIG) < 128) {  // a narrow layer above the state: smaller tiles fill the chip
+      HIP_TRY((launch_gemm_dma4<bf16_t, 128, BIG, 2, 4, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, epi, -4)));
     } else {
-      HIP_TRY((big_gemm<T, 2, 4, KROW, ROWK, true>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, epi, -2)));
+      HIP_TRY((big_gemm<2, 4, KROW, ROWK, true>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, epi, -2)));
     }
     }
     }
@@ -1020,7 +1083,11 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     epi.C = c.P;
     epi.alpha = u.alpha;
     epi.lr = u.lr;
-    HIP_TRY((launch_gemm<T, 64, 64, 2, 2, KROW, KROW>(st, at<T>(h, h->L.Xp_c), h->Pp, dA_c, Hp, h->Pp, Hp, Mp, 1, epi)));
+    if constexpr (sizeof(T) == 4) {
+      HIP_TRY((f32_gemm<KROW, KROW>(st, at<T>(h, h->L.Xp_c), h->Pp, dA_c, Hp, h->Pp, Hp, Mp, f32_plan(h->Pp, Hp, Mp, 1), epi)));
+    } else {
+      HIP_TRY((launch_gemm<T, 64, 64, 2, 2, KROW, KROW>(st, at<T>(h, h->L.Xp_c), h->Pp, dA_c, Hp, h->Pp, Hp, Mp, 1, epi)));
+    }
   }
 
   if (!early_rec) {

@@ -1,0 +1,33 @@
+"""GPU parity of the contraction kernels' size-dependent forms against the fp64 CPU oracle, through the C ABI: shapes
+on both sides of every rule that picks a tile, a split or a trimmed contraction depth.  Tolerances as in
+test_gpu_parity.py (fp32: log-probs 1e-4 relative + 1e-6, gradients 1e-3 of each tensor's scale)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_1502_00512_amd import binding
+from test_gpu_parity import check_grad, check_logp, dev, make_pair, tokens
+
+pytestmark = pytest.mark.gpu
+
+FP32, BF16 = binding.RNNLM_FP32, binding.RNNLM_BF16_FP32MASTER
+
+
+@pytest.mark.parametrize("V,H,B,T", [
+    (33000, 520, 128, 5),    # 64-wide tiles in the output layer, 128-wide with 7 splits over the vocabulary
+    (24000, 500, 128, 6),    # 128-wide tiles with 10 splits; 256-wide ones in the weight update
+    (12000, 1000, 128, 9),   # 256-wide tiles in both, depth 1000 (not a multiple of 32)
+    (100000, 8, 256, 22),    # logits beyond 2^31 bytes as K-major operand; depth 8
+    (257, 33, 1, 1),         # one position, one column past a tile
+])
+def test_fp32_contraction_tiles(V, H, B, T):
+    g, o = make_pair(V, H, B, T, FP32, seed=V + H, scale=0.3 if H < 100 else 0.05, bias_scale=0.5)
+    tok = tokens(V, B * T + B + 1, 6)
+    x, y = O.stream_chunk(tok, B, T, 0)
+    r = g.rnnlm_grad_chunk(dev(x), dev(y))
+    ref = O.grad_chunk(o, x, y)
+    check_logp(r["logp"], ref["logp"])
+    for k in ("gE", "gU", "gWo", "gb"):
+        check_grad(k, r[k], ref[k])
+    g.rnnlm_check()
