@@ -270,7 +270,7 @@ int rnnlm_sort_segments(rnnlm_t *h, const int32_t *x, int32_t T, int32_t *perm, 
 int rnnlm_sort_segments_static(const int32_t *x, int32_t T, int32_t B, int32_t V, int32_t *perm, int32_t *seg_start,
                                int32_t *nseg, int32_t *range_flag, void *stream);
 
-/* Number of polls a grid-wide barrier of the persistent recurrent kernels waits before it gives up,
+/* Number of polls a wait of the persistent recurrent kernels makes before it gives up,
  * raises the flag that rnnlm_check reports as RNNLM_ERR_TIMEOUT and lets the kernel run to its end
  * (default 2^18, about a second).  For tests of that error path: polls = 1 makes waits expire at once. */
 int rnnlm_set_barrier_spin_limit(rnnlm_t *h, uint32_t polls);
@@ -278,8 +278,7 @@ int rnnlm_set_barrier_spin_limit(rnnlm_t *h, uint32_t polls);
 /* How the workgroups of a persistent recurrent kernel hand the state h_t (backward: the gradient dA_t) to one
  * another between the steps of a window (Sec. 4.2: the state-to-state work of all streams is done together).
  * AUTO (default): the XCD-local exchange when the placement probe at init allows it and there are at most 8
- * blocks of 32 streams, else the chip-wide one.  CHIP_WIDE: always agent-scope accesses and one counter for the
- * whole grid.  XCD_LOCAL: like AUTO, but RNNLM_ERR_ARG when the XCD-local exchange is not available for this
+ * blocks of 32 streams, else the chip-wide one.  CHIP_WIDE: always agent-scope accesses.  XCD_LOCAL: like AUTO, but RNNLM_ERR_ARG when the XCD-local exchange is not available for this
  * handle.  Both exchanges compute the same values in the same order: results are bitwise equal (tested).
  * The widest recurrent shape (bf16, H padded to 4096, 256 streams) runs as one launch that keeps the
  * state-to-state matrix in the register files of all compute units; it needs the same placement as the XCD-local

@@ -22,37 +22,78 @@ __global__ void stream_chunk_kernel(const int32_t *__restrict__ tok, long L, lon
 //   get -1.  Ids outside [0, V) are clamped and raise flags[0].  Also marks padded positions with
 //   lse = +inf so that the softmax-gradient pass produces exact zeros there, copies the carried state into
 //   slot 0 of the hidden-state buffer (compute type, padded with zeros) and clears the barrier / ticket
-//   counters of the persistent recurrent kernel that follows (slot / counters == nullptr: tokens only).
-//   prep_blocks covers max(Mp, Bp*Hp) threads.
-// blockIdx.x >= prep_blocks (present when X or Xc != nullptr): a1, embedding gather of padded row
-//   r = blockIdx.x - prep_blocks: X[r][:] = E[x of that position][:] (fp32), zero on padding.  Compressed
-//   architecture (Xc != nullptr): the row is an operand of the contraction through the layer below the
-//   state, so it is copied in the compute type from the tile-padded compute copy Ec[.][ldc] into Xc[r][ldc].
+//   counters of the persistent recurrent kernel that follows (slot / counters == nullptr: tokens only).  Also
+//   gives the exchange buffers of the persistent recurrent kernels (ring[0] forward, ring[1] backward; nullptr: none)
+//   their first contents: UNWRITTEN, and the carried state, in operand order, as the forward step before the first.
+//   prep_blocks covers max(Mp, Bp*Hp, ring pieces of 16 bytes) threads.
+// blockIdx.x >= prep_blocks (present when X or Xc != nullptr), padded row r = blockIdx.x - prep_blocks:
+//   - a1, embedding gather (r < T*Bp): X[r][:] = E[x of that position][:] (fp32), zero on padding.  Compressed
+//     architecture (Xc != nullptr): the row is an operand of the contraction through the layer below the
+//     state, so it is copied in the compute type from the tile-padded compute copy Ec[.][ldc] into Xc[r][ldc];
+//   - zeros where the persistent recurrent kernels write nothing but the contractions read: padding positions, and
+//     units from `width` on, of the state (next, r < T*Bp) and of the gradient (dA, training windows).
+constexpr unsigned UNWRITTEN = 0xffffffffu;  // an exchanged word that its step has not written yet
+constexpr int RING = 4;                      // steps the exchange buffer holds
+
+// How the persistent recurrent kernel covers a shape (nwg = 0: it does not).
+struct RecurrentPlan {
+  int waves, units, nwg;  // per workgroup; workgroups per group
+  int R, groups, rt;      // streams per group, groups, blocks of 16 streams per group
+  int width;              // units the kernel writes: H rounded up to whole workgroups
+  int nkb, ks;            // 32-wide blocks of the contraction, and how many a wave takes
+  __host__ __device__ long ring_bytes(int es) const { return (long)RING * groups * rt * nkb * 512 * es; }
+};
+
 template <typename T>
-__global__ void __launch_bounds__(256) prep_tokens_kernel(const int32_t *__restrict__ x, const int32_t *__restrict__ y,
-                                                          int Tn, int B, int Bp, int Mp, int V,
-                                                          int32_t *__restrict__ xp, int32_t *__restrict__ yp,
-                                                          float *__restrict__ lse, int32_t *__restrict__ flags,
-                                                          const float *__restrict__ h_state, int H, int Hp,
-                                                          T *__restrict__ slot, unsigned *__restrict__ counters,
-                                                          int prep_blocks, const float *__restrict__ E,
-                                                          float *__restrict__ X, const T *__restrict__ Ec = nullptr,
-                                                          int ldc = 0, T *__restrict__ Xc = nullptr) {
-  if ((int)blockIdx.x >= prep_blocks) {
-    const int row = blockIdx.x - prep_blocks;
+struct PrepWindow {
+  const int32_t *x, *y;
+  int Tn, B, Bp, Mp, V;
+  int32_t *xp, *yp;
+  float *lse;
+  int32_t *flags;
+  const float *h_state;
+  int H, Hp;
+  T *slot;
+  unsigned *counters;
+  int prep_blocks;
+  const float *E;
+  float *X;
+  const T *Ec;
+  int ldc;
+  T *Xc;
+  T *next, *dA;
+  RecurrentPlan plan;
+  char *ring[2];
+};
+
+template <typename T>
+__global__ void __launch_bounds__(256) prep_tokens_kernel(const PrepWindow<T> p) {
+  const int B = p.B, Bp = p.Bp, H = p.H, Hp = p.Hp;
+  if ((int)blockIdx.x >= p.prep_blocks) {
+    const int row = blockIdx.x - p.prep_blocks;
     const int t = row / Bp, s = row % Bp;
+    const bool valid = t < p.Tn && s < B;
+    if (p.next) {
+      const int n16 = Hp * (int)sizeof(T) / 16, first = valid ? p.plan.width * (int)sizeof(T) / 16 : 0;
+      const u32x4_t zero = {0u, 0u, 0u, 0u};
+      for (int c = first + threadIdx.x; c < n16; c += 256) {
+        if (t < p.Tn) reinterpret_cast<u32x4_t *>(p.next + (long)row * Hp)[c] = zero;
+        if (p.dA) reinterpret_cast<u32x4_t *>(p.dA + (long)row * Hp)[c] = zero;
+      }
+    }
+    if (t >= p.Tn) return;
     int w = -1;
-    if (t < Tn && s < B) w = min(max(x[t * B + s], 0), V - 1);
-    if (Xc) {
-      const u32x4_t *src16 = reinterpret_cast<const u32x4_t *>(Ec + (long)max(w, 0) * ldc);
-      u32x4_t *dst16 = reinterpret_cast<u32x4_t *>(Xc + (long)row * ldc);
-      const int n16 = ldc * (int)sizeof(T) / 16;
+    if (valid) w = min(max(p.x[t * B + s], 0), p.V - 1);
+    if (p.Xc) {
+      const u32x4_t *src16 = reinterpret_cast<const u32x4_t *>(p.Ec + (long)max(w, 0) * p.ldc);
+      u32x4_t *dst16 = reinterpret_cast<u32x4_t *>(p.Xc + (long)row * p.ldc);
+      const int n16 = p.ldc * (int)sizeof(T) / 16;
       const u32x4_t zero = {0u, 0u, 0u, 0u};
       for (int c = threadIdx.x; c < n16; c += 256) dst16[c] = (w >= 0) ? src16[c] : zero;
       return;
     }
-    const float *src = E + (long)max(w, 0) * H;
-    float *dst = X + (long)row * Hp;
+    const float *src = p.E + (long)max(w, 0) * H;
+    float *dst = p.X + (long)row * Hp;
     if ((H & 3) == 0) {
       for (int c = threadIdx.x * 4; c < Hp; c += 256 * 4) {
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -65,27 +106,55 @@ __global__ void __launch_bounds__(256) prep_tokens_kernel(const int32_t *__restr
     return;
   }
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (counters && i < SYNC_WORDS) counters[i] = 0u;
-  if (slot && i < (long)Bp * Hp) {
+  if (p.counters && i < SYNC_WORDS) p.counters[i] = 0u;
+  if (p.slot && i < (long)Bp * Hp) {
     const int s = (int)(i / Hp), c = (int)(i % Hp);
-    slot[i] = from_f32<T>((s < B && c < H) ? h_state[(long)s * H + c] : 0.0f);
+    p.slot[i] = from_f32<T>((s < B && c < H) ? p.h_state[(long)s * H + c] : 0.0f);
   }
-  if (i >= Mp) return;
+  if (p.ring[0] && i < p.plan.ring_bytes(sizeof(T)) / 16) {
+    constexpr int E16 = 16 / (int)sizeof(T), PIECES = 2 / (E16 / 4);  // values in 16 bytes; pieces of a fragment
+    const u32x4_t unwritten = {UNWRITTEN, UNWRITTEN, UNWRITTEN, UNWRITTEN};
+    const RecurrentPlan &q = p.plan;
+    const long per = q.ring_bytes(sizeof(T)) / 16 / RING;
+    u32x4_t v = unwritten;
+    if (i / per == RING - 1) {  // what step 0 reads
+      long c = i % per;
+      const int l = (int)(c & 63);
+      c >>= 6;
+      const int piece = (int)(c % PIECES);
+      c /= PIECES;
+      const int kb = (int)(c % q.nkb);
+      c /= q.nkb;
+      const int r = (int)(c % q.rt) * 16 + (l & 15), s = (int)(c / q.rt) * q.R + r;
+      const int unit = kb * 32 + (l >> 4) * 8 + piece * E16;
+      union {
+        u32x4_t u;
+        T t[E16];
+      } o;
+#pragma unroll
+      for (int e = 0; e < E16; ++e)
+        o.t[e] = from_f32<T>((r < q.R && s < B && unit + e < H) ? p.h_state[(long)s * H + unit + e] : 0.0f);
+      v = o.u;
+    }
+    reinterpret_cast<u32x4_t *>(p.ring[0])[i] = v;
+    if (p.ring[1]) reinterpret_cast<u32x4_t *>(p.ring[1])[i] = unwritten;
+  }
+  if (i >= p.Mp) return;
   const int t = (int)i / Bp, s = (int)i % Bp;
   int xv = -1, yv = -1;
-  if (t < Tn && s < B) {
-    xv = x[t * B + s];
-    yv = y ? y[t * B + s] : 0;
-    if (xv < 0 || xv >= V || yv < 0 || yv >= V) {
-      flags[0] = 1;
-      xv = min(max(xv, 0), V - 1);
-      yv = min(max(yv, 0), V - 1);
+  if (t < p.Tn && s < B) {
+    xv = p.x[t * B + s];
+    yv = p.y ? p.y[t * B + s] : 0;
+    if (xv < 0 || xv >= p.V || yv < 0 || yv >= p.V) {
+      p.flags[0] = 1;
+      xv = min(max(xv, 0), p.V - 1);
+      yv = min(max(yv, 0), p.V - 1);
     }
   } else {
-    lse[i] = INFINITY;
+    p.lse[i] = INFINITY;
   }
-  xp[i] = xv;
-  if (yp) yp[i] = yv;
+  p.xp[i] = xv;
+  if (p.yp) p.yp[i] = yv;
 }
 
 template <typename T>

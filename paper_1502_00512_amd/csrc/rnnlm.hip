@@ -39,7 +39,7 @@ struct WsLayout {
   // compressed architecture (present when cfg.P > 0; then Wo_c holds the compute copy of the tied matrix E)
   size_t A_c, C_c, Xp_c, P_c, dP32, dP_c, dX32;
   // partial sums of the chip-resident recurrent kernel (present for Hp = 4096, 256 streams, bf16)
-  size_t part_res, sync;
+  size_t part_res, sync, ring;
   bool has_part_res;
   long partElems;
 };
@@ -57,6 +57,7 @@ struct rnnlm {
   int D, Dp;  // width of the output layer's input: H / Hp, or P / Pp for the compressed architecture
   int KpMax;  // K_max rounded up to the tile size (0: no noise-contrastive workspace)
   int nPart;
+  RecurrentPlan plan;
   WsLayout L;
   char *ws;
   // stage timing (host-side only)
@@ -227,6 +228,26 @@ int desired_splits(long Mp, long Hp, long kBlocks) {
   return (int)s;
 }
 
+// A wave's share of the matrix has to fit its registers: four waves and 32 units per workgroup up to 1024 units, eight
+// waves with half the registers and 64 units up to 2048 (bf16 fragments only).  Streams are split into at most eight
+// groups where 32 streams per group allow it (one group per XCD: a step's time grows with the state a compute unit
+// loads), and the grid is small enough to be co-resident with one workgroup per compute unit.
+RecurrentPlan recurrent_plan(const rnnlm_config &c) {
+  RecurrentPlan p = {};
+  if (c.H > (c.precision == RNNLM_FP32 ? 1024 : 2048)) return p;
+  p.waves = c.H <= 1024 ? 4 : 8;
+  p.units = c.H <= 1024 ? 32 : 64;
+  const int nwg = (c.H + p.units - 1) / p.units;
+  p.R = std::min(32, (c.B + NUM_XCD - 1) / NUM_XCD);
+  p.groups = (c.B + p.R - 1) / p.R;
+  p.rt = (p.R + 15) / 16;
+  p.width = nwg * p.units;
+  p.nkb = p.width / 32;
+  p.ks = (p.nkb + p.waves - 1) / p.waves;
+  if ((long)p.groups * nwg <= 256) p.nwg = nwg;
+  return p;
+}
+
 void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, int &nPart, int &KpMax, WsLayout &L) {
   const size_t es = (c.precision == RNNLM_FP32) ? 4 : 2;
   const int Pp = (int)round_up(c.P, PAD_H);
@@ -311,6 +332,8 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   L.has_part_res = es == 2 && Pp == 0 && Hp == RES_HP && Bp == RES_BP;
   if (L.has_part_res) L.part_res = take((size_t)RES_PART_STEP * 4);
   L.sync = take((size_t)SYNC_WORDS * 4);  // barrier / ticket counters of the persistent recurrent kernels
+  const RecurrentPlan plan = recurrent_plan(c);
+  L.ring = take(plan.nwg > 0 ? 2 * align256(plan.ring_bytes((int)es)) : 0);  // forward, backward
   L.scalars = take(256);  // [0]: int nseg, [4]: int nseg of the noise-contrastive update list, [8..19]: int flags[3], [32]: double sum, [40]: double running
   L.total = o;
 }
@@ -350,16 +373,7 @@ int sync_copies(rnnlm_t *h, hipStream_t st) {
   return RNNLM_OK;
 }
 
-// The persistent recurrent kernel applies when each wave's share of the contraction fits its register
-// file (4 waves up to Hp = 1024, 8 waves up to Hp = 2048) and the grid is small enough to be co-resident
-// with a wide margin (at most half of what the chip can hold at once).
-bool persistent_ok(const rnnlm_t *h) {
-  const long grid = (long)(h->Bp / 32) * (h->Hp / 32);
-  if (h->Hp <= 1024) return h->Hp % 256 == 0 && grid <= 256;
-  // the 8-wave variant has half the registers per wave: bf16 fragments only
-  if (h->Hp <= 2048) return h->cfg.precision == RNNLM_BF16_FP32MASTER && h->Hp % 256 == 0 && grid <= 256;
-  return false;
-}
+bool persistent_ok(const rnnlm_t *h) { return h->plan.nwg > 0; }
 
 // Per-step recurrent path for shapes the persistent kernel does not cover: with whole blocks of 256 streams
 // and a wide hidden layer the step's contraction is split over its contraction dimension (0: not split).
@@ -403,41 +417,36 @@ int launch_rnn_persistent(rnnlm_t *h, int Tn, bool advance_state, hipStream_t st
   a.Bp = h->Bp;
   a.Hp = h->Hp;
   a.spin_limit = h->spin_limit;
+  const RecurrentPlan &p = h->plan;
+  a.ring = h->ws + h->L.ring + (BACKWARD ? align256(p.ring_bytes(sizeof(T))) : 0);
+  a.R = p.R;
+  a.groups = p.groups;
+  a.nwg = p.nwg;
+  a.nkb = p.nkb;
+  a.ks = p.ks;
   // the counters are zero here: cleared by the token-preparation kernel (forward) and by the
   // log-probability sum (backward), which always run before this launch on the same stream
-  // XCD-local mode: one group of Hp/32 workgroups per block of 32 streams, group x on XCD x
-  const bool xcd = h->xcd_local && h->exchange_mode != RNNLM_EXCHANGE_CHIP_WIDE && h->Bp / 32 <= NUM_XCD;
-  const dim3 grid(xcd ? (unsigned)(NUM_XCD * (h->Hp / 32)) : (unsigned)((h->Bp / 32) * (h->Hp / 32)));
-  // bf16, XCD-local, whole [32][64] blocks per wave: the state goes through LDS (coalesced loads): 4 waves keep
-  // their blocks resident; 8 waves (1024 < Hp <= 2048) take the wide kernel, 64 units per workgroup and one
-  // workgroup per compute unit, provided the runtime confirms that it fits one
-#define RNNLM_LAUNCH_PERSIST(KS, NW)                                                                        \
-  do {                                                                                                      \
-    if constexpr (sizeof(T) == 2 && KS % 4 == 0 && NW == 8) {                                               \
-      if (xcd && blocks_per_cu<rnn_persistent_wide_kernel<KS, BACKWARD>>(512) >= 1) {                       \
-        hipLaunchKernelGGL((rnn_persistent_wide_kernel<KS, BACKWARD>), dim3(NUM_XCD * (h->Hp / 64)), dim3(512), 0, st, a); \
-        break;                                                                                              \
-      }                                                                                                     \
-    }                                                                                                       \
-    if constexpr (sizeof(T) == 2 && KS % 4 == 0 && NW == 4) {                                               \
-      if (xcd && 32 * blocks_per_cu<rnn_persistent_kernel<T, KS, NW, BACKWARD, true, true>>(64 * NW) >= h->Hp / 32) { \
-        hipLaunchKernelGGL((rnn_persistent_kernel<T, KS, NW, BACKWARD, true, true>), grid, dim3(64 * NW), 0, st, a); \
-        break;                                                                                              \
-      }                                                                                                     \
-    }                                                                                                       \
-    if (xcd) hipLaunchKernelGGL((rnn_persistent_kernel<T, KS, NW, BACKWARD, true>), grid, dim3(64 * NW), 0, st, a); \
-    else hipLaunchKernelGGL((rnn_persistent_kernel<T, KS, NW, BACKWARD, false>), grid, dim3(64 * NW), 0, st, a);    \
+  a.xcd = h->xcd_local && h->exchange_mode != RNNLM_EXCHANGE_CHIP_WIDE && p.groups <= NUM_XCD;
+  const dim3 grid((unsigned)((a.xcd ? NUM_XCD : p.groups) * p.nwg));
+#define RNNLM_LAUNCH_PERSIST(KS, NW, UT)                                                                              \
+  do {                                                                                                                \
+    if (p.R <= 16) hipLaunchKernelGGL((rnn_persistent_kernel<T, KS, NW, UT, 1, BACKWARD>), grid, dim3(64 * NW), 0, st, a); \
+    else hipLaunchKernelGGL((rnn_persistent_kernel<T, KS, NW, UT, 2, BACKWARD>), grid, dim3(64 * NW), 0, st, a);      \
   } while (0)
-  switch (h->Hp / 256) {
-    case 1: RNNLM_LAUNCH_PERSIST(4, 4); break;
-    case 2: RNNLM_LAUNCH_PERSIST(8, 4); break;
-    case 3: RNNLM_LAUNCH_PERSIST(12, 4); break;
-    case 4: RNNLM_LAUNCH_PERSIST(16, 4); break;
-    case 5: RNNLM_LAUNCH_PERSIST(10, 8); break;
-    case 6: RNNLM_LAUNCH_PERSIST(12, 8); break;
-    case 7: RNNLM_LAUNCH_PERSIST(14, 8); break;
-    case 8: RNNLM_LAUNCH_PERSIST(16, 8); break;
-    default: return RNNLM_ERR_ARG;
+  if (p.waves == 4) {
+    if (p.ks <= 1) RNNLM_LAUNCH_PERSIST(1, 4, 2);
+    else if (p.ks <= 2) RNNLM_LAUNCH_PERSIST(2, 4, 2);
+    else if (p.ks <= 3) RNNLM_LAUNCH_PERSIST(3, 4, 2);
+    else if (p.ks <= 4) RNNLM_LAUNCH_PERSIST(4, 4, 2);
+    else if (p.ks <= 6) RNNLM_LAUNCH_PERSIST(6, 4, 2);
+    else if (p.ks <= 8) RNNLM_LAUNCH_PERSIST(8, 4, 2);
+    else return RNNLM_ERR_ARG;
+  } else if constexpr (sizeof(T) == 2) {
+    if (p.ks <= 6) RNNLM_LAUNCH_PERSIST(6, 8, 4);
+    else if (p.ks <= 8) RNNLM_LAUNCH_PERSIST(8, 8, 4);
+    else return RNNLM_ERR_ARG;
+  } else {
+    return RNNLM_ERR_ARG;
   }
 #undef RNNLM_LAUNCH_PERSIST
   HIP_TRY(hipGetLastError());
@@ -525,17 +534,46 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
 
   {
     StageTimer tm(h, RNNLM_STAGE_PREP, st);
-    const int prep_blocks = (int)blocks_for(std::max<long>(Mp, (long)Bp * Hp), 256);
+    const long ring16 = persistent_ok(h) ? h->plan.ring_bytes(sizeof(T)) / 16 : 0;
+    const int prep_blocks = (int)blocks_for(std::max(std::max<long>(Mp, (long)Bp * Hp), ring16), 256);
+    PrepWindow<T> pw = {};
+    pw.x = x;
+    pw.y = y;
+    pw.Tn = Tn;
+    pw.B = c.B;
+    pw.Bp = Bp;
+    pw.Mp = Mp;
+    pw.V = c.V;
+    pw.xp = xp;
+    pw.yp = yp;
+    pw.lse = lse;
+    pw.flags = p_flags(h);
+    pw.h_state = h->buf.h_state;
+    pw.H = c.H;
+    pw.Hp = Hp;
+    pw.slot = Hs_c;
+    pw.counters = p_counter(h);
+    pw.prep_blocks = prep_blocks;
     if (c.P > 0) {  // compressed architecture: the gathered rows are operands of the contraction below
-      hipLaunchKernelGGL(prep_tokens_kernel<T>, dim3(prep_blocks + Mrows), dim3(256), 0, st, x, y, Tn, c.B, Bp, Mp, c.V,
-                         xp, yp, lse, p_flags(h), h->buf.h_state, c.H, Hp, Hs_c, p_counter(h), prep_blocks,
-                         (const float *)nullptr, (float *)nullptr, (const T *)at<T>(h, h->L.Wo_c), h->Pp,
-                         at<T>(h, h->L.Xp_c));
+      pw.Ec = at<T>(h, h->L.Wo_c);
+      pw.ldc = h->Pp;
+      pw.Xc = at<T>(h, h->L.Xp_c);
     } else {
-      hipLaunchKernelGGL(prep_tokens_kernel<T>, dim3(prep_blocks + Mrows), dim3(256), 0, st, x, y, Tn, c.B, Bp, Mp, c.V,
-                         xp, yp, lse, p_flags(h), h->buf.h_state, c.H, Hp, Hs_c, p_counter(h), prep_blocks, h->buf.E,
-                         X32, (const T *)nullptr, 0, (T *)nullptr);
+      pw.E = h->buf.E;
+      pw.X = X32;
     }
+    int rows = Mrows;
+    if (persistent_ok(h)) {
+      pw.plan = h->plan;
+      pw.next = Hs_c + (long)Bp * Hp;
+      pw.ring[0] = h->ws + h->L.ring;
+      if (sort_inputs) {
+        pw.ring[1] = pw.ring[0] + align256(h->plan.ring_bytes(sizeof(T)));
+        pw.dA = at<T>(h, h->L.dA_c);
+        rows = Mp;  // rows [Mrows, Mp) of dA take part in the dU contraction: zero
+      }
+    }
+    hipLaunchKernelGGL(prep_tokens_kernel<T>, dim3(prep_blocks + rows), dim3(256), 0, st, pw);
     HIP_TRY(hipGetLastError());
     if (sort_inputs) {
       int rc = side_fork(h, 0, st);
@@ -857,8 +895,9 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   }
   }
 
-  // rows [Mrows, Mp) of dA take part in the dU contraction: keep them zero
-  if (Mp > Mrows) {
+  // rows [Mrows, Mp) of dA take part in the dU contraction: keep them zero (the persistent path has them from
+  // the token preparation)
+  if (Mp > Mrows && !persistent_ok(h)) {
     const long n = (long)(Mp - Mrows) * Hp * (long)sizeof(T) / 4;
     hipLaunchKernelGGL(fill_kernel<uint32_t>, dim3(blocks_for(n, 256)), dim3(256), 0, st,
                        reinterpret_cast<uint32_t *>(dA_c + (long)Mrows * Hp), n, 0u);
@@ -1198,6 +1237,7 @@ int rnnlm_init(const rnnlm_config *cfg, const rnnlm_buffers *buf, rnnlm_t **out)
   h->cfg = *cfg;
   h->buf = *buf;
   make_layout(*cfg, h->Hp, h->Vp, h->Bp, h->MpMax, h->nPart, h->KpMax, h->L);
+  h->plan = recurrent_plan(*cfg);
   h->Pp = (int)round_up(cfg->P, PAD_H);
   h->D = cfg->P > 0 ? cfg->P : cfg->H;
   h->Dp = cfg->P > 0 ? h->Pp : h->Hp;
@@ -1568,11 +1608,18 @@ int rnnlm_sort_segments(rnnlm_t *h, const int32_t *x, int32_t T, int32_t *perm, 
   hipStream_t st = (hipStream_t)stream;
   const int Mp = (int)round_up((long)T * h->Bp, PAD_M);
   const int prep_blocks = (int)blocks_for(Mp, 256);
-  hipLaunchKernelGGL(prep_tokens_kernel<float>, dim3(prep_blocks), dim3(256), 0, st, x, (const int32_t *)nullptr, T,
-                     h->cfg.B, h->Bp, Mp, h->cfg.V, at<int32_t>(h, h->L.xp), (int32_t *)nullptr,
-                     at<float>(h, h->L.lse), p_flags(h), (const float *)nullptr, 0, 0, (float *)nullptr,
-                     (unsigned *)nullptr, prep_blocks, (const float *)nullptr, (float *)nullptr,
-                     (const float *)nullptr, 0, (float *)nullptr);
+  PrepWindow<float> pw = {};
+  pw.x = x;
+  pw.Tn = T;
+  pw.B = h->cfg.B;
+  pw.Bp = h->Bp;
+  pw.Mp = Mp;
+  pw.V = h->cfg.V;
+  pw.xp = at<int32_t>(h, h->L.xp);
+  pw.lse = at<float>(h, h->L.lse);
+  pw.flags = p_flags(h);
+  pw.prep_blocks = prep_blocks;
+  hipLaunchKernelGGL(prep_tokens_kernel<float>, dim3(prep_blocks), dim3(256), 0, st, pw);
   HIP_TRY(hipGetLastError());
   return sort_segments<float>(h, T, perm, seg_start, nseg, st);
 }
@@ -1632,10 +1679,18 @@ int rnnlm_sort_segments_static(const int32_t *x, int32_t T, int32_t B, int32_t V
   const int prep_blocks = (int)blocks_for(Mp, 256);
   // the array keeps the previous call's contents: the flag starts at zero, the ids of all Mp positions are rewritten
   hipLaunchKernelGGL(fill_kernel<int32_t>, dim3(1), dim3(64), 0, st, sc->flags, 64L, 0);
-  hipLaunchKernelGGL(prep_tokens_kernel<float>, dim3(prep_blocks), dim3(256), 0, st, x, (const int32_t *)nullptr, T, B,
-                     (int)Bp, (int)Mp, V, sc->xp, (int32_t *)nullptr, sc->lse, sc->flags, (const float *)nullptr, 0, 0,
-                     (float *)nullptr, (unsigned *)nullptr, prep_blocks, (const float *)nullptr, (float *)nullptr,
-                     (const float *)nullptr, 0, (float *)nullptr);
+  PrepWindow<float> pw = {};
+  pw.x = x;
+  pw.Tn = T;
+  pw.B = B;
+  pw.Bp = (int)Bp;
+  pw.Mp = (int)Mp;
+  pw.V = V;
+  pw.xp = sc->xp;
+  pw.lse = sc->lse;
+  pw.flags = sc->flags;
+  pw.prep_blocks = prep_blocks;
+  hipLaunchKernelGGL(prep_tokens_kernel<float>, dim3(prep_blocks), dim3(256), 0, st, pw);
   hipLaunchKernelGGL(rank_sort_kernel, dim3(blocks_for(M, 64)), dim3(1024), 0, st, sc->xp, M, B, (int)Bp, perm);
   hipLaunchKernelGGL(segment_kernel, dim3(1), dim3(1024), 0, st, sc->xp, perm, M, B, (int)Bp, seg_start, nseg);
   hipLaunchKernelGGL(static_flag_kernel, dim3(1), dim3(64), 0, st, sc->flags, range_flag);

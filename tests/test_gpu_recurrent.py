@@ -1,0 +1,63 @@
+"""GPU parity of the persistent recurrent kernel over the forms its launch rule picks (number of 32-wide contraction
+blocks per wave, one or two 16-row blocks of streams, four or eight waves, streams per group): fp32 against the fp64 CPU
+oracle at test_gpu_parity.py's tolerances; bf16 bitwise between the two state exchanges and between a window scored
+with all its streams and with a few of them (the order of every sum depends on the hidden size alone)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_1502_00512_amd import binding, synth
+from test_gpu_parity import check_grad, check_logp, dev, make_pair, tokens
+
+pytestmark = pytest.mark.gpu
+
+FP32, BF16 = binding.RNNLM_FP32, binding.RNNLM_BF16_FP32MASTER
+
+
+@pytest.mark.parametrize("V,H,B,T", [
+    (300, 8, 1, 3),       # one workgroup, one wave with work
+    (300, 33, 9, 4),      # two streams per group, the last group one
+    (300, 161, 130, 3),   # 17 streams per group: two row blocks
+    (300, 290, 17, 2),    # 10 blocks over four waves: the last wave has one
+    (300, 1000, 200, 2),  # 25 streams per group, 32 blocks
+])
+def test_fp32_against_oracle(V, H, B, T):
+    g, o = make_pair(V, H, B, T, FP32, seed=V + H + B, scale=0.3 if H < 100 else 0.05, bias_scale=0.5)
+    tok = tokens(V, 2 * B * T + B + 1, 6)
+    x, y = O.stream_chunk(tok, B, T, 0)
+    g.rnnlm_forward_logprob(dev(x), dev(y))
+    O.forward_logprob(o, x, y)
+    assert np.abs(g.h_state.cpu().numpy() - o.h).max() < 2e-5
+    x, y = O.stream_chunk(tok, B, T, 1)
+    r = g.rnnlm_grad_chunk(dev(x), dev(y))
+    ref = O.grad_chunk(o, x, y)
+    check_logp(r["logp"], ref["logp"])
+    for k in ("gE", "gU", "gWo", "gb"):
+        check_grad(k, r[k], ref[k])
+    g.rnnlm_check()
+
+
+@pytest.mark.parametrize("H,B,few", [(40, 256, 3), (200, 100, 1), (650, 250, 7), (1024, 129, 16), (1100, 256, 5), (2000, 120, 9)])
+def test_bf16_exchange_and_group_size(H, B, few):
+    V, T = 500, 5
+    E, U, Wo, b = synth.make_weights(V, H, "normal", 0.1 if H < 500 else 0.03, 3)
+    x = tokens(V, T * B, 11).reshape(T, B)
+    y = tokens(V, T * B, 12).reshape(T, B)
+
+    def run(n, mode):
+        m = binding.Rnnlm(E, U, Wo, b, n, T, BF16)
+        m.rnnlm_set_recurrent_exchange(mode)
+        for _ in range(3):
+            m.rnnlm_forward_logprob(dev(x[:, :n]), dev(y[:, :n]))
+        grads = m.rnnlm_grad_chunk(dev(x[:, :n]), dev(y[:, :n]))
+        m.rnnlm_check()
+        return m.h_state.cpu(), grads
+
+    h, g = run(B, binding.RNNLM_EXCHANGE_AUTO)
+    hc, gc = run(B, binding.RNNLM_EXCHANGE_CHIP_WIDE)
+    assert torch.equal(h, hc)
+    for k in g:
+        assert torch.equal(g[k], gc[k]), k
+    hf, _ = run(few, binding.RNNLM_EXCHANGE_AUTO)
+    assert torch.equal(h[:few], hf)
