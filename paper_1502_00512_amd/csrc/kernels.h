@@ -25,7 +25,7 @@ __global__ void stream_chunk_kernel(const int32_t *__restrict__ tok, long L, lon
 //   counters of the persistent recurrent kernel that follows (slot / counters == nullptr: tokens only).  Also
 //   gives the exchange buffers of the persistent recurrent kernels (ring[0] forward, ring[1] backward; nullptr: none)
 //   their first contents: UNWRITTEN, and the carried state, in operand order, as the forward step before the first.
-//   prep_blocks covers max(Mp, Bp*Hp, ring pieces of 16 bytes) threads.
+//   prep_blocks covers max(Mp, Bp*Hp, ring pieces of 16 bytes, SYNC_WORDS) threads.
 // blockIdx.x >= prep_blocks (present when X or Xc != nullptr), padded row r = blockIdx.x - prep_blocks:
 //   - a1, embedding gather (r < T*Bp): X[r][:] = E[x of that position][:] (fp32), zero on padding.  Compressed
 //     architecture (Xc != nullptr): the row is an operand of the contraction through the layer below the

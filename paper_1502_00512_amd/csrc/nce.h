@@ -62,6 +62,27 @@ __global__ void __launch_bounds__(256) nce_prep_kernel(const int32_t *__restrict
   for (int c = threadIdx.x; c < Hp / VEC; c += 256) dst[c] = (j < K) ? src[c] : zero;
 }
 
+// Dot product of two compute-type rows of n values (n a multiple of 16 / sizeof(T)), one wave: 16-byte loads, per-lane
+// sums, then a butterfly.  Every lane returns the sum.
+template <typename T>
+__device__ inline float wave_dot(const T *__restrict__ x, const T *__restrict__ y, int n, int lane) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  float acc = 0.0f;
+  for (int c = lane * VEC; c < n; c += 64 * VEC) {
+    union {
+      u32x4_t u;
+      T t[VEC];
+    } a, b;
+    a.u = *reinterpret_cast<const u32x4_t *>(x + c);
+    b.u = *reinterpret_cast<const u32x4_t *>(y + c);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc = fmaf(to_f32(a.t[e]), to_f32(b.t[e]), acc);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  return acc;
+}
+
 // Score of the target word of every position: dt[row] = Wo_c[y].Hs[row] + b[y] - shift - lnq[y]
 // (lnq == nullptr: no noise term).  One wave per padded position (4 per workgroup); lanes stride the
 // row, then a butterfly sum.  out (may be nullptr) receives the valid positions in compact order t*B + s.
@@ -80,10 +101,7 @@ __global__ void __launch_bounds__(256) nce_target_score_kernel(const T *__restri
     return;
   }
   const T *hrow = Hs1 + (long)row * Hp, *wrow = Wo_c + (long)y * Hp;
-  float acc = 0.0f;
-  for (int c = lane; c < Hp; c += 64) acc = fmaf(to_f32(hrow[c]), to_f32(wrow[c]), acc);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  const float acc = wave_dot(hrow, wrow, Hp, lane);
   if (lane == 0) {
     const float v = acc + b[y] - shift - (lnq ? lnq[y] : 0.0f);
     dt[row] = v;
@@ -111,10 +129,7 @@ __global__ void __launch_bounds__(256) score_candidates_kernel(const T *__restri
     w = min(max(w, 0), V - 1);
   }
   const T *frow = F + row * Dp, *wrow = Wc + (long)w * Dp;
-  float acc = 0.0f;
-  for (int c = lane; c < Dp; c += 64) acc = fmaf(to_f32(frow[c]), to_f32(wrow[c]), acc);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  const float acc = wave_dot(frow, wrow, Dp, lane);
   if (lane == 0) out[item] = acc + b[w] - shift;
 }
 

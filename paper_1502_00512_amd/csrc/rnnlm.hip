@@ -254,7 +254,9 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   Hp = (int)round_up(c.H, PAD_H);
   const int Dp = Pp > 0 ? Pp : Hp;
   Vp = (int)round_up(c.V, PAD_V);
-  Bp = (int)round_up(c.B, PAD_B);
+  // the persistent recurrent kernel takes streams as they come; the per-step contractions need whole 32-row blocks
+  const RecurrentPlan plan = recurrent_plan(c);
+  Bp = plan.nwg > 0 ? c.B : (int)round_up(c.B, PAD_B);
   MpMax = (int)round_up((long)c.T_max * Bp, PAD_M);
   nPart = Vp / (es == 4 ? 64 : BIG);  // one softmax-statistics partial per tile row block (fp32: of the smaller tile)
   if (es == 4) {
@@ -332,7 +334,6 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   L.has_part_res = es == 2 && Pp == 0 && Hp == RES_HP && Bp == RES_BP;
   if (L.has_part_res) L.part_res = take((size_t)RES_PART_STEP * 4);
   L.sync = take((size_t)SYNC_WORDS * 4);  // barrier / ticket counters of the persistent recurrent kernels
-  const RecurrentPlan plan = recurrent_plan(c);
   L.ring = take(plan.nwg > 0 ? 2 * align256(plan.ring_bytes((int)es)) : 0);  // forward, backward
   L.scalars = take(256);  // [0]: int nseg, [4]: int nseg of the noise-contrastive update list, [8..19]: int flags[3], [32]: double sum, [40]: double running
   L.total = o;
@@ -535,7 +536,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
   {
     StageTimer tm(h, RNNLM_STAGE_PREP, st);
     const long ring16 = persistent_ok(h) ? h->plan.ring_bytes(sizeof(T)) / 16 : 0;
-    const int prep_blocks = (int)blocks_for(std::max(std::max<long>(Mp, (long)Bp * Hp), ring16), 256);
+    const int prep_blocks = (int)blocks_for(std::max({(long)Mp, (long)Bp * Hp, ring16, (long)SYNC_WORDS}), 256);
     PrepWindow<T> pw = {};
     pw.x = x;
     pw.y = y;
@@ -1709,7 +1710,7 @@ int rnnlm_set_recurrent_exchange(rnnlm_t *h, int32_t mode) {
   if (mode != RNNLM_EXCHANGE_AUTO && mode != RNNLM_EXCHANGE_CHIP_WIDE && mode != RNNLM_EXCHANGE_XCD_LOCAL)
     return RNNLM_ERR_ARG;
   // the XCD-local exchange needs the placement the probe at init looks for and at most one block of 32 streams per XCD
-  if (mode == RNNLM_EXCHANGE_XCD_LOCAL && !(h->xcd_local && h->Bp / 32 <= NUM_XCD)) return RNNLM_ERR_ARG;
+  if (mode == RNNLM_EXCHANGE_XCD_LOCAL && !(h->xcd_local && round_up(h->cfg.B, PAD_B) / 32 <= NUM_XCD)) return RNNLM_ERR_ARG;
   h->exchange_mode = mode;
   return RNNLM_OK;
 }
