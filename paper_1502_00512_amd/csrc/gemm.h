@@ -478,7 +478,7 @@ struct EpiRnnFwd : EpiZeroInit {
 template <typename T>
 struct EpiOutFwd : EpiZeroInit {
   const float *b;   // [V]
-  T *ZT;            // [Vp][ldz]
+  T *ZT;            // [Vp][ldz], or nullptr: statistics only
   float2 *part;     // [Vp / BM][ldz]: one (max, sum exp) per tile row block and position
   const int *yp;    // [Mp] target id per position, -1 on padding
   float *zy;        // [Mp] target logit
@@ -587,6 +587,7 @@ struct EpiOutFwd : EpiZeroInit {
       }
       part[(long)(c.tile_row0 / BM) * ldz + c.tile_col0 + c.tid] = a;
     }
+    if (!ZT) return;  // evaluation: nobody reads the logits, and writing them takes a quarter of the kernel's time
     __syncthreads();
     store_tile<BM, BN, TM, TN, NT>(acc, c, ZT, ldz);
   }

@@ -653,7 +653,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     StageTimer tm(h, RNNLM_STAGE_OUT_FWD, st);
     EpiOutFwd<T> epi;
     epi.b = h->buf.b;
-    epi.ZT = at<T>(h, h->L.ZT);
+    epi.ZT = sort_inputs ? at<T>(h, h->L.ZT) : nullptr;  // evaluation wants the statistics only
     epi.part = at<float2>(h, h->L.stat);
     epi.yp = yp;
     epi.zy = zy;
