@@ -248,80 +248,103 @@ __global__ void rnn_step_bwd_kernel(const float *__restrict__ part, long split_s
   }
 }
 
+// Sum of n log-probabilities in fp64 with a fixed reduction tree, by a workgroup of 1024 threads; raises flags[1] when
+// the result is not finite.  counters != nullptr: also clears the counters of the persistent recurrent kernel (the sum
+// sits between its forward and its backward launch).
+struct WindowSum {
+  double *out, *running;  // either may be nullptr: the sum, and what it is added to
+  int32_t *flags;
+  unsigned *counters;
+};
+template <class Load>
+__device__ inline void window_sum(const WindowSum &w, int n, Load &&load) {
+  __shared__ double sh[1024];
+  if (w.counters)
+    for (int i = threadIdx.x; i < SYNC_WORDS; i += 1024) w.counters[i] = 0u;
+  double a = 0.0;
+  for (int i = threadIdx.x; i < n; i += 1024) a += (double)load(i);
+  sh[threadIdx.x] = a;
+  __syncthreads();
+  for (int k = 512; k > 0; k >>= 1) {
+    if ((int)threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    const double s = sh[0];
+    if (w.out) *w.out = s;
+    if (w.running) *w.running += s;
+    if (!(s == s) || s - s != 0.0) w.flags[1] = 1;
+  }
+}
+__global__ void __launch_bounds__(1024) sum_logp_kernel(const float *__restrict__ logp, int n, const WindowSum w) {
+  window_sum(w, n, [&](int i) { return logp[i]; });
+}
+
 // ---- a4 (part 1): merge the per-row-block (max, sum exp) partials of each position into the log
 // normaliser, and form log P(target) = z_target - lse (Sec. 4.2: explicitly normalised output).
-// Block = 64 positions x 16 groups of partials; each group is merged sequentially in a fixed order, then
-// the 16 group results are merged in order by the group-0 thread.
+// Workgroup = MERGE_M positions x 1024 / MERGE_M groups of partials: a group is merged sequentially in a fixed order,
+// the four groups of a wave by exchanges between its lanes, then the 16 waves' results in order.  Bound by memory
+// latency: with 64 positions per workgroup 2560 positions ran on 40 compute units (9.5 us, and 5 for the sum; here 8 for both).
+// done != nullptr: the last workgroup to finish also forms the window's sum (a launch of its own took 4-5 us): the
+// log-probabilities it adds up move with agent-scope accesses, each workgroup's before its arrival at the counter.
+constexpr int MERGE_M = 16;
 __global__ void __launch_bounds__(1024) merge_stats_kernel(const float2 *__restrict__ part, int nPart, long ldz, int T,
                                                            int B, int Bp, const float *__restrict__ zy,
                                                            float *__restrict__ lse, float *__restrict__ logp_int,
-                                                           float *__restrict__ logp_out) {
-  __shared__ float2 sh[16][64];
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int m = blockIdx.x * 64 + lane;
+                                                           float *__restrict__ logp_out, unsigned *__restrict__ done,
+                                                           const WindowSum w) {
+  constexpr int GROUPS = 1024 / MERGE_M;
+  __shared__ float2 sh[16][MERGE_M];
+  __shared__ int last;
+  const int pos = threadIdx.x % MERGE_M, grp = threadIdx.x / MERGE_M;
+  const int m = blockIdx.x * MERGE_M + pos;
   const bool valid = m < T * Bp;
   float mx = -INFINITY, sum = 0.0f;
-  if (valid) {
-    auto merge = [&](const float2 q) {
-      if (q.y > 0.0f) {
-        const float nmx = fmaxf(mx, q.x);
-        sum = sum * __expf(mx - nmx) + q.y * __expf(q.x - nmx);
-        mx = nmx;
-      }
-    };
-    int p = grp;
-    for (; p + 48 < nPart; p += 64) {  // four partials per round: their loads are independent
-      float2 q[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) q[u] = part[(long)(p + 16 * u) * ldz + m];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) merge(q[u]);
-    }
-    for (; p < nPart; p += 16) merge(part[(long)p * ldz + m]);
-  }
-  sh[grp][lane] = make_float2(mx, sum);
-  __syncthreads();
-  if (grp != 0 || !valid) return;
-  const int t = m / Bp, s = m % Bp;
-  if (s >= B) return;  // padding keeps lse = +inf
-  for (int g = 1; g < 16; ++g) {
-    const float2 q = sh[g][lane];
+  auto merge = [&](const float2 q) {
     if (q.y > 0.0f) {
       const float nmx = fmaxf(mx, q.x);
       sum = sum * __expf(mx - nmx) + q.y * __expf(q.x - nmx);
       mx = nmx;
     }
+  };
+  if (valid) {
+    int p = grp;
+    for (; p + 3 * GROUPS < nPart; p += 4 * GROUPS) {  // four partials per round: their loads are independent
+      float2 q[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) q[u] = part[(long)(p + GROUPS * u) * ldz + m];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) merge(q[u]);
+    }
+    for (; p < nPart; p += GROUPS) merge(part[(long)p * ldz + m]);
   }
-  const float l = mx + __logf(sum);
-  lse[m] = l;
-  const float lp = zy[m] - l;
-  logp_int[t * B + s] = lp;
-  if (logp_out) logp_out[t * B + s] = lp;
-}
-
-// Sum of the window's log-probabilities in fp64 with a fixed reduction tree; raises flags[1] when the
-// result is not finite.  counters != nullptr: also clears the barrier / ticket counters of the
-// persistent recurrent kernel (this kernel sits between its forward and its backward launch).
-__global__ void sum_logp_kernel(const float *__restrict__ logp, int n, double *__restrict__ out,
-                                double *__restrict__ running, int32_t *__restrict__ flags,
-                                unsigned *__restrict__ counters) {
-  __shared__ double sh[1024];
-  if (counters)  // for the backward recurrent kernel
-    for (int i = threadIdx.x; i < SYNC_WORDS; i += 1024) counters[i] = 0u;
-  double a = 0.0;
-  for (int i = threadIdx.x; i < n; i += 1024) a += (double)logp[i];
-  sh[threadIdx.x] = a;
+#pragma unroll
+  for (int o = MERGE_M; o < 64; o <<= 1) {
+    float2 q;
+    q.x = __shfl_xor(mx, o, 64);
+    q.y = __shfl_xor(sum, o, 64);
+    merge(q);
+  }
+  if ((threadIdx.x & 63) < MERGE_M) sh[threadIdx.x >> 6][pos] = make_float2(mx, sum);
   __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
+  const int t = m / Bp, s = m % Bp;
+  if (threadIdx.x < MERGE_M && valid && s < B) {  // padding keeps lse = +inf
+    for (int g = 1; g < 16; ++g) merge(sh[g][pos]);
+    const float l = mx + __logf(sum);
+    lse[m] = l;
+    const float lp = zy[m] - l;
+    __hip_atomic_store(logp_int + t * B + s, lp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (logp_out) logp_out[t * B + s] = lp;
   }
-  if (threadIdx.x == 0) {
-    const double s = sh[0];
-    if (out) *out = s;
-    if (running) *running += s;
-    if (!(s == s) || s - s != 0.0) flags[1] = 1;
+  if (!done) return;
+  if (threadIdx.x < 64) {  // the wave that stored: its stores are acknowledged before the arrival
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (threadIdx.x == 0)
+      last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
   }
+  __syncthreads();
+  if (!last) return;
+  window_sum(w, T * B, [&](int i) { return __hip_atomic_load(logp_int + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); });
 }
 
 // ---- a4 (part 2) + a5: fused softmax gradient, in place on the vocabulary-major logits ----------

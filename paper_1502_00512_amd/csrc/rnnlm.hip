@@ -522,7 +522,8 @@ int sort_segments(rnnlm_t *h, int Tn, int32_t *perm, int32_t *seg, int32_t *nseg
 // started on the side stream as soon as the padded ids exist (joined in backward_window).
 template <typename T>
 int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float *logp_out, bool advance_state,
-                   bool with_output, hipStream_t st, bool sort_inputs = false, bool need_feat = false) {
+                   bool with_output, hipStream_t st, bool sort_inputs = false, bool need_feat = false,
+                   const WindowSum *wsum = nullptr) {
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp, Vp = h->Vp;
   const int Mrows = Tn * Bp;
@@ -672,8 +673,9 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     }
   }
   StageTimer tm(h, RNNLM_STAGE_STATS, st);
-  hipLaunchKernelGGL(merge_stats_kernel, dim3(blocks_for(Mrows, 64)), dim3(1024), 0, st, at<float2>(h, h->L.stat),
-                     nPart, ldz, Tn, c.B, Bp, zy, lse, at<float>(h, h->L.logp_int), logp_out);
+  hipLaunchKernelGGL(merge_stats_kernel, dim3(blocks_for(Mrows, MERGE_M)), dim3(1024), 0, st, at<float2>(h, h->L.stat),
+                     nPart, ldz, Tn, c.B, Bp, zy, lse, at<float>(h, h->L.logp_int), logp_out,
+                     wsum ? p_counter(h) + sync_word(0, 0) : nullptr, wsum ? *wsum : WindowSum{});
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
@@ -1141,16 +1143,18 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
 template <typename T>
 int window_call(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float *logp, double *sum_logp,
                 const UpdateTargets *u, bool advance_state, hipStream_t st, const NceCall *nce = nullptr) {
-  int rc = forward_window<T>(h, x, y, Tn, logp, advance_state, nce == nullptr, st, u != nullptr);
+  const bool want_sum = sum_logp || u;
+  const WindowSum ws = {sum_logp ? sum_logp : p_sum(h), nullptr, p_flags(h), u ? p_counter(h) : nullptr};
+  int rc = forward_window<T>(h, x, y, Tn, logp, advance_state, nce == nullptr, st, u != nullptr, false,
+                             want_sum && !nce ? &ws : nullptr);
   if (rc) return rc;
   if (nce) {  // per-position losses take the place of the log-probabilities
     rc = nce_forward<T>(h, Tn, *nce, st);
     if (rc) return rc;
-  }
-  if (sum_logp || u) {
-    hipLaunchKernelGGL(sum_logp_kernel, dim3(1), dim3(1024), 0, st, at<float>(h, h->L.logp_int), Tn * h->cfg.B,
-                       sum_logp ? sum_logp : p_sum(h), (double *)nullptr, p_flags(h), u ? p_counter(h) : nullptr);
-    HIP_TRY(hipGetLastError());
+    if (want_sum) {
+      hipLaunchKernelGGL(sum_logp_kernel, dim3(1), dim3(1024), 0, st, at<float>(h, h->L.logp_int), Tn * h->cfg.B, ws);
+      HIP_TRY(hipGetLastError());
+    }
   }
   if (u) rc = backward_window<T>(h, Tn, *u, nce, st);
   return rc;
@@ -1585,11 +1589,11 @@ int rnnlm_perplexity(rnnlm_t *h, const int32_t *tok, int64_t N, int32_t T, doubl
   for (long k = 0; k < nchunks; ++k) {
     hipLaunchKernelGGL(stream_chunk_kernel, dim3(blocks_for((long)T * B, 256)), dim3(256), 0, st, tok, L, k, T, B, xt,
                        yt);
-    rc = (h->cfg.precision == RNNLM_FP32) ? forward_window<float>(h, xt, yt, T, nullptr, true, true, st)
-                                          : forward_window<bf16_t>(h, xt, yt, T, nullptr, true, true, st);
+    const WindowSum ws = {nullptr, p_running(h), p_flags(h), nullptr};
+    rc = (h->cfg.precision == RNNLM_FP32)
+             ? forward_window<float>(h, xt, yt, T, nullptr, true, true, st, false, false, &ws)
+             : forward_window<bf16_t>(h, xt, yt, T, nullptr, true, true, st, false, false, &ws);
     if (rc) return rc;
-    hipLaunchKernelGGL(sum_logp_kernel, dim3(1), dim3(1024), 0, st, at<float>(h, h->L.logp_int), T * B,
-                       (double *)nullptr, p_running(h), p_flags(h), (unsigned *)nullptr);
   }
   HIP_TRY(hipGetLastError());
   double total = 0.0;
