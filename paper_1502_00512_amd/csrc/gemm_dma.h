@@ -23,9 +23,11 @@ typedef const __attribute__((address_space(1))) void *global_void_ptr;
 // physical chunk = logical ^ ((row >> 1) & 7).
 // KROW tile: one row per k, ROWS*2 bytes; a transposing 8-byte read is served 32 lanes per clock =
 // 4 k rows x 64 contiguous bytes, which must land in 4 distinct 64-byte bank groups:
-// physical chunk = logical ^ (4 * (k & 3)) (a multiple of 4, so each 64-byte run stays contiguous).
+// physical chunk = logical ^ (4 * (k & 3)) (a multiple of 4, so each 64-byte run stays contiguous).  64-row tiles have
+// two k rows per 256 bytes, so only rows k and k + 2 collide: physical chunk = logical ^ (4 * (k / 2 % 2)).
 __device__ inline int rowk_swz(int row) { return (row >> 1) & 7; }
-__device__ inline int krow_swz(int k) { return (k & 3) << 2; }
+template <int ROWS>
+__device__ inline int krow_swz(int k) { return ROWS == 64 ? ((k >> 1) & 1) << 2 : (k & 3) << 2; }
 
 // (Device pass only: the buffer-resource type does not exist for the host target, and a kernel template
 // whose body fails to instantiate there loses its launch stub.)
@@ -55,7 +57,7 @@ struct DmaLoader {
       } else {
         constexpr int CPR = ROWS / 8;
         const int k = q / CPR, p = q % CPR;
-        off[i] = (int)(k * ld_bytes + ((p ^ krow_swz(k)) << 4));
+        off[i] = (int)(k * ld_bytes + ((p ^ krow_swz<ROWS>(k)) << 4));
       }
     }
     const long start = (LAYOUT == ROWK) ? row0 * ld_bytes + k0 * 2 : k0 * ld_bytes + row0 * 2;
@@ -85,7 +87,7 @@ struct DmaLoader {
 //   KROW: transposing reads (see FragReader<bf16_t, ROWS, KROW> in gemm.h): source lane s of a 16-lane
 //         block points at tile[k][n .. n+3], k = 16 st + 8 h + s/4 (+4 for the second read),
 //         n = r0' + 32 i + 4 (s % 4); byte offset k*ROWS*2 + (((n >> 3) ^ swz(k)) << 4) + (n & 7)*2, and
-//         swz(k) = 4 (s/4 & 3) is a per-lane constant: pre[i] = (8 h + s/4)*ROWS*2 + that chunk term,
+//         swz(k) = 4 (s/4 & 3) (64 rows: 4 (s/8 & 1)) is a per-lane constant: pre[i] = (8 h + s/4)*ROWS*2 + that chunk term,
 //         immediate = st * 16 * ROWS * 2 (+ 4 * ROWS * 2).
 template <int ROWS, int LAYOUT>
 struct DmaFragAddr;
@@ -110,7 +112,7 @@ struct DmaFragAddr<ROWS, KROW> {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int n = (r0 - s) + 32 * i + 4 * (s & 3);
-      pre[i] = k * (ROWS * 2) + ((((n >> 3) ^ krow_swz(k)) << 4) | ((n & 7) << 1));
+      pre[i] = k * (ROWS * 2) + ((((n >> 3) ^ krow_swz<ROWS>(k)) << 4) | ((n & 7) << 1));
     }
   }
   __device__ inline bf16x8_t get(const char *tile, int i, int st) const {

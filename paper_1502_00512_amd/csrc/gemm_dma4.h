@@ -74,7 +74,7 @@ struct DmaLoader32 {
       } else {
         constexpr int CPR = ROWS * ES / 16;
         const int k = q / CPR, p = q % CPR;
-        off[i] = (int)(k * ld_bytes + ((p ^ (ES == 2 ? krow_swz(k) : krow_swz_f32(k))) << 4));
+        off[i] = (int)(k * ld_bytes + ((p ^ (ES == 2 ? krow_swz<ROWS>(k) : krow_swz_f32(k))) << 4));
       }
     }
     const long start = (LAYOUT == ROWK) ? row0 * ld_bytes + k0 * ES : k0 * ld_bytes + row0 * ES;

@@ -183,8 +183,11 @@ hipError_t big_gemm(hipStream_t st, const void *A, long lda, const void *B, long
   }
 }
 
-// The mid-sized contractions (128x128 output tiles: noise-panel products, the layers of the compressed
-// architecture): bf16 operands take the direct global->LDS kernels (the ring when an operand is K-major).
+// The mid-sized contractions (noise-panel products, the layers of the compressed architecture, the recurrent weight
+// gradient): 128x128 output tiles, or 64x64 where those would leave compute units without a workgroup.  bf16 operands
+// take the direct global->LDS kernels (the ring when an operand is K-major or the tile is 64x64: its three K blocks in
+// flight are what keeps a lone workgroup's matrix cores fed; register-staged 64x64 tiles took 0.65 us per 64 values of
+// the contraction, the ring 0.4).
 template <typename T, int LA, int LB, class Epi>
 hipError_t mid_gemm(hipStream_t st, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
                     int splits, const Epi &epi, int band = 4) {
@@ -195,6 +198,8 @@ hipError_t mid_gemm(hipStream_t st, const void *A, long lda, const void *B, long
     F32Plan plan = f32_plan(Mg, Ng, K, 1);
     plan.splits = splits;
     return f32_gemm<LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, plan, epi, band);
+  } else if (fits && (Mg % 128 || Ng % 128 || (Mg / 128) * (Ng / 128) * splits < 256)) {
+    return launch_gemm_dma4<bf16_t, 64, 64, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
   } else if constexpr (LA == KROW || LB == KROW) {
     if (fits) return launch_gemm_dma4<bf16_t, 128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
     return launch_gemm<T, 128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
@@ -990,14 +995,11 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     epi.C = c.H;
     epi.alpha = u.alpha;
     epi.lr = u.lr;
-    if constexpr (sizeof(T) == 4) {
-      HIP_TRY((f32_gemm<KROW, KROW>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, f32_plan(Hp, Hp, Mp, 1), epi)));
-    } else if ((long)(Hp / BIG) * (Hp / BIG) >= 64) {
-      HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, 1, epi)));
-    } else if (Hp <= 1024) {  // small matrix: 64x64 tiles give up to 256 workgroups
-      HIP_TRY((launch_gemm<T, 64, 64, 2, 2, KROW, KROW>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, 1, epi)));
+    if (sizeof(T) == 2 && (long)(Hp / BIG) * (Hp / BIG) >= 64) {
+      if constexpr (sizeof(T) == 2)
+        HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, 1, epi)));
     } else {
-      HIP_TRY((launch_gemm<T, 128, 128, 2, 2, KROW, KROW>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, 1, epi)));
+      HIP_TRY((mid_gemm<T, KROW, KROW>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, 1, epi)));
     }
   }
     return RNNLM_OK;
@@ -1036,13 +1038,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
       epi.C = c.H;
       epi.alpha = u.alpha;
       epi.lr = u.lr;
-      if constexpr (sizeof(T) == 4) {
-        HIP_TRY((f32_gemm<KROW, KROW>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.dP_c), h->Pp, Hp, h->Pp, Mp,
-                                      f32_plan(Hp, h->Pp, Mp, 1), epi)));
-      } else {
-        HIP_TRY((launch_gemm<T, 64, 64, 2, 2, KROW, KROW>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.dP_c), h->Pp, Hp,
-                                                          h->Pp, Mp, 1, epi)));
-      }
+      HIP_TRY((mid_gemm<T, KROW, KROW>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.dP_c), h->Pp, Hp, h->Pp, Mp, 1, epi)));
     }
     {
     // Wo[v][j] -= lr * sum_m dz[v][m] Hs[m][j]: bf16 in the matrix's own orientation, fp32 and the compressed
@@ -1125,11 +1121,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     epi.C = c.P;
     epi.alpha = u.alpha;
     epi.lr = u.lr;
-    if constexpr (sizeof(T) == 4) {
-      HIP_TRY((f32_gemm<KROW, KROW>(st, at<T>(h, h->L.Xp_c), h->Pp, dA_c, Hp, h->Pp, Hp, Mp, f32_plan(h->Pp, Hp, Mp, 1), epi)));
-    } else {
-      HIP_TRY((launch_gemm<T, 64, 64, 2, 2, KROW, KROW>(st, at<T>(h, h->L.Xp_c), h->Pp, dA_c, Hp, h->Pp, Hp, Mp, 1, epi)));
-    }
+    HIP_TRY((mid_gemm<T, KROW, KROW>(st, at<T>(h, h->L.Xp_c), h->Pp, dA_c, Hp, h->Pp, Hp, Mp, 1, epi)));
   }
 
   if (!early_rec) {
