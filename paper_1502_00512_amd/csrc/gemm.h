@@ -702,45 +702,37 @@ struct EpiSgdT : EpiZeroInit {
       }
       return;
     }
+    // Ragged edge, or rows that are not 16-byte aligned: a 32-row block's master values are all requested before any is
+    // used (one by one, every store holds up the next load: V x H = 33278 x 650 spent 100 us in its edge tiles alone).
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int r = col0 + j * 32 + (lane & 31);  // weight row
       if (r >= R) continue;
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i) {
+        float w[4][4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int j0 = row0 + i * 32 + 8 * g + ((lane >> 5) << 2);  // first of 4 weight columns
-          if (j0 >= C) continue;
-          const long idx = (long)r * ldw + j0;
-          if (vec_ok && j0 + 3 < C) {
-            f32x4_t nv;
-            if (alpha != 0.0f) {
-              const f32x4_t w = *reinterpret_cast<const f32x4_t *>(W + idx);
 #pragma unroll
-              for (int e = 0; e < 4; ++e) nv[e] = alpha * w[e] - lr * acc[i][j][4 * g + e];
-            } else {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) nv[e] = -lr * acc[i][j][4 * g + e];
-            }
-            *reinterpret_cast<f32x4_t *>(out + idx) = nv;
-            if (Wc) store4(Wc + (long)r * ldc + j0, nv);
-            if (WcT) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) WcT[(long)(j0 + e) * ldc + r] = from_f32<T>(nv[e]);
-            }
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (j0 + e < C) {
-                const float w = (alpha != 0.0f) ? alpha * W[idx + e] : 0.0f;
-                const float nv = w - lr * acc[i][j][4 * g + e];
-                out[idx + e] = nv;
-                if (Wc) Wc[(long)r * ldc + j0 + e] = from_f32<T>(nv);
-                if (WcT) WcT[(long)(j0 + e) * ldc + r] = from_f32<T>(nv);
-              }
-          }
+          for (int e = 0; e < 4; ++e) w[g][e] = (alpha != 0.0f && j0 + e < C) ? W[(long)r * ldw + j0 + e] : 0.0f;
         }
+#if defined(__HIP_DEVICE_COMPILE__)
+        __builtin_amdgcn_sched_barrier(0);
+#endif
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int j0 = row0 + i * 32 + 8 * g + ((lane >> 5) << 2);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (j0 + e < C) {
+              const float nv = ((alpha != 0.0f) ? alpha * w[g][e] : 0.0f) - lr * acc[i][j][4 * g + e];
+              out[(long)r * ldw + j0 + e] = nv;
+              if (Wc) Wc[(long)r * ldc + j0 + e] = from_f32<T>(nv);
+              if (WcT) WcT[(long)(j0 + e) * ldc + r] = from_f32<T>(nv);
+            }
+        }
+      }
     }
   }
 };
@@ -872,22 +864,35 @@ struct EpiSgd : EpiZeroInit {
       return;
     }
 #endif
+    // wave tile at the ragged edge: a 32x32 block's master values are all requested before any is used
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j) {
+      const int col = col0 + j * 32 + lc;
+      if (col >= C) continue;
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = col0 + j * 32 + lc;
-        if (col >= C) continue;
+      for (int i = 0; i < TM; ++i) {
+        const int top = row0 + i * 32 + ((lane >> 5) << 2);
+        const float *wp = W + (long)top * ldw + col;
+        float *op = out + (long)top * ldw + col;
+        float w[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const long row = row0 + i * 32 + RNNLM_ACC_ROW(r, lane);
-          if (row >= R) continue;
-          const float w = (alpha != 0.0f) ? alpha * W[row * ldw + col] : 0.0f;
-          const float nv = w - lr * acc[i][j][r];
-          out[row * ldw + col] = nv;
-          if (Wc) Wc[row * ldc + col] = from_f32<T>(nv);
+          const int d = 8 * (r >> 2) + (r & 3);
+          w[r] = (alpha != 0.0f && top + d < R) ? wp[(long)d * ldw] : 0.0f;
+        }
+#if defined(__HIP_DEVICE_COMPILE__)
+        __builtin_amdgcn_sched_barrier(0);
+#endif
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int d = 8 * (r >> 2) + (r & 3);
+          if (top + d >= R) continue;
+          const float nv = ((alpha != 0.0f) ? alpha * w[r] : 0.0f) - lr * acc[i][j][r];
+          op[(long)d * ldw] = nv;
+          if (Wc) Wc[(long)(top + d) * ldc + col] = from_f32<T>(nv);
         }
       }
+    }
   }
 };
 

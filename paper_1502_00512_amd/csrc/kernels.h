@@ -508,17 +508,18 @@ __global__ void segment_kernel(const int32_t *__restrict__ xp, const int32_t *__
 
 // ---- a10: segmented embedding update, atomic-free and order-fixed -------------------------------
 //   out[w][:] = alpha*E[w][:] - lr * sum_{m in run of w} dA[m][:]
-// blockIdx.x = run index (exits when >= *nseg), blockIdx.y = block of 256*VEC columns; a thread owns VEC
-// consecutive columns.  The run's members are dealt round-robin to PARTS partial sums (member i of the run goes
+// blockIdx.x = run index (exits when >= *nseg), blockIdx.y = block of 1024 columns.  The run's members are dealt
+// round-robin to PARTS partial sums (member i of the run goes
 // to sum i mod PARTS, each sum accumulated in ascending m), which are then added in order 0..PARTS-1: a fixed
 // summation tree, so results are bitwise reproducible.  All PARTS sums live in the thread's registers: a group
 // of 16 members is 16 independent row loads in flight, and the small workgroups (no LDS, no barrier) leave
 // eight of them resident per compute unit, which is what a pass made of dependent memory round trips (run
 // bounds -> position -> rows) needs: it is bound by latency times occupancy, not by bandwidth.
-// VEC = 4: H % 4 == 0; VEC = 1: any H.
+// A thread owns 4 consecutive columns (the rows of dA are tile-padded and aligned).  ALIGNED: H % 4 == 0, the rows of the
+// updated matrix are accessed 16 bytes at a time; otherwise (any H) element by element, the last group partly.
 // Ec (may be nullptr): compute copy [.][ldc] of the updated matrix, refreshed with the new row (the tied word
 // matrix of the compressed architecture is an operand of the output layer as well).
-template <int VEC, typename T>
+template <bool ALIGNED, typename T>
 __global__ void __launch_bounds__(256) scatter_update_kernel(const float *__restrict__ dA, int Hp, int H, int B,
                                                              int Bp, const int32_t *__restrict__ xp,
                                                              const int32_t *__restrict__ perm,
@@ -527,7 +528,7 @@ __global__ void __launch_bounds__(256) scatter_update_kernel(const float *__rest
                                                              const float *__restrict__ E, float *__restrict__ out,
                                                              float alpha, float lr, int compact_ld,
                                                              T *__restrict__ Ec, int ldc) {
-  constexpr int PARTS = 4, GROUP = 4 * PARTS;
+  constexpr int PARTS = 4, GROUP = 4 * PARTS, VEC = 4;
   const int g = blockIdx.x;
   if (g >= *nseg) return;
   const int col = (blockIdx.y * 256 + threadIdx.x) * VEC;
@@ -541,12 +542,14 @@ __global__ void __launch_bounds__(256) scatter_update_kernel(const float *__rest
 #pragma unroll
   for (int e = 0; e < VEC; ++e) old[e] = 0.0f;
   if (alpha != 0.0f) {
-    if (VEC == 4) {
+    if (ALIGNED) {
       const f32x4_t t = *reinterpret_cast<const f32x4_t *>(E + idx);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) old[e] = t[e];
     } else {
-      old[0] = E[idx];
+#pragma unroll
+      for (int e = 0; e < VEC; ++e)
+        if (col + e < H) old[e] = E[idx + e];
     }
   }
   auto row_of = [&](int r) {
@@ -554,13 +557,9 @@ __global__ void __launch_bounds__(256) scatter_update_kernel(const float *__rest
     return ((long)(m / B) * Bp + (m % B)) * Hp + col;
   };
   auto load_row = [&](long at, float (&v)[VEC]) {
-    if (VEC == 4) {
-      const f32x4_t t = *reinterpret_cast<const f32x4_t *>(dA + at);
+    const f32x4_t t = *reinterpret_cast<const f32x4_t *>(dA + at);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) v[e] = t[e];
-    } else {
-      v[0] = dA[at];
-    }
+    for (int e = 0; e < VEC; ++e) v[e] = t[e];
   };
   float acc[PARTS][VEC];
 #pragma unroll
@@ -604,17 +603,20 @@ __global__ void __launch_bounds__(256) scatter_update_kernel(const float *__rest
   float nv[VEC];
 #pragma unroll
   for (int e = 0; e < VEC; ++e) nv[e] = ((alpha != 0.0f) ? alpha * old[e] : 0.0f) - lr * acc[0][e];
-  if (VEC == 4) {
+  if (ALIGNED) {
     f32x4_t t;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) t[e] = nv[e];
     *reinterpret_cast<f32x4_t *>(out + oidx) = t;
   } else {
-    out[oidx] = nv[0];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+      if (col + e < H) out[oidx + e] = nv[e];
   }
   if (Ec) {
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) Ec[(long)w * ldc + col + e] = from_f32<T>(nv[e]);
+    for (int e = 0; e < VEC; ++e)
+      if (ALIGNED || col + e < H) Ec[(long)w * ldc + col + e] = from_f32<T>(nv[e]);
   }
 }
 

@@ -970,10 +970,10 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     T *Ec = (c.P > 0 && u.refresh_copies) ? Wo_c : nullptr;
     const int W = h->D, Wp = h->Dp;
     if (W % 4 == 0) {
-      hipLaunchKernelGGL((scatter_update_kernel<4, T>), dim3(Tn * c.B, (W + 1023) / 1024), dim3(256), 0, h->side, rows,
+      hipLaunchKernelGGL((scatter_update_kernel<true, T>), dim3(Tn * c.B, (W + 1023) / 1024), dim3(256), 0, h->side, rows,
                          Wp, W, c.B, Bp, xp, perm, seg, p_nseg(h), src, u.E, e_alpha, u.lr, u.e_compact_ld, Ec, Wp);
     } else {
-      hipLaunchKernelGGL((scatter_update_kernel<1, T>), dim3(Tn * c.B, (W + 255) / 256), dim3(256), 0, h->side, rows,
+      hipLaunchKernelGGL((scatter_update_kernel<false, T>), dim3(Tn * c.B, (W + 1023) / 1024), dim3(256), 0, h->side, rows,
                          Wp, W, c.B, Bp, xp, perm, seg, p_nseg(h), src, u.E, e_alpha, u.lr, u.e_compact_ld, Ec, Wp);
     }
     HIP_TRY(hipGetLastError());
