@@ -519,7 +519,13 @@ __global__ void segment_kernel(const int32_t *__restrict__ xp, const int32_t *__
 // updated matrix are accessed 16 bytes at a time; otherwise (any H) element by element, the last group partly.
 // Ec (may be nullptr): compute copy [.][ldc] of the updated matrix, refreshed with the new row (the tied word
 // matrix of the compressed architecture is an operand of the output layer as well).
-template <bool ALIGNED, typename T>
+// SCAN (windows of at most SCAN_MAX positions): no sorted list at all.  blockIdx.x = window position m; the workgroup
+// compares m's id with all others, gives up if it is not the first of its run, and otherwise has the run's members, in
+// ascending order, in LDS.  The 16 keys a thread compares are loaded together, so this costs one memory round trip and
+// two barriers, where the sort is two launches on a second stream and the events that tie it in (a window of 32
+// positions spent 30 us of host time on them).
+constexpr int SCAN_MAX = 4096;
+template <bool ALIGNED, bool SCAN, typename T>
 __global__ void __launch_bounds__(256) scatter_update_kernel(const float *__restrict__ dA, int Hp, int H, int B,
                                                              int Bp, const int32_t *__restrict__ xp,
                                                              const int32_t *__restrict__ perm,
@@ -527,15 +533,61 @@ __global__ void __launch_bounds__(256) scatter_update_kernel(const float *__rest
                                                              const int32_t *__restrict__ nseg,
                                                              const float *__restrict__ E, float *__restrict__ out,
                                                              float alpha, float lr, int compact_ld,
-                                                             T *__restrict__ Ec, int ldc) {
+                                                             T *__restrict__ Ec, int ldc, int M) {
   constexpr int PARTS = 4, GROUP = 4 * PARTS, VEC = 4;
   const int g = blockIdx.x;
-  if (g >= *nseg) return;
   const int col = (blockIdx.y * 256 + threadIdx.x) * VEC;
+  __shared__ unsigned short members[SCAN ? SCAN_MAX : 1];
+  int r0, r1, w;
+  if constexpr (SCAN) {
+    constexpr int KEYS = SCAN_MAX / 256;  // keys per thread: positions threadIdx.x + 256 k
+    __shared__ unsigned long long found[KEYS][4];
+    __shared__ int before[KEYS * 4], total;
+    auto key_of = [&](int m) { return xp[(m / B) * Bp + (m % B)]; };
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    w = key_of(g);
+    int key[KEYS];
+#pragma unroll
+    for (int k = 0; k < KEYS; ++k) key[k] = threadIdx.x + 256 * k < M ? key_of(threadIdx.x + 256 * k) : -1;
+    unsigned mine = 0;
+#pragma unroll
+    for (int k = 0; k < KEYS; ++k) {
+      const unsigned long long b = __ballot(key[k] == w);
+      if (lane == 0) found[k][wave] = b;
+      mine |= (unsigned)(key[k] == w) << k;
+    }
+    __syncthreads();
+    if (wave == 0) {  // members before each group of 64 positions
+      const int n = __popcll(found[lane >> 2][lane & 3]);
+      int incl = n;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
+      }
+      before[lane] = incl - n;
+      if (lane == 63) total = incl;
+    }
+    __syncthreads();
+    auto rank = [&](int m) {  // members before position m
+      return before[m >> 6] + __popcll(found[m >> 8][(m >> 6) & 3] & ((1ull << (m & 63)) - 1));
+    };
+    if (rank(g) != 0) return;  // an earlier position starts this run
+    for (; mine; mine &= mine - 1) {
+      const int m = threadIdx.x + 256 * (__ffs(mine) - 1);
+      members[rank(m)] = (unsigned short)m;
+    }
+    __syncthreads();
+    r0 = 0;
+    r1 = total;
+  } else {
+    if (g >= *nseg) return;
+    r0 = seg_start[g];
+    r1 = seg_start[g + 1];
+    const int m0 = perm[r0];
+    w = xp[(m0 / B) * Bp + (m0 % B)];
+  }
   if (col >= H) return;
-  const int r0 = seg_start[g], r1 = seg_start[g + 1];
-  const int m0 = perm[r0];
-  const int w = xp[(m0 / B) * Bp + (m0 % B)];
   const long idx = (long)w * H + col;
   // the row being updated does not depend on the sum: ask for it first
   float old[VEC];
@@ -553,7 +605,7 @@ __global__ void __launch_bounds__(256) scatter_update_kernel(const float *__rest
     }
   }
   auto row_of = [&](int r) {
-    const int m = perm[r];
+    const int m = SCAN ? members[r] : perm[r];
     return ((long)(m / B) * Bp + (m % B)) * Hp + col;
   };
   auto load_row = [&](long at, float (&v)[VEC]) {

@@ -523,11 +523,20 @@ int side_join(rnnlm_t *h, int slot, hipStream_t st) {
 template <typename T>
 int sort_segments(rnnlm_t *h, int Tn, int32_t *perm, int32_t *seg, int32_t *nseg, hipStream_t st);
 
-// sort_inputs: the window will be trained on, so the sort of its input ids for the embedding update is
-// started on the side stream as soon as the padded ids exist (joined in backward_window).
+// Does the embedding update find the positions of each word by itself (no sorted list)?  Not where the list names the
+// rows of a compact buffer, nor in windows its workgroups cannot compare in one go.  Beyond 1024 positions the plain
+// architecture sorts: its embedding update runs next to the output weight update, which every workgroup's comparisons
+// slow down (V = 64000, H = 1024, 128x20: 1253 us with them, 1241 sorted; compressed, where the update stands alone and
+// the sort delays the recurrent steps: 382 against 389).
+bool scan_ids(const rnnlm_t *h, int Tn, const UpdateTargets &u) {
+  return u.e_compact_ld == 0 && (long)Tn * h->cfg.B <= (h->cfg.P > 0 ? SCAN_MAX : 1024);
+}
+
+// train: a backward pass follows.  sort_inputs: its embedding update wants the input ids sorted: started on the side
+// stream as soon as the padded ids exist (the update runs on that stream too).
 template <typename T>
 int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float *logp_out, bool advance_state,
-                   bool with_output, hipStream_t st, bool sort_inputs = false, bool need_feat = false,
+                   bool with_output, hipStream_t st, bool train = false, bool sort_inputs = false, bool need_feat = false,
                    const WindowSum *wsum = nullptr) {
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp, Vp = h->Vp;
@@ -574,7 +583,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
       pw.plan = h->plan;
       pw.next = Hs_c + (long)Bp * Hp;
       pw.ring[0] = h->ws + h->L.ring;
-      if (sort_inputs) {
+      if (train) {
         pw.ring[1] = pw.ring[0] + align256(h->plan.ring_bytes(sizeof(T)));
         pw.dA = at<T>(h, h->L.dA_c);
         rows = Mp;  // rows [Mrows, Mp) of dA take part in the dU contraction: zero
@@ -659,7 +668,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     StageTimer tm(h, RNNLM_STAGE_OUT_FWD, st);
     EpiOutFwd<T> epi;
     epi.b = h->buf.b;
-    epi.ZT = sort_inputs ? at<T>(h, h->L.ZT) : nullptr;  // evaluation wants the statistics only
+    epi.ZT = train ? at<T>(h, h->L.ZT) : nullptr;  // evaluation wants the statistics only
     epi.part = at<float2>(h, h->L.stat);
     epi.yp = yp;
     epi.zy = zy;
@@ -956,11 +965,17 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     }
   }
 
+  // Where the output weight update is over before a second stream is tied in and out (four events: 20-30 us of host
+  // time and of latency between the streams), the small updates stay on the caller's stream (V = 1000, H = 64, 4x8:
+  // 117 -> 67 us; V = 10000, H = 256, 32x10 is faster with the second stream).
+  const double out_w_us = 2.0 * Vp * h->Dp * Mp / (sizeof(T) == 4 ? 1e8 : 6e8) + 8.0 * Vp * h->Dp / 4e6;
+  const bool serial = !nce && scan_ids(h, Tn, u) && out_w_us < 15.0;
+  hipStream_t es = serial ? st : h->side;
   // E[w] -= lr * sum_{m: x[m] = w} dA[m]: on the side stream, behind the sort helpers already queued there (joined at
   // the end of this function).
   auto embedding_update = [&]() -> int {
   {
-    StageTimer tm(h, RNNLM_STAGE_EMB, h->side);
+    StageTimer tm(h, RNNLM_STAGE_EMB, es);
     // plain: rows of dA, width H.  Compressed: rows of dx, width P, added on top of the output-side update the
     // same matrix has just received (training: in the master; gradient export: in the caller's buffer), and
     // the compute copy of the tied matrix follows.
@@ -969,13 +984,16 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     const float e_alpha = (c.P > 0 && !u.refresh_copies) ? 1.0f : u.alpha;
     T *Ec = (c.P > 0 && u.refresh_copies) ? Wo_c : nullptr;
     const int W = h->D, Wp = h->Dp;
+    const bool scan = scan_ids(h, Tn, u);
+#define RNNLM_SCATTER(ALIGNED, SCAN)                                                                                     \
+  hipLaunchKernelGGL((scatter_update_kernel<ALIGNED, SCAN, T>), dim3(Tn * c.B, (W + 1023) / 1024), dim3(256), 0, es, rows, \
+                     Wp, W, c.B, Bp, xp, perm, seg, p_nseg(h), src, u.E, e_alpha, u.lr, u.e_compact_ld, Ec, Wp, Tn * c.B)
     if (W % 4 == 0) {
-      hipLaunchKernelGGL((scatter_update_kernel<true, T>), dim3(Tn * c.B, (W + 1023) / 1024), dim3(256), 0, h->side, rows,
-                         Wp, W, c.B, Bp, xp, perm, seg, p_nseg(h), src, u.E, e_alpha, u.lr, u.e_compact_ld, Ec, Wp);
+      if (scan) RNNLM_SCATTER(true, true); else RNNLM_SCATTER(true, false);
     } else {
-      hipLaunchKernelGGL((scatter_update_kernel<false, T>), dim3(Tn * c.B, (W + 1023) / 1024), dim3(256), 0, h->side, rows,
-                         Wp, W, c.B, Bp, xp, perm, seg, p_nseg(h), src, u.E, e_alpha, u.lr, u.e_compact_ld, Ec, Wp);
+      if (scan) RNNLM_SCATTER(false, true); else RNNLM_SCATTER(false, false);
     }
+#undef RNNLM_SCATTER
     HIP_TRY(hipGetLastError());
   }
     return RNNLM_OK;
@@ -1012,12 +1030,12 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   const bool early_side = !nce && c.P == 0;
   const bool early_rec = early_side && (long)(Hp / BIG) * (Hp / BIG) < 256;
   if (early_side) {
-    int rc = side_fork(h, 0, st);
+    int rc = serial ? RNNLM_OK : side_fork(h, 0, st);
     if (rc) return rc;
     rc = embedding_update();
     if (rc) return rc;
     if (early_rec) {
-      rc = recurrent_update(h->side);
+      rc = recurrent_update(es);
       if (rc) return rc;
     }
   }
@@ -1103,7 +1121,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     }
   }
   if (!early_side) {
-    int rc = side_fork(h, 0, st);  // the side stream waits for everything queued so far
+    int rc = serial ? RNNLM_OK : side_fork(h, 0, st);  // the side stream waits for everything queued so far
     if (rc) return rc;
     rc = embedding_update();
     if (rc) return rc;
@@ -1129,7 +1147,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     if (rc) return rc;
   }
   // wait for the embedding update running on the side stream
-  return side_join(h, 0, st);
+  return serial ? RNNLM_OK : side_join(h, 0, st);
 }
 
 template <typename T>
@@ -1137,8 +1155,8 @@ int window_call(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float *l
                 const UpdateTargets *u, bool advance_state, hipStream_t st, const NceCall *nce = nullptr) {
   const bool want_sum = sum_logp || u;
   const WindowSum ws = {sum_logp ? sum_logp : p_sum(h), nullptr, p_flags(h), u ? p_counter(h) : nullptr};
-  int rc = forward_window<T>(h, x, y, Tn, logp, advance_state, nce == nullptr, st, u != nullptr, false,
-                             want_sum && !nce ? &ws : nullptr);
+  int rc = forward_window<T>(h, x, y, Tn, logp, advance_state, nce == nullptr, st, u != nullptr,
+                             u && !scan_ids(h, Tn, *u), false, want_sum && !nce ? &ws : nullptr);
   if (rc) return rc;
   if (nce) {  // per-position losses take the place of the log-probabilities
     rc = nce_forward<T>(h, Tn, *nce, st);
@@ -1154,7 +1172,7 @@ int window_call(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float *l
 
 template <typename T>
 int score_call(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float lnZ, float *score, hipStream_t st) {
-  int rc = forward_window<T>(h, x, y, Tn, nullptr, true, false, st, false, true);
+  int rc = forward_window<T>(h, x, y, Tn, nullptr, true, false, st, false, false, true);
   if (rc) return rc;
   const int Mrows = Tn * h->Bp;
   StageTimer tm(h, RNNLM_STAGE_NCE_SCORE, st);
@@ -1172,7 +1190,7 @@ int score_call(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float lnZ
 template <typename T>
 int shortlist_call(rnnlm_t *h, const int32_t *x, const int32_t *cand, int C, int Tn, float lnZ, float *score,
                    hipStream_t st) {
-  int rc = forward_window<T>(h, x, nullptr, Tn, nullptr, true, false, st, false, true);
+  int rc = forward_window<T>(h, x, nullptr, Tn, nullptr, true, false, st, false, false, true);
   if (rc) return rc;
   StageTimer tm(h, RNNLM_STAGE_NCE_SCORE, st);
   const T *feat = h->cfg.P > 0 ? at<T>(h, h->L.P_c) : at<T>(h, h->L.Hs_c) + (long)h->Bp * h->Hp;
@@ -1583,8 +1601,8 @@ int rnnlm_perplexity(rnnlm_t *h, const int32_t *tok, int64_t N, int32_t T, doubl
                        yt);
     const WindowSum ws = {nullptr, p_running(h), p_flags(h), nullptr};
     rc = (h->cfg.precision == RNNLM_FP32)
-             ? forward_window<float>(h, xt, yt, T, nullptr, true, true, st, false, false, &ws)
-             : forward_window<bf16_t>(h, xt, yt, T, nullptr, true, true, st, false, false, &ws);
+             ? forward_window<float>(h, xt, yt, T, nullptr, true, true, st, false, false, false, &ws)
+             : forward_window<bf16_t>(h, xt, yt, T, nullptr, true, true, st, false, false, false, &ws);
     if (rc) return rc;
   }
   HIP_TRY(hipGetLastError());
