@@ -10,10 +10,13 @@
 
 namespace rnnlm_dev {
 
-// r[i] *= rho: decay of a per-word statistic; the words touched in this window add (1-rho)*s afterwards.
-__global__ void rms_decay_kernel(float *__restrict__ r, long n, float rho) {
+// r[i] *= rho: decay of up to three per-word statistics (blockIdx.y picks one; nullptr: none); the words touched in this
+// window add (1-rho)*s afterwards.
+__global__ void rms_decay_kernel(float *__restrict__ r0, float *__restrict__ r1, float *__restrict__ r2, long n,
+                                 float rho) {
+  float *r = blockIdx.y == 0 ? r0 : (blockIdx.y == 1 ? r1 : r2);
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) r[i] *= rho;
+  if (r && i < n) r[i] *= rho;
 }
 
 // One statistic per word; one workgroup per gradient row.
@@ -126,22 +129,47 @@ __global__ void rms_bias_compact_kernel(const float *__restrict__ g, const int32
   if (gv != 0.0f) b[w] -= lr * gv / (sqrtf(rnew) + eps);
 }
 
-// One statistic per element (U: R x C with a compute copy of leading dimension ldc; b: 1 x V, no copy).
-template <typename T>
-__global__ void rms_elem_apply_kernel(const float *__restrict__ G, int R, int C, float *__restrict__ W,
-                                      T *__restrict__ Wc, int ldc, float *__restrict__ r, float rho, float lr,
-                                      float eps) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long)R * C) return;
-  const float gv = G[i];
-  const float rnew = rho * r[i] + (1.0f - rho) * gv * gv;
-  r[i] = rnew;
-  float v = W[i];
+// theta <- theta - lr * g / (sqrt(r) + eps) of one element; returns the new weight.
+__device__ inline float rms_elem(float gv, float *r, float *w, float rho, float lr, float eps) {
+  const float rnew = rho * *r + (1.0f - rho) * gv * gv;
+  *r = rnew;
+  float v = *w;
   if (gv != 0.0f) {
     v -= lr * gv / (sqrtf(rnew) + eps);
-    W[i] = v;
+    *w = v;
   }
-  if (Wc) Wc[(i / C) * ldc + (i % C)] = from_f32<T>(v);
+  return v;
+}
+
+// One statistic per element of a vector (the output bias).
+__global__ void rms_elem_apply_kernel(const float *__restrict__ G, int n, float *__restrict__ W, float *__restrict__ r,
+                                      float rho, float lr, float eps) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) rms_elem(G[i], r + i, W + i, rho, lr, eps);
+}
+
+// One statistic per element of the n x n recurrent matrix, whose compute copy and its transpose (leading dimension ldc,
+// padding left alone) are refreshed with it: a workgroup of 256 threads takes a 32 x 32 tile, which it turns in LDS.
+// (The transpose by a launch of its own: 4 us and another pass over the copy.)
+template <typename T>
+__global__ void __launch_bounds__(256) rms_square_apply_kernel(const float *__restrict__ G, int n, float *__restrict__ W,
+                                                               T *__restrict__ Wc, T *__restrict__ WcT, int ldc,
+                                                               float *__restrict__ r, float rho, float lr, float eps) {
+  __shared__ T tile[32][33];
+  const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int k = ty; k < 32; k += 8) {
+    const int row = by + k, col = bx + tx;
+    if (row < n && col < n) {
+      const long i = (long)row * n + col;
+      const T v = from_f32<T>(rms_elem(G[i], r + i, W + i, rho, lr, eps));
+      Wc[(long)row * ldc + col] = v;
+      tile[k][tx] = v;
+    }
+  }
+  __syncthreads();
+  for (int k = ty; k < 32; k += 8)
+    if (bx + k < n && by + tx < n) WcT[(long)(bx + k) * ldc + by + tx] = tile[tx][k];
 }
 
 }  // namespace rnnlm_dev

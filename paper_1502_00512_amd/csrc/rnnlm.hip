@@ -744,6 +744,7 @@ int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
                          at<int32_t>(h, h->L.perm2));
       hipLaunchKernelGGL(segment_kernel, dim3(1), dim3(1024), 0, h->side, ids, at<int32_t>(h, h->L.perm2), nent, 1, 1,
                          at<int32_t>(h, h->L.seg2), p_nseg2(h));
+      HIP_TRY(hipEventRecord(h->ev_join[1], h->side));  // here, not where it is waited for: more work follows on that stream
     }
     hipLaunchKernelGGL(nce_target_score_kernel<T>, dim3(blocks_for(Mrows, 4)), dim3(256), 0, st, Hs1,
                        at<T>(h, h->L.Wo_c), Hp, yp, h->buf.b, n.lnq, lnZ_lnK, Mrows, c.B, Bp, at<float>(h, h->L.ndt),
@@ -817,10 +818,7 @@ int nce_update(rnnlm_t *h, int Tn, const NceCall &n, const UpdateTargets &u, hip
   StageTimer tm(h, RNNLM_STAGE_NCE_UPDATE, st);
   const int nent = K + M;
   int32_t *ids = at<int32_t>(h, h->L.ids), *perm = at<int32_t>(h, h->L.perm2), *seg = at<int32_t>(h, h->L.seg2);
-  {  // the sort of the list was started on the side stream by nce_forward
-    int rc = side_join(h, 1, st);
-    if (rc) return rc;
-  }
+  HIP_TRY(hipStreamWaitEvent(st, h->ev_join[1], 0));  // the sort of the list, started on the side stream by nce_forward
   T *Wc = u.refresh_copies ? at<T>(h, h->L.Wo_c) : nullptr;
   if (c.H % 4 == 0) {
     hipLaunchKernelGGL((nce_row_update_kernel<T, 4>), dim3(nent, (c.H + 255) / 256), dim3(1024), 0, st, G, Hs1, Hp,
@@ -1027,8 +1025,11 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   // that its last, partly empty round of tiles leaves idle (window time -2 % at H = 2048, -1.3 % at H = 1024).  At
   // H = 4096 the recurrent update is a full round of 256 tiles by itself and keeps its place after the output
   // weight update; the embedding update goes first there as well.
-  const bool early_side = !nce && c.P == 0;
-  const bool early_rec = early_side && (long)(Hp / BIG) * (Hp / BIG) < 256;
+  // Under the noise-contrastive criterion they run next to the update of the touched rows, which is latency-bound (V =
+  // 64000, H = 1024, 128x20, 1024 noise words, rmsprop: with the decay and the steps of E and U on that stream as well
+  // 319 -> 265 us).
+  const bool early_side = c.P == 0;
+  const bool early_rec = early_side && (nce || (long)(Hp / BIG) * (Hp / BIG) < 256);
   if (early_side) {
     int rc = serial ? RNNLM_OK : side_fork(h, 0, st);
     if (rc) return rc;
@@ -1223,6 +1224,61 @@ bool window_args_ok(rnnlm_t *h, const int32_t *x, const int32_t *y, int T) {
   return h && x && y && T >= 1 && T <= h->cfg.T_max;
 }
 
+// The statistics' decay depends on nothing in the window: it starts on the side stream with it (joined with that stream's
+// other work at the end of the backward pass).
+int rms_decay(rnnlm_t *h, float *r0, float *r1, float *r2, float rho, hipStream_t st) {
+  int rc = side_fork(h, 0, st);
+  if (rc) return rc;
+  hipLaunchKernelGGL(rms_decay_kernel, dim3(blocks_for(h->cfg.V, 256), r1 ? 3 : 1), dim3(256), 0, h->side, r0, r1, r2,
+                     (long)h->cfg.V, rho);
+  HIP_TRY(hipGetLastError());
+  return RNNLM_OK;
+}
+// Steps of the embedding rows and of the recurrent matrix: on the side stream, behind the kernels that formed their
+// gradients and next to the steps of the output layer.
+template <typename T>
+int rms_apply_side(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, float lr, float eps) {
+  const rnnlm_config &c = h->cfg;
+  hipLaunchKernelGGL(rms_row_apply_kernel<T>, dim3(Tn * c.B), dim3(256), 0, h->side, at<float>(h, h->L.dHs32), (long)h->Hp,
+                     at<int32_t>(h, h->L.xp), at<int32_t>(h, h->L.perm), at<int32_t>(h, h->L.seg), p_nseg(h), c.B, h->Bp,
+                     c.H, h->Hp, h->buf.E, (T *)nullptr, state.rE, rho, lr, eps);
+  const unsigned tiles = blocks_for(c.H, 32);
+  hipLaunchKernelGGL(rms_square_apply_kernel<T>, dim3(tiles, tiles), dim3(256), 0, h->side, at<float>(h, h->L.gU), c.H,
+                     h->buf.U, at<T>(h, h->L.U_c), at<T>(h, h->L.UT_c), h->Hp, state.rU, rho, lr, eps);
+  HIP_TRY(hipGetLastError());
+  return RNNLM_OK;
+}
+template <typename T>
+int rms_apply(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, float lr, float eps, hipStream_t st) {
+  const rnnlm_config &c = h->cfg;
+  StageTimer tm(h, RNNLM_STAGE_RMSPROP, st);
+  int rc = rms_apply_side<T>(h, Tn, state, rho, lr, eps);
+  if (rc) return rc;
+  hipLaunchKernelGGL(rms_row_apply_kernel<T>, dim3(c.V), dim3(256), 0, st, at<float>(h, h->L.gWo), (long)c.H, nullptr,
+                     nullptr, nullptr, nullptr, c.B, h->Bp, c.H, h->Hp, h->buf.Wo, at<T>(h, h->L.Wo_c), state.rWo, rho, lr,
+                     eps);
+  hipLaunchKernelGGL(rms_elem_apply_kernel, dim3(blocks_for(c.V, 256)), dim3(256), 0, st, at<float>(h, h->L.gb), c.V,
+                     h->buf.b, state.rb, rho, lr, eps);
+  HIP_TRY(hipGetLastError());
+  return side_join(h, 0, st);
+}
+template <typename T>
+int rms_apply_nce(rnnlm_t *h, int Tn, int K, const rnnlm_rmsprop_state &state, float rho, float lr, float eps,
+                  hipStream_t st) {
+  const rnnlm_config &c = h->cfg;
+  StageTimer tm(h, RNNLM_STAGE_RMSPROP, st);
+  int rc = rms_apply_side<T>(h, Tn, state, rho, lr, eps);
+  if (rc) return rc;
+  const int nent = K + Tn * c.B;
+  const int32_t *ids = at<int32_t>(h, h->L.ids), *perm2 = at<int32_t>(h, h->L.perm2), *seg2 = at<int32_t>(h, h->L.seg2);
+  // the sort helpers' key indexing key[(i / B) * Bp + i % B] with B = Bp = 1 reads the compact id list
+  hipLaunchKernelGGL(rms_row_apply_kernel<T>, dim3(nent), dim3(256), 0, st, at<float>(h, h->L.gN), (long)h->Hp, ids, perm2,
+                     seg2, p_nseg2(h), 1, 1, c.H, h->Hp, h->buf.Wo, at<T>(h, h->L.Wo_c), state.rWo, rho, lr, eps);
+  hipLaunchKernelGGL(rms_bias_compact_kernel, dim3(blocks_for(nent, 256)), dim3(256), 0, st, at<float>(h, h->L.gbN), ids,
+                     perm2, seg2, p_nseg2(h), h->buf.b, state.rb, rho, lr, eps);
+  HIP_TRY(hipGetLastError());
+  return side_join(h, 0, st);
+}
 }  // namespace
 
 extern "C" {
@@ -1456,47 +1512,19 @@ int rnnlm_train_chunk_rmsprop(rnnlm_t *h, const int32_t *x, const int32_t *y, in
                               void *stream) {
   if (!window_args_ok(h, x, y, T) || !rms_args_ok(h, lr, rho, eps, state)) return RNNLM_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
-  const rnnlm_config &c = h->cfg;
   // gradients through the plain step's kernels, update epilogues redirected (out = 0*W + 1*g); the
   // embedding rows go to a compact buffer (one row per distinct input word): the hidden-state gradient
   // buffer, which is free once back-propagation through time is done
   float *gWo = reinterpret_cast<float *>(h->ws + h->L.gWo), *gU = reinterpret_cast<float *>(h->ws + h->L.gU),
         *gb = reinterpret_cast<float *>(h->ws + h->L.gb), *gE = reinterpret_cast<float *>(h->ws + h->L.dHs32);
   UpdateTargets u{gE, gU, gWo, gb, 0.0f, -1.0f, false, true, h->Hp};
-  const bool f32 = c.precision == RNNLM_FP32;
-  int rc = f32 ? window_call<float>(h, x, y, T, logp, sum_logp, &u, true, st)
-               : window_call<bf16_t>(h, x, y, T, logp, sum_logp, &u, true, st);
+  const bool f32 = h->cfg.precision == RNNLM_FP32;
+  int rc = rms_decay(h, state->rE, nullptr, nullptr, rho, st);
   if (rc) return rc;
-  StageTimer tm(h, RNNLM_STAGE_RMSPROP, st);
-  const long nU = (long)c.H * c.H;
-  const int32_t *xp = reinterpret_cast<int32_t *>(h->ws + h->L.xp), *perm = reinterpret_cast<int32_t *>(h->ws + h->L.perm),
-                *seg = reinterpret_cast<int32_t *>(h->ws + h->L.seg);
-  hipLaunchKernelGGL(rms_decay_kernel, dim3(blocks_for(c.V, 256)), dim3(256), 0, st, state->rE, (long)c.V, rho);
-  if (f32) {
-    float *Wo_c = reinterpret_cast<float *>(h->ws + h->L.Wo_c), *U_c = reinterpret_cast<float *>(h->ws + h->L.U_c);
-    hipLaunchKernelGGL(rms_row_apply_kernel<float>, dim3(c.V), dim3(256), 0, st, gWo, (long)c.H, nullptr, nullptr,
-                       nullptr, nullptr, c.B, h->Bp, c.H, h->Hp, h->buf.Wo, Wo_c, state->rWo, rho, lr, eps);
-    hipLaunchKernelGGL(rms_elem_apply_kernel<float>, dim3(blocks_for(nU, 256)), dim3(256), 0, st, gU, c.H, c.H, h->buf.U,
-                       U_c, h->Hp, state->rU, rho, lr, eps);
-    hipLaunchKernelGGL(transpose_kernel<float>, dim3(h->Hp / 32, h->Hp / 32), dim3(256), 0, st, U_c, h->Hp,
-                       reinterpret_cast<float *>(h->ws + h->L.UT_c));
-    hipLaunchKernelGGL(rms_row_apply_kernel<float>, dim3(T * c.B), dim3(256), 0, st, gE, (long)h->Hp, xp, perm, seg,
-                       p_nseg(h), c.B, h->Bp, c.H, h->Hp, h->buf.E, (float *)nullptr, state->rE, rho, lr, eps);
-  } else {
-    bf16_t *Wo_c = reinterpret_cast<bf16_t *>(h->ws + h->L.Wo_c), *U_c = reinterpret_cast<bf16_t *>(h->ws + h->L.U_c);
-    hipLaunchKernelGGL(rms_row_apply_kernel<bf16_t>, dim3(c.V), dim3(256), 0, st, gWo, (long)c.H, nullptr, nullptr,
-                       nullptr, nullptr, c.B, h->Bp, c.H, h->Hp, h->buf.Wo, Wo_c, state->rWo, rho, lr, eps);
-    hipLaunchKernelGGL(rms_elem_apply_kernel<bf16_t>, dim3(blocks_for(nU, 256)), dim3(256), 0, st, gU, c.H, c.H,
-                       h->buf.U, U_c, h->Hp, state->rU, rho, lr, eps);
-    hipLaunchKernelGGL(transpose_kernel<bf16_t>, dim3(h->Hp / 32, h->Hp / 32), dim3(256), 0, st, U_c, h->Hp,
-                       reinterpret_cast<bf16_t *>(h->ws + h->L.UT_c));
-    hipLaunchKernelGGL(rms_row_apply_kernel<bf16_t>, dim3(T * c.B), dim3(256), 0, st, gE, (long)h->Hp, xp, perm, seg,
-                       p_nseg(h), c.B, h->Bp, c.H, h->Hp, h->buf.E, (bf16_t *)nullptr, state->rE, rho, lr, eps);
-  }
-  hipLaunchKernelGGL(rms_elem_apply_kernel<float>, dim3(blocks_for(c.V, 256)), dim3(256), 0, st, gb, 1, c.V, h->buf.b,
-                     (float *)nullptr, 0, state->rb, rho, lr, eps);
-  HIP_TRY(hipGetLastError());
-  return RNNLM_OK;
+  rc = f32 ? window_call<float>(h, x, y, T, logp, sum_logp, &u, true, st)
+           : window_call<bf16_t>(h, x, y, T, logp, sum_logp, &u, true, st);
+  if (rc) return rc;
+  return f32 ? rms_apply<float>(h, T, *state, rho, lr, eps, st) : rms_apply<bf16_t>(h, T, *state, rho, lr, eps, st);
 }
 
 int rnnlm_nce_train_chunk_rmsprop(rnnlm_t *h, const int32_t *x, const int32_t *y, int32_t T, const int32_t *noise,
@@ -1505,55 +1533,20 @@ int rnnlm_nce_train_chunk_rmsprop(rnnlm_t *h, const int32_t *x, const int32_t *y
   if (!window_args_ok(h, x, y, T) || !nce_args_ok(h, noise, K, lnq, lnZ) || !rms_args_ok(h, lr, rho, eps, state))
     return RNNLM_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
-  const rnnlm_config &c = h->cfg;
   float *gU = reinterpret_cast<float *>(h->ws + h->L.gU), *gE = reinterpret_cast<float *>(h->ws + h->L.dHs32),
         *gN = reinterpret_cast<float *>(h->ws + h->L.gN), *gbN = reinterpret_cast<float *>(h->ws + h->L.gbN);
   // gradients through the plain step's kernels; the touched rows of Wo / entries of b and the embedding rows
   // go to compact one-row-per-word buffers
   UpdateTargets u{gE, gU, gN, gbN, 0.0f, -1.0f, false, true, h->Hp, h->Hp};
   NceCall n{noise, K, lnq, lnZ, J, true};
-  const bool f32 = c.precision == RNNLM_FP32;
-  int rc = f32 ? window_call<float>(h, x, y, T, nullptr, sum_J, &u, true, st, &n)
-               : window_call<bf16_t>(h, x, y, T, nullptr, sum_J, &u, true, st, &n);
+  const bool f32 = h->cfg.precision == RNNLM_FP32;
+  int rc = rms_decay(h, state->rE, state->rWo, state->rb, rho, st);
   if (rc) return rc;
-  StageTimer tm(h, RNNLM_STAGE_RMSPROP, st);
-  const long nU = (long)c.H * c.H;
-  const int nent = K + T * c.B;
-  const int32_t *xp = reinterpret_cast<int32_t *>(h->ws + h->L.xp), *perm = reinterpret_cast<int32_t *>(h->ws + h->L.perm),
-                *seg = reinterpret_cast<int32_t *>(h->ws + h->L.seg);
-  const int32_t *ids = reinterpret_cast<int32_t *>(h->ws + h->L.ids),
-                *perm2 = reinterpret_cast<int32_t *>(h->ws + h->L.perm2),
-                *seg2 = reinterpret_cast<int32_t *>(h->ws + h->L.seg2);
-  const unsigned vb = blocks_for(c.V, 256);
-  hipLaunchKernelGGL(rms_decay_kernel, dim3(vb), dim3(256), 0, st, state->rE, (long)c.V, rho);
-  hipLaunchKernelGGL(rms_decay_kernel, dim3(vb), dim3(256), 0, st, state->rWo, (long)c.V, rho);
-  hipLaunchKernelGGL(rms_decay_kernel, dim3(vb), dim3(256), 0, st, state->rb, (long)c.V, rho);
-  if (f32) {
-    float *Wo_c = reinterpret_cast<float *>(h->ws + h->L.Wo_c), *U_c = reinterpret_cast<float *>(h->ws + h->L.U_c);
-    // the sort helpers' key indexing key[(i / B) * Bp + i % B] with B = Bp = 1 reads the compact id list
-    hipLaunchKernelGGL(rms_row_apply_kernel<float>, dim3(nent), dim3(256), 0, st, gN, (long)h->Hp, ids, perm2, seg2,
-                       p_nseg2(h), 1, 1, c.H, h->Hp, h->buf.Wo, Wo_c, state->rWo, rho, lr, eps);
-    hipLaunchKernelGGL(rms_elem_apply_kernel<float>, dim3(blocks_for(nU, 256)), dim3(256), 0, st, gU, c.H, c.H, h->buf.U,
-                       U_c, h->Hp, state->rU, rho, lr, eps);
-    hipLaunchKernelGGL(transpose_kernel<float>, dim3(h->Hp / 32, h->Hp / 32), dim3(256), 0, st, U_c, h->Hp,
-                       reinterpret_cast<float *>(h->ws + h->L.UT_c));
-    hipLaunchKernelGGL(rms_row_apply_kernel<float>, dim3(T * c.B), dim3(256), 0, st, gE, (long)h->Hp, xp, perm, seg,
-                       p_nseg(h), c.B, h->Bp, c.H, h->Hp, h->buf.E, (float *)nullptr, state->rE, rho, lr, eps);
-  } else {
-    bf16_t *Wo_c = reinterpret_cast<bf16_t *>(h->ws + h->L.Wo_c), *U_c = reinterpret_cast<bf16_t *>(h->ws + h->L.U_c);
-    hipLaunchKernelGGL(rms_row_apply_kernel<bf16_t>, dim3(nent), dim3(256), 0, st, gN, (long)h->Hp, ids, perm2, seg2,
-                       p_nseg2(h), 1, 1, c.H, h->Hp, h->buf.Wo, Wo_c, state->rWo, rho, lr, eps);
-    hipLaunchKernelGGL(rms_elem_apply_kernel<bf16_t>, dim3(blocks_for(nU, 256)), dim3(256), 0, st, gU, c.H, c.H,
-                       h->buf.U, U_c, h->Hp, state->rU, rho, lr, eps);
-    hipLaunchKernelGGL(transpose_kernel<bf16_t>, dim3(h->Hp / 32, h->Hp / 32), dim3(256), 0, st, U_c, h->Hp,
-                       reinterpret_cast<bf16_t *>(h->ws + h->L.UT_c));
-    hipLaunchKernelGGL(rms_row_apply_kernel<bf16_t>, dim3(T * c.B), dim3(256), 0, st, gE, (long)h->Hp, xp, perm, seg,
-                       p_nseg(h), c.B, h->Bp, c.H, h->Hp, h->buf.E, (bf16_t *)nullptr, state->rE, rho, lr, eps);
-  }
-  hipLaunchKernelGGL(rms_bias_compact_kernel, dim3(blocks_for(nent, 256)), dim3(256), 0, st, gbN, ids, perm2, seg2,
-                     p_nseg2(h), h->buf.b, state->rb, rho, lr, eps);
-  HIP_TRY(hipGetLastError());
-  return RNNLM_OK;
+  rc = f32 ? window_call<float>(h, x, y, T, nullptr, sum_J, &u, true, st, &n)
+           : window_call<bf16_t>(h, x, y, T, nullptr, sum_J, &u, true, st, &n);
+  if (rc) return rc;
+  return f32 ? rms_apply_nce<float>(h, T, K, *state, rho, lr, eps, st)
+             : rms_apply_nce<bf16_t>(h, T, K, *state, rho, lr, eps, st);
 }
 
 int rnnlm_reset_state(rnnlm_t *h, void *stream) {
