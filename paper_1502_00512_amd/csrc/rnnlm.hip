@@ -130,11 +130,11 @@ constexpr int BIG = 256;
 // whole rounds reach 92 % (256), 90 % (128) and 82 % (64); every split adds a pass over the output.
 struct F32Plan {
   int tile, splits;
+  double us;
 };
 F32Plan f32_plan(long Mg, long Ng, long K, int max_splits) {
   const long kb = (K + 31) / 32;
-  F32Plan best = {64, 1};
-  double best_us = 1e30;
+  F32Plan best = {64, 1, 1e30};
   for (int tile = 64; tile <= 256; tile *= 2) {
     if (Mg % tile || Ng % tile) continue;
     const double unit = (tile == 256 ? 16 / 0.92 : tile == 128 ? 4 / 0.90 : 1 / 0.82) * 0.43;
@@ -147,10 +147,22 @@ F32Plan f32_plan(long Mg, long Ng, long K, int max_splits) {
       const long last = rest == 0 ? 0 : rounds == 0 ? (rest + 255) / 256 : share;
       double us = (double)(rounds * share + last) * unit * per;
       if (S > 1) us += 5.0 + (S + 1) * (double)Mg * Ng * 4.0 / 4e6;
-      if (us < best_us) {
-        best_us = us;
-        best = {tile, S};
-      }
+      if (us < best.us) best = {tile, S, us};
+    }
+  }
+  return best;
+}
+// fp32: an extent of `valid` rows or columns, padded to 64, 128 or 256 by what the product with the other extent takes
+// (the buffers are padded to 256; bf16 contractions take all of it).
+long f32_extent(long valid, long other, long K, int max_splits) {
+  long best = round_up(valid, 256);
+  double us = f32_plan(best, other, K, max_splits).us;
+  for (long pad = 128; pad >= 64; pad /= 2) {
+    const long n = round_up(valid, pad);
+    const double t = f32_plan(n, other, K, max_splits).us;
+    if (t < us) {
+      us = t;
+      best = n;
     }
   }
   return best;
@@ -253,6 +265,18 @@ RecurrentPlan recurrent_plan(const rnnlm_config &c) {
   return p;
 }
 
+// Rows the contractions of a window of Mrows positions walk (MpMax is a multiple of 256).  Long fp32 windows keep whole
+// 256-row tiles: the padding is below 2 % there.
+constexpr long F32_TRIM_ROWS = 16384;
+long window_rows(const rnnlm_config &c, long Mrows) {
+  if (c.precision != RNNLM_FP32 || Mrows > F32_TRIM_ROWS) return round_up(Mrows, PAD_M);
+  return f32_extent(Mrows, round_up(c.V, PAD_V), c.P > 0 ? c.P : c.H, 1);
+}
+// Columns the contraction over the vocabulary forms: the compressed architecture reads the padding, too.
+long features_formed(const rnnlm_config &c, long Mp, int max_splits) {
+  return c.P > 0 ? round_up(c.P, PAD_H) : f32_extent(c.H, Mp, c.V, max_splits);
+}
+
 void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, int &nPart, int &KpMax, WsLayout &L) {
   const size_t es = (c.precision == RNNLM_FP32) ? 4 : 2;
   const int Pp = (int)round_up(c.P, PAD_H);
@@ -266,8 +290,8 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   nPart = Vp / (es == 4 ? 64 : BIG);  // one softmax-statistics partial per tile row block (fp32: of the smaller tile)
   if (es == 4) {
     L.partElems = (long)MpMax * Dp;
-    for (long M = PAD_M; M <= MpMax; M += PAD_M)
-      L.partElems = std::max(L.partElems, (long)f32_plan(M, Dp, Vp, MAX_SPLITS).splits * M * Dp);
+    for (long M = 64; M <= MpMax; M += M < F32_TRIM_ROWS ? 64 : PAD_M)
+      L.partElems = std::max(L.partElems, (long)f32_plan(M, features_formed(c, M, MAX_SPLITS), c.V, MAX_SPLITS).splits * M * Dp);
   } else {
     L.partElems = (long)desired_splits(MpMax, Dp, Vp / 64) * MpMax * Dp;
   }
@@ -541,7 +565,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp, Vp = h->Vp;
   const int Mrows = Tn * Bp;
-  const int Mp = (int)round_up(Mrows, PAD_M);
+  const int Mp = (int)window_rows(h->cfg, Mrows);
   const long ldz = h->MpMax;
   T *Hs_c = at<T>(h, h->L.Hs_c);
   float *X32 = at<float>(h, h->L.X32);
@@ -721,7 +745,7 @@ template <typename T>
 int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp;
-  const int Mrows = Tn * Bp, Mp = (int)round_up(Mrows, PAD_M), M = Tn * c.B;
+  const int Mrows = Tn * Bp, Mp = (int)window_rows(h->cfg, Mrows), M = Tn * c.B;
   const int K = n.K, Kp = (int)round_up(K, 256);
   T *Hs1 = at<T>(h, h->L.Hs_c) + (long)Bp * Hp;
   T *Wn = at<T>(h, h->L.Wn_c);
@@ -771,7 +795,7 @@ int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
 template <typename T>
 int nce_backward_h(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
   const int Hp = h->Hp, Bp = h->Bp;
-  const int Mrows = Tn * Bp, Mp = (int)round_up(Mrows, PAD_M);
+  const int Mrows = Tn * Bp, Mp = (int)window_rows(h->cfg, Mrows);
   const int Kp = (int)round_up(n.K, 256);
   float *dHs32 = at<float>(h, h->L.dHs32);
   StageTimer tm(h, RNNLM_STAGE_NCE_BWD_H, st);
@@ -793,7 +817,7 @@ template <typename T>
 int nce_update(rnnlm_t *h, int Tn, const NceCall &n, const UpdateTargets &u, hipStream_t st) {
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp;
-  const int Mrows = Tn * Bp, Mp = (int)round_up(Mrows, PAD_M), M = Tn * c.B;
+  const int Mrows = Tn * Bp, Mp = (int)window_rows(h->cfg, Mrows), M = Tn * c.B;
   const int K = n.K, Kp = (int)round_up(K, 256);
   T *Hs1 = at<T>(h, h->L.Hs_c) + (long)Bp * Hp;
   float *G = at<float>(h, h->L.G32);
@@ -839,7 +863,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp, Vp = h->Vp;
   const int Mrows = Tn * Bp;
-  const int Mp = (int)round_up(Mrows, PAD_M);
+  const int Mp = (int)window_rows(h->cfg, Mrows);
   const long ldz = h->MpMax;
   constexpr int BK = Elem<T>::BK;
   T *Hs_c = at<T>(h, h->L.Hs_c);
@@ -872,7 +896,9 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     const int Dp = h->Dp;
     float *dF32 = c.P > 0 ? at<float>(h, h->L.dP32) : dHs32;
     const long per = (long)Mp * Dp;
-    const F32Plan plan = f32_plan(Mp, Dp, Vp, (int)std::min<long>(MAX_SPLITS, std::max<long>(1, h->L.partElems / per)));
+    const int max_splits = (int)std::min<long>(MAX_SPLITS, std::max<long>(1, h->L.partElems / per));
+    const long Dn = sizeof(T) == 4 ? features_formed(c, Mp, max_splits) : Dp;
+    const F32Plan plan = sizeof(T) == 4 ? f32_plan(Mp, Dn, c.V, max_splits) : F32Plan{};
     int S = sizeof(T) == 4 ? plan.splits : desired_splits(Mp, Dp, Vp / BK);
     if ((long)S * per > h->L.partElems) S = (int)(h->L.partElems / per);
     if (S < 1) S = 1;
@@ -883,7 +909,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     {
       StageTimer tm(h, RNNLM_STAGE_OUT_BWD_H, st);
       if constexpr (sizeof(T) == 4) {
-        HIP_TRY((f32_gemm<KROW, KROW>(st, ZT, ldz, Wo_c, Dp, Mp, Dp, round_up(c.V, 32), plan, epi)));
+        HIP_TRY((f32_gemm<KROW, KROW>(st, ZT, ldz, Wo_c, Dp, Mp, Dn, round_up(c.V, 32), plan, epi)));
       } else {
         HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(st, ZT, ldz, Wo_c, Dp, Mp, Dp, Vp, S, epi)));
       }
@@ -1015,7 +1041,8 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
       if constexpr (sizeof(T) == 2)
         HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, 1, epi)));
     } else {
-      HIP_TRY((mid_gemm<T, KROW, KROW>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, 1, epi)));
+      const long n = sizeof(T) == 4 ? round_up(c.H, 64) : Hp;  // (the epilogue writes valid entries only)
+      HIP_TRY((mid_gemm<T, KROW, KROW>(rs, Hs_c, Hp, dA_c, Hp, n, n, Mp, 1, epi)));
     }
   }
     return RNNLM_OK;
@@ -1102,7 +1129,8 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     epi.lr = u.lr;
     const T *feat = c.P > 0 ? at<T>(h, h->L.P_c) : Hs_c + (long)Bp * Hp;
     if constexpr (sizeof(T) == 4) {
-      HIP_TRY((f32_gemm<KROW, ROWK>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, round_up(Mrows, 32), f32_plan(h->Dp, Vp, Mrows, 1),
+      const long Dn = f32_extent(h->D, Vp, Mrows, 1);
+      HIP_TRY((f32_gemm<KROW, ROWK>(st, feat, h->Dp, ZT, ldz, Dn, Vp, round_up(Mrows, 32), f32_plan(Dn, Vp, Mrows, 1),
                                     epi, -4)));
     } else if ((long)(h->Dp / BIG) * (Vp / BIG) < 128) {  // a narrow layer above the state: smaller tiles fill the chip
       HIP_TRY((launch_gemm_dma4<bf16_t, 128, BIG, 2, 4, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, epi, -4)));
