@@ -17,7 +17,7 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 // stated, merely finite), so the contraction kernels carry no bounds checks.
 constexpr int PAD_H = 256;  // hidden dimension
 constexpr int PAD_V = 256;  // vocabulary dimension
-constexpr int PAD_B = 32;   // streams per timestep (per-step recurrent contractions; the persistent kernel needs none)
+constexpr int PAD_B = 32;   // streams per timestep, where a kernel built for whole blocks of 256 streams runs
 constexpr int PAD_M = 256;  // rows of a window (T * padded B)
 
 __host__ __device__ inline long round_up(long a, long b) { return (a + b - 1) / b * b; }

@@ -440,36 +440,6 @@ constexpr int stage_lds_bytes() {
 // the main loop's final barrier (so LDS may be reused and barriers are allowed), and
 // lds_bytes<BM, BN>() = LDS it needs.
 
-// Recurrent forward step (Sec. 4.1): h = sigmoid(X + Hprev U^T).  Rows = streams, cols = units.
-template <typename T>
-struct EpiRnnFwd : EpiZeroInit {
-  const float *X;   // [Bp][ld]  gathered embedding rows of this timestep
-  T *Hnext;         // [Bp][ld]  hidden state slot of this timestep (padding written as zero)
-  float *h_state;   // [B][H] or nullptr: carried state, written at the window's last step
-  int B, H, ld;
-  template <int BM, int BN>
-  static constexpr int lds_bytes() { return 0; }
-  template <int BM, int BN, int TM, int TN, int NT>
-  __device__ inline void run(f32x16_t (&acc)[TM][TN], const EpiCtx &c) const {
-    const int row0 = c.tile_row0 + c.wrow, col0 = c.tile_col0 + c.wcol, lane = c.lane;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = col0 + j * 32 + (lane & 31);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = row0 + i * 32 + RNNLM_ACC_ROW(r, lane);
-          const bool ok = row < B && col < H;
-          float hval = 0.0f;
-          if (ok) hval = sigmoidf_(acc[i][j][r] + X[(long)row * ld + col]);
-          Hnext[(long)row * ld + col] = from_f32<T>(hval);
-          if (ok && h_state) h_state[(long)row * H + col] = hval;
-        }
-      }
-  }
-};
-
 // Output layer forward: z[v][m] = Wo[v] . h[m] + b[v] (rows = vocabulary, cols = window positions),
 // stored vocabulary-major for the softmax pass and both gradient contractions, plus per-(wave row
 // block, position) partial (max, sum exp) statistics of the fp32 logits and the fp32 logit of each
@@ -893,40 +863,6 @@ struct EpiSgd : EpiZeroInit {
         }
       }
     }
-  }
-};
-
-// Recurrent backward step: dA = (dH_out + dA_next U) * h * (1 - h).  Rows = streams, cols = units.
-template <typename T>
-struct EpiRnnBwd : EpiZeroInit {
-  const float *dHs;  // [Bp][ld] gradient arriving from the output layer at this timestep
-  const T *Hs;       // [Bp][ld] hidden state of this timestep
-  float *dA32;       // [Bp][ld]
-  T *dAc;            // [Bp][ld]
-  int B, H, ld;
-  template <int BM, int BN>
-  static constexpr int lds_bytes() { return 0; }
-  template <int BM, int BN, int TM, int TN, int NT>
-  __device__ inline void run(f32x16_t (&acc)[TM][TN], const EpiCtx &c) const {
-    const int row0 = c.tile_row0 + c.wrow, col0 = c.tile_col0 + c.wcol, lane = c.lane;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = col0 + j * 32 + (lane & 31);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = row0 + i * 32 + RNNLM_ACC_ROW(r, lane);
-          const long idx = (long)row * ld + col;
-          float d = 0.0f;
-          if (row < B && col < H) {
-            const float hv = to_f32(Hs[idx]);
-            d = (dHs[idx] + acc[i][j][r]) * hv * (1.0f - hv);
-          }
-          dA32[idx] = d;
-          dAc[idx] = from_f32<T>(d);
-        }
-      }
   }
 };
 

@@ -265,6 +265,29 @@ RecurrentPlan recurrent_plan(const rnnlm_config &c) {
   return p;
 }
 
+// Per-step recurrent path for shapes the persistent kernel does not cover: the step's contraction is split over its
+// contraction dimension, then one pass sums the parts and applies the elementwise part.  Whole blocks of 256 streams of a
+// wide layer: 256 x 128 tiles (fp32: 256 x 64, register-staged), one workgroup per compute unit.  Everything else: 64 x 64
+// tiles of the ring, up to eight splits and two workgroups per compute unit: the step is bound by the latency of a
+// workgroup's share of the contraction and by the matrix's way through the caches, so many short shares beat few long
+// ones (per step, 32 x 64 tiles over the whole contraction dimension against this: fp32 H = 1408, 64 streams 42 and 12.5 us;
+// bf16 H = 4096, 64 streams 39 and 15, H = 2500, 8 streams 24 and 11).
+struct StepPlan {
+  bool wide;   // 256-row tiles
+  int splits;
+  long rows;   // rows of a partial product
+};
+StepPlan step_plan(const rnnlm_config &c, int Bp, int Hp) {
+  const bool f32 = c.precision == RNNLM_FP32;
+  const long kBlocks = Hp / (f32 ? 32 : 64);
+  if (Bp % 256 == 0 && Hp >= 2048) {
+    const long tiles = (long)(Bp / 256) * (Hp / (f32 ? 64 : 128));
+    return {true, (int)std::min({std::max<long>(1, 256 / tiles), 8L, kBlocks}), Bp};
+  }
+  const long rows = round_up(Bp, 64), tiles = (rows / 64) * (Hp / 64);
+  return {false, (int)std::min({std::max<long>(1, 512 / tiles), 8L, kBlocks}), rows};
+}
+
 // Rows the contractions of a window of Mrows positions walk (MpMax is a multiple of 256).  Long fp32 windows keep whole
 // 256-row tiles: the padding is below 2 % there.
 constexpr long F32_TRIM_ROWS = 16384;
@@ -283,9 +306,9 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   Hp = (int)round_up(c.H, PAD_H);
   const int Dp = Pp > 0 ? Pp : Hp;
   Vp = (int)round_up(c.V, PAD_V);
-  // the persistent recurrent kernel takes streams as they come; the per-step contractions need whole 32-row blocks
+  // streams are taken as they come, except by the kernels built for whole blocks of 256
   const RecurrentPlan plan = recurrent_plan(c);
-  Bp = plan.nwg > 0 ? c.B : (int)round_up(c.B, PAD_B);
+  Bp = plan.nwg == 0 && Hp >= 2048 && round_up(c.B, PAD_B) % 256 == 0 ? (int)round_up(c.B, PAD_B) : c.B;
   MpMax = (int)round_up((long)c.T_max * Bp, PAD_M);
   nPart = Vp / (es == 4 ? 64 : BIG);  // one softmax-statistics partial per tile row block (fp32: of the smaller tile)
   if (es == 4) {
@@ -295,6 +318,8 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   } else {
     L.partElems = (long)desired_splits(MpMax, Dp, Vp / 64) * MpMax * Dp;
   }
+  const StepPlan step = step_plan(c, Bp, Hp);
+  if (plan.nwg == 0) L.partElems = std::max(L.partElems, (long)step.splits * step.rows * Hp);
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -304,9 +329,9 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   L.Wo_c = take((size_t)Vp * Dp * es);
   L.U_c = take((size_t)Hp * Hp * es);
   L.UT_c = take((size_t)Hp * Hp * es);
-  L.Hs_c = take((size_t)(MpMax + Bp) * Hp * es);
+  L.Hs_c = take((size_t)(MpMax + Bp + 64) * Hp * es);  // (+ 64: a per-step tile may read past the last stream)
   L.ZT = take((size_t)Vp * MpMax * es);
-  L.dA_c = take((size_t)(MpMax + Bp) * Hp * es);
+  L.dA_c = take((size_t)(MpMax + Bp + 64) * Hp * es);
   L.X32 = take((size_t)MpMax * Hp * 4);
   L.dHs32 = take((size_t)MpMax * Hp * 4);
   L.dA32 = take((size_t)MpMax * Hp * 4);
@@ -404,19 +429,6 @@ int sync_copies(rnnlm_t *h, hipStream_t st) {
 }
 
 bool persistent_ok(const rnnlm_t *h) { return h->plan.nwg > 0; }
-
-// Per-step recurrent path for shapes the persistent kernel does not cover: with whole blocks of 256 streams
-// and a wide hidden layer the step's contraction is split over its contraction dimension (0: not split).
-// bf16: 256 x 128 tiles through the direct global->LDS kernels; fp32: 256 x 64 tiles through the register-staged one.
-int rnn_step_tile_n(const rnnlm_t *h) { return h->cfg.precision == RNNLM_FP32 ? 64 : 128; }
-int rnn_step_splits(const rnnlm_t *h) {
-  if (h->Bp % 256 != 0 || h->Hp < 2048) return 0;
-  const long tiles = (long)(h->Bp / 256) * (h->Hp / rnn_step_tile_n(h));
-  long S = std::max<long>(1, 256 / tiles);
-  const int BK = (h->cfg.precision == RNNLM_FP32) ? 32 : 64;
-  S = std::min<long>(std::min<long>(S, 8), std::min<long>(h->Hp / BK, h->L.partElems / ((long)h->Bp * h->Hp)));
-  return S >= 2 ? (int)S : 0;
-}
 
 // Workgroups of a kernel that one compute unit holds at once, as the runtime computes it (asked once).
 template <auto Kern>
@@ -645,34 +657,25 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
   } else
   for (int t = 0; t < Tn; ++t) {
     StageTimer tm(h, (t == 0 || t == Tn - 1) ? RNNLM_STAGE_RNN_FWD : -1, st, t == 0, t == Tn - 1);
-    EpiRnnFwd<T> epi;
-    epi.X = X32 + (long)t * Bp * Hp;
-    epi.Hnext = Hs_c + (long)(t + 1) * Bp * Hp;
-    epi.h_state = (advance_state && t == Tn - 1) ? h->buf.h_state : nullptr;
-    epi.B = c.B;
-    epi.H = c.H;
-    epi.ld = Hp;
     const T *A_ = Hs_c + (long)t * Bp * Hp;
     const T *B_ = at<T>(h, h->L.U_c);
-    const int S = rnn_step_splits(h);
-    if (S > 0) {
-      // wide step: all streams x 128 (fp32: 64) units per workgroup, contraction split S ways, then sum + sigmoid
-      const long per = (long)Bp * Hp;
-      EpiPartial ep;
-      ep.part = at<float>(h, h->L.part32);
-      ep.ld = Hp;
-      ep.split_stride = per;
-      if constexpr (sizeof(T) == 2) {
-        HIP_TRY((launch_gemm_dma<256, 128, 4, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, Bp, Hp, Hp, S, ep)));
-      } else {
-        HIP_TRY((launch_gemm<T, 256, 64, 4, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, Bp, Hp, Hp, S, ep)));
-      }
-      hipLaunchKernelGGL(rnn_step_fwd_kernel<T>, dim3(blocks_for(per / 4, 256)), dim3(256), 0, st,
-                         at<float>(h, h->L.part32), per, S, epi.X, c.B, c.H, Hp, per / 4, epi.Hnext, epi.h_state);
-      HIP_TRY(hipGetLastError());
+    const StepPlan p = step_plan(c, Bp, Hp);
+    const long per = (long)Bp * Hp;
+    EpiPartial ep;
+    ep.part = at<float>(h, h->L.part32);
+    ep.ld = Hp;
+    ep.split_stride = p.rows * Hp;
+    if (!p.wide) {
+      HIP_TRY((launch_gemm_dma4<T, 64, 64, 2, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, p.rows, Hp, Hp, p.splits, ep)));
+    } else if constexpr (sizeof(T) == 2) {
+      HIP_TRY((launch_gemm_dma<256, 128, 4, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, Bp, Hp, Hp, p.splits, ep)));
     } else {
-      HIP_TRY((launch_gemm<T, 32, 64, 1, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, Bp, Hp, Hp, 1, epi)));
+      HIP_TRY((launch_gemm<T, 256, 64, 4, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, Bp, Hp, Hp, p.splits, ep)));
     }
+    hipLaunchKernelGGL(rnn_step_fwd_kernel<T>, dim3(blocks_for(per / 4, 256)), dim3(256), 0, st,
+                       at<float>(h, h->L.part32), p.rows * Hp, p.splits, X32 + (long)t * Bp * Hp, c.B, c.H, Hp, per / 4,
+                       Hs_c + (long)(t + 1) * Bp * Hp, (advance_state && t == Tn - 1) ? h->buf.h_state : nullptr);
+    HIP_TRY(hipGetLastError());
   }
   if (!with_output && !(need_feat && c.P > 0)) return RNNLM_OK;  // the noise-contrastive calls score the hidden states themselves
   const T *feat = Hs_c + (long)Bp * Hp;  // what the output layer reads: the states, or the layer above them
@@ -956,37 +959,27 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   } else
   for (int t = Tn - 1; t >= 0; --t) {
     StageTimer tm(h, (t == 0 || t == Tn - 1) ? RNNLM_STAGE_RNN_BWD : -1, st, t == Tn - 1, t == 0);
-    EpiRnnBwd<T> epi;
-    epi.dHs = dHs32 + (long)t * Bp * Hp;
-    epi.Hs = Hs_c + (long)(t + 1) * Bp * Hp;
-    epi.dA32 = dA32 + (long)t * Bp * Hp;
-    epi.dAc = dA_c + (long)t * Bp * Hp;
-    epi.B = c.B;
-    epi.H = c.H;
-    epi.ld = Hp;
-    const long K = (t == Tn - 1) ? 0 : Hp;
+    const bool contract = t < Tn - 1;  // nothing flows into the window's last position
     const T *A_ = dA_c + (long)(t + 1) * Bp * Hp;
-    const int S = rnn_step_splits(h);
-    if (S > 0) {
-      const long per = (long)Bp * Hp;
-      EpiPartial ep;
-      ep.part = at<float>(h, h->L.part32);
-      ep.ld = Hp;
-      ep.split_stride = per;
-      if (K > 0) {
-        if constexpr (sizeof(T) == 2) {
-          HIP_TRY((launch_gemm_dma4<bf16_t, 256, 128, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, K, S, ep)));
-        } else {
-          HIP_TRY((launch_gemm<T, 256, 64, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, K, S, ep)));
-        }
+    const StepPlan p = step_plan(c, Bp, Hp);
+    const long per = (long)Bp * Hp, at_t = (long)t * per;
+    EpiPartial ep;
+    ep.part = at<float>(h, h->L.part32);
+    ep.ld = Hp;
+    ep.split_stride = p.rows * Hp;
+    if (contract) {
+      if (!p.wide) {
+        HIP_TRY((launch_gemm_dma4<T, 64, 64, 2, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, p.rows, Hp, Hp, p.splits, ep)));
+      } else if constexpr (sizeof(T) == 2) {
+        HIP_TRY((launch_gemm_dma4<bf16_t, 256, 128, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, Hp, p.splits, ep)));
+      } else {
+        HIP_TRY((launch_gemm<T, 256, 64, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, Hp, p.splits, ep)));
       }
-      hipLaunchKernelGGL(rnn_step_bwd_kernel<T>, dim3(blocks_for(per / 4, 256)), dim3(256), 0, st,
-                         at<float>(h, h->L.part32), per, K > 0 ? S : 0, epi.dHs, epi.Hs, c.B, c.H, Hp, per / 4,
-                         epi.dA32, epi.dAc);
-      HIP_TRY(hipGetLastError());
-    } else {
-      HIP_TRY((launch_gemm<T, 32, 64, 1, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, K, 1, epi)));
     }
+    hipLaunchKernelGGL(rnn_step_bwd_kernel<T>, dim3(blocks_for(per / 4, 256)), dim3(256), 0, st,
+                       at<float>(h, h->L.part32), p.rows * Hp, contract ? p.splits : 0, dHs32 + at_t, Hs_c + at_t + per,
+                       c.B, c.H, Hp, per / 4, dA32 + at_t, dA_c + at_t);
+    HIP_TRY(hipGetLastError());
   }
 
   // Where the output weight update is over before a second stream is tied in and out (four events: 20-30 us of host

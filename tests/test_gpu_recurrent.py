@@ -21,6 +21,8 @@ FP32, BF16 = binding.RNNLM_FP32, binding.RNNLM_BF16_FP32MASTER
     (300, 161, 130, 3),   # 17 streams per group: two row blocks
     (300, 290, 17, 2),    # 10 blocks over four waves: the last wave has one
     (300, 1000, 200, 2),  # 25 streams per group, 32 blocks
+    (300, 1100, 1, 8),    # one launch pair per step: one stream, the window's rows a multiple of nothing
+    (300, 1600, 70, 4),   # the same, two 64-row tiles
 ])
 def test_fp32_against_oracle(V, H, B, T):
     g, o = make_pair(V, H, B, T, FP32, seed=V + H + B, scale=0.3 if H < 100 else 0.05, bias_scale=0.5)
@@ -61,3 +63,22 @@ def test_bf16_exchange_and_group_size(H, B, few):
         assert torch.equal(g[k], gc[k]), k
     hf, _ = run(few, binding.RNNLM_EXCHANGE_AUTO)
     assert torch.equal(h[:few], hf)
+
+
+@pytest.mark.parametrize("H,B,T", [(2100, 1, 8), (2400, 64, 4), (4000, 33, 3), (4096, 128, 2)])
+def test_bf16_per_step_against_oracle(H, B, T):
+    """Hidden sizes beyond the persistent kernel.  Tolerances: the state is rounded to bf16 (2^-9) each step; log-probs
+    and gradients as in test_gpu_parity.py's bf16 comparisons."""
+    V = 300
+    E, U, Wo, b = synth.make_weights(V, H, "normal", 0.02, 5)
+    g = binding.Rnnlm(E, U, Wo, b, B, T, BF16)
+    o = O.Model.from_weights(E, U, Wo, b, B)
+    tok = tokens(V, B * T + B + 1, 8)
+    x, y = O.stream_chunk(tok, B, T, 0)
+    r = g.rnnlm_grad_chunk(dev(x), dev(y))
+    ref = O.grad_chunk(o, x, y)
+    assert np.abs(r["logp"].cpu().numpy() - ref["logp"]).max() < 2e-2
+    for k in ("gE", "gU", "gWo", "gb"):
+        d = r[k].cpu().numpy() - ref[k]
+        assert np.linalg.norm(d) <= 2e-2 * np.linalg.norm(ref[k]), k
+    g.rnnlm_check()
