@@ -18,14 +18,15 @@
 // The exchange buffer is a ring of RING = 4 steps' states in operand order: the fragment of 16 streams x 32 values is
 // one contiguous kilobyte (fp32: two), lane l's 16 bytes at 16 l.  (Loaded from the row-major state instead, adjacent
 // lanes ask for different rows and the vector L1 looks every lane up by itself: 2.0 us per step at 128 streams.)
+// At step t a thread sets its words of step t - 2 back to UNWRITTEN.  It may: the barrier inside step t follows the
+// arrival of every workgroup's step t - 1, each of which had read step t - 2 before.  The reset is in place before step
+// t + 2 is stored there and polled: the wave waits for its own stores at its next poll, before it stores step t + 1, and
+// a reader polls for a wave's step t + 2 only after it has that wave's step t + 1.
 //
 // Measured (bf16, per step, forward / backward): H = 1024, one stream 0.93 / 0.94 us, 128 streams 1.24 / 0.97 (with the
 // counter barrier 2.4 / 2.8), 256 streams 1.8 / 1.6; H = 2048, 128 streams 2.6 / 2.5 (4.5 / 5.9); fp32, H = 1024, 128
 // streams 3.2 / 2.8 (9.2 / 10.4).  What is left is latency: an L2 round trip and a half for the wait, the contraction,
-// one LDS exchange and the elementwise part.  At step t a thread sets its words of step t - 2 back to UNWRITTEN.  It may: the barrier inside step t
-// follows the arrival of every workgroup's step t - 1, each of which had read step t - 2 before.  The reset is in
-// place before step t + 2 is stored there and polled: the wave waits for its own stores at its next poll, before it
-// stores step t + 1, and a reader polls for a wave's step t + 2 only after it has that wave's step t + 1.
+// one LDS exchange and the elementwise part.
 #pragma once
 #include <type_traits>
 
@@ -50,7 +51,7 @@ struct RnnPersistArgs {
   // rnn_persistent_kernel: streams per group, groups, workgroups per group, 32-wide blocks of the contraction and how
   // many of them a wave takes; xcd: one group per XCD (see below)
   int R, groups, nwg, nkb, ks, xcd;
-  void *ring;  // exchange buffer, see RingGeom
+  void *ring;  // exchange buffer: [RING][groups][RT][nkb] fragments
 };
 
 // Where the exchanged words travel.  The workgroups that exchange state with one another are exactly those of one
