@@ -860,9 +860,12 @@ int nce_update(rnnlm_t *h, int Tn, const NceCall &n, const UpdateTargets &u, hip
   return RNNLM_OK;
 }
 
-// Backward half of a window + fused updates.
+// Backward half of a window + fused updates.  Everything it starts is ordered before whatever comes next on st.
+// rec_stream (may be nullptr) receives the stream whose next launch is ordered behind the recurrent update: work on the
+// other stream is not.
 template <typename T>
-int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *nce, hipStream_t st) {
+int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *nce, hipStream_t st,
+                    hipStream_t *rec_stream = nullptr) {
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp, Vp = h->Vp;
   const int Mrows = Tn * Bp;
@@ -1050,6 +1053,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   // 319 -> 265 us).
   const bool early_side = c.P == 0;
   const bool early_rec = early_side && (nce || (long)(Hp / BIG) * (Hp / BIG) < 256);
+  if (rec_stream) *rec_stream = early_rec ? es : st;
   if (early_side) {
     int rc = serial ? RNNLM_OK : side_fork(h, 0, st);
     if (rc) return rc;
@@ -1174,7 +1178,8 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
 
 template <typename T>
 int window_call(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float *logp, double *sum_logp,
-                const UpdateTargets *u, bool advance_state, hipStream_t st, const NceCall *nce = nullptr) {
+                const UpdateTargets *u, bool advance_state, hipStream_t st, const NceCall *nce = nullptr,
+                hipStream_t *rec_stream = nullptr) {
   const bool want_sum = sum_logp || u;
   const WindowSum ws = {sum_logp ? sum_logp : p_sum(h), nullptr, p_flags(h), u ? p_counter(h) : nullptr};
   int rc = forward_window<T>(h, x, y, Tn, logp, advance_state, nce == nullptr, st, u != nullptr,
@@ -1188,7 +1193,7 @@ int window_call(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float *l
       HIP_TRY(hipGetLastError());
     }
   }
-  if (u) rc = backward_window<T>(h, Tn, *u, nce, st);
+  if (u) rc = backward_window<T>(h, Tn, *u, nce, st, rec_stream);
   return rc;
 }
 
@@ -1255,25 +1260,27 @@ int rms_decay(rnnlm_t *h, float *r0, float *r1, float *r2, float rho, hipStream_
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
-// Steps of the embedding rows and of the recurrent matrix: on the side stream, behind the kernels that formed their
-// gradients and next to the steps of the output layer.
+// Steps of the embedding rows and of the recurrent matrix, next to the steps of the output layer: each on the stream
+// that formed its gradient (the side stream; rec_stream: as backward_window says).
 template <typename T>
-int rms_apply_side(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, float lr, float eps) {
+int rms_apply_side(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, float lr, float eps,
+                   hipStream_t rec_stream) {
   const rnnlm_config &c = h->cfg;
   hipLaunchKernelGGL(rms_row_apply_kernel<T>, dim3(Tn * c.B), dim3(256), 0, h->side, at<float>(h, h->L.dHs32), (long)h->Hp,
                      at<int32_t>(h, h->L.xp), at<int32_t>(h, h->L.perm), at<int32_t>(h, h->L.seg), p_nseg(h), c.B, h->Bp,
                      c.H, h->Hp, h->buf.E, (T *)nullptr, state.rE, rho, lr, eps);
   const unsigned tiles = blocks_for(c.H, 32);
-  hipLaunchKernelGGL(rms_square_apply_kernel<T>, dim3(tiles, tiles), dim3(256), 0, h->side, at<float>(h, h->L.gU), c.H,
+  hipLaunchKernelGGL(rms_square_apply_kernel<T>, dim3(tiles, tiles), dim3(256), 0, rec_stream, at<float>(h, h->L.gU), c.H,
                      h->buf.U, at<T>(h, h->L.U_c), at<T>(h, h->L.UT_c), h->Hp, state.rU, rho, lr, eps);
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
 template <typename T>
-int rms_apply(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, float lr, float eps, hipStream_t st) {
+int rms_apply(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, float lr, float eps, hipStream_t st,
+              hipStream_t rec_stream) {
   const rnnlm_config &c = h->cfg;
   StageTimer tm(h, RNNLM_STAGE_RMSPROP, st);
-  int rc = rms_apply_side<T>(h, Tn, state, rho, lr, eps);
+  int rc = rms_apply_side<T>(h, Tn, state, rho, lr, eps, rec_stream);
   if (rc) return rc;
   hipLaunchKernelGGL(rms_row_apply_kernel<T>, dim3(c.V), dim3(256), 0, st, at<float>(h, h->L.gWo), (long)c.H, nullptr,
                      nullptr, nullptr, nullptr, c.B, h->Bp, c.H, h->Hp, h->buf.Wo, at<T>(h, h->L.Wo_c), state.rWo, rho, lr,
@@ -1285,10 +1292,10 @@ int rms_apply(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, f
 }
 template <typename T>
 int rms_apply_nce(rnnlm_t *h, int Tn, int K, const rnnlm_rmsprop_state &state, float rho, float lr, float eps,
-                  hipStream_t st) {
+                  hipStream_t st, hipStream_t rec_stream) {
   const rnnlm_config &c = h->cfg;
   StageTimer tm(h, RNNLM_STAGE_RMSPROP, st);
-  int rc = rms_apply_side<T>(h, Tn, state, rho, lr, eps);
+  int rc = rms_apply_side<T>(h, Tn, state, rho, lr, eps, rec_stream);
   if (rc) return rc;
   const int nent = K + Tn * c.B;
   const int32_t *ids = at<int32_t>(h, h->L.ids), *perm2 = at<int32_t>(h, h->L.perm2), *seg2 = at<int32_t>(h, h->L.seg2);
@@ -1542,10 +1549,12 @@ int rnnlm_train_chunk_rmsprop(rnnlm_t *h, const int32_t *x, const int32_t *y, in
   const bool f32 = h->cfg.precision == RNNLM_FP32;
   int rc = rms_decay(h, state->rE, nullptr, nullptr, rho, st);
   if (rc) return rc;
-  rc = f32 ? window_call<float>(h, x, y, T, logp, sum_logp, &u, true, st)
-           : window_call<bf16_t>(h, x, y, T, logp, sum_logp, &u, true, st);
+  hipStream_t rec = nullptr;
+  rc = f32 ? window_call<float>(h, x, y, T, logp, sum_logp, &u, true, st, nullptr, &rec)
+           : window_call<bf16_t>(h, x, y, T, logp, sum_logp, &u, true, st, nullptr, &rec);
   if (rc) return rc;
-  return f32 ? rms_apply<float>(h, T, *state, rho, lr, eps, st) : rms_apply<bf16_t>(h, T, *state, rho, lr, eps, st);
+  return f32 ? rms_apply<float>(h, T, *state, rho, lr, eps, st, rec)
+             : rms_apply<bf16_t>(h, T, *state, rho, lr, eps, st, rec);
 }
 
 int rnnlm_nce_train_chunk_rmsprop(rnnlm_t *h, const int32_t *x, const int32_t *y, int32_t T, const int32_t *noise,
@@ -1563,11 +1572,12 @@ int rnnlm_nce_train_chunk_rmsprop(rnnlm_t *h, const int32_t *x, const int32_t *y
   const bool f32 = h->cfg.precision == RNNLM_FP32;
   int rc = rms_decay(h, state->rE, state->rWo, state->rb, rho, st);
   if (rc) return rc;
-  rc = f32 ? window_call<float>(h, x, y, T, nullptr, sum_J, &u, true, st, &n)
-           : window_call<bf16_t>(h, x, y, T, nullptr, sum_J, &u, true, st, &n);
+  hipStream_t rec = nullptr;
+  rc = f32 ? window_call<float>(h, x, y, T, nullptr, sum_J, &u, true, st, &n, &rec)
+           : window_call<bf16_t>(h, x, y, T, nullptr, sum_J, &u, true, st, &n, &rec);
   if (rc) return rc;
-  return f32 ? rms_apply_nce<float>(h, T, K, *state, rho, lr, eps, st)
-             : rms_apply_nce<bf16_t>(h, T, K, *state, rho, lr, eps, st);
+  return f32 ? rms_apply_nce<float>(h, T, K, *state, rho, lr, eps, st, rec)
+             : rms_apply_nce<bf16_t>(h, T, K, *state, rho, lr, eps, st, rec);
 }
 
 int rnnlm_reset_state(rnnlm_t *h, void *stream) {

@@ -62,6 +62,30 @@ def test_rmsprop_train_chunks_fp32(V, H, B, T, W, r0, rho, eps):
     g.rnnlm_check()
 
 
+@pytest.mark.parametrize("precision,H,rel", [(FP32, 3900, 1e-3), (FP32, 4096, 1e-3), (BF16, 3900, 2e-2), (BF16, 4096, 2e-2)])
+def test_rmsprop_widest_layers(precision, H, rel):
+    """H > 3840: the recurrent gradient is formed behind the output weight update.  Gradients agree within `rel` in the
+    2-norm (test_gpu_parity.py's bound; bf16: its rounding of the state); with statistics that start at zero and
+    eps far above their root the step is linear in the gradient and the statistics are quadratic in it."""
+    V, B, T, lr, rho, eps = 3000, 16, 4, 1e-3, 0.9, 1e-3
+    E, U, Wo, b = synth.make_weights(V, H, "normal", 0.01, 7)
+    g = binding.Rnnlm(E, U, Wo, b, B, T, precision, rmsprop=True, r_init=0.0)
+    o, st = O.Model.from_weights(E, U, Wo, b, B), O.RmspropState.filled(V, H, 0.0)
+    tok = synth.zipf_tokens(3 * B * T + B + 1, V, 1.1, 8)
+    norm = np.linalg.norm
+    for k in range(3):
+        x, y = O.stream_chunk(tok, B, T, k)
+        logp = torch.empty(T, B, device="cuda")
+        g.rnnlm_train_chunk_rmsprop(dev(x), dev(y), lr, rho, eps, logp)
+        ref, _ = O.train_chunk_rmsprop(o, st, x, y, lr, rho, eps)
+        assert norm(logp.cpu().numpy() - ref) <= rel * norm(ref), k
+        moved, moved_ref = g.U.cpu().numpy() - np.float64(U), o.U - np.float64(U)
+        assert norm(moved - moved_ref) <= 2 * rel * norm(moved_ref), (k, norm(moved - moved_ref) / norm(moved_ref))
+        rU = g.rU.cpu().numpy()
+        assert norm(rU - st.rU) <= 4 * rel * norm(st.rU), (k, norm(rU - st.rU) / norm(st.rU))
+    g.rnnlm_check()
+
+
 def test_rmsprop_untouched_words_keep_weights_and_decay():
     V, H, B, T, rho = 500, 32, 4, 4, 0.9
     g, o, st = make(V, H, B, T, FP32, seed=3, r0=0.5)

@@ -1,0 +1,103 @@
+"""The order in which calls enqueue their work, without a GPU: the library runs against a HIP runtime that logs launches,
+event records and event waits (launch_log.cpp), and the happens-before relation between launches is rebuilt from the log.
+Nothing is computed; device addresses are made up and never followed."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_1502_00512_amd import binding
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+STREAM = 0x5000
+FP32, BF16 = 0, 1
+
+# (ctypes alone: torch would bring the real runtime along)
+DRIVER = """
+import ctypes as C, sys
+C.CDLL(sys.argv[1], C.RTLD_GLOBAL)
+lib = C.CDLL(sys.argv[2])
+lib.rnnlm_workspace_bytes.restype = C.c_size_t
+call, args = sys.argv[3], eval(sys.argv[4])
+cfg = (C.c_int32 * 9)(*[args[k] for k in ("V", "H", "B", "T_max", "precision")], 0, args.get("K", 0), args.get("rmsprop", 0), 0)
+at = [1 << 44]
+def dev():
+    at[0] += 1 << 40
+    return at[0]
+class Buffers(C.Structure):
+    _fields_ = [(n, C.c_void_p) for n in ("E", "U", "Wo", "b", "h", "ws")] + [("bytes", C.c_size_t), ("A", C.c_void_p), ("C", C.c_void_p)]
+buf = Buffers(dev(), dev(), dev(), dev(), dev(), dev(), lib.rnnlm_workspace_bytes(cfg), None, None)
+h = C.c_void_p()
+assert lib.rnnlm_init(cfg, C.byref(buf), C.byref(h)) == 0
+f, p, x, y, st, T = C.c_float, C.c_void_p, C.c_void_p(dev()), C.c_void_p(dev()), C.c_void_p(int(sys.argv[5])), args["T"]
+rms = (C.c_void_p * 4)(dev(), dev(), dev(), dev())
+noise, lnq = C.c_void_p(dev()), C.c_void_p(dev())
+for _ in range(2):
+    if call == "train":
+        rc = lib.rnnlm_train_chunk(h, x, y, T, f(0.1), None, None, st)
+    elif call == "rmsprop":
+        rc = lib.rnnlm_train_chunk_rmsprop(h, x, y, T, f(0.1), f(0.9), f(1e-6), rms, None, None, st)
+    elif call == "nce_rmsprop":
+        rc = lib.rnnlm_nce_train_chunk_rmsprop(h, x, y, T, noise, args["K"], lnq, f(7.0), f(0.1), f(0.9), f(1e-6), rms, None, None, st)
+    assert rc == 0, rc
+"""
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_1502_00512_amd.build import build
+        build()
+    so = str(tmp_path_factory.mktemp("runtime") / "liblaunch_log.so")
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "launch_log.cpp")], check=True)
+    return so
+
+
+def enqueue(runtime, tmp_path, call, **args):
+    """Two calls; returns their launches as (stream, kernel, words) and before(i, j): launch i is ordered before launch j."""
+    log = str(tmp_path / "log")
+    r = subprocess.run([sys.executable, "-c", DRIVER, runtime, binding.LIB_PATH, call, repr(args), str(STREAM)],
+                       env=dict(os.environ, LAUNCH_LOG=log), capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    launches, seen, events = [], {}, {}  # seen[stream]: launches that whatever comes next on it is ordered behind
+    known = []
+    for line in open(log):
+        op, stream, rest = line.split(None, 2)
+        past = seen.setdefault(stream, set())
+        if op == "L":
+            kernel, *words = rest.split()
+            known.append(set(past))
+            past.add(len(launches))
+            launches.append((int(stream, 16) if stream != "(nil)" else 0, kernel, [int(w, 16) for w in words if w != "|"]))
+        elif op == "R":
+            events[rest.strip()] = set(past)
+        else:
+            past |= events[rest.strip()]
+    return launches, lambda i, j: i in known[j]
+
+
+@pytest.mark.parametrize("call", ["rmsprop", "nce_rmsprop"])
+@pytest.mark.parametrize("precision", [FP32, BF16])
+@pytest.mark.parametrize("H", [64, 1024, 3840, 3841, 4096])  # from 3841 on the recurrent gradient is formed last
+def test_rmsprop_steps_the_recurrent_matrix_behind_its_gradient(runtime, tmp_path, call, precision, H):
+    launches, before = enqueue(runtime, tmp_path, call, V=3000, H=H, B=16, T_max=4, T=4, precision=precision, rmsprop=1, K=64)
+    steps = [i for i, (_, k, _) in enumerate(launches) if "rms_square_apply" in k]
+    assert len(steps) == 2
+    gradient = launches[steps[0]][2][0]
+    formed = [i for i, (_, k, w) in enumerate(launches) if "gemm" in k and gradient in w]
+    assert len(formed) == 2 and formed[0] < steps[0] < formed[1] < steps[1]
+    for f, s in zip(formed, steps):
+        assert before(f, s)
+    assert before(steps[0], formed[1])  # and the next window's is formed behind the step that read this one's
+
+
+@pytest.mark.parametrize("call,H", [("train", 64), ("train", 1024), ("train", 4096), ("rmsprop", 256), ("rmsprop", 4096),
+                                    ("nce_rmsprop", 256), ("nce_rmsprop", 4096)])
+def test_the_callers_stream_is_behind_all_work_of_a_call(runtime, tmp_path, call, H):
+    launches, before = enqueue(runtime, tmp_path, call, V=3000, H=H, B=16, T_max=4, T=4, precision=BF16, K=64,
+                               rmsprop=int("rmsprop" in call))
+    starts = [i for i, (_, k, _) in enumerate(launches) if "prep_tokens" in k]  # (the second call's decay comes before its)
+    assert len(starts) == 2 and launches[starts[1]][0] == STREAM
+    for i in range(starts[0], starts[1]):
+        assert before(i, starts[1]) or "rms_decay" in launches[i][1], launches[i]
