@@ -322,6 +322,14 @@ __global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShap
 #endif  // __HIP_DEVICE_COMPILE__
 }
 
+// The 32-bit byte offsets of the loads cover an operand's rows within a tile (ROWK), or its k rows (KROW; fp32: those of
+// one block, whose resource moves along).  Callers with larger operands take launch_gemm, which has no such limit.
+template <typename T>
+inline bool dma4_reaches(int layout, long ld, int rows, long K) {
+  constexpr int ES = sizeof(T);
+  return (layout == ROWK ? rows : ES == 4 ? 64 / ES : K) * ld * ES < (1L << 31);
+}
+
 template <typename T, int BM, int BN, int WGM, int WGN, int LA, int LB, bool PERSIST = false, class Epi>
 inline hipError_t launch_gemm_dma4(hipStream_t stream, const void *A, long lda, const void *B, long ldb, long Mg,
                                    long Ng, long K, int splits, const Epi &epi, int band = 4) {
@@ -335,11 +343,7 @@ inline hipError_t launch_gemm_dma4(hipStream_t stream, const void *A, long lda, 
   g.ldb = ldb;
   g.bytesA = ES * lda * (LA == ROWK ? Mg : K);
   g.bytesB = ES * ldb * (LB == ROWK ? Ng : K);
-  // the k blocks of a K-major operand must stay within a 32-bit scalar offset (fp32: each block by itself)
-  const long reach = ES == 4 ? BK : K;
-  if ((LA == KROW && reach * lda * ES >= (1L << 31)) || (LB == KROW && reach * ldb * ES >= (1L << 31)) ||
-      lda * ES * BM >= (1L << 31) || ldb * ES * BN >= (1L << 31))
-    return hipErrorInvalidValue;
+  if (!dma4_reaches<T>(LA, lda, BM, K) || !dma4_reaches<T>(LB, ldb, BN, K)) return hipErrorInvalidValue;
   g.tilesM = (int)(Mg / BM);
   g.tilesN = (int)(Ng / BN);
   g.kBlocks = (int)(K / BK);

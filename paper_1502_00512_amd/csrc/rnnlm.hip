@@ -1126,9 +1126,15 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     epi.lr = u.lr;
     const T *feat = c.P > 0 ? at<T>(h, h->L.P_c) : Hs_c + (long)Bp * Hp;
     if constexpr (sizeof(T) == 4) {
-      const long Dn = f32_extent(h->D, Vp, Mrows, 1);
-      HIP_TRY((f32_gemm<KROW, ROWK>(st, feat, h->Dp, ZT, ldz, Dn, Vp, round_up(Mrows, 32), f32_plan(Dn, Vp, Mrows, 1),
-                                    epi, -4)));
+      const long Dn = f32_extent(h->D, Vp, Mrows, 1), K = round_up(Mrows, 32);
+      const F32Plan plan = f32_plan(Dn, Vp, Mrows, 1);
+      if (dma4_reaches<T>(ROWK, ldz, plan.tile, K)) {
+        HIP_TRY((f32_gemm<KROW, ROWK>(st, feat, h->Dp, ZT, ldz, Dn, Vp, K, plan, epi, -4)));
+      } else if (Dn % 128 == 0) {  // handles of millions of positions
+        HIP_TRY((launch_gemm<T, 128, 128, 2, 2, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, Dn, Vp, K, 1, epi, -4)));
+      } else {
+        HIP_TRY((launch_gemm<T, 64, 64, 2, 2, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, Dn, Vp, K, 1, epi, -4)));
+      }
     } else if ((long)(h->Dp / BIG) * (Vp / BIG) < 128) {  // a narrow layer above the state: smaller tiles fill the chip
       HIP_TRY((launch_gemm_dma4<bf16_t, 128, BIG, 2, 4, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, epi, -4)));
     } else {

@@ -31,3 +31,19 @@ def test_fp32_contraction_tiles(V, H, B, T):
     for k in ("gE", "gU", "gWo", "gb"):
         check_grad(k, r[k], ref[k])
     g.rnnlm_check()
+
+
+def test_fp32_window_of_a_handle_of_millions_of_positions():
+    """Rows of the logits 2^25 bytes apart: beyond what the direct-load kernels' offsets reach over a tile (60 GB of
+    workspace, nearly all of it untouched by the short window)."""
+    V, H, B, T = 200, 8, 65536, 1
+    g, o = make_pair(V, H, B, 129, FP32, seed=5, scale=0.3, bias_scale=0.5)
+    tok = tokens(V, B * T + B + 1, 6)
+    x, y = O.stream_chunk(tok, B, T, 0)
+    r = g.rnnlm_grad_chunk(dev(x), dev(y))
+    ref = O.grad_chunk(o, x, y)
+    check_logp(r["logp"], ref["logp"])
+    for k in ("gE", "gU", "gWo", "gb"):
+        check_grad(k, r[k], ref[k])
+    g.rnnlm_check()
+    g.close()

@@ -1,4 +1,4 @@
-"""The order in which calls enqueue their work, without a GPU: the library runs against a HIP runtime that logs launches,
+"""What calls enqueue and in which order, without a GPU: the library runs against a HIP runtime that logs launches,
 event records and event waits (launch_log.cpp), and the happens-before relation between launches is rebuilt from the log.
 Nothing is computed; device addresses are made up and never followed."""
 import os
@@ -101,3 +101,16 @@ def test_the_callers_stream_is_behind_all_work_of_a_call(runtime, tmp_path, call
     assert len(starts) == 2 and launches[starts[1]][0] == STREAM
     for i in range(starts[0], starts[1]):
         assert before(i, starts[1]) or "rms_decay" in launches[i][1], launches[i]
+
+
+@pytest.mark.parametrize("V,H,B,T_max,T,precision", [
+    (20000, 1000, 65536, 33, 1, FP32),  # 2^21 positions and more: 256 rows of the logits span 2^31 bytes
+    (20000, 1000, 65536, 33, 33, FP32),
+    (200, 8, 65536, 129, 1, FP32),   # 2^23: 64 rows
+    (300, 40, 65536, 256, 3, FP32),  # the most positions a handle may have
+    (300, 300, 65536, 256, 256, FP32),
+])
+def test_sizes_beyond_32_bit_offsets_are_taken(runtime, tmp_path, V, H, B, T_max, T, precision):
+    """Operands whose bytes a contraction kernel's 32-bit offsets do not reach take another kernel."""
+    launches, _ = enqueue(runtime, tmp_path, "train", V=V, H=H, B=B, T_max=T_max, T=T, precision=precision)
+    assert sum("gemm" in k for _, k, _ in launches) >= 6
