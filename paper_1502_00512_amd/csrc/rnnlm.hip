@@ -971,7 +971,9 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     ep.ld = Hp;
     ep.split_stride = p.rows * Hp;
     if (contract) {
-      if (!p.wide) {
+      if (!dma4_reaches<T>(KROW, Hp, 64, Hp)) {  // bf16, a matrix of 2^31 bytes and more
+        HIP_TRY((launch_gemm<T, 64, 64, 2, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, p.rows, Hp, Hp, p.splits, ep)));
+      } else if (!p.wide) {
         HIP_TRY((launch_gemm_dma4<T, 64, 64, 2, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, p.rows, Hp, Hp, p.splits, ep)));
       } else if constexpr (sizeof(T) == 2) {
         HIP_TRY((launch_gemm_dma4<bf16_t, 256, 128, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, Hp, p.splits, ep)));

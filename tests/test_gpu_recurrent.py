@@ -82,3 +82,34 @@ def test_bf16_per_step_against_oracle(H, B, T):
         d = r[k].cpu().numpy() - ref[k]
         assert np.linalg.norm(d) <= 2e-2 * np.linalg.norm(ref[k]), k
     g.rnnlm_check()
+
+
+def test_bf16_state_to_state_matrix_of_2_gib():
+    """H = 32768: the per-step backward product's K-major operand is beyond the direct-load kernels' offsets.  One window
+    against 64-bit arithmetic on the device (the oracle would take minutes); tolerances as above."""
+    V, H, B, T = 200, 32768, 3, 3
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    draw = lambda *shape: torch.randn(*shape, generator=gen, device="cuda")
+    E, Wo, b = draw(V, H) * 0.1, draw(V, H) * 0.01, draw(V)
+    U = draw(H, H) * 0.005
+    x, y = dev(tokens(V, T * B, 21).reshape(T, B)), dev(tokens(V, T * B, 22).reshape(T, B))
+    m = binding.Rnnlm(E, U, Wo, b, B, T, BF16)
+    r = m.rnnlm_grad_chunk(x, y)
+    m.rnnlm_check()
+    m.close()
+    E, U, Wo, b = (t.double() for t in (E, U, Wo, b))
+    h = [torch.zeros(B, H, dtype=torch.float64, device="cuda")]
+    for t in range(T):
+        h.append(torch.sigmoid(E[x[t].long()] + h[-1] @ U.t()))
+    z = torch.stack(h[1:]) @ Wo.t() + b
+    logp = z.log_softmax(2)
+    dz = (logp.exp() - torch.nn.functional.one_hot(y.long(), V)) / (B * T)
+    da, dU, dE = torch.zeros_like(h[0]), torch.zeros_like(U), torch.zeros_like(E)
+    for t in reversed(range(T)):
+        da = (dz[t] @ Wo + da @ U) * h[t + 1] * (1 - h[t + 1])
+        dU += da.t() @ h[t]
+        dE.index_add_(0, x[t].long(), da)
+    want = dict(gE=dE, gU=dU, gWo=(dz.reshape(T * B, V).t() @ torch.cat(h[1:])), gb=dz.sum((0, 1)))
+    assert (r["logp"] - logp.gather(2, y.long()[..., None])[..., 0]).abs().max() < 2e-2
+    for k, w in want.items():
+        assert (r[k] - w).norm() <= 2e-2 * w.norm(), k

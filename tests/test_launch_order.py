@@ -109,6 +109,9 @@ def test_the_callers_stream_is_behind_all_work_of_a_call(runtime, tmp_path, call
     (200, 8, 65536, 129, 1, FP32),   # 2^23: 64 rows
     (300, 40, 65536, 256, 3, FP32),  # the most positions a handle may have
     (300, 300, 65536, 256, 256, FP32),
+    (200, 32768, 2, 4, 3, BF16),     # a state-to-state matrix of 2^31 bytes, few streams and whole blocks of 256
+    (200, 33000, 256, 4, 3, BF16),
+    (200, 33000, 3, 4, 3, FP32),
 ])
 def test_sizes_beyond_32_bit_offsets_are_taken(runtime, tmp_path, V, H, B, T_max, T, precision):
     """Operands whose bytes a contraction kernel's 32-bit offsets do not reach take another kernel."""
