@@ -270,9 +270,11 @@ int rnnlm_sort_segments(rnnlm_t *h, const int32_t *x, int32_t T, int32_t *perm, 
 int rnnlm_sort_segments_static(const int32_t *x, int32_t T, int32_t B, int32_t V, int32_t *perm, int32_t *seg_start,
                                int32_t *nseg, int32_t *range_flag, void *stream);
 
-/* Number of polls a wait of the persistent recurrent kernels makes before it gives up,
- * raises the flag that rnnlm_check reports as RNNLM_ERR_TIMEOUT and lets the kernel run to its end
- * (default 2^18, about a second).  For tests of that error path: polls = 1 makes waits expire at once. */
+/* Number of polls, of about 4 us each (or as many shorter ones as take that time), a wait of the persistent
+ * recurrent kernels makes before it gives up, raises the flag that rnnlm_check reports as RNNLM_ERR_TIMEOUT and
+ * lets the kernel run to its end (default 2^18, about a second).  A wait lasts longer than a step's few
+ * microseconds where other work on the GPU keeps a workgroup from starting.  For tests of that error path:
+ * polls = 1 makes waits expire at the first. */
 int rnnlm_set_barrier_spin_limit(rnnlm_t *h, uint32_t polls);
 
 /* How the workgroups of a persistent recurrent kernel hand the state h_t (backward: the gradient dA_t) to one

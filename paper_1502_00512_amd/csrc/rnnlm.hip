@@ -67,7 +67,7 @@ struct rnnlm {
   hipEvent_t ev_fork[2] = {nullptr, nullptr}, ev_join[2] = {nullptr, nullptr};
   bool xcd_local = false;        // the probe at init saw round-robin placement over 8 XCDs
   int exchange_mode = RNNLM_EXCHANGE_AUTO;  // how the persistent recurrent kernels exchange state between workgroups
-  unsigned spin_limit = 1u << 18;  // polls of a grid barrier before giving up (about a second)
+  unsigned spin_limit = 1u << 18;  // polls of a recurrent kernel's wait before giving up (about a second)
   uint32_t prof_mask = 0;
   std::vector<EventPair> prof_pool;
   size_t prof_used = 0;
@@ -458,7 +458,10 @@ int launch_rnn_persistent(rnnlm_t *h, int Tn, bool advance_state, hipStream_t st
   a.H = h->cfg.H;
   a.Bp = h->Bp;
   a.Hp = h->Hp;
-  a.spin_limit = h->spin_limit;
+  // This kernel's poll is one reload of a wave's fragments (0.21 us at H = 2048, 256 streams), a counter's 4 us: 20 for
+  // one, or a workgroup that other work on the device keeps from starting is given up after 0.06 s instead of a second.
+  // (Spacing the polls out inside the kernel cost 2 % of a scored sentence.)
+  a.spin_limit = h->spin_limit == 1 ? 1u : (unsigned)std::min<unsigned long>(h->spin_limit * 20ul, 0xffffffffu);
   const RecurrentPlan &p = h->plan;
   a.ring = h->ws + h->L.ring + (BACKWARD ? align256(p.ring_bytes(sizeof(T))) : 0);
   a.R = p.R;

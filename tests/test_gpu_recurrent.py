@@ -113,3 +113,27 @@ def test_bf16_state_to_state_matrix_of_2_gib():
     assert (r["logp"] - logp.gather(2, y.long()[..., None])[..., 0]).abs().max() < 2e-2
     for k, w in want.items():
         assert (r[k] - w).norm() <= 2e-2 * w.norm(), k
+
+
+def test_late_workgroups_are_waited_for():
+    """Another stream's kernel holds a compute unit (a scan along the rows of one block of columns, some 0.3 s) while a
+    window starts whose recurrent kernel wants all of them: its last workgroup starts when the scan is over, the others
+    wait for it within the default limit of about a second, and the window is scored as on an idle device."""
+    V, H, B, T = 500, 2048, 256, 6
+    E, U, Wo, b = synth.make_weights(V, H, "normal", 0.02, 3)
+    x = dev(tokens(V, T * B, 11).reshape(T, B))
+    y = dev(tokens(V, T * B, 12).reshape(T, B))
+    m = binding.Rnnlm(E, U, Wo, b, B, T, BF16)
+    want = m.rnnlm_forward_logprob(x, y).clone()
+    m.rnnlm_check()
+    m.rnnlm_reset_state()
+    rows = torch.zeros(700000, 512, device="cuda")
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(other):
+        held = torch.cumsum(rows, 0)
+    got = m.rnnlm_forward_logprob(x, y)
+    m.rnnlm_check()
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    del held
