@@ -280,14 +280,17 @@ int rnnlm_set_barrier_spin_limit(rnnlm_t *h, uint32_t polls);
 /* How the workgroups of a persistent recurrent kernel hand the state h_t (backward: the gradient dA_t) to one
  * another between the steps of a window (Sec. 4.2: the state-to-state work of all streams is done together).
  * AUTO (default): the XCD-local exchange when the placement probe at init allows it and there are at most 8
- * blocks of 32 streams, else the chip-wide one.  CHIP_WIDE: always agent-scope accesses.  XCD_LOCAL: like AUTO, but RNNLM_ERR_ARG when the XCD-local exchange is not available for this
- * handle.  Both exchanges compute the same values in the same order: results are bitwise equal (tested).
+ * blocks of 32 streams, else the chip-wide one.  CHIP_WIDE: always agent-scope accesses.  XCD_LOCAL: like AUTO, but
+ * RNNLM_ERR_ARG when the XCD-local exchange is not available for this handle.  Both exchanges compute the same values in the same order: results are bitwise equal (tested).
  * The widest recurrent shape (bf16, H padded to 4096, 256 streams) runs as one launch that keeps the
  * state-to-state matrix in the register files of all compute units; it needs the same placement as the XCD-local
  * exchange, and CHIP_WIDE selects one launch pair per step for it instead (same products, another order of
- * additions: equal to bf16 rounding of the state, not bitwise).  That one-launch kernel occupies every compute
- * unit for its duration: calls on two handles of that shape must not overlap in time on one GPU (their waits
- * would expire: RNNLM_ERR_TIMEOUT).  No effect on other shapes that run one launch per step. */
+ * additions: equal to bf16 rounding of the state, not bitwise).  No effect on other shapes that run one launch per
+ * step (bf16 from H = 2049 on, fp32 from 1025, very many streams).
+ * Overlap: all workgroups of a one-launch recurrence have to be on the GPU at once.  The calls of two handles may
+ * overlap in time on one GPU where two such kernels fit it together: bf16 up to H = 768, and up to 1024 with at most
+ * 128 streams; fp32 up to H = 256, and up to 512 with at most 128 streams; any shape that runs one launch per step.
+ * Beyond that calls on two handles must not overlap on one GPU (their waits would expire: RNNLM_ERR_TIMEOUT). */
 typedef enum { RNNLM_EXCHANGE_AUTO = 0, RNNLM_EXCHANGE_CHIP_WIDE = 1, RNNLM_EXCHANGE_XCD_LOCAL = 2 } rnnlm_exchange;
 int rnnlm_set_recurrent_exchange(rnnlm_t *h, int32_t mode);
 

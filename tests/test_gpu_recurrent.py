@@ -137,3 +137,31 @@ def test_late_workgroups_are_waited_for():
     torch.cuda.synchronize()
     assert torch.equal(got, want)
     del held
+
+
+@pytest.mark.parametrize("precision,H,B", [(BF16, 1024, 128), (BF16, 700, 256), (FP32, 512, 128), (FP32, 250, 256)])
+def test_two_handles_train_side_by_side(precision, H, B):
+    """Windows of two handles on streams of their own overlap, at the largest shapes the header allows: the workgroups of two
+    recurrent kernels fit the device together, however they are dispatched.  Both handles end up with the weights that
+    each trains to alone."""
+    V, T, K = 300, 6, 60
+    E, U, Wo, b = synth.make_weights(V, H, "normal", 0.03, 3)
+    x = dev(tokens(V, K * T * B, 31).reshape(K, T, B))
+    y = dev(tokens(V, K * T * B, 32).reshape(K, T, B))
+
+    def train(models, streams):
+        torch.cuda.synchronize()
+        for k in range(K):
+            for m, s in zip(models, streams):
+                m.rnnlm_train_chunk(x[k], y[k], 0.05, stream=s)
+        torch.cuda.synchronize()
+        for m in models:
+            m.rnnlm_check()
+
+    alone = binding.Rnnlm(E, U, Wo, b, B, T, precision)
+    train([alone], [torch.cuda.current_stream()])
+    pair = [binding.Rnnlm(E, U, Wo, b, B, T, precision) for _ in range(2)]
+    train(pair, [torch.cuda.Stream(), torch.cuda.Stream()])
+    for m in pair:
+        for n in ("E", "U", "Wo", "b", "h_state"):
+            assert torch.equal(getattr(m, n), getattr(alone, n)), n
