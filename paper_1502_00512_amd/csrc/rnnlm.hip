@@ -574,6 +574,14 @@ bool scan_ids(const rnnlm_t *h, int Tn, const UpdateTargets &u) {
   return u.e_compact_ld == 0 && (long)Tn * h->cfg.B <= (h->cfg.P > 0 ? SCAN_MAX : 1024);
 }
 
+// Where the output weight update is over before a second stream is tied in and out (four events: 20-30 us of host time
+// and of latency between the streams), the small updates stay on the caller's stream (V = 1000, H = 64, 4x8: 117 -> 67
+// us; V = 10000, H = 256, 32x10 is faster with the second stream).
+bool short_output_update(const rnnlm_t *h, int Tn) {
+  const double n = (double)h->Vp * h->Dp, rate = h->cfg.precision == RNNLM_FP32 ? 1e8 : 6e8;  // per us
+  return 2.0 * n * window_rows(h->cfg, (long)Tn * h->Bp) / rate + 8.0 * n / 4e6 < 15.0;
+}
+
 // train: a backward pass follows.  sort_inputs: its embedding update wants the input ids sorted: started on the side
 // stream as soon as the padded ids exist (the update runs on that stream too).
 template <typename T>
@@ -993,11 +1001,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     HIP_TRY(hipGetLastError());
   }
 
-  // Where the output weight update is over before a second stream is tied in and out (four events: 20-30 us of host
-  // time and of latency between the streams), the small updates stay on the caller's stream (V = 1000, H = 64, 4x8:
-  // 117 -> 67 us; V = 10000, H = 256, 32x10 is faster with the second stream).
-  const double out_w_us = 2.0 * Vp * h->Dp * Mp / (sizeof(T) == 4 ? 1e8 : 6e8) + 8.0 * Vp * h->Dp / 4e6;
-  const bool serial = !nce && scan_ids(h, Tn, u) && out_w_us < 15.0;
+  const bool serial = !nce && scan_ids(h, Tn, u) && short_output_update(h, Tn);
   hipStream_t es = serial ? st : h->side;
   // E[w] -= lr * sum_{m: x[m] = w} dA[m]: on the side stream, behind the sort helpers already queued there (joined at
   // the end of this function).
@@ -1265,22 +1269,30 @@ bool window_args_ok(rnnlm_t *h, const int32_t *x, const int32_t *y, int T) {
 }
 
 // The statistics' decay depends on nothing in the window: it starts on the side stream with it (joined with that stream's
-// other work at the end of the backward pass).
-int rms_decay(rnnlm_t *h, float *r0, float *r1, float *r2, float rho, hipStream_t st) {
-  int rc = side_fork(h, 0, st);
+// other work at the end of the backward pass).  Short windows spend their time in the host's calls: there neither the
+// decay nor the steps overlap anything, which saves a pair of events each.  With and without the overlap, bf16: softmax, V
+// = 1000, H = 64, one position 160 and 138 us, 1024 positions 167 and 157, 2048 positions 175 and 180 (V = 20000, H = 1024,
+// 128 positions, not short: 229 and 232); noise-contrastive, V = 10000, H = 512, 256 positions 213 and 182, V = 64000,
+// H = 1024, 1280 positions 205 and 187, 2560 positions 249 and 253.
+bool rms_overlaps(const rnnlm_t *h, int Tn, bool nce) {
+  return (long)Tn * h->cfg.B > 1024 || !(nce || short_output_update(h, Tn));
+}
+int rms_decay(rnnlm_t *h, float *r0, float *r1, float *r2, float rho, bool overlap, hipStream_t st) {
+  int rc = overlap ? side_fork(h, 0, st) : RNNLM_OK;
   if (rc) return rc;
-  hipLaunchKernelGGL(rms_decay_kernel, dim3(blocks_for(h->cfg.V, 256), r1 ? 3 : 1), dim3(256), 0, h->side, r0, r1, r2,
-                     (long)h->cfg.V, rho);
+  hipLaunchKernelGGL(rms_decay_kernel, dim3(blocks_for(h->cfg.V, 256), r1 ? 3 : 1), dim3(256), 0, overlap ? h->side : st,
+                     r0, r1, r2, (long)h->cfg.V, rho);
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
-// Steps of the embedding rows and of the recurrent matrix, next to the steps of the output layer: each on the stream
-// that formed its gradient (the side stream; rec_stream: as backward_window says).
+// Steps of the embedding rows and of the recurrent matrix, on streams that are ordered behind their gradients: next to the
+// steps of the output layer, the stream that formed the gradient (the side stream; backward_window says which one formed
+// the recurrent one), otherwise the caller's.
 template <typename T>
-int rms_apply_side(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, float lr, float eps,
-                   hipStream_t rec_stream) {
+int rms_apply_inner(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, float lr, float eps,
+                    hipStream_t emb_stream, hipStream_t rec_stream) {
   const rnnlm_config &c = h->cfg;
-  hipLaunchKernelGGL(rms_row_apply_kernel<T>, dim3(Tn * c.B), dim3(256), 0, h->side, at<float>(h, h->L.dHs32), (long)h->Hp,
+  hipLaunchKernelGGL(rms_row_apply_kernel<T>, dim3(Tn * c.B), dim3(256), 0, emb_stream, at<float>(h, h->L.dHs32), (long)h->Hp,
                      at<int32_t>(h, h->L.xp), at<int32_t>(h, h->L.perm), at<int32_t>(h, h->L.seg), p_nseg(h), c.B, h->Bp,
                      c.H, h->Hp, h->buf.E, (T *)nullptr, state.rE, rho, lr, eps);
   const unsigned tiles = blocks_for(c.H, 32);
@@ -1294,7 +1306,8 @@ int rms_apply(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, f
               hipStream_t rec_stream) {
   const rnnlm_config &c = h->cfg;
   StageTimer tm(h, RNNLM_STAGE_RMSPROP, st);
-  int rc = rms_apply_side<T>(h, Tn, state, rho, lr, eps, rec_stream);
+  const bool overlap = rms_overlaps(h, Tn, false);
+  int rc = rms_apply_inner<T>(h, Tn, state, rho, lr, eps, overlap ? h->side : st, overlap ? rec_stream : st);
   if (rc) return rc;
   hipLaunchKernelGGL(rms_row_apply_kernel<T>, dim3(c.V), dim3(256), 0, st, at<float>(h, h->L.gWo), (long)c.H, nullptr,
                      nullptr, nullptr, nullptr, c.B, h->Bp, c.H, h->Hp, h->buf.Wo, at<T>(h, h->L.Wo_c), state.rWo, rho, lr,
@@ -1302,14 +1315,15 @@ int rms_apply(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, f
   hipLaunchKernelGGL(rms_elem_apply_kernel, dim3(blocks_for(c.V, 256)), dim3(256), 0, st, at<float>(h, h->L.gb), c.V,
                      h->buf.b, state.rb, rho, lr, eps);
   HIP_TRY(hipGetLastError());
-  return side_join(h, 0, st);
+  return overlap ? side_join(h, 0, st) : RNNLM_OK;
 }
 template <typename T>
 int rms_apply_nce(rnnlm_t *h, int Tn, int K, const rnnlm_rmsprop_state &state, float rho, float lr, float eps,
                   hipStream_t st, hipStream_t rec_stream) {
   const rnnlm_config &c = h->cfg;
   StageTimer tm(h, RNNLM_STAGE_RMSPROP, st);
-  int rc = rms_apply_side<T>(h, Tn, state, rho, lr, eps, rec_stream);
+  const bool overlap = rms_overlaps(h, Tn, true);
+  int rc = rms_apply_inner<T>(h, Tn, state, rho, lr, eps, overlap ? h->side : st, overlap ? rec_stream : st);
   if (rc) return rc;
   const int nent = K + Tn * c.B;
   const int32_t *ids = at<int32_t>(h, h->L.ids), *perm2 = at<int32_t>(h, h->L.perm2), *seg2 = at<int32_t>(h, h->L.seg2);
@@ -1319,7 +1333,7 @@ int rms_apply_nce(rnnlm_t *h, int Tn, int K, const rnnlm_rmsprop_state &state, f
   hipLaunchKernelGGL(rms_bias_compact_kernel, dim3(blocks_for(nent, 256)), dim3(256), 0, st, at<float>(h, h->L.gbN), ids,
                      perm2, seg2, p_nseg2(h), h->buf.b, state.rb, rho, lr, eps);
   HIP_TRY(hipGetLastError());
-  return side_join(h, 0, st);
+  return overlap ? side_join(h, 0, st) : RNNLM_OK;
 }
 }  // namespace
 
@@ -1561,7 +1575,7 @@ int rnnlm_train_chunk_rmsprop(rnnlm_t *h, const int32_t *x, const int32_t *y, in
         *gb = reinterpret_cast<float *>(h->ws + h->L.gb), *gE = reinterpret_cast<float *>(h->ws + h->L.dHs32);
   UpdateTargets u{gE, gU, gWo, gb, 0.0f, -1.0f, false, true, h->Hp};
   const bool f32 = h->cfg.precision == RNNLM_FP32;
-  int rc = rms_decay(h, state->rE, nullptr, nullptr, rho, st);
+  int rc = rms_decay(h, state->rE, nullptr, nullptr, rho, rms_overlaps(h, T, false), st);
   if (rc) return rc;
   hipStream_t rec = nullptr;
   rc = f32 ? window_call<float>(h, x, y, T, logp, sum_logp, &u, true, st, nullptr, &rec)
@@ -1584,7 +1598,7 @@ int rnnlm_nce_train_chunk_rmsprop(rnnlm_t *h, const int32_t *x, const int32_t *y
   UpdateTargets u{gE, gU, gN, gbN, 0.0f, -1.0f, false, true, h->Hp, h->Hp};
   NceCall n{noise, K, lnq, lnZ, J, true};
   const bool f32 = h->cfg.precision == RNNLM_FP32;
-  int rc = rms_decay(h, state->rE, state->rWo, state->rb, rho, st);
+  int rc = rms_decay(h, state->rE, state->rWo, state->rb, rho, rms_overlaps(h, T, true), st);
   if (rc) return rc;
   hipStream_t rec = nullptr;
   rc = f32 ? window_call<float>(h, x, y, T, nullptr, sum_J, &u, true, st, &n, &rec)

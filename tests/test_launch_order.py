@@ -103,6 +103,14 @@ def test_the_callers_stream_is_behind_all_work_of_a_call(runtime, tmp_path, call
         assert before(i, starts[1]) or "rms_decay" in launches[i][1], launches[i]
 
 
+@pytest.mark.parametrize("call", ["rmsprop", "nce_rmsprop"])
+@pytest.mark.parametrize("V,H,B,T,beside", [(1000, 64, 1, 1, False), (1375, 384, 4, 3, False), (64000, 1024, 128, 20, True)])
+def test_rmsprop_steps_leave_the_callers_stream_in_long_windows_only(runtime, tmp_path, call, V, H, B, T, beside):
+    """Every pair of events that ties the second stream in costs a short window, which the host bounds, some 10 us."""
+    launches, _ = enqueue(runtime, tmp_path, call, V=V, H=H, B=B, T_max=T, T=T, precision=BF16, rmsprop=1, K=64)
+    assert {s != STREAM for s, k, _ in launches if "rms_decay" in k or "rms_square_apply" in k} == {beside}
+
+
 @pytest.mark.parametrize("V,H,B,T_max,T,precision", [
     (20000, 1000, 65536, 33, 1, FP32),  # 2^21 positions and more: 256 rows of the logits span 2^31 bytes
     (20000, 1000, 65536, 33, 33, FP32),
