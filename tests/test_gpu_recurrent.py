@@ -49,19 +49,22 @@ def test_bf16_exchange_and_group_size(H, B, few):
 
     def run(n, mode):
         m = binding.Rnnlm(E, U, Wo, b, n, T, BF16)
-        m.rnnlm_set_recurrent_exchange(mode)
+        try:
+            m.rnnlm_set_recurrent_exchange(mode)
+        except binding.RnnlmError:
+            pytest.skip("this device does not place workgroups round-robin over 8 XCDs: no XCD-local exchange")
         for _ in range(3):
             m.rnnlm_forward_logprob(dev(x[:, :n]), dev(y[:, :n]))
         grads = m.rnnlm_grad_chunk(dev(x[:, :n]), dev(y[:, :n]))
         m.rnnlm_check()
         return m.h_state.cpu(), grads
 
-    h, g = run(B, binding.RNNLM_EXCHANGE_AUTO)
+    h, g = run(B, binding.RNNLM_EXCHANGE_XCD_LOCAL)
     hc, gc = run(B, binding.RNNLM_EXCHANGE_CHIP_WIDE)
     assert torch.equal(h, hc)
     for k in g:
         assert torch.equal(g[k], gc[k]), k
-    hf, _ = run(few, binding.RNNLM_EXCHANGE_AUTO)
+    hf, _ = run(few, binding.RNNLM_EXCHANGE_XCD_LOCAL)
     assert torch.equal(h[:few], hf)
 
 
