@@ -322,7 +322,8 @@ typedef enum {
   RNNLM_STAGE_NCE_BWD_H = 13,   /* gradient w.r.t. the hidden states (contraction over the noise words + targets) */
   RNNLM_STAGE_NCE_BWD_W = 14,   /* noise-row weight gradient contraction */
   RNNLM_STAGE_NCE_UPDATE = 15,  /* sort/segments of the touched words + row and bias updates */
-  RNNLM_STAGE_RMSPROP = 16,     /* rmsprop calls: statistics + scaled updates from the gradient buffers */
+  RNNLM_STAGE_RMSPROP = 16,     /* rmsprop calls: statistics + scaled updates from the gradient buffers, on both
+                                   streams (not the decay of the per-word statistics, which starts with the window) */
   RNNLM_STAGE_PROJ = 17,        /* compressed architecture: the contractions through the layers below and above
                                    the state (forward, backward and their weight updates) */
   RNNLM_STAGE_COUNT = 18

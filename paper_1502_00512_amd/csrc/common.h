@@ -47,15 +47,16 @@ __device__ inline bf16_t from_f32<bf16_t>(float v) { return (bf16_t)v; }  // rou
 // Barrier and ticket counters of the persistent recurrent kernels.  Every counter has a 256-byte line to itself:
 // polls queue at the address they read, and with the counters of all eight XCDs in one line (or all workgroups
 // of the chip polling one word) an arrival took several microseconds to become visible to the pollers instead
-// of under one.  kind 0 (x = 0): workgroups of the statistics merge that have finished; kind 1: step barrier of the group on XCD x (resident kernel); kind 2: ticket dispenser of XCD x; kinds
-// 3 and 4: the two levels of the resident kernel's chip-wide barrier (arrivals of XCD x's workgroups; XCDs that have
-// fully arrived, one copy per XCD).
+// of under one.  kind 0 (x = 0): workgroups of the statistics merge that have finished; kind 1: step barrier of the
+// group on XCD x (resident kernel); kind 2: ticket dispenser of XCD x; kinds 3 and 4: the two levels of the resident
+// kernel's chip-wide barrier (arrivals of XCD x's workgroups; XCDs that have fully arrived, one copy per XCD).
 constexpr int SYNC_WORDS = 5 * 8 * 64;
 __host__ __device__ inline int sync_word(int kind, int x) { return (kind * 8 + x) * 64; }
 
 // 1 / (1 + e^-a).  The quotient is the hardware reciprocal with one Newton step, which is as close to the exact one as
 // the compiler's division is (both within 0.51 ulp) in a third of its instructions: in the recurrent kernels it stands
-// between a step's sums and the next step.  (An infinite denominator has no Newton step: the quotient is 0 as it is.)
+// between a step's sums and the next step.  (An infinite denominator has no Newton step: the quotient is 0 as it is.  A
+// quotient below the smallest normal number, a < -87.3, is 0 as well: the reciprocal has no denormal results.)
 __device__ inline float sigmoidf_(float a) {
   const float d = 1.0f + __expf(-a), q = __builtin_amdgcn_rcpf(d);
   const float r = fmaf(fmaf(-d, q, 1.0f), q, q);

@@ -576,10 +576,9 @@ struct EpiPartial : EpiZeroInit {
   }
 };
 
-// Plain store of the tile into a tile-padded buffer, in fp32 (out32) and/or in the compute type (outc).
+// Plain store of the tile into a tile-padded buffer, in the compute type.
 template <typename T>
 struct EpiStore : EpiZeroInit {
-  float *out32;
   T *outc;
   long ld;
   template <int BM, int BN>
@@ -594,8 +593,7 @@ struct EpiStore : EpiZeroInit {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const long row = c.tile_row0 + c.wrow + i * 32 + RNNLM_ACC_ROW(r, c.lane);
-          if (out32) out32[row * ld + col] = acc[i][j][r];
-          if (outc) outc[row * ld + col] = from_f32<T>(acc[i][j][r]);
+          outc[row * ld + col] = from_f32<T>(acc[i][j][r]);
         }
       }
   }

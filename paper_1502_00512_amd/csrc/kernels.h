@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(256) transpose_kernel(const T *__restrict__ sr
 // ---- a2 / a8, per-step path for hidden sizes beyond the persistent kernel: the step's contraction runs
 // split over the contraction dimension (so that every compute unit gets a workgroup and each operand panel
 // is fetched by few of them); these kernels sum the partial products in a fixed order and apply the step's
-// elementwise part.  n4 = Bp*Hp/4 groups of 4 columns; part[split][Bp][Hp].
+// elementwise part.  n4 = Bp*Hp/4 groups of 4 columns; part[split][rows][Hp], rows >= Bp of whole tiles (split_stride).
 template <typename T>
 __global__ void rnn_step_fwd_kernel(const float *__restrict__ part, long split_stride, int splits,
                                     const float *__restrict__ X, int B, int H, int Hp, long n4,
@@ -512,9 +512,9 @@ __global__ void segment_kernel(const int32_t *__restrict__ xp, const int32_t *__
 // round-robin to PARTS partial sums (member i of the run goes
 // to sum i mod PARTS, each sum accumulated in ascending m), which are then added in order 0..PARTS-1: a fixed
 // summation tree, so results are bitwise reproducible.  All PARTS sums live in the thread's registers: a group
-// of 16 members is 16 independent row loads in flight, and the small workgroups (no LDS, no barrier) leave
-// eight of them resident per compute unit, which is what a pass made of dependent memory round trips (run
-// bounds -> position -> rows) needs: it is bound by latency times occupancy, not by bandwidth.
+// of 16 members is 16 independent row loads in flight, and the small workgroups (with a sorted list no LDS and no
+// barrier) leave eight of them resident per compute unit, which is what a pass made of dependent memory round trips
+// (run bounds -> position -> rows) needs: it is bound by latency times occupancy, not by bandwidth.
 // A thread owns 4 consecutive columns (the rows of dA are tile-padded and aligned).  ALIGNED: H % 4 == 0, the rows of the
 // updated matrix are accessed 16 bytes at a time; otherwise (any H) element by element, the last group partly.
 // Ec (may be nullptr): compute copy [.][ldc] of the updated matrix, refreshed with the new row (the tied word

@@ -56,7 +56,6 @@ struct rnnlm {
   int Pp;     // cfg.P rounded up to the tile size (0: plain architecture)
   int D, Dp;  // width of the output layer's input: H / Hp, or P / Pp for the compressed architecture
   int KpMax;  // K_max rounded up to the tile size (0: no noise-contrastive workspace)
-  int nPart;
   RecurrentPlan plan;
   WsLayout L;
   char *ws;
@@ -303,7 +302,7 @@ long features_formed(const rnnlm_config &c, long Mp, int max_splits) {
   return c.P > 0 ? round_up(c.P, PAD_H) : f32_extent(c.H, Mp, c.V, max_splits);
 }
 
-void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, int &nPart, int &KpMax, WsLayout &L) {
+void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, int &KpMax, WsLayout &L) {
   const size_t es = (c.precision == RNNLM_FP32) ? 4 : 2;
   const int Pp = (int)round_up(c.P, PAD_H);
   Hp = (int)round_up(c.H, PAD_H);
@@ -313,7 +312,7 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   const RecurrentPlan plan = recurrent_plan(c);
   Bp = plan.nwg == 0 && Hp >= 2048 && round_up(c.B, PAD_B) % 256 == 0 ? (int)round_up(c.B, PAD_B) : c.B;
   MpMax = (int)round_up((long)c.T_max * Bp, PAD_M);
-  nPart = Vp / (es == 4 ? 64 : BIG);  // one softmax-statistics partial per tile row block (fp32: of the smaller tile)
+  const int nPart = Vp / (es == 4 ? 64 : BIG);  // one softmax-statistics partial per tile row block (fp32: of the smallest tile)
   if (es == 4) {
     L.partElems = (long)MpMax * Dp;
     for (long M = 64; M <= MpMax; M += M < F32_TRIM_ROWS ? 64 : PAD_M)
@@ -568,15 +567,20 @@ int sort_segments(rnnlm_t *h, int Tn, int32_t *perm, int32_t *seg, int32_t *nseg
 // Does the embedding update find the positions of each word by itself (no sorted list)?  Not where the list names the
 // rows of a compact buffer, nor in windows its workgroups cannot compare in one go.  Beyond 1024 positions the plain
 // architecture sorts: its embedding update runs next to the output weight update, which every workgroup's comparisons
-// slow down (V = 64000, H = 1024, 128x20: 1253 us with them, 1241 sorted; compressed, where the update stands alone and
-// the sort delays the recurrent steps: 382 against 389).
+// slow down; in the compressed one the update stands alone and the sort delays the recurrent steps.  Compared and sorted,
+// bf16: V = 10000, H = 256, 512 positions 132 and 139 us, 1024 155 and 153, 2560 220 and 223; V = 3000, H = 64, 512
+// positions 128 and 132, 1024 154 and 148, 2560 216 and 189; V = 64000, H = 1024, 512 positions 470 and 473, 1024 631 and
+// 628, 2560 1221 and 1210; compressed, V = 10000, H = 1024, P = 512, 512 positions 214 and 217, 2560 353 and 359, 4000 467
+// and 483.
 bool scan_ids(const rnnlm_t *h, int Tn, const UpdateTargets &u) {
   return u.e_compact_ld == 0 && (long)Tn * h->cfg.B <= (h->cfg.P > 0 ? SCAN_MAX : 1024);
 }
 
 // Where the output weight update is over before a second stream is tied in and out (four events: 20-30 us of host time
-// and of latency between the streams), the small updates stay on the caller's stream (V = 1000, H = 64, 4x8: 117 -> 67
-// us; V = 10000, H = 256, 32x10 is faster with the second stream).
+// and of latency between the streams), the small updates stay on the caller's stream.  With and without the second
+// stream: fp32 V = 1000, H = 64, 4x8 92 and 67 us; bf16 V = 3000, H = 256, 16x8 111 and 106, 32x30 164 and 170.  Beyond the
+// line fp32 still gains (V = 10000, H = 256, 32x10 165 and 146; V = 10000, H = 512, 32x30 476 and 469; V = 20000, H = 1024,
+// 32x30 1269 and 1273), bf16 below some 500 positions (V = 30000, H = 256, 16x8 148 and 140; 32x30 227 and 231).
 bool short_output_update(const rnnlm_t *h, int Tn) {
   const double n = (double)h->Vp * h->Dp, rate = h->cfg.precision == RNNLM_FP32 ? 1e8 : 6e8;  // per us
   return 2.0 * n * window_rows(h->cfg, (long)Tn * h->Bp) / rate + 8.0 * n / 4e6 < 15.0;
@@ -696,7 +700,6 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
   if (c.P > 0) {
     StageTimer tm(h, RNNLM_STAGE_PROJ, st);
     EpiStore<T> epi;
-    epi.out32 = nullptr;
     epi.outc = at<T>(h, h->L.P_c);
     epi.ld = h->Pp;
     HIP_TRY((mid_gemm<T, ROWK, ROWK>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.C_c), Hp, Mp,
@@ -1341,9 +1344,9 @@ extern "C" {
 
 size_t rnnlm_workspace_bytes(const rnnlm_config *cfg) {
   if (!cfg_ok(cfg)) return 0;
-  int Hp, Vp, Bp, MpMax, nPart, KpMax;
+  int Hp, Vp, Bp, MpMax, KpMax;
   WsLayout L;
-  make_layout(*cfg, Hp, Vp, Bp, MpMax, nPart, KpMax, L);
+  make_layout(*cfg, Hp, Vp, Bp, MpMax, KpMax, L);
   return L.total;
 }
 
@@ -1363,7 +1366,7 @@ int rnnlm_init(const rnnlm_config *cfg, const rnnlm_buffers *buf, rnnlm_t **out)
   if (!h) return RNNLM_ERR_NOMEM;
   h->cfg = *cfg;
   h->buf = *buf;
-  make_layout(*cfg, h->Hp, h->Vp, h->Bp, h->MpMax, h->nPart, h->KpMax, h->L);
+  make_layout(*cfg, h->Hp, h->Vp, h->Bp, h->MpMax, h->KpMax, h->L);
   h->plan = recurrent_plan(*cfg);
   h->Pp = (int)round_up(cfg->P, PAD_H);
   h->D = cfg->P > 0 ? cfg->P : cfg->H;
@@ -1386,7 +1389,7 @@ int rnnlm_init(const rnnlm_config *cfg, const rnnlm_buffers *buf, rnnlm_t **out)
     rc = (cfg->precision == RNNLM_FP32) ? sync_copies<float>(h, nullptr) : sync_copies<bf16_t>(h, nullptr);
   if (rc == RNNLM_OK && hipDeviceSynchronize() != hipSuccess) rc = RNNLM_ERR_HIP;
   if (rc == RNNLM_OK) {
-    // where do the workgroups of a grid land?  (uses the start of the not-yet-used logits buffer)
+    // where do the workgroups of a grid land?  (uses the start of the not-yet-used embedding rows)
     constexpr int N = 64 * NUM_XCD;
     int32_t *dev = at<int32_t>(h, h->L.X32);
     int32_t host[N];

@@ -272,9 +272,8 @@ def test_bf16_training_tracks_oracle():
 
 @pytest.mark.parametrize("precision", [FP32, BF16])
 def test_grid_barrier_timeout_is_reported(precision):
-    """With a spin limit of one poll the grid barriers of the persistent recurrent kernel expire: the
-    kernels still run to their end and the next check reports the condition (fp32: operands straight from
-    memory; bf16: the LDS-staged variant)."""
+    """With a spin limit of one poll the waits of the persistent recurrent kernel expire: the kernels still run
+    to their end and the next check reports the condition."""
     g, _ = make_pair(1000, 256, 64, 6, precision, seed=5)
     tok = tokens(1000, 2000, 3)
     x, y = O.stream_chunk(tok, 64, 6, 0)
@@ -529,10 +528,10 @@ def test_bf16_training_tracks_oracle_at_cfg3_model_size():
 # ---- the two state exchanges of the persistent recurrent kernels ---------------------------------------
 
 @pytest.mark.parametrize("precision,V,H,B,T,K", [
-    (BF16, 64000, 1024, 128, 20, 200),   # cfg3's shape: 4-wave kernels, state staged through LDS
-    (BF16, 2000, 2048, 128, 20, 60),     # cfg4's hidden size: the wide kernel, one workgroup per compute unit
+    (BF16, 64000, 1024, 128, 20, 200),   # cfg3's shape: four waves and 32 units per workgroup
+    (BF16, 2000, 2048, 128, 20, 60),     # cfg4's hidden size: eight waves and 64 units, one workgroup per compute unit
     (BF16, 1500, 1536, 70, 5, 40),       # ragged streams, 1024 < H < 2048
-    (FP32, 1000, 256, 64, 6, 60),        # fp32: operands straight from memory
+    (FP32, 1000, 256, 64, 6, 60),        # fp32: two pieces per fragment
 ])
 def test_state_exchange_modes_agree_bitwise(precision, V, H, B, T, K):
     """The XCD-local exchange (plain stores and loads through one XCD's L2) against the chip-wide one
