@@ -289,7 +289,7 @@ int rnnlm_set_barrier_spin_limit(rnnlm_t *h, uint32_t polls);
  * step (bf16 from H = 2049 on, fp32 from 1025, very many streams).
  * Overlap: all workgroups of a one-launch recurrence have to be on the GPU at once.  The calls of two handles may
  * overlap in time on one GPU where two such kernels fit it together: bf16 up to H = 768, and up to 1024 with at most
- * 128 streams; fp32 up to H = 256, and up to 512 with at most 128 streams; any shape that runs one launch per step.
+ * 128 streams; fp32 up to H = 512; any shape that runs one launch per step.
  * Beyond that calls on two handles must not overlap on one GPU (their waits would expire: RNNLM_ERR_TIMEOUT). */
 typedef enum { RNNLM_EXCHANGE_AUTO = 0, RNNLM_EXCHANGE_CHIP_WIDE = 1, RNNLM_EXCHANGE_XCD_LOCAL = 2 } rnnlm_exchange;
 int rnnlm_set_recurrent_exchange(rnnlm_t *h, int32_t mode);

@@ -164,8 +164,16 @@ __device__ inline void mma_block(f32x4_t (&acc)[2], int, const StepFrag<float> &
 // one per compute unit of an XCD.
 // The host guarantees that the grid is small enough to be co-resident; every wait is bounded: on expiry flags[2] is
 // raised, the wave waits no more and the kernel runs to its end.
+// Two handles' kernels are certain to fit the device together where a wave takes at most 168 of the 512 registers a SIMD
+// lane has (three waves): one of 200 can start, next to a wave of another kernel that ends later, where neither side of
+// it has room for a second, and then both handles' waits expired.  rnn_pairs: the forms held to that (no form is slower
+// for it: fp32, H = 512, 256 streams, a 20-step scoring call 82.5 us, before 83.5).
+template <typename T, int KS, int NWAVE, int RT>
+constexpr bool rnn_pairs() {
+  return NWAVE == 4 && (sizeof(T) == 2 ? RT == 1 || KS <= 6 : KS <= 4);
+}
 template <typename T, int KS, int NWAVE, int UT, int RT, bool BACKWARD>
-__global__ void __launch_bounds__(64 * NWAVE) rnn_persistent_kernel(const RnnPersistArgs a) {
+__global__ void __launch_bounds__(64 * NWAVE, (rnn_pairs<T, KS, NWAVE, RT>() ? 3 : 1)) rnn_persistent_kernel(const RnnPersistArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int ES = sizeof(T);
   constexpr int V = RT * UT * 4 / NWAVE;  // consecutive units per thread in the elementwise part
@@ -262,19 +270,20 @@ __global__ void __launch_bounds__(64 * NWAVE) rnn_persistent_kernel(const RnnPer
     return reinterpret_cast<char *>(((unsigned long long)hi << 32) | lo);
   };
   int expired = 0;
-  constexpr int RB = NWAVE == 8 ? 1 : RT;  // row blocks whose fragments fit the registers at once
+  // row blocks whose fragments fit the registers at once (fp32, KS = 3 and 4: at two, 174 and 206 registers)
+  constexpr int RB = NWAVE == 8 || (ES == 4 && KS >= 3 && KS <= 4) ? 1 : RT;
   StepFrag<T> f[RB][KS];
   auto step_of = [&](auto first, int step_, Operands &now, Operands &next) {
     const int step = __builtin_amdgcn_readfirstlane(step_);
     const int t = BACKWARD ? a.T - 1 - step : step;
     constexpr bool contract = !(BACKWARD && first.value);  // nothing flows into the window's last position
-    f32x4_t acc[RT][UT][2];
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-#pragma unroll
-      for (int u = 0; u < UT; ++u)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) acc[r][u][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // partial tiles through LDS: lane l holds units 4 (l / 16) .. +3 of stream l % 16.  Two buffers, one barrier per
+    // step: a wave writes a buffer again only after the barrier of the step between, which follows every read of it.
+    float *rd = red[step & 1];
+    auto hand_over = [&](int r, int u, const f32x4_t &v) {
+      *reinterpret_cast<f32x4_t *>(rd + ((wave * RT + r) * UT + u) * TILE +
+                                   ((lane & 48) + (lr ^ ((lane >> 4) << 2))) * 4) = v;
+    };
     if constexpr (contract) {
       // (a block past this wave's share reads through a resource without extent: zeros, no memory access)
       char *const src = uniform(ring + (long)((step - 1) & (RING - 1)) * ring_slot + kb0 * (LOADS * 1024));
@@ -282,6 +291,11 @@ __global__ void __launch_bounds__(64 * NWAVE) rnn_persistent_kernel(const RnnPer
       const unsigned limit = first.value ? 0u : __builtin_amdgcn_readfirstlane(expired ? 0u : a.spin_limit);
 #pragma unroll
       for (int r0 = 0; r0 < RT; r0 += RB) {
+        f32x4_t acc[RB][UT][2];
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int u = 0; u < UT; ++u) acc[r][u][0] = acc[r][u][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         unsigned spins = 0;
         bool missing;
         do {
@@ -320,21 +334,22 @@ __global__ void __launch_bounds__(64 * NWAVE) rnn_persistent_kernel(const RnnPer
 #pragma unroll
           for (int r = 0; r < RB; ++r)
 #pragma unroll
-            for (int u = 0; u < UT; ++u) mma_block(acc[r0 + r][u], kk, w[u][kk], f[r][kk]);
+            for (int u = 0; u < UT; ++u) mma_block(acc[r][u], kk, w[u][kk], f[r][kk]);
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int u = 0; u < UT; ++u) hand_over(r0 + r, u, acc[r][u][0] + acc[r][u][1]);
       }
-    } else if (step + 1 < a.T) {
-      __builtin_amdgcn_s_waitcnt(0x0F70);  // as above: step 0's own operands would be waited for together with the next ones
-      request(BACKWARD ? t - 1 : t + 1, next);
+    } else {
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int u = 0; u < UT; ++u) hand_over(r, u, f32x4_t{0.f, 0.f, 0.f, 0.f});
+      if (step + 1 < a.T) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // as above: step 0's own operands would be waited for together with the next ones
+        request(BACKWARD ? t - 1 : t + 1, next);
+      }
     }
-    // partial tiles through LDS: lane l holds units 4 (l / 16) .. +3 of stream l % 16.  Two buffers, one barrier per
-    // step: a wave writes a buffer again only after the barrier of the step between, which follows every read of it.
-    float *rd = red[step & 1];
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-#pragma unroll
-      for (int u = 0; u < UT; ++u)
-        *reinterpret_cast<f32x4_t *>(rd + ((wave * RT + r) * UT + u) * TILE +
-                                     ((lane & 48) + (lr ^ ((lane >> 4) << 2))) * 4) = acc[r][u][0] + acc[r][u][1];
     __syncthreads();
     float s[V];
 #pragma unroll

@@ -248,9 +248,6 @@ int desired_splits(long Mp, long Hp, long kBlocks) {
 // waves with half the registers and 64 units up to 2048 (bf16 fragments only).  Streams are split into at most eight
 // groups where 32 streams per group allow it (one group per XCD: a step's time grows with the state a compute unit
 // loads), and the grid is small enough to be co-resident with one workgroup per compute unit.
-// Two handles' kernels are certain to fit the device together while a wave takes at most 168 of the 512 registers a lane
-// has on a SIMD: one of 184 (bf16, H = 1024, 256 streams) can start, next to a wave of another kernel that ends later,
-// where neither side of it has room for a second, and then both handles' waits expired.  The header says which shapes.
 RecurrentPlan recurrent_plan(const rnnlm_config &c) {
   RecurrentPlan p = {};
   if (c.H > (c.precision == RNNLM_FP32 ? 1024 : 2048)) return p;
