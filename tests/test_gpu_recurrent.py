@@ -119,7 +119,7 @@ def test_bf16_state_to_state_matrix_of_2_gib():
 
 
 def test_late_workgroups_are_waited_for():
-    """Another stream's kernel holds a compute unit (a scan along the rows of one block of columns, some 0.3 s) while a
+    """Another stream's kernel holds a compute unit (a scan along the rows of one block of columns, some 0.2 s) while a
     window starts whose recurrent kernel wants all of them: its last workgroup starts when the scan is over, the others
     wait for it within the default limit of about a second, and the window is scored as on an idle device."""
     V, H, B, T = 500, 2048, 256, 6
@@ -130,7 +130,7 @@ def test_late_workgroups_are_waited_for():
     want = m.rnnlm_forward_logprob(x, y).clone()
     m.rnnlm_check()
     m.rnnlm_reset_state()
-    rows = torch.zeros(700000, 512, device="cuda")
+    rows = torch.zeros(400000, 512, device="cuda")
     other = torch.cuda.Stream()
     torch.cuda.synchronize()
     with torch.cuda.stream(other):
