@@ -18,12 +18,8 @@
 //
 // fp32 operands (K blocks of 16 in two steps of 8; ROWK fragments are one 16-byte read as above, KROW fragments four
 // 4-byte reads of 32 consecutive rows, the half-waves reading k and k + 4, whose rows start at the same bank: physical
-// chunk = logical ^ (8 * (k / 4 % 2)) moves one of them to the other 32 banks).  The fp32 matrix rate is a sixteenth of
-// the bf16 one, so the contraction is bound by the matrix cores alone if nothing delays them:
-//   - no staging registers: a register-staged 256 x 256 tile spilled 120-205 registers and ran at 69-73 TFLOP/s (64,000 x
-//     1280 outputs, depth 1024; the same product here: 136; a bare fp32 MFMA loop: 155);
-//   - few barriers per MFMA: 256 x 256 tiles on eight waves 140 TFLOP/s, 128 x 128 on four 136, 64 x 64 126 (the last for
-//     outputs with few tiles; five and two such workgroups share a compute unit).
+// chunk = logical ^ (8 * (k / 4 % 2)) moves one of them to the other 32 banks): 64 x 64 tiles, for the steps of a
+// recurrence outside the persistent kernel and contractions of up to 64 terms; everything else takes gemm_split.h.
 #pragma once
 #include "gemm_dma.h"
 

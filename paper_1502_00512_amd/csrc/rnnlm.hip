@@ -18,6 +18,7 @@
 #include "nce.h"
 #include "rmsprop.h"
 #include "gemm_ring64.h"
+#include "gemm_split.h"
 #include "rnn_persistent.h"
 #include "rnn_resident.h"
 
@@ -121,33 +122,47 @@ namespace {
 // output tile, 8 waves as 2 x 4 (wave tile 128 x 64).
 constexpr int BIG = 256;
 
-// fp32 contractions: 256x256 output tiles on eight waves (one workgroup per compute unit), 128x128 or 64x64 on four (two
-// and five workgroups).  The tile and the number of splits of the contraction dimension minimise an estimate of the time.
-// A 64x64 tile's K block of 32 takes 1024 clocks (0.43 us) of a compute unit's matrix cores; workgroups that share a
-// compute unit share its rate, and a round of them ends together (the last, partly filled round fills compute units in
-// pairs: 640 workgroups of 128x128 took as long as 1024); measured against the rate of a bare MFMA loop (155 TFLOP/s),
-// whole rounds reach 92 % (256), 90 % (128) and 82 % (64); every split adds a pass over the output.
+// fp32 contractions (gemm_split.h): 256x256 output tiles on eight waves, 128x128 on eight that share out the contraction in
+// pairs, 64x64 on four or, where there are few tiles, on eight or sixteen that share it out.  The contraction over the
+// vocabulary (the only one that may be split) takes 256x128 tiles instead of 256x256, which leave registers for the lesser
+// products' own accumulators: 7 % slower, but the errors of a long sum in one accumulator are alike at all positions, and
+// the recurrent gradient, which adds up the positions, was 1.2 times as far from 64 bits as through the fp32 matrix cores
+// (now 0.3).  Contractions of up to 64 terms take 64x64 tiles on the fp32 cores (parts = 0, gemm_dma4.h), which round less
+// there (split, 4..30 terms: 1.3 times as far from 64 bits).
+// The tile and the number of splits of the contraction dimension minimise an estimate of the time, fitted to runs of
+// 16..2560 tiles and depths of 32..4096 (both operands K-contiguous, both K-major; us, kb = 32-deep blocks): every full
+// round of 256 tiles 10.5 + 4.45 kb (256x256) and 4.6 + 1.3 kb (128x128: one workgroup per compute unit; a partly filled
+// round runs at a higher clock); 64x64, one workgroup per compute unit 3.2 + 0.69 kb on four waves, 3.8 + 0.51 kb on eight,
+// 5.7 + 0.47 kb on sixteen, four per compute unit 5.2 + 1.77 kb; every split adds a pass over the output.
 struct F32Plan {
-  int tile, splits;
+  // parts: groups of waves that share out the contraction (0: fp32 matrix cores; tile 256, parts 2: 256x128)
+  int tile, parts, splits;
   double us;
 };
 F32Plan f32_plan(long Mg, long Ng, long K, int max_splits) {
   const long kb = (K + 31) / 32;
-  F32Plan best = {64, 1, 1e30};
-  for (int tile = 64; tile <= 256; tile *= 2) {
-    if (Mg % tile || Ng % tile) continue;
-    const double unit = (tile == 256 ? 16 / 0.92 : tile == 128 ? 4 / 0.90 : 1 / 0.82) * 0.43;
-    const int share = tile == 256 ? 1 : tile == 128 ? 2 : 5;
-    const long tiles = (Mg / tile) * (Ng / tile);
-    for (int S = 1; S <= max_splits && S <= kb; ++S) {
-      const long per = (kb + S - 1) / S, wgs = tiles * S;
-      const long rounds = wgs / (256 * share), rest = wgs % (256 * share);
-      // the rest: one per compute unit when it is all there is, otherwise packed
-      const long last = rest == 0 ? 0 : rounds == 0 ? (rest + 255) / 256 : share;
-      double us = (double)(rounds * share + last) * unit * per;
-      if (S > 1) us += 5.0 + (S + 1) * (double)Mg * Ng * 4.0 / 4e6;
-      if (us < best.us) best = {tile, S, us};
-    }
+  const bool split = kb > 2;  // shorter sums round less on the fp32 cores
+  F32Plan best = {64, 0, 1, 1e30};
+  for (int S = 1; S <= max_splits && S <= kb; ++S) {
+    const long per = (kb + S - 1) / S;
+    const double pass = S > 1 ? 5.0 + (S + 1) * (double)Mg * Ng * 4.0 / 4e6 : 0.0;
+    auto consider = [&](int tile, int parts, double us) {
+      if (us + pass < best.us) best = {tile, parts, S, us + pass};
+    };
+    auto whole = [&](int rows, int cols, double fixed, double unit, double half) {  // one workgroup per compute unit
+      const long w = (Mg / rows) * (Ng / cols) * S, rest = w % 256;
+      return 2.0 + w / 256 * (fixed + unit * per) + (rest ? fixed + (half + (unit - half) * rest / 256) * per : 0.0);
+    };
+    if (split && max_splits == 1 && Mg % 256 == 0 && Ng % 256 == 0) consider(256, 1, whole(256, 256, 10.5, 4.45, 3.2));
+    if (split && max_splits > 1 && Mg % 256 == 0 && Ng % 128 == 0) consider(256, 2, whole(256, 128, 7.0, 2.4, 1.75));
+    if (split && Mg % 128 == 0 && Ng % 128 == 0) consider(128, 2, whole(128, 128, 4.6, 1.3, 1.05));
+    const long w = (Mg / 64) * (Ng / 64) * S, share = std::min<long>((w + 255) / 256, 4);
+    const double more = std::max(1.0, w / 1024.0);
+    consider(64, 0, 2.1 + 0.85 * share + (more - 1) * 2.0 + (0.15 + 0.49 * share) * per * more);
+    if (!split) continue;
+    consider(64, 1, 2.6 + 0.65 * share + (more - 1) * 2.2 + (0.33 + 0.36 * share) * per * more);
+    if (w <= 256) consider(64, 2, 3.8 + 0.51 * per);
+    if (w <= 256) consider(64, 4, 5.7 + 0.47 * (per + per % 2));
   }
   return best;
 }
@@ -155,11 +170,11 @@ F32Plan f32_plan(long Mg, long Ng, long K, int max_splits) {
 // (the buffers are padded to 256; bf16 contractions take all of it).
 long f32_extent(long valid, long other, long K, int max_splits) {
   long best = round_up(valid, 256);
-  double us = f32_plan(best, other, K, max_splits).us;
+  double us = f32_plan(other, best, K, max_splits).us;
   for (long pad = 128; pad >= 64; pad /= 2) {
     const long n = round_up(valid, pad);
-    const double t = f32_plan(n, other, K, max_splits).us;
-    if (t < us) {
+    const double t = f32_plan(other, n, K, max_splits).us;
+    if (t <= us) {
       us = t;
       best = n;
     }
@@ -169,12 +184,19 @@ long f32_extent(long valid, long other, long K, int max_splits) {
 template <int LA, int LB, class Epi>
 hipError_t f32_gemm(hipStream_t st, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
                     const F32Plan &plan, const Epi &epi, int band = 4) {
-  if (plan.tile == 256) {
-    constexpr bool PERSIST = Epi::template lds_bytes<256, 256>() == 0;
-    return launch_gemm_dma4<float, 256, 256, 2, 4, LA, LB, PERSIST>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
-  }
+  if constexpr (LA == KROW && LB == KROW)
+    if (plan.tile == 256 && plan.parts == 2)
+      return launch_gemm_split<256, 128, 4, 2, 1, LA, LB, 2, 1>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
+  if (plan.tile == 256)
+    return launch_gemm_split<256, 256, 2, 4, 1, LA, LB, 1, 1>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
   if (plan.tile == 128)
-    return launch_gemm_dma4<float, 128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
+    return launch_gemm_split<128, 128, 2, 2, 2, LA, LB, 2, 1>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
+  if (plan.parts == 4)  // (operands are padded to 64 at least)
+    return launch_gemm_split<64, 64, 2, 2, 4, LA, LB, 4, 2>(st, A, lda, B, ldb, Mg, Ng, round_up(K, 64), plan.splits, epi, band);
+  if (plan.parts == 2)
+    return launch_gemm_split<64, 64, 2, 2, 2, LA, LB, 2, 2>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
+  if (plan.parts == 1)
+    return launch_gemm_split<64, 64, 2, 2, 1, LA, LB, 1, 2>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
   return launch_gemm_dma4<float, 64, 64, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
 }
 
@@ -1096,62 +1118,54 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
       HIP_TRY((mid_gemm<T, KROW, KROW>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.dP_c), h->Pp, Hp, h->Pp, Mp, 1, epi)));
     }
     {
-    // Wo[v][j] -= lr * sum_m dz[v][m] Hs[m][j]: bf16 in the matrix's own orientation, fp32 and the compressed
-    // architecture contracted transposed (tile rows = j, tile columns = v); compressed architecture: the
-    // output-side update of the tied matrix, E[v][p] -= lr * sum_m dz[v][m] p[m][p]
+    // Wo[v][j] -= lr * sum_m dz[v][m] Hs[m][j]; compressed architecture: the output-side update of the tied matrix,
+    // E[v][p] -= lr * sum_m dz[v][m] p[m][p].  bf16 compressed: contracted transposed (tile rows = p, tile columns = v).
+    // Everything else in the matrix's own orientation (tile rows = v, tile columns = j), whose update epilogue touches two
+    // 128-byte lines per wave instruction instead of 32 (fp32, V = 64000, H = 1024, 1280 positions: 893 -> 841 us).
     StageTimer tm(h, RNNLM_STAGE_OUT_BWD_W, st);
-    if (sizeof(T) == 2 && c.P == 0) {
-      // bf16 path: contracted in the matrix's own orientation (tile rows = v, tile columns = j), whose update
-      // epilogue touches two 128-byte lines per wave instruction instead of 32.  Tiles are walked in bands of 4
-      // (wide matrices: 8) tile columns, so that the 32 tiles an XCD works on at a time share few operand panels
-      // in its L2 (8 x 4 or 4 x 8 instead of 2 x 16: 4 % faster on the widest configuration)
-      EpiSgd<T> e2;
-      e2.W = h->buf.Wo;
-      e2.out = u.Wo;
-      e2.Wc = u.refresh_copies ? Wo_c : nullptr;
-      e2.ldw = c.H;
-      e2.ldc = Hp;
-      e2.R = c.V;
-      e2.C = c.H;
-      e2.alpha = u.alpha;
-      e2.lr = u.lr;
-      if constexpr (sizeof(T) == 2) {
-        // dz is the K-contiguous operand: up to 8 tile columns its tiles travel as whole cache lines (64-deep
-        // blocks, gemm_ring64.h: 8-9 % faster at H = 1024 and 2048); the widest layer runs at the chip's power
-        // limit, where the symmetric ring measured 0.5 % better
-        if (Hp / BIG >= 16) {
-          HIP_TRY((big_gemm<2, 4, ROWK, KROW, true>(st, ZT, ldz, Hs_c + (long)Bp * Hp, Hp, Vp, Hp, Mp, 1, e2, -8)));
-        } else {
-          HIP_TRY((launch_gemm_ring64<BIG, BIG, 2, 4>(st, ZT, ldz, Hs_c + (long)Bp * Hp, Hp, Vp, Hp, Mp, 1, e2, -4)));
-        }
-      }
-    } else {
-    EpiSgdT<T> epi;
-    epi.W = c.P > 0 ? h->buf.E : h->buf.Wo;
-    epi.out = c.P > 0 ? u.E : u.Wo;
-    epi.Wc = u.refresh_copies ? Wo_c : nullptr;
-    epi.ldw = h->D;
-    epi.ldc = h->Dp;
-    epi.R = c.V;
-    epi.C = h->D;
-    epi.alpha = u.alpha;
-    epi.lr = u.lr;
+    auto aim = [&](auto &epi) {
+      epi.W = c.P > 0 ? h->buf.E : h->buf.Wo;
+      epi.out = c.P > 0 ? u.E : u.Wo;
+      epi.Wc = u.refresh_copies ? Wo_c : nullptr;
+      epi.ldw = h->D;
+      epi.ldc = h->Dp;
+      epi.R = c.V;
+      epi.C = h->D;
+      epi.alpha = u.alpha;
+      epi.lr = u.lr;
+    };
     const T *feat = c.P > 0 ? at<T>(h, h->L.P_c) : Hs_c + (long)Bp * Hp;
+    EpiSgd<T> epi;
+    aim(epi);
     if constexpr (sizeof(T) == 4) {
       const long Dn = f32_extent(h->D, Vp, Mrows, 1), K = round_up(Mrows, 32);
-      const F32Plan plan = f32_plan(Dn, Vp, Mrows, 1);
-      if (dma4_reaches<T>(ROWK, ldz, plan.tile, K)) {
-        HIP_TRY((f32_gemm<KROW, ROWK>(st, feat, h->Dp, ZT, ldz, Dn, Vp, K, plan, epi, -4)));
+      const F32Plan plan = f32_plan(Vp, Dn, Mrows, 1);
+      if (split_reaches(ROWK, ldz, plan.tile, 64)) {
+        HIP_TRY((f32_gemm<ROWK, KROW>(st, ZT, ldz, feat, h->Dp, Vp, Dn, K, plan, epi, -4)));
       } else if (Dn % 128 == 0) {  // handles of millions of positions
-        HIP_TRY((launch_gemm<T, 128, 128, 2, 2, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, Dn, Vp, K, 1, epi, -4)));
+        HIP_TRY((launch_gemm<T, 128, 128, 2, 2, ROWK, KROW>(st, ZT, ldz, feat, h->Dp, Vp, Dn, K, 1, epi, -4)));
       } else {
-        HIP_TRY((launch_gemm<T, 64, 64, 2, 2, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, Dn, Vp, K, 1, epi, -4)));
+        HIP_TRY((launch_gemm<T, 64, 64, 2, 2, ROWK, KROW>(st, ZT, ldz, feat, h->Dp, Vp, Dn, K, 1, epi, -4)));
       }
-    } else if ((long)(h->Dp / BIG) * (Vp / BIG) < 128) {  // a narrow layer above the state: smaller tiles fill the chip
-      HIP_TRY((launch_gemm_dma4<bf16_t, 128, BIG, 2, 4, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, epi, -4)));
+    } else if (c.P == 0) {
+      // Tiles are walked in bands of 4 (wide matrices: 8) tile columns, so that the 32 tiles an XCD works on at a time
+      // share few operand panels in its L2 (8 x 4 or 4 x 8 instead of 2 x 16: 4 % faster on the widest configuration).
+      // dz is the K-contiguous operand: up to 8 tile columns its tiles travel as whole cache lines (64-deep blocks,
+      // gemm_ring64.h: 8-9 % faster at H = 1024 and 2048); the widest layer runs at the chip's power limit, where the
+      // symmetric ring measured 0.5 % better
+      if (Hp / BIG >= 16) {
+        HIP_TRY((big_gemm<2, 4, ROWK, KROW, true>(st, ZT, ldz, feat, Hp, Vp, Hp, Mp, 1, epi, -8)));
+      } else {
+        HIP_TRY((launch_gemm_ring64<BIG, BIG, 2, 4>(st, ZT, ldz, feat, Hp, Vp, Hp, Mp, 1, epi, -4)));
+      }
     } else {
-      HIP_TRY((big_gemm<2, 4, KROW, ROWK, true>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, epi, -2)));
-    }
+      EpiSgdT<T> et;
+      aim(et);
+      if ((long)(h->Dp / BIG) * (Vp / BIG) < 128) {  // a narrow layer above the state: smaller tiles fill the chip
+        HIP_TRY((launch_gemm_dma4<bf16_t, 128, BIG, 2, 4, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, et, -4)));
+      } else {
+        HIP_TRY((big_gemm<2, 4, KROW, ROWK, true>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, et, -2)));
+      }
     }
     }
     if (c.P > 0) {

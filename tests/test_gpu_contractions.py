@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from oracle import oracle as O
-from paper_1502_00512_amd import binding
+from paper_1502_00512_amd import binding, synth
 from test_gpu_parity import check_grad, check_logp, dev, make_pair, tokens
 
 pytestmark = pytest.mark.gpu
@@ -47,3 +47,41 @@ def test_fp32_window_of_a_handle_of_millions_of_positions():
         check_grad(k, r[k], ref[k])
     g.rnnlm_check()
     g.close()
+
+
+@pytest.mark.parametrize("V,H,B,T", [
+    (1500, 64, 13, 5),      # output layer of 64 terms: the fp32 matrix cores; 65 positions: a weight update just beyond them
+    (1500, 65, 8, 8),       # and the other way round
+    (600, 200, 64, 30),     # few 64-wide tiles, long sums: the recurrent update on sixteen waves
+    (900, 900, 5, 40),      # 64-wide tiles on eight waves, extents padded to 64
+    (2000, 300, 60, 20),    # and on four
+])
+def test_fp32_contractions_of_split_operands(V, H, B, T):
+    g, o = make_pair(V, H, B, T, FP32, seed=V + H, scale=0.2 if H < 100 else 0.05, bias_scale=0.5)
+    tok = tokens(V, B * T + B + 1, 8)
+    x, y = O.stream_chunk(tok, B, T, 0)
+    r = g.rnnlm_grad_chunk(dev(x), dev(y))
+    ref = O.grad_chunk(o, x, y)
+    check_logp(r["logp"], ref["logp"])
+    for k in ("gE", "gU", "gWo", "gb"):
+        check_grad(k, r[k], ref[k])
+    g.rnnlm_check()
+
+
+@pytest.mark.parametrize("V,H,B,T", [(700, 200, 8, 9), (3000, 520, 60, 7), (12000, 1000, 128, 9)])
+def test_fp32_contractions_of_infinite_and_huge_operands(V, H, B, T):
+    """A word with an infinite weight has probability 0 or is never the target; one near the largest fp32 value, which a
+    bf16 cannot hold, still has its own sum.  Both leave the other words' results as they are."""
+    E, U, Wo, b = synth.make_weights(V, H, "uniform", 0.05, V)
+    Wo[V - 1, 3] = -np.inf
+    Wo[5, H - 1] = np.float32(-3.4e38)
+    Wo[7, 2] = np.float32(1e37)
+    Wo[7, 5] = np.float32(-2e37)
+    g = binding.Rnnlm(E, U, Wo, b, B, T, FP32)
+    tok = tokens(V - 10, B * T + B + 1, 9) + 8
+    x, y = O.stream_chunk(tok, B, T, 0)
+    got = g.rnnlm_forward_logprob(dev(x), dev(y)).cpu().numpy()
+    Wo[[V - 1, 5, 7]] = -1e6  # words of probability 0
+    ref = O.forward_logprob(O.Model.from_weights(E, U, Wo, b, B), x, y)
+    check_logp(torch.as_tensor(got), ref)
+    g.rnnlm_check()
