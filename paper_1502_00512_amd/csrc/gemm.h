@@ -348,6 +348,16 @@ __device__ inline char *quarter_ptr(const EpiCtx &c, int qi) {
 // ---- Tile store helpers --------------------------------------------------------------------------
 
 
+// Two adjacent columns of one row from two lanes' pairs of rows (lower row in the lower half): the even lane keeps its lower
+// row, the odd one its upper.  (One byte permutation: as a choice between two expressions it became a branch.)
+__device__ inline unsigned join_pair(unsigned mine, unsigned theirs, bool odd) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_perm(mine, theirs, odd ? 0x07060302u : 0x01000504u);
+#else
+  return 0;
+#endif
+}
+
 // Writes the workgroup's BM x BN tile of values (already final, in MFMA accumulator layout) to
 // out[row][col] (leading dimension ld, no bounds: the caller's buffer is tile-padded).
 // fp32: direct stores, 32 lanes cover 128 contiguous bytes of a row.
@@ -396,7 +406,7 @@ __device__ inline void store_tile(const f32x16_t (&val)[TM][TN], const EpiCtx &c
         pk.h[1] = (bf16_t)val[i][j][r0 + 1];
         const unsigned mine = pk.u;
         const unsigned theirs = (unsigned)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xF, 0xF, true);  // lane ^ 1
-        const unsigned word = odd ? ((theirs >> 16) | (mine & 0xffff0000u)) : ((mine & 0xffffu) | (theirs << 16));
+        const unsigned word = join_pair(mine, theirs, odd);
         const int rin = RNNLM_ACC_ROW(r0, c.lane) + (odd ? 1 : 0);  // row inside the 32-row block
         if constexpr (QR >= 32) {
           *reinterpret_cast<unsigned *>(blk_base + rin * PITCH + (col & ~1) * 2) = word;
@@ -725,142 +735,139 @@ struct EpiSgd : EpiZeroInit {
   template <int BM, int BN, int TM, int TN, int NT>
   __device__ inline void run(f32x16_t (&acc)[TM][TN], const EpiCtx &c) const {
     const int row0 = c.tile_row0 + c.wrow, col0 = c.tile_col0 + c.wcol, lane = c.lane;
-    const int lc = lane & 31;
 #if defined(__HIP_DEVICE_COMPILE__)
-    if (row0 + 32 * TM <= R && col0 + 32 * TN <= C && (ldc & 1) == 0) {
-      // Interior wave tile: no checks.  What bounds this epilogue is memory latency (a compute unit moves 640 KB
-      // per tile; its matrix cores idle meanwhile), so the master values of TWO 32-row blocks are in flight at
-      // any time: block i + 2 is requested as soon as block i has been stored.  All accesses go through buffer
-      // resources based at the wave tile's origin: one lane-dependent offset register serves every access and
-      // the row part is a scalar, which leaves the registers for the 2 x TN x 16 values in flight (with pointer
-      // arithmetic the addresses alone would not fit).  W and out are the same array when training in place:
-      // buffer accesses are kept in program order.  The copy in the compute type leaves as packed pairs:
-      // neighbouring lanes swap one value so that each lane owns two adjacent columns of one row.
-      // (the wave tile's origin is the same for all lanes: say so, or every access becomes a loop over lanes)
-      const long origin = (long)__builtin_amdgcn_readfirstlane(row0) * ldw + __builtin_amdgcn_readfirstlane(col0);
-      const long origin_c = (long)__builtin_amdgcn_readfirstlane(row0) * ldc + __builtin_amdgcn_readfirstlane(col0);
-      auto uniform = [](auto *p) {
-        const unsigned long long v = reinterpret_cast<unsigned long long>(p);
-        const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
-        const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-        return reinterpret_cast<decltype(p)>(((unsigned long long)hi << 32) | lo);
-      };
-      const __amdgpu_buffer_rsrc_t rw =
-          __builtin_amdgcn_make_buffer_rsrc(uniform(const_cast<float *>(W) + origin), 0, 0x7fffffff, 0x00020000);
-      const __amdgpu_buffer_rsrc_t ro =
-          __builtin_amdgcn_make_buffer_rsrc(uniform(out + origin), 0, 0x7fffffff, 0x00020000);
-      const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
-          uniform(Wc ? Wc + origin_c : reinterpret_cast<T *>(out + origin)), 0, 0x7fffffff, 0x00020000);
-      const int half = lane >> 5;
-      const int voff = (int)((half * 4 * ldw + lc) * 4);  // this lane's byte offset inside a 32-row block
-      const bool odd = lane & 1;
-      const int voffc = (int)(((half * 4 + (odd ? 1 : 0)) * ldc + (lc & ~1)) * (long)sizeof(T));
-      const int ldw4 = (int)(ldw * 4), ldcb = (int)(ldc * (long)sizeof(T));
-      auto request = [&](int i, float (&w)[TN][16]) {
+    // What bounds this epilogue is memory latency (a compute unit moves 640 KB per tile; its matrix cores idle meanwhile), so
+    // the master values of TWO 32-row blocks are in flight at any time: block i + 2 is requested as soon as block i has been
+    // stored.  All accesses go through buffer resources based at the wave tile's origin: one lane-dependent offset register
+    // per column block serves every access and the row part is a scalar, which leaves the registers for the 2 x TN x 16 values
+    // in flight (with pointer arithmetic the addresses alone would not fit).  W and out are the same array when training in
+    // place: buffer accesses are kept in program order.  The copy in the compute type leaves as packed pairs: neighbouring
+    // lanes swap one value so that each lane owns two adjacent columns of one row.
+    // Ragged edges cost no branch: the resources end with row R - 1, and a lane past column C - 1 gets an offset past every
+    // end, so its reads are 0 and its writes are dropped.  (The last pair of an odd C includes a padding column of the copy,
+    // whose value is 0 like everything it is formed from.)  Tested entry by entry instead, with one 32 x 32 block in flight,
+    // the edge tiles held up the whole launch: V = 33278, H = 650, 960 positions, 118 us, now 96.
+    if (row0 >= R || col0 >= C) return;
+    // (the wave tile's origin is the same for all lanes: say so, or every access becomes a loop over lanes)
+    const int urow = __builtin_amdgcn_readfirstlane(row0), ucol = __builtin_amdgcn_readfirstlane(col0);
+    const long origin = (long)urow * ldw + ucol, origin_c = (long)urow * ldc + ucol;
+    auto uniform = [](auto *p) {
+      const unsigned long long v = reinterpret_cast<unsigned long long>(p);
+      const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
+      const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+      return reinterpret_cast<decltype(p)>(((unsigned long long)hi << 32) | lo);
+    };
+    auto extent = [&](long ld, long first, int es) {  // bytes from `first` to the end of row R - 1
+      const long left = ((long)R * ld - first) * es;
+      return __builtin_amdgcn_readfirstlane((int)(left < 0x7fffffffL ? left : 0x7fffffffL));
+    };
+    const __amdgpu_buffer_rsrc_t rw =
+        __builtin_amdgcn_make_buffer_rsrc(uniform(const_cast<float *>(W) + origin), 0, extent(ldw, origin, 4), 0x00020000);
+    const __amdgpu_buffer_rsrc_t ro =
+        __builtin_amdgcn_make_buffer_rsrc(uniform(out + origin), 0, extent(ldw, origin, 4), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rc =
+        __builtin_amdgcn_make_buffer_rsrc(uniform(Wc ? Wc + origin_c : reinterpret_cast<T *>(out + origin)), 0,
+                                          Wc ? extent(ldc, origin_c, (int)sizeof(T)) : 0, 0x00020000);
+    const bool odd = lane & 1;
+    constexpr int PAST = 0x7fffffff;
+    // This lane's byte offsets inside a 32-row block, formed anew for every block: kept, they would be the registers that
+    // keep a wave of the embedding update from running next to two waves of the 256 x 256 form (226 instead of 224: the
+    // embedding and the recurrent update waited for the whole launch, 1.5 % of a window at H = 1024).
+    auto fresh = [&]() {
+      int l = lane;
+      asm volatile("" : "+v"(l));
+      return l;
+    };
+    auto voff = [&](int j) {
+      const int l = fresh(), c32 = l & 31;
+      return col0 + j * 32 + c32 < C ? (int)(((l >> 5) * 4 * ldw + c32) * 4) + j * 128 : PAST;
+    };
+    auto voffc = [&](int j) {
+      const int l = fresh(), c32 = l & 31;
+      if constexpr (sizeof(T) == 2)
+        return col0 + j * 32 + (c32 & ~1) < C ? (int)(((l >> 5) * 4 + (l & 1)) * ldc + (c32 & ~1)) * 2 + j * 64 : PAST;
+      else
+        return col0 + j * 32 + c32 < C ? (int)(((l >> 5) * 4 * ldc + c32) * 4) + j * 128 : PAST;
+    };
+    const int ldw4 = (int)(ldw * 4), ldcb = (int)(ldc * (long)sizeof(T));
+    auto request = [&](int i, float (&w)[TN][16]) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j) {
+        const int vo = voff(j);
 #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            w[j][r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                          rw, voff, (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4 + j * 128, 0));
-      };
-      auto apply = [&](int i, const float (&w)[TN][16]) {
+        for (int r = 0; r < 16; ++r)
+          w[j][r] = __builtin_bit_cast(
+              float, __builtin_amdgcn_raw_buffer_load_b32(rw, vo, (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4, 0));
+      }
+    };
+    auto apply = [&](int i, const float (&w)[TN][16]) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          float nv[16];
+      for (int j = 0; j < TN; ++j) {
+        float nv[16];
+        const int vo = voff(j);
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            nv[r] = ((alpha != 0.0f) ? alpha * w[j][r] : 0.0f) - lr * acc[i][j][r];
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, nv[r]), ro, voff,
-                                                  (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4 + j * 128, 0);
-          }
-          if (Wc) {
-            if constexpr (sizeof(T) == 2) {
-              typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+        for (int r = 0; r < 16; ++r) {
+          nv[r] = ((alpha != 0.0f) ? alpha * w[j][r] : 0.0f) - lr * acc[i][j][r];
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, nv[r]), ro, vo,
+                                                (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4, 0);
+        }
+        if (Wc) {
+          const int vc = voffc(j);
+          if constexpr (sizeof(T) == 2) {
+            typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 #pragma unroll
-              for (int q = 0; q < 8; ++q) {  // rows 2q, 2q+1 of this lane's 16: even lanes keep 2q, odd lanes 2q+1
-                union {
-                  bf16x2_t h;
-                  unsigned u;
-                } pk;
-                pk.h[0] = (bf16_t)nv[2 * q];
-                pk.h[1] = (bf16_t)nv[2 * q + 1];
-                const unsigned mine = pk.u;
-                const unsigned theirs = (unsigned)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xF, 0xF, true);  // lane ^ 1
-                const unsigned word = odd ? ((theirs >> 16) | (mine & 0xffff0000u)) : ((mine & 0xffffu) | (theirs << 16));
-                const int r0 = 2 * q;
-                __builtin_amdgcn_raw_buffer_store_b32(word, rc, voffc,
-                                                      (i * 32 + 8 * (r0 >> 2) + (r0 & 3)) * ldcb + j * 32 * (int)sizeof(T), 0);
-              }
-            } else {
-#pragma unroll
-              for (int r = 0; r < 16; ++r)
-                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, nv[r]), rc, (int)((half * 4 * ldc + lc) * 4),
-                                                      (i * 32 + 8 * (r >> 2) + (r & 3)) * ldcb + j * 128, 0);
+            for (int q = 0; q < 8; ++q) {  // rows 2q, 2q+1 of this lane's 16: even lanes keep 2q, odd lanes 2q+1
+              union {
+                bf16x2_t h;
+                unsigned u;
+              } pk;
+              pk.h[0] = (bf16_t)nv[2 * q];
+              pk.h[1] = (bf16_t)nv[2 * q + 1];
+              const unsigned mine = pk.u;
+              const unsigned theirs = (unsigned)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xF, 0xF, true);  // lane ^ 1
+              const unsigned word = join_pair(mine, theirs, odd);
+              const int r0 = 2 * q;
+              __builtin_amdgcn_raw_buffer_store_b32(word, rc, vc,
+                                                    (i * 32 + 8 * (r0 >> 2) + (r0 & 3)) * ldcb, 0);
             }
+          } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, nv[r]), rc, vc,
+                                                    (i * 32 + 8 * (r >> 2) + (r & 3)) * ldcb, 0);
           }
         }
-      };
-      if (alpha != 0.0f) {
-        static_assert(TM == 1 || TM % 2 == 0, "two row blocks in flight");
-        // (scheduling barriers: left alone, the compiler starts applying the first values after a third of the
-        // requests and issues the rest only when those have arrived, one memory round trip later)
-        float wa[TN][16], wb[TN][16];
-        request(0, wa);
-        if constexpr (TM > 1) request(1, wb);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < TM; i += 2) {
-          apply(i, wa);
-          __builtin_amdgcn_sched_barrier(0);
-          if (i + 2 < TM) request(i + 2, wa);
-          __builtin_amdgcn_sched_barrier(0);
-          if (i + 1 < TM) apply(i + 1, wb);
-          __builtin_amdgcn_sched_barrier(0);
-          if (i + 3 < TM) request(i + 3, wb);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      } else {
-        float wz[TN][16];
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) wz[j][r] = 0.0f;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) apply(i, wz);
       }
-      return;
+    };
+    if (alpha != 0.0f) {
+      static_assert(TM == 1 || TM % 2 == 0, "two row blocks in flight");
+      // (scheduling barriers: left alone, the compiler starts applying the first values after a third of the
+      // requests and issues the rest only when those have arrived, one memory round trip later)
+      float wa[TN][16], wb[TN][16];
+      request(0, wa);
+      if constexpr (TM > 1) request(1, wb);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < TM; i += 2) {
+        apply(i, wa);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + 2 < TM) request(i + 2, wa);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + 1 < TM) apply(i + 1, wb);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + 3 < TM) request(i + 3, wb);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      float wz[TN][16];
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) wz[j][r] = 0.0f;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) apply(i, wz);
     }
 #endif
-    // wave tile at the ragged edge: a 32x32 block's master values are all requested before any is used
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = col0 + j * 32 + lc;
-      if (col >= C) continue;
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int top = row0 + i * 32 + ((lane >> 5) << 2);
-        const float *wp = W + (long)top * ldw + col;
-        float *op = out + (long)top * ldw + col;
-        float w[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int d = 8 * (r >> 2) + (r & 3);
-          w[r] = (alpha != 0.0f && top + d < R) ? wp[(long)d * ldw] : 0.0f;
-        }
-#if defined(__HIP_DEVICE_COMPILE__)
-        __builtin_amdgcn_sched_barrier(0);
-#endif
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int d = 8 * (r >> 2) + (r & 3);
-          if (top + d >= R) continue;
-          const float nv = ((alpha != 0.0f) ? alpha * w[r] : 0.0f) - lr * acc[i][j][r];
-          op[(long)d * ldw] = nv;
-          if (Wc) Wc[(long)(top + d) * ldc + col] = from_f32<T>(nv);
-        }
-      }
-    }
   }
 };
 

@@ -85,3 +85,27 @@ def test_fp32_contractions_of_infinite_and_huge_operands(V, H, B, T):
     ref = O.forward_logprob(O.Model.from_weights(E, U, Wo, b, B), x, y)
     check_logp(torch.as_tensor(got), ref)
     g.rnnlm_check()
+
+
+@pytest.mark.parametrize("precision", [FP32, BF16])
+@pytest.mark.parametrize("V,H", [(257, 33), (300, 255), (511, 257), (1000, 650), (256, 65), (769, 512)])
+def test_update_epilogue_at_ragged_edges(V, H, precision):
+    """Every master entry is updated (against the oracle), and the compute copies, their padding included, are what a
+    rebuild from the masters gives: the next window's results do not change."""
+    B, T = 5, 31
+    g, o = make_pair(V, H, B, T, precision, seed=V + H, scale=0.1, bias_scale=0.5)
+    tok = tokens(V, 2 * B * T + B + 1, 6)
+    x, y = O.stream_chunk(tok, B, T, 0)
+    g.rnnlm_train_chunk(dev(x), dev(y), 0.5)
+    O.train_chunk(o, x, y, 0.5)
+    tol = 1e-4 if precision == FP32 else 2e-2
+    for name in ("Wo", "U", "E"):
+        got, ref = getattr(g, name).cpu().numpy().astype(np.float64), getattr(o, name)
+        assert np.abs(got - ref).max() <= tol * max(1.0, np.abs(ref).max()), name
+    h0 = g.h_state.clone()
+    x, y = O.stream_chunk(tok, B, T, 1)
+    a = g.rnnlm_forward_logprob(dev(x), dev(y)).clone()
+    g.h_state.copy_(h0)
+    g.rnnlm_sync_compute_copies()
+    assert torch.equal(a, g.rnnlm_forward_logprob(dev(x), dev(y)))
+    g.rnnlm_check()
