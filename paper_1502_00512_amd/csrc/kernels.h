@@ -506,170 +506,254 @@ __global__ void segment_kernel(const int32_t *__restrict__ xp, const int32_t *__
   }
 }
 
+// ---- a10: sums over the members of a run, atomic-free and order-fixed ----------------------------
+// The row updates (embedding rows here, touched output rows in nce.h) add up, per word, one source row per member of
+// the word's run.  They are made of dependent round trips (run bounds -> positions -> coefficients -> rows) and a
+// Zipf text has runs of one member by the thousand and a few of hundreds, so a wave sums a short run by itself, over 256
+// columns, and the RUN_WAVES waves of a workgroup share out a run of more than RUN_ALONE members in slices.  A wave
+// loads 64 members' positions at once, one a lane, and then has RUN_FLIGHT rows in flight.  Member i of a slice goes to
+// sum i mod RUN_FLIGHT, the sums are added as a tree, slices in order: results are bitwise reproducible.
+// H = 1024, 2560 positions: embedding rows 34 -> 11 us (a workgroup of four waves took a run, one row group of 16 after the
+// other), the noise-contrastive update of 3584 entries 56 -> 16 us (sixteen waves a run, most of them idle).
+constexpr int RUN_WAVES = 8, RUN_ALONE = 16, RUN_FLIGHT = 8, RUN_COLS = 256;
+struct RunSum {
+  f32x4_t part[RUN_FLIGHT];
+  __device__ RunSum() {
+#pragma unroll
+    for (int q = 0; q < RUN_FLIGHT; ++q) part[q] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  // members i = first .. n-1, the same in every lane: raw(i) asks for a member's row, add(i, value, sum) takes it up
+  template <class Raw, class Add>
+  __device__ void take(int first, int n, Raw raw, Add add) {
+    for (int i = first; i < n; i += RUN_FLIGHT) {
+      decltype(raw(0)) v[RUN_FLIGHT];
+#pragma unroll
+      for (int q = 0; q < RUN_FLIGHT; ++q)
+        if (i + q < n) v[q] = raw(i + q);
+#pragma unroll
+      for (int q = 0; q < RUN_FLIGHT; ++q)
+        if (i + q < n) add(i + q, v[q], part[q]);
+    }
+  }
+  __device__ f32x4_t total() const {
+    return ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
+  }
+};
+
+// Four columns of an updated row: out = alpha * old - lr * sum.  ALIGNED: 16-byte accesses; otherwise element by element,
+// the last group partly (rows of H values; the compute copy's rows are padded).
+template <bool ALIGNED>
+__device__ inline f32x4_t load_row4(const float *__restrict__ row, int col, int H) {
+  f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (ALIGNED) {
+    if (col < H) v = *reinterpret_cast<const f32x4_t *>(row + col);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (col + e < H) v[e] = row[col + e];
+  }
+  return v;
+}
+template <bool ALIGNED, typename T>
+__device__ inline void store_row4(f32x4_t v, int col, int H, float *__restrict__ row, T *__restrict__ copy) {
+  if (col >= H) return;
+  if (ALIGNED) {
+    *reinterpret_cast<f32x4_t *>(row + col) = v;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (col + e < H) row[col + e] = v[e];
+  }
+  if (!copy) return;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (ALIGNED || col + e < H) copy[col + e] = from_f32<T>(v[e]);
+}
+
+// The runs of a workgroup: runs blockIdx.x + k * gridDim.x, k < RUN_WAVES (frequent words often lie side by side: a
+// workgroup takes runs that are far apart).  request(r0) asks for what is updated, sum(r0, r1) is a wave's sum over members
+// [r0, r1) of the sorted list, finish(run, requested, sum) stores the run's result.
+struct RowSum {
+  f32x4_t v;  // the lane's four columns
+  float b;    // a term of the whole row (bias), the same in every lane
+};
+struct RunShared {  // the slices' sums of a run that the waves share out
+  f32x4_t v[RUN_WAVES][64];
+  float b[RUN_WAVES];
+};
+template <class Request, class Sum, class Finish>
+__device__ inline void walk_runs(const int32_t *__restrict__ seg_start, int nseg, RunShared &shared, Request request, Sum sum,
+                                 Finish finish) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int run = (int)blockIdx.x + (lane % RUN_WAVES) * (int)gridDim.x;
+  const int lo = run < nseg ? seg_start[run] : 0, hi = run < nseg ? seg_start[run + 1] : 0;
+  {
+    const int r0 = __builtin_amdgcn_readlane(lo, wave), r1 = __builtin_amdgcn_readlane(hi, wave);
+    if (r1 > r0 && r1 - r0 <= RUN_ALONE) {
+      const auto old = request(r0);
+      finish((int)blockIdx.x + wave * (int)gridDim.x, old, sum(r0, r1));
+    }
+  }
+  for (int k = 0; k < RUN_WAVES; ++k) {
+    const int r0 = __builtin_amdgcn_readlane(lo, k), r1 = __builtin_amdgcn_readlane(hi, k);
+    if (r1 - r0 <= RUN_ALONE) continue;  // (the same in every wave)
+    const int per = (r1 - r0 + RUN_WAVES - 1) / RUN_WAVES, s0 = min(r0 + wave * per, r1), s1 = min(s0 + per, r1);
+    const auto old = request(r0);
+    const RowSum mine = sum(s0, s1);
+    __syncthreads();  // the sums of the shared run before have been read
+    shared.v[wave][lane] = mine.v;
+    if (lane == 0) shared.b[wave] = mine.b;
+    __syncthreads();
+    if (wave == k) {
+      RowSum tot = {shared.v[0][lane], shared.b[0]};
+#pragma unroll
+      for (int q = 1; q < RUN_WAVES; ++q) {
+        tot.v += shared.v[q][lane];
+        tot.b += shared.b[q];
+      }
+      finish((int)blockIdx.x + k * (int)gridDim.x, old, tot);
+    }
+  }
+}
+
 // ---- a10: segmented embedding update, atomic-free and order-fixed -------------------------------
 //   out[w][:] = alpha*E[w][:] - lr * sum_{m in run of w} dA[m][:]
-// blockIdx.x = run index (exits when >= *nseg), blockIdx.y = block of 1024 columns.  The run's members are dealt
-// round-robin to PARTS partial sums (member i of the run goes
-// to sum i mod PARTS, each sum accumulated in ascending m), which are then added in order 0..PARTS-1: a fixed
-// summation tree, so results are bitwise reproducible.  All PARTS sums live in the thread's registers: a group
-// of 16 members is 16 independent row loads in flight, and the small workgroups (with a sorted list no LDS and no
-// barrier) leave eight of them resident per compute unit, which is what a pass made of dependent memory round trips
-// (run bounds -> position -> rows) needs: it is bound by latency times occupancy, not by bandwidth.
-// A thread owns 4 consecutive columns (the rows of dA are tile-padded and aligned).  ALIGNED: H % 4 == 0, the rows of the
-// updated matrix are accessed 16 bytes at a time; otherwise (any H) element by element, the last group partly.
+// Sorted windows: RUN_WAVES runs a workgroup, blockIdx.y = block of 256 columns (see walk_runs).
 // Ec (may be nullptr): compute copy [.][ldc] of the updated matrix, refreshed with the new row (the tied word
 // matrix of the compressed architecture is an operand of the output layer as well).
-// SCAN (windows of at most SCAN_MAX positions): no sorted list at all.  blockIdx.x = window position m; the workgroup
+template <bool ALIGNED, typename T>
+__global__ void __launch_bounds__(64 * RUN_WAVES) scatter_runs_kernel(const float *__restrict__ dA, int Hp, int H, int B,
+                                                                      int Bp, const int32_t *__restrict__ xp,
+                                                                      const int32_t *__restrict__ perm,
+                                                                      const int32_t *__restrict__ seg_start,
+                                                                      const int32_t *__restrict__ nseg,
+                                                                      const float *__restrict__ E,
+                                                                      float *__restrict__ out, float alpha, float lr,
+                                                                      int compact_ld, T *__restrict__ Ec, int ldc) {
+  __shared__ RunShared shared;
+  const int lane = threadIdx.x & 63, col = blockIdx.y * RUN_COLS + lane * 4;
+  auto row_of = [&](int m) { return (m / B) * Bp + m % B; };
+  struct Old {
+    int w;
+    f32x4_t v;
+  };
+  walk_runs(
+      seg_start, *nseg, shared,
+      [&](int r0) {  // the row being updated does not depend on the sum: ask for it first
+        Old o;
+        o.w = __builtin_amdgcn_readfirstlane(xp[row_of(perm[r0])]);
+        o.v = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        if (alpha != 0.0f) o.v = load_row4<ALIGNED>(E + (long)o.w * H, col, H) * alpha;
+        return o;
+      },
+      [&](int r0, int r1) {
+        RunSum s;
+        for (int c = r0; c < r1; c += 64) {
+          const int n = min(64, r1 - c), row = lane < n ? row_of(perm[c + lane]) : 0;
+          s.take(0, n,
+                 [&](int i) {
+                   return *reinterpret_cast<const f32x4_t *>(dA + (long)__builtin_amdgcn_readlane(row, i) * Hp + col);
+                 },
+                 [](int, f32x4_t v, f32x4_t &acc) { acc += v; });
+        }
+        return RowSum{s.total(), 0.0f};
+      },
+      [&](int run, const Old &o, const RowSum &tot) {
+        // compact_ld > 0: the run's result goes to row `run` of a compact [runs][compact_ld] buffer instead of row w
+        float *dst = compact_ld > 0 ? out + (long)run * compact_ld : out + (long)o.w * H;
+        store_row4<ALIGNED>(o.v - lr * tot.v, col, H, dst, Ec ? Ec + (long)o.w * ldc : nullptr);
+      });
+}
+
+// Windows of at most SCAN_MAX positions can do without a sorted list.  blockIdx.x = window position m; the workgroup
 // compares m's id with all others, gives up if it is not the first of its run, and otherwise has the run's members, in
-// ascending order, in LDS.  The 16 keys a thread compares are loaded together, so this costs one memory round trip and
+// ascending order, in LDS.  The keys a thread compares are loaded together, so this costs one memory round trip and
 // two barriers, where the sort is two launches on a second stream and the events that tie it in (a window of 32
-// positions spent 30 us of host time on them).
+// positions spent 30 us of host time on them).  The waves are then laid out as column blocks of 256 (`blocks` of them, a
+// power of two) times slices of the run's members; the sums are the same tree as a sorted window's.  P = 512, 2560
+// positions: 35 -> 21 us.
 constexpr int SCAN_MAX = 4096;
-template <bool ALIGNED, bool SCAN, typename T>
-__global__ void __launch_bounds__(256) scatter_update_kernel(const float *__restrict__ dA, int Hp, int H, int B,
-                                                             int Bp, const int32_t *__restrict__ xp,
-                                                             const int32_t *__restrict__ perm,
-                                                             const int32_t *__restrict__ seg_start,
-                                                             const int32_t *__restrict__ nseg,
-                                                             const float *__restrict__ E, float *__restrict__ out,
-                                                             float alpha, float lr, int compact_ld,
-                                                             T *__restrict__ Ec, int ldc, int M) {
-  constexpr int PARTS = 4, GROUP = 4 * PARTS, VEC = 4;
-  const int g = blockIdx.x;
-  const int col = (blockIdx.y * 256 + threadIdx.x) * VEC;
-  __shared__ unsigned short members[SCAN ? SCAN_MAX : 1];
-  int r0, r1, w;
-  if constexpr (SCAN) {
-    constexpr int KEYS = SCAN_MAX / 256;  // keys per thread: positions threadIdx.x + 256 k
-    __shared__ unsigned long long found[KEYS][4];
-    __shared__ int before[KEYS * 4], total;
-    auto key_of = [&](int m) { return xp[(m / B) * Bp + (m % B)]; };
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    w = key_of(g);
-    int key[KEYS];
+template <bool ALIGNED, typename T>
+__global__ void __launch_bounds__(64 * RUN_WAVES) scatter_scan_kernel(const float *__restrict__ dA, int Hp, int H, int B,
+                                                                      int Bp, const int32_t *__restrict__ xp,
+                                                                      const float *__restrict__ E,
+                                                                      float *__restrict__ out, float alpha, float lr,
+                                                                      T *__restrict__ Ec, int ldc, int M, int blocks) {
+  constexpr int THREADS = 64 * RUN_WAVES, KEYS = SCAN_MAX / THREADS;  // keys per thread: threadIdx.x + THREADS k
+  __shared__ unsigned short members[SCAN_MAX];
+  __shared__ f32x4_t shared[2 * RUN_WAVES][64];  // (RUN_WAVES - each) * blocks rows are in use
+  __shared__ unsigned long long found[KEYS * RUN_WAVES];  // group of 64 positions -> which of them
+  __shared__ int before[KEYS * RUN_WAVES], total;
+  static_assert(KEYS * RUN_WAVES == 64, "one lane per group");
+  auto row_of = [&](int m) { return (m / B) * Bp + m % B; };
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = blockIdx.x, w = xp[row_of(g)];
+  int key[KEYS];
 #pragma unroll
-    for (int k = 0; k < KEYS; ++k) key[k] = threadIdx.x + 256 * k < M ? key_of(threadIdx.x + 256 * k) : -1;
-    unsigned mine = 0;
+  for (int k = 0; k < KEYS; ++k) key[k] = threadIdx.x + THREADS * k < M ? xp[row_of(threadIdx.x + THREADS * k)] : -1;
+  unsigned mine = 0;
 #pragma unroll
-    for (int k = 0; k < KEYS; ++k) {
-      const unsigned long long b = __ballot(key[k] == w);
-      if (lane == 0) found[k][wave] = b;
-      mine |= (unsigned)(key[k] == w) << k;
-    }
-    __syncthreads();
-    if (wave == 0) {  // members before each group of 64 positions
-      const int n = __popcll(found[lane >> 2][lane & 3]);
-      int incl = n;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += up;
-      }
-      before[lane] = incl - n;
-      if (lane == 63) total = incl;
-    }
-    __syncthreads();
-    auto rank = [&](int m) {  // members before position m
-      return before[m >> 6] + __popcll(found[m >> 8][(m >> 6) & 3] & ((1ull << (m & 63)) - 1));
-    };
-    if (rank(g) != 0) return;  // an earlier position starts this run
-    for (; mine; mine &= mine - 1) {
-      const int m = threadIdx.x + 256 * (__ffs(mine) - 1);
-      members[rank(m)] = (unsigned short)m;
-    }
-    __syncthreads();
-    r0 = 0;
-    r1 = total;
-  } else {
-    if (g >= *nseg) return;
-    r0 = seg_start[g];
-    r1 = seg_start[g + 1];
-    const int m0 = perm[r0];
-    w = xp[(m0 / B) * Bp + (m0 % B)];
+  for (int k = 0; k < KEYS; ++k) {
+    const unsigned long long b = __ballot(key[k] == w);
+    if (lane == 0) found[k * RUN_WAVES + wave] = b;
+    mine |= (unsigned)(key[k] == w) << k;
   }
-  if (col >= H) return;
-  const long idx = (long)w * H + col;
-  // the row being updated does not depend on the sum: ask for it first
-  float old[VEC];
+  __syncthreads();
+  if (wave == 0) {  // members before each group of 64 positions
+    const int n = __popcll(found[lane]);
+    int incl = n;
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) old[e] = 0.0f;
-  if (alpha != 0.0f) {
-    if (ALIGNED) {
-      const f32x4_t t = *reinterpret_cast<const f32x4_t *>(E + idx);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) old[e] = t[e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < VEC; ++e)
-        if (col + e < H) old[e] = E[idx + e];
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += up;
     }
+    before[lane] = incl - n;
+    if (lane == 63) total = incl;
   }
-  auto row_of = [&](int r) {
-    const int m = SCAN ? members[r] : perm[r];
-    return ((long)(m / B) * Bp + (m % B)) * Hp + col;
+  __syncthreads();
+  auto rank = [&](int m) { return before[m >> 6] + __popcll(found[m >> 6] & ((1ull << (m & 63)) - 1)); };
+  if (rank(g) != 0) return;  // an earlier position starts this run
+  for (; mine; mine &= mine - 1) {
+    const int m = threadIdx.x + THREADS * (__ffs(mine) - 1);
+    members[rank(m)] = (unsigned short)m;
+  }
+  __syncthreads();
+  const int slices = RUN_WAVES / blocks, slice = wave / blocks, cb = wave % blocks;
+  const int each = RUN_WAVES / slices;  // slices of the members a wave takes
+  const int n = __builtin_amdgcn_readfirstlane(total);
+  const int col = (blockIdx.y * blocks + cb) * RUN_COLS + lane * 4;
+  f32x4_t old = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (slice == 0 && alpha != 0.0f) old = load_row4<ALIGNED>(E + (long)w * H, col, H) * alpha;
+  auto sum = [&](int s0, int s1) {
+    RunSum s;
+    if (col < Hp)
+      s.take(s0, s1,
+             [&](int i) {
+               return *reinterpret_cast<const f32x4_t *>(
+                   dA + (long)row_of(__builtin_amdgcn_readfirstlane(members[i])) * Hp + col);
+             },
+             [](int, f32x4_t v, f32x4_t &acc) { acc += v; });
+    return s.total();
   };
-  auto load_row = [&](long at, float (&v)[VEC]) {
-    const f32x4_t t = *reinterpret_cast<const f32x4_t *>(dA + at);
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) v[e] = t[e];
-  };
-  float acc[PARTS][VEC];
-#pragma unroll
-  for (int p = 0; p < PARTS; ++p)
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[p][e] = 0.0f;
-  int r = r0;
-  for (; r + GROUP <= r1; r += GROUP) {
-    long at[GROUP];
-#pragma unroll
-    for (int k = 0; k < GROUP; ++k) at[k] = row_of(r + k);
-    float v[GROUP][VEC];
-#pragma unroll
-    for (int k = 0; k < GROUP; ++k) load_row(at[k], v[k]);
-#pragma unroll
-    for (int k = 0; k < GROUP; ++k)  // member r + k belongs to sum k % PARTS (r - r0 is a multiple of GROUP)
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) acc[k % PARTS][e] += v[k][e];
-  }
-  for (; r < r1; r += PARTS) {
-    float v[PARTS][VEC];
-#pragma unroll
-    for (int p = 0; p < PARTS; ++p) {
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) v[p][e] = 0.0f;
-      if (r + p < r1) load_row(row_of(r + p), v[p]);
-    }
-#pragma unroll
-    for (int p = 0; p < PARTS; ++p)
-      if (r + p < r1) {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) acc[p][e] += v[p][e];
-      }
-  }
-#pragma unroll
-  for (int p = 1; p < PARTS; ++p)
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[0][e] += acc[p][e];
-  // compact_ld > 0: the run's result goes to row g of a compact [runs][compact_ld] buffer instead of row w
-  const long oidx = compact_ld > 0 ? (long)g * compact_ld + col : idx;
-  float nv[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) nv[e] = ((alpha != 0.0f) ? alpha * old[e] : 0.0f) - lr * acc[0][e];
-  if (ALIGNED) {
-    f32x4_t t;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) t[e] = nv[e];
-    *reinterpret_cast<f32x4_t *>(out + oidx) = t;
+  f32x4_t tot;
+  if (n <= RUN_ALONE) {
+    if (slice != 0) return;
+    tot = sum(0, n);
   } else {
-#pragma unroll
-    for (int e = 0; e < VEC; ++e)
-      if (col + e < H) out[oidx + e] = nv[e];
+    const int per = (n + RUN_WAVES - 1) / RUN_WAVES;
+    for (int j = 0; j < each; ++j) {
+      const int q = slice * each + j, s0 = min(q * per, n);
+      const f32x4_t v = sum(s0, min(s0 + per, n));
+      if (slice != 0)
+        shared[(q - each) * blocks + cb][lane] = v;
+      else
+        tot = j == 0 ? v : tot + v;
+    }
+    __syncthreads();
+    if (slice != 0) return;
+    for (int q = each; q < RUN_WAVES; ++q) tot += shared[(q - each) * blocks + cb][lane];
   }
-  if (Ec) {
-#pragma unroll
-    for (int e = 0; e < VEC; ++e)
-      if (ALIGNED || col + e < H) Ec[(long)w * ldc + col + e] = from_f32<T>(nv[e]);
-  }
+  store_row4<ALIGNED>(old - lr * tot, col, H, out + (long)w * H, Ec ? Ec + (long)w * ldc : nullptr);
 }
 
 // fp32 -> compute type, element by element (n elements).

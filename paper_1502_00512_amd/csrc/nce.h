@@ -13,6 +13,7 @@
 // e of the update list is noise word e for e < K and the target of compact position e - K otherwise.
 #pragma once
 #include "common.h"
+#include "kernels.h"
 
 namespace rnnlm_dev {
 
@@ -219,139 +220,101 @@ __global__ void __launch_bounds__(256) nce_target_dhs_kernel(const T *__restrict
 
 // Update of the touched rows of Wo, atomic-free and order-fixed:
 //   out[w][:] = alpha*Wo[w][:] - lr * ( sum_{noise entries e of w} G[e][:] + sum_{target entries} ct*Hs[row][:] )
-// blockIdx.x = run of equal ids in the sorted update list (exits when >= *nseg), blockIdx.y = block of
-// 64*VEC columns.  The run's members are dealt round-robin to 16 partial sums (each in ascending list
-// order) which are then added in order.  Also refreshes the compute copy of the row when Wc != nullptr.
+// Runs of equal ids of the sorted update list, RUN_WAVES a workgroup; blockIdx.y = block of 256 columns (walk_runs).  A
+// run's noise entries come before its target entries.  Also refreshes the compute copy of the row when Wc != nullptr.
 // compact_ld > 0 redirects the results to compact per-run buffers (see below).
-// The first column block also updates the word's bias the same way:
+// The first column block also updates the word's bias, one member a lane:
 //   b_out[w] = alpha*b[w] - lr * (sum over w's noise entries of their column sums + sum of ct over its target
 //   entries); a noise entry's column sum is the sum, in order, of the NCE_COLSUM_PARTS row-block partials
 //   gpart[y][Kp].
-template <typename T, int VEC>
-__global__ void __launch_bounds__(1024) nce_row_update_kernel(const float *__restrict__ G, const T *__restrict__ Hs1,
-                                                              int Hp, int H, int K, int B, int Bp,
-                                                              const float *__restrict__ ct,
-                                                              const int32_t *__restrict__ ids,
-                                                              const int32_t *__restrict__ perm,
-                                                              const int32_t *__restrict__ seg_start,
-                                                              const int32_t *__restrict__ nseg,
-                                                              const float *__restrict__ W, float *__restrict__ out,
-                                                              T *__restrict__ Wc, const float *__restrict__ gpart,
-                                                              int Kp,
-                                                              const float *__restrict__ b, float *__restrict__ b_out,
-                                                              float alpha, float lr, int compact_ld) {
-  constexpr int PARTS = 16, LANES = 64;
-  __shared__ float sh[PARTS][LANES * VEC];
-  __shared__ float shb[PARTS];
-  const int g = blockIdx.x;
-  if (g >= *nseg) return;
-  const int lane = threadIdx.x % LANES, partn = threadIdx.x / LANES;
-  const int col = (blockIdx.y * LANES + lane) * VEC;
-  const int r0 = seg_start[g], r1 = seg_start[g + 1];
-  float acc[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) acc[e] = 0.0f;
-  float bacc = 0.0f;  // bias sum of the part (meaningful in its first lane)
-  const bool live = col < H;
-  // one member: its row (times its coefficient) and its bias term
-  auto fetch = [&](int r, float (&v)[VEC], float &bv) {
-    const int ent = perm[r];
-    if (ent < K) {
-      bv = 0.0f;
-      if (lane == 0) {  // the part's bias sum is kept by its first lane only
-        float pv[NCE_COLSUM_PARTS];  // all partials requested before any is added
-#pragma unroll
-        for (int y = 0; y < NCE_COLSUM_PARTS; ++y) pv[y] = gpart[(long)y * Kp + ent];
-        bv = pv[0];
-#pragma unroll
-        for (int y = 1; y < NCE_COLSUM_PARTS; ++y) bv += pv[y];
-      }
-      if (live) {
-        const float *src = G + (long)ent * Hp + col;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) v[e] = src[e];
-      }
-    } else {
-      const int m = ent - K;
-      const long row = (long)(m / B) * Bp + (m % B);
-      const float c = ct[row];
-      bv = c;
-      if (live) {
-        const T *src = Hs1 + row * Hp + col;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) v[e] = c * to_f32(src[e]);
-      }
-    }
+template <bool ALIGNED, typename T>
+__global__ void __launch_bounds__(64 * RUN_WAVES) nce_row_update_kernel(
+    const float *__restrict__ G, const T *__restrict__ Hs1, int Hp, int H, int K, int B, int Bp,
+    const float *__restrict__ ct, const int32_t *__restrict__ ids, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ seg_start, const int32_t *__restrict__ nseg, const float *__restrict__ W,
+    float *__restrict__ out, T *__restrict__ Wc, const float *__restrict__ gpart, int Kp, const float *__restrict__ b,
+    float *__restrict__ b_out, float alpha, float lr, int compact_ld) {
+  __shared__ RunShared shared;
+  const int lane = threadIdx.x & 63;
+  const int col = blockIdx.y * RUN_COLS + lane * 4;
+  const bool bias = blockIdx.y == 0;
+  struct Old {
+    int w;
+    f32x4_t v;
+    float b;
   };
-  int r = r0 + partn;
-  for (; r + 3 * PARTS < r1; r += 4 * PARTS) {  // four members at a time: their loads are independent
-    float v[4][VEC], bv[4];
+  walk_runs(
+      seg_start, *nseg, shared,
+      [&](int r0) {  // what is being updated does not depend on the sum: ask for it first
+        Old o;
+        o.w = __builtin_amdgcn_readfirstlane(ids[perm[r0]]);
+        o.v = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        o.b = 0.0f;
+        if (alpha != 0.0f) {
+          o.v = load_row4<ALIGNED>(W + (long)o.w * H, col, H) * alpha;
+          if (bias) o.b = alpha * b[o.w];
+        }
+        return o;
+      },
+      [&](int r0, int r1) {
+        RunSum s;
+        float bacc = 0.0f;
+        for (int c = r0; c < r1; c += 64) {
+          const int n = min(64, r1 - c);
+          int row = 0;
+          float coef = 0.0f;
+          bool noise = false;
+          if (lane < n) {
+            row = perm[c + lane];
+            noise = row < K;
+            if (!noise) {
+              const int m = row - K;
+              row = (m / B) * Bp + m % B;
+              coef = ct[row];
+            }
+            if (bias) {
+              float bv = coef;
+              if (noise) {
+                float pv[NCE_COLSUM_PARTS];  // all partials requested before any is added
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+                for (int y = 0; y < NCE_COLSUM_PARTS; ++y) pv[y] = gpart[(long)y * Kp + row];
+                bv = pv[0];
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) v[q][e] = 0.0f;
-      fetch(r + q * PARTS, v[q], bv[q]);
-    }
+                for (int y = 1; y < NCE_COLSUM_PARTS; ++y) bv += pv[y];
+              }
+              bacc += bv;
+            }
+          }
+          const int nn = __popcll(__ballot(noise));
+          s.take(0, nn,
+                 [&](int i) {
+                   return *reinterpret_cast<const f32x4_t *>(G + (long)__builtin_amdgcn_readlane(row, i) * Hp + col);
+                 },
+                 [](int, f32x4_t v, f32x4_t &acc) { acc += v; });
+          typedef T t4 __attribute__((ext_vector_type(4)));
+          s.take(nn, n,
+                 [&](int i) {
+                   return *reinterpret_cast<const t4 *>(Hs1 + (long)__builtin_amdgcn_readlane(row, i) * Hp + col);
+                 },
+                 [&](int i, t4 v, f32x4_t &acc) {
+                   const float k = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(coef), i));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      bacc += bv[q];
+                   for (int e = 0; e < 4; ++e) acc[e] = fmaf(k, to_f32((T)v[e]), acc[e]);
+                 });
+        }
+        if (bias) {
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) acc[e] += v[q][e];
-    }
-  }
-  for (; r < r1; r += PARTS) {
-    float v[VEC], bv;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) v[e] = 0.0f;
-    fetch(r, v, bv);
-    bacc += bv;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[e] += v[e];
-  }
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) sh[partn][lane * VEC + e] = acc[e];
-  if (lane == 0) shb[partn] = bacc;
-  __syncthreads();
-  if (blockIdx.y == 0 && threadIdx.x == 0) {
-    const int wb = ids[perm[r0]];
-    float tot = shb[0];
-    for (int q = 1; q < PARTS; ++q) tot += shb[q];
-    b_out[compact_ld > 0 ? g : wb] = ((alpha != 0.0f) ? alpha * b[wb] : 0.0f) - lr * tot;
-  }
-  if (partn != 0 || !live) return;
-#pragma unroll
-  for (int q = 1; q < PARTS; ++q)
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[e] += sh[q][lane * VEC + e];
-  const int w = ids[perm[r0]];
-  const long idx = (long)w * H + col;
-  // compact_ld > 0: the run's result goes to row g of a compact [runs][compact_ld] buffer (and its bias
-  // term to entry g of b_out) instead of the word's own row
-  const long oidx = compact_ld > 0 ? (long)g * compact_ld + col : idx;
-  if constexpr (VEC == 4) {  // H % 4 == 0: 16-byte accesses to the master row
-    f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (alpha != 0.0f) v = *reinterpret_cast<const f32x4_t *>(W + idx) * alpha;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] -= lr * acc[e];
-    *reinterpret_cast<f32x4_t *>(out + oidx) = v;
-    if (Wc) {
-      if constexpr (sizeof(T) == 2) {
-        bf16x4_t hv;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) hv[e] = (bf16_t)v[e];
-        *reinterpret_cast<bf16x4_t *>(Wc + (long)w * Hp + col) = hv;
-      } else {
-        *reinterpret_cast<f32x4_t *>(Wc + (long)w * Hp + col) = v;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const float v = ((alpha != 0.0f) ? alpha * W[idx + e] : 0.0f) - lr * acc[e];
-      out[oidx + e] = v;
-      if (Wc) Wc[(long)w * Hp + col + e] = from_f32<T>(v);
-    }
-  }
+          for (int o = 32; o > 0; o >>= 1) bacc += __shfl_xor(bacc, o, 64);
+        }
+        return RowSum{s.total(), bacc};
+      },
+      [&](int run, const Old &o, const RowSum &tot) {
+        // compact_ld > 0: the run's result goes to row `run` of a compact [runs][compact_ld] buffer (and its bias term to
+        // entry `run` of b_out) instead of the word's own row
+        float *dst = compact_ld > 0 ? out + (long)run * compact_ld : out + (long)o.w * H;
+        if (bias && lane == 0) b_out[compact_ld > 0 ? run : o.w] = o.b - lr * tot.b;
+        store_row4<ALIGNED>(o.v - lr * tot.v, col, H, dst, Wc ? Wc + (long)o.w * Hp : nullptr);
+      });
 }
 
 }  // namespace rnnlm_dev

@@ -883,15 +883,10 @@ int nce_update(rnnlm_t *h, int Tn, const NceCall &n, const UpdateTargets &u, hip
   int32_t *ids = at<int32_t>(h, h->L.ids), *perm = at<int32_t>(h, h->L.perm2), *seg = at<int32_t>(h, h->L.seg2);
   HIP_TRY(hipStreamWaitEvent(st, h->ev_join[1], 0));  // the sort of the list, started on the side stream by nce_forward
   T *Wc = u.refresh_copies ? at<T>(h, h->L.Wo_c) : nullptr;
-  if (c.H % 4 == 0) {
-    hipLaunchKernelGGL((nce_row_update_kernel<T, 4>), dim3(nent, (c.H + 255) / 256), dim3(1024), 0, st, G, Hs1, Hp,
-                       c.H, K, c.B, Bp, at<float>(h, h->L.nct), ids, perm, seg, p_nseg2(h), h->buf.Wo, u.Wo, Wc,
-                       at<float>(h, h->L.gcol), Kp, h->buf.b, u.b, u.alpha, u.lr, u.wo_compact_ld);
-  } else {
-    hipLaunchKernelGGL((nce_row_update_kernel<T, 1>), dim3(nent, (c.H + 63) / 64), dim3(1024), 0, st, G, Hs1, Hp,
-                       c.H, K, c.B, Bp, at<float>(h, h->L.nct), ids, perm, seg, p_nseg2(h), h->buf.Wo, u.Wo, Wc,
-                       at<float>(h, h->L.gcol), Kp, h->buf.b, u.b, u.alpha, u.lr, u.wo_compact_ld);
-  }
+  hipLaunchKernelGGL((c.H % 4 == 0 ? nce_row_update_kernel<true, T> : nce_row_update_kernel<false, T>),
+                     dim3(blocks_for(nent, RUN_WAVES), blocks_for(c.H, RUN_COLS)), dim3(64 * RUN_WAVES), 0, st, G, Hs1, Hp, c.H,
+                     K, c.B, Bp, at<float>(h, h->L.nct), ids, perm, seg, p_nseg2(h), h->buf.Wo, u.Wo, Wc,
+                     at<float>(h, h->L.gcol), Kp, h->buf.b, u.b, u.alpha, u.lr, u.wo_compact_ld);
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
@@ -1039,15 +1034,18 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     T *Ec = (c.P > 0 && u.refresh_copies) ? Wo_c : nullptr;
     const int W = h->D, Wp = h->Dp;
     const bool scan = scan_ids(h, Tn, u);
-#define RNNLM_SCATTER(ALIGNED, SCAN)                                                                                     \
-  hipLaunchKernelGGL((scatter_update_kernel<ALIGNED, SCAN, T>), dim3(Tn * c.B, (W + 1023) / 1024), dim3(256), 0, es, rows, \
-                     Wp, W, c.B, Bp, xp, perm, seg, p_nseg(h), src, u.E, e_alpha, u.lr, u.e_compact_ld, Ec, Wp, Tn * c.B)
-    if (W % 4 == 0) {
-      if (scan) RNNLM_SCATTER(true, true); else RNNLM_SCATTER(true, false);
+    const dim3 threads(64 * RUN_WAVES);
+    if (scan) {
+      int blocks = 1;  // 256-column blocks a workgroup has waves for
+      while (blocks < RUN_WAVES && blocks * RUN_COLS < W) blocks *= 2;
+      hipLaunchKernelGGL((W % 4 == 0 ? scatter_scan_kernel<true, T> : scatter_scan_kernel<false, T>),
+                         dim3(Tn * c.B, blocks_for(W, blocks * RUN_COLS)), threads, 0, es, rows, Wp, W, c.B, Bp, xp, src, u.E,
+                         e_alpha, u.lr, Ec, Wp, Tn * c.B, blocks);
     } else {
-      if (scan) RNNLM_SCATTER(false, true); else RNNLM_SCATTER(false, false);
+      hipLaunchKernelGGL((W % 4 == 0 ? scatter_runs_kernel<true, T> : scatter_runs_kernel<false, T>),
+                         dim3(blocks_for(Tn * c.B, RUN_WAVES), blocks_for(W, RUN_COLS)), threads, 0, es, rows, Wp, W, c.B, Bp,
+                         xp, perm, seg, p_nseg(h), src, u.E, e_alpha, u.lr, u.e_compact_ld, Ec, Wp);
     }
-#undef RNNLM_SCATTER
     HIP_TRY(hipGetLastError());
   }
     return RNNLM_OK;
