@@ -13,11 +13,10 @@
 // e of the update list is noise word e for e < K and the target of compact position e - K otherwise.
 #pragma once
 #include "common.h"
+#include "gemm.h"
 #include "kernels.h"
 
 namespace rnnlm_dev {
-
-constexpr int NCE_COLSUM_PARTS = 16;  // row-block partials of the noise words' bias gradient
 
 __device__ inline float softplusf_(float d) { return fmaxf(d, 0.0f) + log1pf(__expf(-fabsf(d))); }
 __device__ inline float logisticf_(float d) {
@@ -134,73 +133,106 @@ __global__ void __launch_bounds__(256) score_candidates_kernel(const T *__restri
   if (lane == 0) out[item] = acc + b[w] - shift;
 }
 
-// Elementwise pass over one padded position (one workgroup per row of the score matrix S[Mp][Kp]):
-// dS[row][j] = sigmoid(S + off[j]) * scale in the contraction operand type (0 for padding rows and
-// columns), the position's loss J, and the target coefficient ct[row] = -(1 - sigmoid(dt)) * scale.
+// Epilogue of the score contraction S = Hs . Wn^T (rows: padded positions, columns: noise slots), elementwise while the
+// scores are in registers: dS[row][j] = sigmoid(S + off[j]) * scale in the contraction operand type (0 for padding rows and
+// columns), and, per 32x32 block, the sums of softplus(S + off[j]) over its columns (jpart[column block][row]) and of dS
+// before rounding over its rows (gpart[row block][j]).  V = 64000, H = 1024, 2560 positions, 1024 noise words: the
+// contraction, a pass over its fp32 scores and one more for the column sums took 17 + 15 + 7 us.
 template <typename T>
-__global__ void __launch_bounds__(256) nce_grad_kernel(const float *__restrict__ S, int Kp, int K,
-                                                       const float *__restrict__ off, const float *__restrict__ dt,
-                                                       int Tn, int B, int Bp, float scale, T *__restrict__ dS,
-                                                       float *__restrict__ ct, float *__restrict__ J_int,
-                                                       float *__restrict__ J_out) {
-  __shared__ float red[4];
-  const int row = blockIdx.x, t = row / Bp, s = row % Bp;
-  const bool valid = t < Tn && s < B;
-  const float *srow = S + (long)row * Kp;
-  T *drow = dS + (long)row * Kp;
-  float cost = 0.0f;
-  for (int j = threadIdx.x; j < Kp; j += 256) {
-    float g = 0.0f;
-    if (valid && j < K) {
-      const float d = srow[j] + off[j];
-      g = logisticf_(d) * scale;
-      cost += softplusf_(d);
-    }
-    drow[j] = from_f32<T>(g);
-  }
+struct EpiNce : EpiZeroInit {
+  T *dS;
+  long ld;  // Kp
+  const float *off;
+  const int *yp;  // [Mp] target id per position, -1 on padding
+  float scale;
+  int K, Mp;
+  float *jpart;  // [Kp / 32][Mp]
+  float *gpart;  // [Mp / 32][Kp]
+  template <int BM, int BN>
+  static constexpr int lds_bytes() { return 0; }
+  template <int BM, int BN, int TM, int TN, int NT>
+  __device__ inline void run(f32x16_t (&acc)[TM][TN], const EpiCtx &c) const {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) cost += __shfl_xor(cost, o, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = cost;
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  if (!valid) {
-    ct[row] = 0.0f;
-    return;
+    for (int i = 0; i < TM; ++i) {
+      const int row0 = c.tile_row0 + c.wrow + i * 32;
+      unsigned valid = 0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) valid |= (unsigned)(yp[row0 + RNNLM_ACC_ROW(r, c.lane)] >= 0) << r;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int col0 = c.tile_col0 + c.wcol + j * 32, col = col0 + (c.lane & 31);
+        const float o = off[col];
+        const unsigned live = col < K ? valid : 0u;
+        float cost[16], gsum = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float d = acc[i][j][r] + o;
+          const bool on = (live >> r) & 1u;
+          const float g = on ? logisticf_(d) * scale : 0.0f;
+          cost[r] = on ? softplusf_(d) : 0.0f;
+          gsum += g;
+          dS[(long)(row0 + RNNLM_ACC_ROW(r, c.lane)) * ld + col] = from_f32<T>(g);
+        }
+        gsum += __shfl_xor(gsum, 32, 64);
+        if (c.lane < 32) gpart[(long)(row0 >> 5) * ld + col] = gsum;
+        // sums over the 32 lanes of a row: at each exchange a lane keeps half of its rows and gives the other half away
+#pragma unroll
+        for (int n = 8; n > 0; n >>= 1) {
+          const bool upper = c.lane & (2 * n);
+#pragma unroll
+          for (int k = 0; k < n; ++k) {
+            const float give = upper ? cost[k] : cost[k + n];
+            cost[k] = (upper ? cost[k + n] : cost[k]) + __shfl_xor(give, 2 * n, 64);
+          }
+        }
+        cost[0] += __shfl_xor(cost[0], 1, 64);
+        const int r = (c.lane & 31) >> 1;  // the row this lane has kept
+        if (!(c.lane & 1)) jpart[(long)(col0 >> 5) * Mp + row0 + RNNLM_ACC_ROW(r, c.lane)] = cost[0];
+      }
+    }
   }
-  const float d = dt[row];
-  const float total = ((red[0] + red[1]) + (red[2] + red[3])) + softplusf_(-d);
-  ct[row] = -logisticf_(-d) * scale;
-  const int m = t * B + s;
-  J_int[m] = total;
-  if (J_out) J_out[m] = total;
-}
+};
 
-// Bias gradient of noise word j: gcol[j] = sum over valid positions of sigmoid(S[row][j] + off[j]) * scale,
-// in two fixed-order levels.  Level 1: workgroup (column block x, row block y) = 64 columns x 16 row
-// groups over the positions m = y, y + gridDim.y, ...; each group sums its positions in ascending order,
-// the 16 group sums are added in order into part[y][j].  Level 2 (the row blocks, in order) is done by the
-// consumer, nce_row_update_kernel, when it forms the word's bias gradient.
-__global__ void __launch_bounds__(1024) nce_colsum_kernel(const float *__restrict__ S, int Kp, int K,
-                                                          const float *__restrict__ off, int Tn, int B, int Bp,
-                                                          float scale, float *__restrict__ part) {
+// Adds up the blocks' partial sums, in fixed order.  The first rowBlocks workgroups, 64 positions each: the position's
+// loss J and the target coefficient ct[row] = -(1 - sigmoid(dt)) * scale (0 on padding rows); the others, 64 noise slots
+// each: their bias gradient gcol[j].  16 groups of threads share out the partials (bound by memory latency).
+__global__ void __launch_bounds__(1024) nce_merge_kernel(const float *__restrict__ jpart, const float *__restrict__ gpart,
+                                                         int Kp, int Mp, int rowBlocks, const float *__restrict__ dt,
+                                                         const int32_t *__restrict__ yp, int rows, int B, int Bp,
+                                                         float scale, float *__restrict__ ct,
+                                                         float *__restrict__ J_int, float *__restrict__ J_out,
+                                                         float *__restrict__ gcol) {
   __shared__ float sh[16][64];
   const int c = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + c;
+  const bool positions = (int)blockIdx.x < rowBlocks;
+  const int i = (positions ? blockIdx.x : blockIdx.x - rowBlocks) * 64 + c;
+  const float *part = positions ? jpart : gpart;
+  const int n = (positions ? Kp : Mp) / 32, ld = positions ? Mp : Kp;
   float acc = 0.0f;
-  if (j < K) {
-    const float o = off[j];
-    const int M = Tn * B;
-    for (int m = blockIdx.y * 16 + grp; m < M; m += 16 * gridDim.y) {
-      const long row = (long)(m / B) * Bp + (m % B);
-      acc += logisticf_(S[row * Kp + j] + o) * scale;
-    }
+  if (i < ld) {
+#pragma unroll 8
+    for (int p = grp; p < n; p += 16) acc += part[(long)p * ld + i];
   }
   sh[grp][c] = acc;
   __syncthreads();
   if (grp != 0) return;
-  float tot = 0.0f;
-  for (int g = 0; g < 16; ++g) tot += sh[g][c];
-  part[(long)blockIdx.y * Kp + j] = tot;
+#pragma unroll
+  for (int g = 1; g < 16; ++g) acc += sh[g][c];
+  if (!positions) {
+    gcol[i] = acc;
+    return;
+  }
+  if (i >= rows) return;
+  if (yp[i] < 0) {
+    ct[i] = 0.0f;
+    return;
+  }
+  const float d = dt[i];
+  const float total = acc + softplusf_(-d);
+  ct[i] = -logisticf_(-d) * scale;
+  const int m = (i / Bp) * B + i % Bp;
+  J_int[m] = total;
+  if (J_out) J_out[m] = total;
 }
 
 // dHs[row][:] += ct[row] * Wo_c[y_row][:]: the target word's share of what the output layer sends back.
@@ -225,14 +257,13 @@ __global__ void __launch_bounds__(256) nce_target_dhs_kernel(const T *__restrict
 // compact_ld > 0 redirects the results to compact per-run buffers (see below).
 // The first column block also updates the word's bias, one member a lane:
 //   b_out[w] = alpha*b[w] - lr * (sum over w's noise entries of their column sums + sum of ct over its target
-//   entries); a noise entry's column sum is the sum, in order, of the NCE_COLSUM_PARTS row-block partials
-//   gpart[y][Kp].
+//   entries), the column sums from gcol.
 template <bool ALIGNED, typename T>
 __global__ void __launch_bounds__(64 * RUN_WAVES) nce_row_update_kernel(
     const float *__restrict__ G, const T *__restrict__ Hs1, int Hp, int H, int K, int B, int Bp,
     const float *__restrict__ ct, const int32_t *__restrict__ ids, const int32_t *__restrict__ perm,
     const int32_t *__restrict__ seg_start, const int32_t *__restrict__ nseg, const float *__restrict__ W,
-    float *__restrict__ out, T *__restrict__ Wc, const float *__restrict__ gpart, int Kp, const float *__restrict__ b,
+    float *__restrict__ out, T *__restrict__ Wc, const float *__restrict__ gcol, const float *__restrict__ b,
     float *__restrict__ b_out, float alpha, float lr, int compact_ld) {
   __shared__ RunShared shared;
   const int lane = threadIdx.x & 63;
@@ -272,18 +303,7 @@ __global__ void __launch_bounds__(64 * RUN_WAVES) nce_row_update_kernel(
               row = (m / B) * Bp + m % B;
               coef = ct[row];
             }
-            if (bias) {
-              float bv = coef;
-              if (noise) {
-                float pv[NCE_COLSUM_PARTS];  // all partials requested before any is added
-#pragma unroll
-                for (int y = 0; y < NCE_COLSUM_PARTS; ++y) pv[y] = gpart[(long)y * Kp + row];
-                bv = pv[0];
-#pragma unroll
-                for (int y = 1; y < NCE_COLSUM_PARTS; ++y) bv += pv[y];
-              }
-              bacc += bv;
-            }
+            if (bias) bacc += noise ? gcol[row] : coef;
           }
           const int nn = __popcll(__ballot(noise));
           s.take(0, nn,

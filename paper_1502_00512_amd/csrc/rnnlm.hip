@@ -34,7 +34,7 @@ struct WsLayout {
   size_t Wo_c, U_c, UT_c, Hs_c, ZT, dA_c, X32, dHs32, dA32, part32, stat, lse, zy, logp_int, xp, yp, perm, seg, xtmp, ytmp,
       scalars, total;
   // noise-contrastive calls (present when K_max > 0)
-  size_t Wn_c, S32, dS_c, G32, noff, ndt, nct, gcol, ids, perm2, seg2;
+  size_t Wn_c, Spart, dS_c, G32, noff, ndt, nct, gcol, ids, perm2, seg2;
   // rmsprop calls (present when cfg.rmsprop != 0): gradient buffers the redirected update epilogues fill
   size_t gWo, gU, gb, gN, gbN;
   // compressed architecture (present when cfg.P > 0; then Wo_c holds the compute copy of the tied matrix E)
@@ -368,17 +368,17 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   L.xtmp = take((size_t)c.T_max * c.B * 4);
   L.ytmp = take((size_t)c.T_max * c.B * 4);
   KpMax = (int)round_up(c.K_max, 256);
-  L.Wn_c = L.S32 = L.dS_c = L.G32 = L.noff = L.ndt = L.nct = L.gcol = L.ids = L.perm2 = L.seg2 = 0;
+  L.Wn_c = L.Spart = L.dS_c = L.G32 = L.noff = L.ndt = L.nct = L.gcol = L.ids = L.perm2 = L.seg2 = 0;
   if (KpMax > 0) {
     const size_t nent = (size_t)KpMax + (size_t)c.T_max * c.B;
     L.Wn_c = take((size_t)KpMax * Hp * es);
-    L.S32 = take((size_t)MpMax * KpMax * 4);
+    L.Spart = take((size_t)(MpMax / 32) * KpMax * 2 * 4);  // partial sums of the score blocks: losses, bias gradients
     L.dS_c = take((size_t)MpMax * KpMax * es);
     L.G32 = take((size_t)KpMax * Hp * 4);
     L.noff = take((size_t)KpMax * 4);
     L.ndt = take((size_t)MpMax * 4);
     L.nct = take((size_t)MpMax * 4);
-    L.gcol = take((size_t)NCE_COLSUM_PARTS * KpMax * 4);  // 16 row-block partials of the noise words' bias gradient
+    L.gcol = take((size_t)KpMax * 4);
     L.ids = take(nent * 4);
     L.perm2 = take(nent * 4);
     L.seg2 = take((nent + 1) * 4);
@@ -778,8 +778,8 @@ struct NceCall {
   bool sort_ids;  // the call updates (or exports) rows: sort the touched-word list
 };
 
-// Scores of all positions against the gathered noise rows, the targets' own scores, then the
-// elementwise pass: coefficients dS (contraction operand), target coefficients, losses, bias column sums.
+// Scores of all positions against the gathered noise rows and the targets' own scores: coefficients dS (contraction
+// operand), target coefficients, losses, bias column sums.
 template <typename T>
 int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
   const rnnlm_config &c = h->cfg;
@@ -788,7 +788,7 @@ int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
   const int K = n.K, Kp = (int)round_up(K, 256);
   T *Hs1 = at<T>(h, h->L.Hs_c) + (long)Bp * Hp;
   T *Wn = at<T>(h, h->L.Wn_c);
-  float *S = at<float>(h, h->L.S32);
+  float *jpart = at<float>(h, h->L.Spart), *gpart = jpart + (long)(Kp / 32) * Mp;
   int32_t *yp = at<int32_t>(h, h->L.yp);
   const float lnZ_lnK = n.lnZ + logf((float)K);
   const float scale = 1.0f / (float)M;
@@ -813,19 +813,23 @@ int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
                        at<T>(h, h->L.Wo_c), Hp, yp, h->buf.b, n.lnq, lnZ_lnK, Mrows, c.B, Bp, at<float>(h, h->L.ndt),
                        (float *)nullptr);
     HIP_TRY(hipGetLastError());
-    EpiPartial epi;
-    epi.part = S;
+    EpiNce<T> epi;
+    epi.dS = at<T>(h, h->L.dS_c);
     epi.ld = Kp;
-    epi.split_stride = 0;
+    epi.off = at<float>(h, h->L.noff);
+    epi.yp = yp;
+    epi.scale = scale;
+    epi.K = K;
+    epi.Mp = Mp;
+    epi.jpart = jpart;
+    epi.gpart = gpart;
     HIP_TRY((mid_gemm<T, ROWK, ROWK>(st, Hs1, Hp, Wn, Hp, Mp, Kp, Hp, 1, epi)));
   }
   StageTimer tm(h, RNNLM_STAGE_NCE_GRAD, st);
-  hipLaunchKernelGGL(nce_grad_kernel<T>, dim3(Mp), dim3(256), 0, st, S, Kp, K, at<float>(h, h->L.noff),
-                     at<float>(h, h->L.ndt), Tn, c.B, Bp, scale, at<T>(h, h->L.dS_c), at<float>(h, h->L.nct),
-                     at<float>(h, h->L.logp_int), n.J_out);
-  // bias-gradient column sums of the noise words: 16 row-block partials, added in order by the row update
-  hipLaunchKernelGGL(nce_colsum_kernel, dim3(Kp / 64, NCE_COLSUM_PARTS), dim3(1024), 0, st, S, Kp, K,
-                     at<float>(h, h->L.noff), Tn, c.B, Bp, scale, at<float>(h, h->L.gcol));
+  const int rowBlocks = (int)blocks_for(Mrows, 64);
+  hipLaunchKernelGGL(nce_merge_kernel, dim3(rowBlocks + Kp / 64), dim3(1024), 0, st, jpart, gpart, Kp, Mp, rowBlocks,
+                     at<float>(h, h->L.ndt), yp, Mrows, c.B, Bp, scale, at<float>(h, h->L.nct), at<float>(h, h->L.logp_int),
+                     n.J_out, at<float>(h, h->L.gcol));
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
@@ -886,7 +890,7 @@ int nce_update(rnnlm_t *h, int Tn, const NceCall &n, const UpdateTargets &u, hip
   hipLaunchKernelGGL((c.H % 4 == 0 ? nce_row_update_kernel<true, T> : nce_row_update_kernel<false, T>),
                      dim3(blocks_for(nent, RUN_WAVES), blocks_for(c.H, RUN_COLS)), dim3(64 * RUN_WAVES), 0, st, G, Hs1, Hp, c.H,
                      K, c.B, Bp, at<float>(h, h->L.nct), ids, perm, seg, p_nseg2(h), h->buf.Wo, u.Wo, Wc,
-                     at<float>(h, h->L.gcol), Kp, h->buf.b, u.b, u.alpha, u.lr, u.wo_compact_ld);
+                     at<float>(h, h->L.gcol), h->buf.b, u.b, u.alpha, u.lr, u.wo_compact_ld);
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
