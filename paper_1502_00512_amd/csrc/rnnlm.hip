@@ -181,6 +181,13 @@ long f32_extent(long valid, long other, long K, int max_splits) {
   }
   return best;
 }
+// Terms of a contraction of n: what lies between them and the padded extent (tiles of 256) is zero in both operands, so
+// only the last block of 128 bytes is taken whole (bf16, V = 33278, H = 650, 100x9, padded terms and these: window 338.8 and
+// 335.5 us).
+template <typename T>
+long terms(long n) {
+  return round_up(n, Elem<T>::BK);
+}
 template <int LA, int LB, class Epi>
 hipError_t f32_gemm(hipStream_t st, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
                     const F32Plan &plan, const Epi &epi, int band = 4) {
@@ -300,7 +307,7 @@ struct StepPlan {
 };
 StepPlan step_plan(const rnnlm_config &c, int Bp, int Hp) {
   const bool f32 = c.precision == RNNLM_FP32;
-  const long kBlocks = Hp / (f32 ? 32 : 64);
+  const long kBlocks = (f32 ? terms<float>(c.H) / 32 : terms<bf16_t>(c.H) / 64);
   if (Bp % 256 == 0 && Hp >= 2048) {
     const long tiles = (long)(Bp / 256) * (Hp / (f32 ? 64 : 128));
     return {true, (int)std::min({std::max<long>(1, 256 / tiles), 8L, kBlocks}), Bp};
@@ -679,8 +686,8 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     epi.part = X32;
     epi.ld = Hp;
     epi.split_stride = 0;
-    HIP_TRY((mid_gemm<T, ROWK, ROWK>(st, at<T>(h, h->L.Xp_c), h->Pp, at<T>(h, h->L.A_c), h->Pp, Mp,
-                                                        Hp, h->Pp, 1, epi)));
+    HIP_TRY((mid_gemm<T, ROWK, ROWK>(st, at<T>(h, h->L.Xp_c), h->Pp, at<T>(h, h->L.A_c), h->Pp, Mp, Hp, terms<T>(c.P), 1,
+                                      epi)));
   }
 
   if (persistent_ok(h)) {
@@ -697,17 +704,17 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     const T *A_ = Hs_c + (long)t * Bp * Hp;
     const T *B_ = at<T>(h, h->L.U_c);
     const StepPlan p = step_plan(c, Bp, Hp);
-    const long per = (long)Bp * Hp;
+    const long per = (long)Bp * Hp, K = terms<T>(c.H);
     EpiPartial ep;
     ep.part = at<float>(h, h->L.part32);
     ep.ld = Hp;
     ep.split_stride = p.rows * Hp;
     if (!p.wide) {
-      HIP_TRY((launch_gemm_dma4<T, 64, 64, 2, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, p.rows, Hp, Hp, p.splits, ep)));
+      HIP_TRY((launch_gemm_dma4<T, 64, 64, 2, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, p.rows, Hp, K, p.splits, ep)));
     } else if constexpr (sizeof(T) == 2) {
-      HIP_TRY((launch_gemm_dma<256, 128, 4, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, Bp, Hp, Hp, p.splits, ep)));
+      HIP_TRY((launch_gemm_dma<256, 128, 4, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, Bp, Hp, K, p.splits, ep)));
     } else {
-      HIP_TRY((launch_gemm<T, 256, 64, 4, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, Bp, Hp, Hp, p.splits, ep)));
+      HIP_TRY((launch_gemm<T, 256, 64, 4, 2, ROWK, ROWK>(st, A_, Hp, B_, Hp, Bp, Hp, K, p.splits, ep)));
     }
     hipLaunchKernelGGL(rnn_step_fwd_kernel<T>, dim3(blocks_for(per / 4, 256)), dim3(256), 0, st,
                        at<float>(h, h->L.part32), p.rows * Hp, p.splits, X32 + (long)t * Bp * Hp, c.B, c.H, Hp, per / 4,
@@ -722,7 +729,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     epi.outc = at<T>(h, h->L.P_c);
     epi.ld = h->Pp;
     HIP_TRY((mid_gemm<T, ROWK, ROWK>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.C_c), Hp, Mp,
-                                                        h->Pp, Hp, 1, epi)));
+                                                        h->Pp, terms<T>(c.H), 1, epi)));
     feat = at<T>(h, h->L.P_c);
   }
   if (!with_output) return RNNLM_OK;  // the scoring calls only wanted the layer above the states
@@ -742,7 +749,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
       // row panels (the 32 tiles an XCD works on at a time then share 8 row panels and 4 position panels in its L2:
       // measured best of 1..16 on all three large configurations)
       HIP_TRY((launch_gemm_dma<BIG, BIG, 4, 2, ROWK, ROWK, true>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp,
-                                                                    Mp, h->Dp, 1, epi, 8)));
+                                                                    Mp, terms<T>(h->D), 1, epi, 8)));
     } else {
       const F32Plan plan = f32_plan(Vp, Mp, h->D, 1);
       HIP_TRY((f32_gemm<ROWK, ROWK>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp, round_up(h->D, 32), plan, epi, 8)));
@@ -823,7 +830,7 @@ int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
     epi.Mp = Mp;
     epi.jpart = jpart;
     epi.gpart = gpart;
-    HIP_TRY((mid_gemm<T, ROWK, ROWK>(st, Hs1, Hp, Wn, Hp, Mp, Kp, Hp, 1, epi)));
+    HIP_TRY((mid_gemm<T, ROWK, ROWK>(st, Hs1, Hp, Wn, Hp, Mp, Kp, terms<T>(c.H), 1, epi)));
   }
   StageTimer tm(h, RNNLM_STAGE_NCE_GRAD, st);
   const int rowBlocks = (int)blocks_for(Mrows, 64);
@@ -846,8 +853,8 @@ int nce_backward_h(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
   epi.part = dHs32;
   epi.ld = Hp;
   epi.split_stride = 0;
-  HIP_TRY((mid_gemm<T, ROWK, KROW>(st, at<T>(h, h->L.dS_c), Kp, at<T>(h, h->L.Wn_c), Hp, Mp, Hp, Kp,
-                                                      1, epi)));
+  HIP_TRY((mid_gemm<T, ROWK, KROW>(st, at<T>(h, h->L.dS_c), Kp, at<T>(h, h->L.Wn_c), Hp, Mp, Hp, terms<T>(n.K),
+                                      1, epi)));
   hipLaunchKernelGGL(nce_target_dhs_kernel<T>, dim3(Mrows), dim3(256), 0, st, at<T>(h, h->L.Wo_c), Hp,
                      at<int32_t>(h, h->L.yp), at<float>(h, h->L.nct), dHs32);
   HIP_TRY(hipGetLastError());
@@ -869,13 +876,14 @@ int nce_update(rnnlm_t *h, int Tn, const NceCall &n, const UpdateTargets &u, hip
     const long per = (long)Kp * Hp;
     constexpr int BK = Elem<T>::BK;
     long S = 256 / ((long)(Kp / 128) * (Hp / 128));  // aim at one round of workgroups
-    S = std::min<long>(std::min<long>(S, 8), std::min<long>(Mp / BK, h->L.partElems / per));
+    const long terms_ = terms<T>(Mrows);
+    S = std::min<long>(std::min<long>(S, 8), std::min<long>(terms_ / BK, h->L.partElems / per));
     if (S < 1) S = 1;
     EpiPartial epi;
     epi.part = (S == 1) ? G : at<float>(h, h->L.part32);
     epi.ld = Hp;
     epi.split_stride = per;
-    HIP_TRY((mid_gemm<T, KROW, KROW>(st, at<T>(h, h->L.dS_c), Kp, Hs1, Hp, Kp, Hp, Mp, (int)S, epi)));
+    HIP_TRY((mid_gemm<T, KROW, KROW>(st, at<T>(h, h->L.dS_c), Kp, Hs1, Hp, Kp, Hp, terms_, (int)S, epi)));
     if (S > 1) {
       hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks_for(per / 4, 256)), dim3(256), 0, st,
                          at<float>(h, h->L.part32), per, per, (int)S, G);
@@ -905,7 +913,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   const int Hp = h->Hp, Bp = h->Bp, Vp = h->Vp;
   const int Mrows = Tn * Bp;
   const int Mp = (int)window_rows(h->cfg, Mrows);
-  const long ldz = h->MpMax;
+  const long ldz = h->MpMax, rowTerms = terms<T>(Mrows);
   constexpr int BK = Elem<T>::BK;
   T *Hs_c = at<T>(h, h->L.Hs_c);
   T *ZT = at<T>(h, h->L.ZT);
@@ -973,7 +981,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     epi.part = dHs32;
     epi.ld = Hp;
     epi.split_stride = 0;
-    HIP_TRY((mid_gemm<T, ROWK, KROW>(st, dP_c, h->Pp, at<T>(h, h->L.C_c), Hp, Mp, Hp, h->Pp, 1, epi)));
+    HIP_TRY((mid_gemm<T, ROWK, KROW>(st, dP_c, h->Pp, at<T>(h, h->L.C_c), Hp, Mp, Hp, terms<T>(c.P), 1, epi)));
   }
   }
 
@@ -1000,20 +1008,20 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     const bool contract = t < Tn - 1;  // nothing flows into the window's last position
     const T *A_ = dA_c + (long)(t + 1) * Bp * Hp;
     const StepPlan p = step_plan(c, Bp, Hp);
-    const long per = (long)Bp * Hp, at_t = (long)t * per;
+    const long per = (long)Bp * Hp, at_t = (long)t * per, K = terms<T>(c.H);
     EpiPartial ep;
     ep.part = at<float>(h, h->L.part32);
     ep.ld = Hp;
     ep.split_stride = p.rows * Hp;
     if (contract) {
       if (!dma4_reaches<T>(KROW, Hp, 64, Hp)) {  // bf16, a matrix of 2^31 bytes and more
-        HIP_TRY((launch_gemm<T, 64, 64, 2, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, p.rows, Hp, Hp, p.splits, ep)));
+        HIP_TRY((launch_gemm<T, 64, 64, 2, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, p.rows, Hp, K, p.splits, ep)));
       } else if (!p.wide) {
-        HIP_TRY((launch_gemm_dma4<T, 64, 64, 2, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, p.rows, Hp, Hp, p.splits, ep)));
+        HIP_TRY((launch_gemm_dma4<T, 64, 64, 2, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, p.rows, Hp, K, p.splits, ep)));
       } else if constexpr (sizeof(T) == 2) {
-        HIP_TRY((launch_gemm_dma4<bf16_t, 256, 128, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, Hp, p.splits, ep)));
+        HIP_TRY((launch_gemm_dma4<bf16_t, 256, 128, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, K, p.splits, ep)));
       } else {
-        HIP_TRY((launch_gemm<T, 256, 64, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, Hp, p.splits, ep)));
+        HIP_TRY((launch_gemm<T, 256, 64, 4, 2, ROWK, KROW>(st, A_, Hp, U_c, Hp, Bp, Hp, K, p.splits, ep)));
       }
     }
     hipLaunchKernelGGL(rnn_step_bwd_kernel<T>, dim3(blocks_for(per / 4, 256)), dim3(256), 0, st,
@@ -1071,10 +1079,10 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     epi.lr = u.lr;
     if (sizeof(T) == 2 && (long)(Hp / BIG) * (Hp / BIG) >= 64) {
       if constexpr (sizeof(T) == 2)
-        HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, Mp, 1, epi)));
+        HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, rowTerms, 1, epi)));
     } else {
       const long n = sizeof(T) == 4 ? round_up(c.H, 64) : Hp;  // (the epilogue writes valid entries only)
-      HIP_TRY((mid_gemm<T, KROW, KROW>(rs, Hs_c, Hp, dA_c, Hp, n, n, Mp, 1, epi)));
+      HIP_TRY((mid_gemm<T, KROW, KROW>(rs, Hs_c, Hp, dA_c, Hp, n, n, rowTerms, 1, epi)));
     }
   }
     return RNNLM_OK;
@@ -1117,7 +1125,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
       epi.C = c.H;
       epi.alpha = u.alpha;
       epi.lr = u.lr;
-      HIP_TRY((mid_gemm<T, KROW, KROW>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.dP_c), h->Pp, Hp, h->Pp, Mp, 1, epi)));
+      HIP_TRY((mid_gemm<T, KROW, KROW>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.dP_c), h->Pp, Hp, h->Pp, rowTerms, 1, epi)));
     }
     {
     // Wo[v][j] -= lr * sum_m dz[v][m] Hs[m][j]; compressed architecture: the output-side update of the tied matrix,
@@ -1156,17 +1164,17 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
       // gemm_ring64.h: 8-9 % faster at H = 1024 and 2048); the widest layer runs at the chip's power limit, where the
       // symmetric ring measured 0.5 % better
       if (Hp / BIG >= 16) {
-        HIP_TRY((big_gemm<2, 4, ROWK, KROW, true>(st, ZT, ldz, feat, Hp, Vp, Hp, Mp, 1, epi, -8)));
+        HIP_TRY((big_gemm<2, 4, ROWK, KROW, true>(st, ZT, ldz, feat, Hp, Vp, Hp, rowTerms, 1, epi, -8)));
       } else {
-        HIP_TRY((launch_gemm_ring64<BIG, BIG, 2, 4>(st, ZT, ldz, feat, Hp, Vp, Hp, Mp, 1, epi, -4)));
+        HIP_TRY((launch_gemm_ring64<BIG, BIG, 2, 4>(st, ZT, ldz, feat, Hp, Vp, Hp, rowTerms, 1, epi, -4)));
       }
     } else {
       EpiSgdT<T> et;
       aim(et);
       if ((long)(h->Dp / BIG) * (Vp / BIG) < 128) {  // a narrow layer above the state: smaller tiles fill the chip
-        HIP_TRY((launch_gemm_dma4<bf16_t, 128, BIG, 2, 4, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, et, -4)));
+        HIP_TRY((launch_gemm_dma4<bf16_t, 128, BIG, 2, 4, KROW, ROWK>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, rowTerms, 1, et, -4)));
       } else {
-        HIP_TRY((big_gemm<2, 4, KROW, ROWK, true>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, Mp, 1, et, -2)));
+        HIP_TRY((big_gemm<2, 4, KROW, ROWK, true>(st, feat, h->Dp, ZT, ldz, h->Dp, Vp, rowTerms, 1, et, -2)));
       }
     }
     }
@@ -1177,7 +1185,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
       epi.part = at<float>(h, h->L.dX32);
       epi.ld = h->Pp;
       epi.split_stride = 0;
-      HIP_TRY((mid_gemm<T, ROWK, KROW>(st, dA_c, Hp, at<T>(h, h->L.A_c), h->Pp, Mp, h->Pp, Hp, 1, epi)));
+      HIP_TRY((mid_gemm<T, ROWK, KROW>(st, dA_c, Hp, at<T>(h, h->L.A_c), h->Pp, Mp, h->Pp, terms<T>(c.H), 1, epi)));
     }
   }
   if (!early_side) {
@@ -1199,7 +1207,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     epi.C = c.P;
     epi.alpha = u.alpha;
     epi.lr = u.lr;
-    HIP_TRY((mid_gemm<T, KROW, KROW>(st, at<T>(h, h->L.Xp_c), h->Pp, dA_c, Hp, h->Pp, Hp, Mp, 1, epi)));
+    HIP_TRY((mid_gemm<T, KROW, KROW>(st, at<T>(h, h->L.Xp_c), h->Pp, dA_c, Hp, h->Pp, Hp, rowTerms, 1, epi)));
   }
 
   if (!early_rec) {
