@@ -734,8 +734,8 @@ struct EpiSgd : EpiZeroInit {
   static constexpr int lds_bytes() { return 0; }
   template <int BM, int BN, int TM, int TN, int NT>
   __device__ inline void run(f32x16_t (&acc)[TM][TN], const EpiCtx &c) const {
-    const int row0 = c.tile_row0 + c.wrow, col0 = c.tile_col0 + c.wcol, lane = c.lane;
 #if defined(__HIP_DEVICE_COMPILE__)
+    const int row0 = c.tile_row0 + c.wrow, col0 = c.tile_col0 + c.wcol, lane = c.lane;
     // What bounds this epilogue is memory latency (a compute unit moves 640 KB per tile; its matrix cores idle meanwhile), so
     // the master values of TWO 32-row blocks are in flight at any time: block i + 2 is requested as soon as block i has been
     // stored.  All accesses go through buffer resources based at the wave tile's origin: one lane-dependent offset register

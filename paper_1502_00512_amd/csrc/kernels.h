@@ -431,6 +431,35 @@ __global__ void splitk_reduce_kernel(const float *__restrict__ part, long n, lon
   *reinterpret_cast<float4 *>(out + i) = a;
 }
 
+// Many parts (more than 16) of a small output: bound by memory latency.  The waves of a workgroup share out the parts of 256
+// values, eight in flight a lane, and the four sums are added in order.
+__global__ void __launch_bounds__(256) splitk_reduce_many_kernel(const float *__restrict__ part, long n, int splits,
+                                                                 float *__restrict__ out) {
+  constexpr int WAVES = 4, FLIGHT = 8;
+  __shared__ f32x4_t sh[WAVES][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long i = ((long)blockIdx.x * 64 + lane) * 4;
+  f32x4_t a = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (i < n) {
+    const int per = (splits + WAVES - 1) / WAVES, s1 = min((wave + 1) * per, splits);
+    for (int s = wave * per; s < s1; s += FLIGHT) {
+      f32x4_t v[FLIGHT];
+#pragma unroll
+      for (int q = 0; q < FLIGHT; ++q)
+        if (s + q < s1) v[q] = *reinterpret_cast<const f32x4_t *>(part + (s + q) * n + i);
+#pragma unroll
+      for (int q = 0; q < FLIGHT; ++q)
+        if (s + q < s1) a += v[q];
+    }
+  }
+  sh[wave][lane] = a;
+  __syncthreads();
+  if (wave != 0 || i >= n) return;
+#pragma unroll
+  for (int q = 1; q < WAVES; ++q) a += sh[q][lane];
+  *reinterpret_cast<f32x4_t *>(out + i) = a;
+}
+
 // ---- a10 helpers (integer-exact): stable order of window positions by input id ------------------
 // rank[m] = #{m' : (x[m'], m') < (x[m], m)};  perm[rank[m]] = m.
 // Block = 64 positions x 16 slices of the key array (1024 threads).

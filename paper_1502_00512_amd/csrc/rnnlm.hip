@@ -264,13 +264,28 @@ bool cfg_ok(const rnnlm_config *c) {
 }
 
 constexpr int MAX_SPLITS = 16;
+// Splits of the bf16 contraction over the vocabulary (kBlocks 64-deep blocks, 256x256 tiles, at most one workgroup per
+// compute unit): up to 16, and more where the output has so few tiles that most of the chip would be idle and an estimate,
+// in us, of a workgroup's share and of the pass that adds up the parts is a tenth lower.  Windows with at most 16 and with
+// these: V = 30000, H = 256, 16x8 144.5 and 125.2 us, 32x16 161.2 and 144.8; V = 64000, H = 1024, 16x16 375.9 and 352.8; V =
+// 100000, H = 2048, 8x8 925.3 and 891.5 (V = 33278, H = 650, 100x9: 16 splits 317.6, 21 would take 329.1).
+constexpr int BF16_SPLITS = 64;
 int desired_splits(long Mp, long Hp, long kBlocks) {
-  const long tiles = (Mp / BIG) * (Hp / BIG);
-  long s = 256 / tiles;  // one workgroup per compute unit: stay within one round
-  if (s > MAX_SPLITS) s = MAX_SPLITS;
-  if (s > kBlocks) s = kBlocks;
-  if (s < 1) s = 1;
-  return (int)s;
+  const long tiles = (Mp / BIG) * (Hp / BIG), most = std::min<long>(std::max<long>(1, 256 / tiles), kBlocks);
+  auto estimate = [&](long S) {
+    return 6.0 + (kBlocks + S - 1) / S * (0.5 + 1.15 * std::min(1.0, tiles * S / 256.0)) +
+           (S > 1 ? 5.0 + (S + 1) * (double)Mp * Hp * 4.0 / 3.5e6 : 0.0);
+  };
+  long best = std::min<long>(most, MAX_SPLITS);
+  double us = 0.9 * estimate(best);
+  for (long S = best + 1; S <= std::min<long>(most, BF16_SPLITS); ++S) {
+    const long per = (kBlocks + S - 1) / S;
+    if ((kBlocks + per - 1) / per == S && estimate(S) < us) {  // (else the last ones would be empty)
+      us = estimate(S);
+      best = S;
+    }
+  }
+  return (int)best;
 }
 
 // A wave's share of the matrix has to fit its registers: four waves and 32 units per workgroup up to 1024 units, eight
@@ -344,7 +359,9 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
     for (long M = 64; M <= MpMax; M += M < F32_TRIM_ROWS ? 64 : PAD_M)
       L.partElems = std::max(L.partElems, (long)f32_plan(M, features_formed(c, M, MAX_SPLITS), c.V, MAX_SPLITS).splits * M * Dp);
   } else {
-    L.partElems = (long)desired_splits(MpMax, Dp, Vp / 64) * MpMax * Dp;
+    L.partElems = 0;
+    for (long M = BIG; M <= MpMax; M += BIG)
+      L.partElems = std::max(L.partElems, (long)desired_splits(M, Dp, Vp / 64) * M * Dp);
   }
   const StepPlan step = step_plan(c, Bp, Hp);
   if (plan.nwg == 0) L.partElems = std::max(L.partElems, (long)step.splits * step.rows * Hp);
@@ -433,6 +450,15 @@ double *p_running(rnnlm_t *h) { return at<double>(h, h->L.scalars + 40); }
 unsigned *p_counter(rnnlm_t *h) { return at<unsigned>(h, h->L.sync); }
 
 inline unsigned blocks_for(long n, int per) { return (unsigned)((n + per - 1) / per); }
+int reduce_splits(hipStream_t st, const float *part, long n, int splits, float *out) {
+  // (786432 entries in 21 parts, shared out: 25 us, 13 expected of whole workgroups)
+  if (splits > 16 && n <= 1 << 18)
+    hipLaunchKernelGGL(splitk_reduce_many_kernel, dim3(blocks_for(n / 4, 64)), dim3(256), 0, st, part, n, splits, out);
+  else
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks_for(n / 4, 256)), dim3(256), 0, st, part, n, n, splits, out);
+  HIP_TRY(hipGetLastError());
+  return RNNLM_OK;
+}
 
 template <typename T>
 int sync_copies(rnnlm_t *h, hipStream_t st) {
@@ -867,7 +893,7 @@ template <typename T>
 int nce_update(rnnlm_t *h, int Tn, const NceCall &n, const UpdateTargets &u, hipStream_t st) {
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp;
-  const int Mrows = Tn * Bp, Mp = (int)window_rows(h->cfg, Mrows), M = Tn * c.B;
+  const int Mrows = Tn * Bp, M = Tn * c.B;
   const int K = n.K, Kp = (int)round_up(K, 256);
   T *Hs1 = at<T>(h, h->L.Hs_c) + (long)Bp * Hp;
   float *G = at<float>(h, h->L.G32);
@@ -885,9 +911,8 @@ int nce_update(rnnlm_t *h, int Tn, const NceCall &n, const UpdateTargets &u, hip
     epi.split_stride = per;
     HIP_TRY((mid_gemm<T, KROW, KROW>(st, at<T>(h, h->L.dS_c), Kp, Hs1, Hp, Kp, Hp, terms_, (int)S, epi)));
     if (S > 1) {
-      hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks_for(per / 4, 256)), dim3(256), 0, st,
-                         at<float>(h, h->L.part32), per, per, (int)S, G);
-      HIP_TRY(hipGetLastError());
+      int rc = reduce_splits(st, at<float>(h, h->L.part32), per, (int)S, G);
+      if (rc) return rc;
     }
   }
   StageTimer tm(h, RNNLM_STAGE_NCE_UPDATE, st);
@@ -965,9 +990,8 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     }
     if (S > 1) {
       StageTimer tm(h, RNNLM_STAGE_REDUCE, st);
-      hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks_for(per / 4, 256)), dim3(256), 0, st,
-                         at<float>(h, h->L.part32), per, per, S, dF32);
-      HIP_TRY(hipGetLastError());
+      int rc = reduce_splits(st, at<float>(h, h->L.part32), per, S, dF32);
+      if (rc) return rc;
     }
   }
   if (c.P > 0) {

@@ -109,3 +109,20 @@ def test_update_epilogue_at_ragged_edges(V, H, precision):
     g.rnnlm_sync_compute_copies()
     assert torch.equal(a, g.rnnlm_forward_logprob(dev(x), dev(y)))
     g.rnnlm_check()
+
+
+# output contractions of few tiles over long vocabularies: 17 to 63 splits of the contraction (the pass over the parts
+# shares them out above 16), an odd number of blocks a split, an output of one tile and of four
+@pytest.mark.parametrize("V,H,B,T", [(30000, 256, 4, 4), (64000, 100, 3, 5), (20001, 512, 24, 16), (7000, 200, 70, 4)])
+def test_bf16_gradients_with_many_splits(V, H, B, T):
+    E, U, Wo, b = synth.make_weights(V, H, "uniform", 0.1, 17)
+    tok = synth.zipf_tokens(B * T + B + 1, V, 1.1, 18)
+    g = binding.Rnnlm(E, U, Wo, b, B, T, BF16)
+    o = O.Model.from_weights(E, U, Wo, b, B)
+    x, y = O.stream_chunk(tok, B, T, 0)
+    got = g.rnnlm_grad_chunk(dev(x), dev(y))
+    ref = O.grad_chunk(o, x, y)
+    # the bf16 gradients' bound of the suite: 2e-2 of each tensor's scale
+    for key in ("gE", "gU", "gWo"):
+        a = got[key].cpu().numpy().astype(np.float64)
+        assert np.abs(a - ref[key]).max() <= 2e-2 * np.abs(ref[key]).max(), key
