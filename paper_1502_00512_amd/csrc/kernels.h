@@ -276,10 +276,6 @@ __device__ inline void window_sum(const WindowSum &w, int n, Load &&load) {
     if (!(s == s) || s - s != 0.0) w.flags[1] = 1;
   }
 }
-__global__ void __launch_bounds__(1024) sum_logp_kernel(const float *__restrict__ logp, int n, const WindowSum w) {
-  window_sum(w, n, [&](int i) { return logp[i]; });
-}
-
 // ---- a4 (part 1): merge the per-row-block (max, sum exp) partials of each position into the log
 // normaliser, and form log P(target) = z_target - lse (Sec. 4.2: explicitly normalised output).
 // Workgroup = MERGE_M positions x 1024 / MERGE_M groups of partials: a group is merged sequentially in a fixed order,

@@ -24,44 +24,6 @@ __device__ inline float logisticf_(float d) {
   return (d >= 0.0f) ? 1.0f / (1.0f + e) : e / (1.0f + e);
 }
 
-// Preparation of a window's noise words, one workgroup per (padded) noise slot j < Kp plus ceil(M/256)
-// workgroups for the targets:
-//   noise id checked (flags[0] on an id outside [0,V), clamped); offset off[j] = b[n_j] - lnZ - ln K - lnq[n_j]
-//   (0 for the padding j >= K); panel row Wn[j][:] = Wo_c[n_j][:] (zero rows for the padding; Hp is a multiple
-//   of 256); update list ids[0..K) = noise words, ids[K + m] = target of compact position m.
-template <typename T>
-__global__ void __launch_bounds__(256) nce_prep_kernel(const int32_t *__restrict__ noise, int K, int Kp, int V,
-                                                       const float *__restrict__ lnq, const float *__restrict__ b,
-                                                       float lnZ_lnK, const int32_t *__restrict__ yp, int M, int B,
-                                                       int Bp, const T *__restrict__ Wo_c, int Hp,
-                                                       T *__restrict__ Wn, float *__restrict__ off,
-                                                       int32_t *__restrict__ ids, int32_t *__restrict__ flags) {
-  constexpr int VEC = 16 / (int)sizeof(T);
-  const int j = blockIdx.x;
-  if (j >= Kp) {  // target part of the update list
-    const int m = (j - Kp) * 256 + threadIdx.x;
-    if (m < M) ids[K + m] = yp[(m / B) * Bp + (m % B)];
-    return;
-  }
-  int w = 0;
-  if (j < K) {
-    w = noise[j];
-    const bool bad = w < 0 || w >= V;
-    w = min(max(w, 0), V - 1);
-    if (threadIdx.x == 0) {
-      if (bad) flags[0] = 1;
-      off[j] = b[w] - lnZ_lnK - lnq[w];
-      ids[j] = w;
-    }
-  } else if (threadIdx.x == 0) {
-    off[j] = 0.0f;
-  }
-  const u32x4_t *src = reinterpret_cast<const u32x4_t *>(Wo_c + (long)w * Hp);
-  u32x4_t *dst = reinterpret_cast<u32x4_t *>(Wn + (long)j * Hp);
-  const u32x4_t zero = {0u, 0u, 0u, 0u};
-  for (int c = threadIdx.x; c < Hp / VEC; c += 256) dst[c] = (j < K) ? src[c] : zero;
-}
-
 // Dot product of two compute-type rows of n values (n a multiple of 16 / sizeof(T)), one wave: 16-byte loads, per-lane
 // sums, then a butterfly.  Every lane returns the sum.
 template <typename T>
@@ -83,18 +45,13 @@ __device__ inline float wave_dot(const T *__restrict__ x, const T *__restrict__ 
   return acc;
 }
 
-// Score of the target word of every position: dt[row] = Wo_c[y].Hs[row] + b[y] - shift - lnq[y]
-// (lnq == nullptr: no noise term).  One wave per padded position (4 per workgroup); lanes stride the
-// row, then a butterfly sum.  out (may be nullptr) receives the valid positions in compact order t*B + s.
+// Score of the target word of a position, by one wave: dt[row] = Wo_c[y].Hs[row] + b[y] - shift - lnq[y]
+// (lnq == nullptr: no noise term).  out (may be nullptr) receives the valid positions in compact order t*B + s.
 template <typename T>
-__global__ void __launch_bounds__(256) nce_target_score_kernel(const T *__restrict__ Hs1, const T *__restrict__ Wo_c,
-                                                               int Hp, const int32_t *__restrict__ yp,
-                                                               const float *__restrict__ b,
-                                                               const float *__restrict__ lnq, float shift, int rows,
-                                                               int B, int Bp, float *__restrict__ dt,
-                                                               float *__restrict__ out) {
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (row >= rows) return;
+__device__ inline void target_score(int row, int lane, const T *__restrict__ Hs1, const T *__restrict__ Wo_c, int Hp,
+                                    const int32_t *__restrict__ yp, const float *__restrict__ b,
+                                    const float *__restrict__ lnq, float shift, int B, int Bp, float *__restrict__ dt,
+                                    float *__restrict__ out) {
   const int y = yp[row];
   if (y < 0) {
     if (lane == 0) dt[row] = 0.0f;
@@ -107,6 +64,61 @@ __global__ void __launch_bounds__(256) nce_target_score_kernel(const T *__restri
     dt[row] = v;
     if (out) out[(row / Bp) * B + (row % Bp)] = v;
   }
+}
+// All padded positions, 4 per workgroup.
+template <typename T>
+__global__ void __launch_bounds__(256) nce_target_score_kernel(const T *__restrict__ Hs1, const T *__restrict__ Wo_c,
+                                                               int Hp, const int32_t *__restrict__ yp,
+                                                               const float *__restrict__ b,
+                                                               const float *__restrict__ lnq, float shift, int rows,
+                                                               int B, int Bp, float *__restrict__ dt,
+                                                               float *__restrict__ out) {
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row < rows) target_score(row, threadIdx.x & 63, Hs1, Wo_c, Hp, yp, b, lnq, shift, B, Bp, dt, out);
+}
+
+// Preparation of a window's noise words, one workgroup per (padded) noise slot j < Kp plus ceil(M/256)
+// workgroups for the targets and rows / 4 for the targets' own scores:
+//   noise id checked (flags[0] on an id outside [0,V), clamped); offset off[j] = b[n_j] - lnZ - ln K - lnq[n_j]
+//   (0 for the padding j >= K); panel row Wn[j][:] = Wo_c[n_j][:] (zero rows for the padding; Hp is a multiple
+//   of 256); update list ids[0..K) = noise words, ids[K + m] = target of compact position m.
+template <typename T>
+__global__ void __launch_bounds__(256) nce_prep_kernel(const int32_t *__restrict__ noise, int K, int Kp, int V,
+                                                       const float *__restrict__ lnq, const float *__restrict__ b,
+                                                       float lnZ_lnK, const int32_t *__restrict__ yp, int M, int B,
+                                                       int Bp, const T *__restrict__ Wo_c, int Hp,
+                                                       T *__restrict__ Wn, float *__restrict__ off,
+                                                       int32_t *__restrict__ ids, int32_t *__restrict__ flags,
+                                                       const T *__restrict__ Hs1, int rows, float *__restrict__ dt) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  const int j = blockIdx.x;
+  if (j >= Kp) {  // target part of the update list
+    const int part = j - Kp, lists = (M + 255) / 256, m = part * 256 + threadIdx.x;
+    if (part >= lists) {
+      const int row = (part - lists) * 4 + (threadIdx.x >> 6);
+      if (row < rows) target_score(row, threadIdx.x & 63, Hs1, Wo_c, Hp, yp, b, lnq, lnZ_lnK, B, Bp, dt, (float *)nullptr);
+    } else if (m < M) {
+      ids[K + m] = yp[(m / B) * Bp + (m % B)];
+    }
+    return;
+  }
+  int w = 0;
+  if (j < K) {
+    w = noise[j];
+    const bool bad = w < 0 || w >= V;
+    w = min(max(w, 0), V - 1);
+    if (threadIdx.x == 0) {
+      if (bad) flags[0] = 1;
+      off[j] = b[w] - lnZ_lnK - lnq[w];
+      ids[j] = w;
+    }
+  } else if (threadIdx.x == 0) {
+    off[j] = 0.0f;
+  }
+  const u32x4_t *src = reinterpret_cast<const u32x4_t *>(Wo_c + (long)w * Hp);
+  u32x4_t *dst = reinterpret_cast<u32x4_t *>(Wn + (long)j * Hp);
+  const u32x4_t zero = {0u, 0u, 0u, 0u};
+  for (int c = threadIdx.x; c < Hp / VEC; c += 256) dst[c] = (j < K) ? src[c] : zero;
 }
 
 // Scores of a shortlist of C candidate words per position (Sec. 5.4 ranks a shortlist of candidates):
@@ -196,13 +208,16 @@ struct EpiNce : EpiZeroInit {
 // Adds up the blocks' partial sums, in fixed order.  The first rowBlocks workgroups, 64 positions each: the position's
 // loss J and the target coefficient ct[row] = -(1 - sigmoid(dt)) * scale (0 on padding rows); the others, 64 noise slots
 // each: their bias gradient gcol[j].  16 groups of threads share out the partials (bound by memory latency).
+// done != nullptr: the last workgroup to finish forms the window's sum as well, as in merge_stats_kernel.
 __global__ void __launch_bounds__(1024) nce_merge_kernel(const float *__restrict__ jpart, const float *__restrict__ gpart,
                                                          int Kp, int Mp, int rowBlocks, const float *__restrict__ dt,
                                                          const int32_t *__restrict__ yp, int rows, int B, int Bp,
                                                          float scale, float *__restrict__ ct,
                                                          float *__restrict__ J_int, float *__restrict__ J_out,
-                                                         float *__restrict__ gcol) {
+                                                         float *__restrict__ gcol, unsigned *__restrict__ done,
+                                                         const WindowSum w, int M) {
   __shared__ float sh[16][64];
+  __shared__ int last;
   const int c = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const bool positions = (int)blockIdx.x < rowBlocks;
   const int i = (positions ? blockIdx.x : blockIdx.x - rowBlocks) * 64 + c;
@@ -215,24 +230,31 @@ __global__ void __launch_bounds__(1024) nce_merge_kernel(const float *__restrict
   }
   sh[grp][c] = acc;
   __syncthreads();
-  if (grp != 0) return;
+  if (grp == 0) {
 #pragma unroll
-  for (int g = 1; g < 16; ++g) acc += sh[g][c];
-  if (!positions) {
-    gcol[i] = acc;
-    return;
+    for (int g = 1; g < 16; ++g) acc += sh[g][c];
+    if (!positions) {
+      gcol[i] = acc;
+    } else if (i < rows && yp[i] < 0) {
+      ct[i] = 0.0f;
+    } else if (i < rows) {
+      const float d = dt[i];
+      const float total = acc + softplusf_(-d);
+      ct[i] = -logisticf_(-d) * scale;
+      const int m = (i / Bp) * B + i % Bp;
+      __hip_atomic_store(J_int + m, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (J_out) J_out[m] = total;
+    }
   }
-  if (i >= rows) return;
-  if (yp[i] < 0) {
-    ct[i] = 0.0f;
-    return;
+  if (!done) return;
+  if (threadIdx.x < 64) {  // the wave that stored: its stores are acknowledged before the arrival
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (threadIdx.x == 0)
+      last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
   }
-  const float d = dt[i];
-  const float total = acc + softplusf_(-d);
-  ct[i] = -logisticf_(-d) * scale;
-  const int m = (i / Bp) * B + i % Bp;
-  J_int[m] = total;
-  if (J_out) J_out[m] = total;
+  __syncthreads();
+  if (!last) return;
+  window_sum(w, M, [&](int m) { return __hip_atomic_load(J_int + m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); });
 }
 
 // dHs[row][:] += ct[row] * Wo_c[y_row][:]: the target word's share of what the output layer sends back.

@@ -33,7 +33,9 @@ __global__ void __launch_bounds__(256) rms_row_apply_kernel(const float *__restr
                                                             const int32_t *__restrict__ seg_start,
                                                             const int32_t *__restrict__ nseg, int B, int Bp, int H,
                                                             int Hp, float *__restrict__ W, T *__restrict__ Wc,
-                                                            float *__restrict__ r, float rho, float lr, float eps) {
+                                                            float *__restrict__ r, float rho, float lr, float eps,
+                                                            const float *__restrict__ gb, float *__restrict__ b,
+                                                            float *__restrict__ rb) {
   __shared__ float red[4];
   int w = blockIdx.x;
   if (perm) {
@@ -73,6 +75,11 @@ __global__ void __launch_bounds__(256) rms_row_apply_kernel(const float *__restr
   const float scale = lr / (sqrtf(rnew) + eps);
   __syncthreads();  // every thread has read r[w] before it is overwritten
   if (threadIdx.x == 0) r[w] = rnew;
+  if (gb && threadIdx.x == 0) {  // the word's entry of the bias, whose statistic (decayed already) is its own
+    const float gv = gb[blockIdx.x], bnew = rb[w] + (1.0f - rho) * gv * gv;
+    rb[w] = bnew;
+    if (gv != 0.0f) b[w] -= lr * gv / (sqrtf(bnew) + eps);
+  }
   auto apply4 = [&](int c, const f32x4_t &gv) {
     f32x4_t v = *reinterpret_cast<const f32x4_t *>(wrow + c);
     bool moved = false;
@@ -112,21 +119,6 @@ __global__ void __launch_bounds__(256) rms_row_apply_kernel(const float *__restr
       if (Wc) Wc[(long)w * Hp + c] = from_f32<T>(v);
     }
   }
-}
-
-// Per-element statistic on a compact list (the output bias under the noise-contrastive criterion): entry i
-// < *nseg holds the gradient of the word of the i-th run of the sorted update list; rb was decayed already.
-__global__ void rms_bias_compact_kernel(const float *__restrict__ g, const int32_t *__restrict__ ids,
-                                        const int32_t *__restrict__ perm, const int32_t *__restrict__ seg_start,
-                                        const int32_t *__restrict__ nseg, float *__restrict__ b,
-                                        float *__restrict__ rb, float rho, float lr, float eps) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= *nseg) return;
-  const int w = ids[perm[seg_start[i]]];
-  const float gv = g[i];
-  const float rnew = rb[w] + (1.0f - rho) * gv * gv;
-  rb[w] = rnew;
-  if (gv != 0.0f) b[w] -= lr * gv / (sqrtf(rnew) + eps);
 }
 
 // theta <- theta - lr * g / (sqrt(r) + eps) of one element; returns the new weight.

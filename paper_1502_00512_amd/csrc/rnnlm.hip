@@ -814,7 +814,7 @@ struct NceCall {
 // Scores of all positions against the gathered noise rows and the targets' own scores: coefficients dS (contraction
 // operand), target coefficients, losses, bias column sums.
 template <typename T>
-int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
+int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, const WindowSum *wsum, hipStream_t st) {
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp;
   const int Mrows = Tn * Bp, Mp = (int)window_rows(h->cfg, Mrows), M = Tn * c.B;
@@ -827,9 +827,9 @@ int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
   const float scale = 1.0f / (float)M;
   {
     StageTimer tm(h, RNNLM_STAGE_NCE_SCORE, st);
-    hipLaunchKernelGGL(nce_prep_kernel<T>, dim3(Kp + blocks_for(M, 256)), dim3(256), 0, st, n.noise, K, Kp, c.V, n.lnq,
+    hipLaunchKernelGGL(nce_prep_kernel<T>, dim3(Kp + blocks_for(M, 256) + blocks_for(Mrows, 4)), dim3(256), 0, st, n.noise, K, Kp, c.V, n.lnq,
                        h->buf.b, lnZ_lnK, yp, M, c.B, Bp, at<T>(h, h->L.Wo_c), Hp, Wn, at<float>(h, h->L.noff),
-                       at<int32_t>(h, h->L.ids), p_flags(h));
+                       at<int32_t>(h, h->L.ids), p_flags(h), Hs1, Mrows, at<float>(h, h->L.ndt));
     if (n.sort_ids) {  // the touched-word list is complete: sort it next to the contractions
       int rc = side_fork(h, 1, st);
       if (rc) return rc;
@@ -842,9 +842,6 @@ int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
                          at<int32_t>(h, h->L.seg2), p_nseg2(h));
       HIP_TRY(hipEventRecord(h->ev_join[1], h->side));  // here, not where it is waited for: more work follows on that stream
     }
-    hipLaunchKernelGGL(nce_target_score_kernel<T>, dim3(blocks_for(Mrows, 4)), dim3(256), 0, st, Hs1,
-                       at<T>(h, h->L.Wo_c), Hp, yp, h->buf.b, n.lnq, lnZ_lnK, Mrows, c.B, Bp, at<float>(h, h->L.ndt),
-                       (float *)nullptr);
     HIP_TRY(hipGetLastError());
     EpiNce<T> epi;
     epi.dS = at<T>(h, h->L.dS_c);
@@ -862,7 +859,7 @@ int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
   const int rowBlocks = (int)blocks_for(Mrows, 64);
   hipLaunchKernelGGL(nce_merge_kernel, dim3(rowBlocks + Kp / 64), dim3(1024), 0, st, jpart, gpart, Kp, Mp, rowBlocks,
                      at<float>(h, h->L.ndt), yp, Mrows, c.B, Bp, scale, at<float>(h, h->L.nct), at<float>(h, h->L.logp_int),
-                     n.J_out, at<float>(h, h->L.gcol));
+                     n.J_out, at<float>(h, h->L.gcol), wsum ? p_counter(h) + sync_word(0, 0) : nullptr, wsum ? *wsum : WindowSum{}, M);
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
@@ -1252,12 +1249,8 @@ int window_call(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float *l
                              u && !scan_ids(h, Tn, *u), false, want_sum && !nce ? &ws : nullptr);
   if (rc) return rc;
   if (nce) {  // per-position losses take the place of the log-probabilities
-    rc = nce_forward<T>(h, Tn, *nce, st);
+    rc = nce_forward<T>(h, Tn, *nce, want_sum ? &ws : nullptr, st);
     if (rc) return rc;
-    if (want_sum) {
-      hipLaunchKernelGGL(sum_logp_kernel, dim3(1), dim3(1024), 0, st, at<float>(h, h->L.logp_int), Tn * h->cfg.B, ws);
-      HIP_TRY(hipGetLastError());
-    }
   }
   if (u) rc = backward_window<T>(h, Tn, *u, nce, st, rec_stream);
   return rc;
@@ -1342,7 +1335,7 @@ int rms_apply_inner(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float 
   const rnnlm_config &c = h->cfg;
   hipLaunchKernelGGL(rms_row_apply_kernel<T>, dim3(Tn * c.B), dim3(256), 0, emb_stream, at<float>(h, h->L.dHs32), (long)h->Hp,
                      at<int32_t>(h, h->L.xp), at<int32_t>(h, h->L.perm), at<int32_t>(h, h->L.seg), p_nseg(h), c.B, h->Bp,
-                     c.H, h->Hp, h->buf.E, (T *)nullptr, state.rE, rho, lr, eps);
+                     c.H, h->Hp, h->buf.E, (T *)nullptr, state.rE, rho, lr, eps, nullptr, nullptr, nullptr);
   const unsigned tiles = blocks_for(c.H, 32);
   hipLaunchKernelGGL(rms_square_apply_kernel<T>, dim3(tiles, tiles), dim3(256), 0, rec_stream, at<float>(h, h->L.gU), c.H,
                      h->buf.U, at<T>(h, h->L.U_c), at<T>(h, h->L.UT_c), h->Hp, state.rU, rho, lr, eps);
@@ -1359,7 +1352,7 @@ int rms_apply(rnnlm_t *h, int Tn, const rnnlm_rmsprop_state &state, float rho, f
   if (rc) return rc;
   hipLaunchKernelGGL(rms_row_apply_kernel<T>, dim3(c.V), dim3(256), 0, st, at<float>(h, h->L.gWo), (long)c.H, nullptr,
                      nullptr, nullptr, nullptr, c.B, h->Bp, c.H, h->Hp, h->buf.Wo, at<T>(h, h->L.Wo_c), state.rWo, rho, lr,
-                     eps);
+                     eps, nullptr, nullptr, nullptr);
   hipLaunchKernelGGL(rms_elem_apply_kernel, dim3(blocks_for(c.V, 256)), dim3(256), 0, st, at<float>(h, h->L.gb), c.V,
                      h->buf.b, state.rb, rho, lr, eps);
   HIP_TRY(hipGetLastError());
@@ -1377,9 +1370,8 @@ int rms_apply_nce(rnnlm_t *h, int Tn, int K, const rnnlm_rmsprop_state &state, f
   const int32_t *ids = at<int32_t>(h, h->L.ids), *perm2 = at<int32_t>(h, h->L.perm2), *seg2 = at<int32_t>(h, h->L.seg2);
   // the sort helpers' key indexing key[(i / B) * Bp + i % B] with B = Bp = 1 reads the compact id list
   hipLaunchKernelGGL(rms_row_apply_kernel<T>, dim3(nent), dim3(256), 0, st, at<float>(h, h->L.gN), (long)h->Hp, ids, perm2,
-                     seg2, p_nseg2(h), 1, 1, c.H, h->Hp, h->buf.Wo, at<T>(h, h->L.Wo_c), state.rWo, rho, lr, eps);
-  hipLaunchKernelGGL(rms_bias_compact_kernel, dim3(blocks_for(nent, 256)), dim3(256), 0, st, at<float>(h, h->L.gbN), ids,
-                     perm2, seg2, p_nseg2(h), h->buf.b, state.rb, rho, lr, eps);
+                     seg2, p_nseg2(h), 1, 1, c.H, h->Hp, h->buf.Wo, at<T>(h, h->L.Wo_c), state.rWo, rho, lr, eps,
+                     at<float>(h, h->L.gbN), h->buf.b, state.rb);
   HIP_TRY(hipGetLastError());
   return overlap ? side_join(h, 0, st) : RNNLM_OK;
 }
