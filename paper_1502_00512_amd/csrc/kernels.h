@@ -412,25 +412,33 @@ __global__ void __launch_bounds__(256) softmax_grad_kernel(T *__restrict__ ZT, l
 }
 
 // ---- a6: fixed-order reduction of the split-K partial sums -------------------------------------
-__global__ void splitk_reduce_kernel(const float *__restrict__ part, long n, long split_stride, int splits,
-                                     float *__restrict__ out) {
+// T: what the sum is stored as (the compressed architecture wants a contraction operand; converted by a launch of its own it
+// took 5 us more of a 2560-position window, P = 512).
+template <typename T>
+__device__ inline void store_sum4(T *out, f32x4_t v) {
+  if constexpr (sizeof(T) == 2) {
+    bf16x4_t h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = (bf16_t)v[e];
+    *reinterpret_cast<bf16x4_t *>(out) = h;
+  } else {
+    *reinterpret_cast<f32x4_t *>(out) = v;
+  }
+}
+template <typename T>
+__global__ void splitk_reduce_kernel(const float *__restrict__ part, long n, int splits, T *__restrict__ out) {
   const long i = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (i >= n) return;
-  float4 a = *reinterpret_cast<const float4 *>(part + i);
-  for (int s = 1; s < splits; ++s) {
-    const float4 q = *reinterpret_cast<const float4 *>(part + (long)s * split_stride + i);
-    a.x += q.x;
-    a.y += q.y;
-    a.z += q.z;
-    a.w += q.w;
-  }
-  *reinterpret_cast<float4 *>(out + i) = a;
+  f32x4_t a = *reinterpret_cast<const f32x4_t *>(part + i);
+  for (int s = 1; s < splits; ++s) a += *reinterpret_cast<const f32x4_t *>(part + s * n + i);
+  store_sum4(out + i, a);
 }
 
 // Many parts (more than 16) of a small output: bound by memory latency.  The waves of a workgroup share out the parts of 256
 // values, eight in flight a lane, and the four sums are added in order.
+template <typename T>
 __global__ void __launch_bounds__(256) splitk_reduce_many_kernel(const float *__restrict__ part, long n, int splits,
-                                                                 float *__restrict__ out) {
+                                                                 T *__restrict__ out) {
   constexpr int WAVES = 4, FLIGHT = 8;
   __shared__ f32x4_t sh[WAVES][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -453,7 +461,7 @@ __global__ void __launch_bounds__(256) splitk_reduce_many_kernel(const float *__
   if (wave != 0 || i >= n) return;
 #pragma unroll
   for (int q = 1; q < WAVES; ++q) a += sh[q][lane];
-  *reinterpret_cast<f32x4_t *>(out + i) = a;
+  store_sum4(out + i, a);
 }
 
 // ---- a10 helpers (integer-exact): stable order of window positions by input id ------------------
@@ -779,14 +787,6 @@ __global__ void __launch_bounds__(64 * RUN_WAVES) scatter_scan_kernel(const floa
     for (int q = each; q < RUN_WAVES; ++q) tot += shared[(q - each) * blocks + cb][lane];
   }
   store_row4<ALIGNED>(old - lr * tot, col, H, out + (long)w * H, Ec ? Ec + (long)w * ldc : nullptr);
-}
-
-// fp32 -> compute type, element by element (n elements).
-template <typename T>
-__global__ void to_compute_kernel(const float *__restrict__ src, long n, T *__restrict__ dst) {
-  long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long stride = (long)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) dst[i] = from_f32<T>(src[i]);
 }
 
 // 8-bit row-wise quantisation (Sec. 5.4 quantises all the weights; the scheme is a reading): one workgroup

@@ -38,7 +38,7 @@ struct WsLayout {
   // rmsprop calls (present when cfg.rmsprop != 0): gradient buffers the redirected update epilogues fill
   size_t gWo, gU, gb, gN, gbN;
   // compressed architecture (present when cfg.P > 0; then Wo_c holds the compute copy of the tied matrix E)
-  size_t A_c, C_c, Xp_c, P_c, dP32, dP_c, dX32;
+  size_t A_c, C_c, Xp_c, P_c, dP_c, dX32;
   // partial sums of the chip-resident recurrent kernel (present for Hp = 4096, 256 streams, bf16)
   size_t part_res, sync, ring;
   bool has_part_res;
@@ -419,13 +419,12 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
     L.gN = take(nent * Hp * 4);
     L.gbN = take(nent * 4);
   }
-  L.A_c = L.C_c = L.Xp_c = L.P_c = L.dP32 = L.dP_c = L.dX32 = 0;
+  L.A_c = L.C_c = L.Xp_c = L.P_c = L.dP_c = L.dX32 = 0;
   if (Pp > 0) {
     L.A_c = take((size_t)Hp * Pp * es);
     L.C_c = take((size_t)Pp * Hp * es);
     L.Xp_c = take((size_t)MpMax * Pp * es);
     L.P_c = take((size_t)MpMax * Pp * es);
-    L.dP32 = take((size_t)MpMax * Pp * 4);
     L.dP_c = take((size_t)MpMax * Pp * es);
     L.dX32 = take((size_t)MpMax * Pp * 4);
   }
@@ -450,12 +449,13 @@ double *p_running(rnnlm_t *h) { return at<double>(h, h->L.scalars + 40); }
 unsigned *p_counter(rnnlm_t *h) { return at<unsigned>(h, h->L.sync); }
 
 inline unsigned blocks_for(long n, int per) { return (unsigned)((n + per - 1) / per); }
-int reduce_splits(hipStream_t st, const float *part, long n, int splits, float *out) {
+template <typename T>
+int reduce_splits(hipStream_t st, const float *part, long n, int splits, T *out) {
   // (786432 entries in 21 parts, shared out: 25 us, 13 expected of whole workgroups)
   if (splits > 16 && n <= 1 << 18)
-    hipLaunchKernelGGL(splitk_reduce_many_kernel, dim3(blocks_for(n / 4, 64)), dim3(256), 0, st, part, n, splits, out);
+    hipLaunchKernelGGL(splitk_reduce_many_kernel<T>, dim3(blocks_for(n / 4, 64)), dim3(256), 0, st, part, n, splits, out);
   else
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks_for(n / 4, 256)), dim3(256), 0, st, part, n, n, splits, out);
+    hipLaunchKernelGGL(splitk_reduce_kernel<T>, dim3(blocks_for(n / 4, 256)), dim3(256), 0, st, part, n, splits, out);
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
@@ -965,7 +965,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   // architecture: the same contraction with the tied matrix gives the gradient of the layer above the state
   {
     const int Dp = h->Dp;
-    float *dF32 = c.P > 0 ? at<float>(h, h->L.dP32) : dHs32;
+    T *dP_c = c.P > 0 ? at<T>(h, h->L.dP_c) : nullptr;  // (an operand of the contraction below)
     const long per = (long)Mp * Dp;
     const int max_splits = (int)std::min<long>(MAX_SPLITS, std::max<long>(1, h->L.partElems / per));
     const long Dn = sizeof(T) == 4 ? features_formed(c, Mp, max_splits) : Dp;
@@ -974,7 +974,10 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     if ((long)S * per > h->L.partElems) S = (int)(h->L.partElems / per);
     if (S < 1) S = 1;
     EpiPartial epi;
-    epi.part = (S == 1) ? dF32 : at<float>(h, h->L.part32);
+    epi.part = at<float>(h, h->L.part32);
+    if (S == 1 && c.P == 0) epi.part = dHs32;
+    if constexpr (sizeof(T) == 4)
+      if (S == 1 && c.P > 0) epi.part = dP_c;
     epi.ld = Dp;
     epi.split_stride = per;
     {
@@ -985,19 +988,16 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
         HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(st, ZT, ldz, Wo_c, Dp, Mp, Dp, Vp, S, epi)));
       }
     }
-    if (S > 1) {
+    if (S > 1 || (c.P > 0 && sizeof(T) == 2)) {
       StageTimer tm(h, RNNLM_STAGE_REDUCE, st);
-      int rc = reduce_splits(st, at<float>(h, h->L.part32), per, S, dF32);
+      int rc = c.P > 0 ? reduce_splits(st, epi.part, per, S, dP_c) : reduce_splits(st, epi.part, per, S, dHs32);
       if (rc) return rc;
     }
   }
   if (c.P > 0) {
     // through the layer above the state: dHs[m][j] = sum_p dp[m][p] C[p][j]
     StageTimer tm(h, RNNLM_STAGE_PROJ, st);
-    const long n = (long)Mp * h->Pp;
-    T *dP_c = at<T>(h, h->L.dP_c);
-    hipLaunchKernelGGL(to_compute_kernel<T>, dim3(blocks_for(n, 256)), dim3(256), 0, st, at<float>(h, h->L.dP32), n, dP_c);
-    HIP_TRY(hipGetLastError());
+    const T *dP_c = at<T>(h, h->L.dP_c);
     EpiPartial epi;
     epi.part = dHs32;
     epi.ld = Hp;
