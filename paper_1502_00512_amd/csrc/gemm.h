@@ -739,14 +739,15 @@ struct EpiSgd : EpiZeroInit {
     // What bounds this epilogue is memory latency (a compute unit moves 640 KB per tile; its matrix cores idle meanwhile), so
     // the master values of TWO 32-row blocks are in flight at any time: block i + 2 is requested as soon as block i has been
     // stored.  All accesses go through buffer resources based at the wave tile's origin: one lane-dependent offset register
-    // per column block serves every access and the row part is a scalar, which leaves the registers for the 2 x TN x 16 values
-    // in flight (with pointer arithmetic the addresses alone would not fit).  W and out are the same array when training in
-    // place: buffer accesses are kept in program order.  The copy in the compute type leaves as packed pairs: neighbouring
-    // lanes swap one value so that each lane owns two adjacent columns of one row.
+    // per column block serves every access, which leaves the registers for the 2 x TN x 16 values in flight (with pointer
+    // arithmetic the addresses alone would not fit).  W and out are the same array when training in place: buffer accesses
+    // are kept in program order.  The copy in the compute type leaves as packed pairs: neighbouring lanes swap one value so
+    // that each lane owns two adjacent columns of one row.
     // Ragged edges cost no branch: the resources end with row R - 1, and a lane past column C - 1 gets an offset past every
-    // end, so its reads are 0 and its writes are dropped.  (The last pair of an odd C includes a padding column of the copy,
-    // whose value is 0 like everything it is formed from.)  Tested entry by entry instead, with one 32 x 32 block in flight,
-    // the edge tiles held up the whole launch: V = 33278, H = 650, 960 positions, 118 us, now 96.
+    // end, so its reads are 0 and its writes are dropped.  The row part is therefore added to the lane's offset: as the
+    // instruction's scalar offset it would not take part in the bounds check.  (The last pair of an odd C includes a padding
+    // column of the copy, whose value is 0 like everything it is formed from.)  Tested entry by entry instead, with one 32 x
+    // 32 block in flight, the edge tiles held up the whole launch: V = 33278, H = 650, 960 positions, 118 us, now 96.
     if (row0 >= R || col0 >= C) return;
     // (the wave tile's origin is the same for all lanes: say so, or every access becomes a loop over lanes)
     const int urow = __builtin_amdgcn_readfirstlane(row0), ucol = __builtin_amdgcn_readfirstlane(col0);
@@ -769,7 +770,7 @@ struct EpiSgd : EpiZeroInit {
         __builtin_amdgcn_make_buffer_rsrc(uniform(Wc ? Wc + origin_c : reinterpret_cast<T *>(out + origin)), 0,
                                           Wc ? extent(ldc, origin_c, (int)sizeof(T)) : 0, 0x00020000);
     const bool odd = lane & 1;
-    constexpr int PAST = 0x7fffffff;
+    constexpr unsigned PAST = 0x7fffffffu;
     // This lane's byte offsets inside a 32-row block, formed anew for every block: kept, they would be the registers that
     // keep a wave of the embedding update from running next to two waves of the 256 x 256 form (226 instead of 224: the
     // embedding and the recurrent update waited for the whole launch, 1.5 % of a window at H = 1024).
@@ -780,39 +781,39 @@ struct EpiSgd : EpiZeroInit {
     };
     auto voff = [&](int j) {
       const int l = fresh(), c32 = l & 31;
-      return col0 + j * 32 + c32 < C ? (int)(((l >> 5) * 4 * ldw + c32) * 4) + j * 128 : PAST;
+      return col0 + j * 32 + c32 < C ? (unsigned)(((l >> 5) * 4 * ldw + c32) * 4) + j * 128u : PAST;
     };
     auto voffc = [&](int j) {
       const int l = fresh(), c32 = l & 31;
       if constexpr (sizeof(T) == 2)
-        return col0 + j * 32 + (c32 & ~1) < C ? (int)(((l >> 5) * 4 + (l & 1)) * ldc + (c32 & ~1)) * 2 + j * 64 : PAST;
+        return col0 + j * 32 + (c32 & ~1) < C ? (unsigned)(((l >> 5) * 4 + (l & 1)) * ldc + (c32 & ~1)) * 2u + j * 64u : PAST;
       else
-        return col0 + j * 32 + c32 < C ? (int)(((l >> 5) * 4 * ldc + c32) * 4) + j * 128 : PAST;
+        return col0 + j * 32 + c32 < C ? (unsigned)(((l >> 5) * 4 * ldc + c32) * 4) + j * 128u : PAST;
     };
-    const int ldw4 = (int)(ldw * 4), ldcb = (int)(ldc * (long)sizeof(T));
+    const unsigned ldw4 = (unsigned)ldw * 4u, ldcb = (unsigned)ldc * (unsigned)sizeof(T);
     auto request = [&](int i, float (&w)[TN][16]) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
-        const int vo = voff(j);
+        const unsigned vo = voff(j);
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           w[j][r] = __builtin_bit_cast(
-              float, __builtin_amdgcn_raw_buffer_load_b32(rw, vo, (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4, 0));
+              float, __builtin_amdgcn_raw_buffer_load_b32(rw, vo + (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4, 0, 0));
       }
     };
     auto apply = [&](int i, const float (&w)[TN][16]) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         float nv[16];
-        const int vo = voff(j);
+        const unsigned vo = voff(j);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           nv[r] = ((alpha != 0.0f) ? alpha * w[j][r] : 0.0f) - lr * acc[i][j][r];
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, nv[r]), ro, vo,
-                                                (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4, 0);
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, nv[r]), ro,
+                                                vo + (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4, 0, 0);
         }
         if (Wc) {
-          const int vc = voffc(j);
+          const unsigned vc = voffc(j);
           if constexpr (sizeof(T) == 2) {
             typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 #pragma unroll
@@ -827,14 +828,13 @@ struct EpiSgd : EpiZeroInit {
               const unsigned theirs = (unsigned)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xF, 0xF, true);  // lane ^ 1
               const unsigned word = join_pair(mine, theirs, odd);
               const int r0 = 2 * q;
-              __builtin_amdgcn_raw_buffer_store_b32(word, rc, vc,
-                                                    (i * 32 + 8 * (r0 >> 2) + (r0 & 3)) * ldcb, 0);
+              __builtin_amdgcn_raw_buffer_store_b32(word, rc, vc + (i * 32 + 8 * (r0 >> 2) + (r0 & 3)) * ldcb, 0, 0);
             }
           } else {
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, nv[r]), rc, vc,
-                                                    (i * 32 + 8 * (r >> 2) + (r & 3)) * ldcb, 0);
+              __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, nv[r]), rc,
+                                                    vc + (i * 32 + 8 * (r >> 2) + (r & 3)) * ldcb, 0, 0);
           }
         }
       }
