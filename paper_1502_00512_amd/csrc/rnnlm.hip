@@ -139,9 +139,12 @@ struct F32Plan {
   int tile, parts, splits;
   double us;
 };
-F32Plan f32_plan(long Mg, long Ng, long K, int max_splits) {
+// ld > 0: the contraction over the vocabulary, whose K-major logits have rows of ld values.  A handle of millions of positions
+// takes the forms whose blocks of 16 KS rows the loads' 32-bit offsets still reach (64 x 64 in steps of 16 always).
+F32Plan f32_plan(long Mg, long Ng, long K, int max_splits, long ld = 0) {
   const long kb = (K + 31) / 32;
   const bool split = kb > 2;  // shorter sums round less on the fp32 cores
+  const bool reach32 = split_reaches(KROW, ld, 0, 32), reach64 = split_reaches(KROW, ld, 0, 64);
   F32Plan best = {64, 0, 1, 1e30};
   for (int S = 1; S <= max_splits && S <= kb; ++S) {
     const long per = (kb + S - 1) / S;
@@ -154,26 +157,27 @@ F32Plan f32_plan(long Mg, long Ng, long K, int max_splits) {
       return 2.0 + w / 256 * (fixed + unit * per) + (rest ? fixed + (half + (unit - half) * rest / 256) * per : 0.0);
     };
     if (split && max_splits == 1 && Mg % 256 == 0 && Ng % 256 == 0) consider(256, 1, whole(256, 256, 10.5, 4.45, 3.2));
-    if (split && max_splits > 1 && Mg % 256 == 0 && Ng % 128 == 0) consider(256, 2, whole(256, 128, 7.0, 2.4, 1.75));
-    if (split && Mg % 128 == 0 && Ng % 128 == 0) consider(128, 2, whole(128, 128, 4.6, 1.3, 1.05));
+    if (split && reach32 && max_splits > 1 && Mg % 256 == 0 && Ng % 128 == 0)
+      consider(256, 2, whole(256, 128, 7.0, 2.4, 1.75));
+    if (split && reach32 && Mg % 128 == 0 && Ng % 128 == 0) consider(128, 2, whole(128, 128, 4.6, 1.3, 1.05));
     const long w = (Mg / 64) * (Ng / 64) * S, share = std::min<long>((w + 255) / 256, 4);
     const double more = std::max(1.0, w / 1024.0);
     consider(64, 0, 2.1 + 0.85 * share + (more - 1) * 2.0 + (0.15 + 0.49 * share) * per * more);
     if (!split) continue;
     consider(64, 1, 2.6 + 0.65 * share + (more - 1) * 2.2 + (0.33 + 0.36 * share) * per * more);
-    if (w <= 256) consider(64, 2, 3.8 + 0.51 * per);
-    if (w <= 256) consider(64, 4, 5.7 + 0.47 * (per + per % 2));
+    if (w <= 256 && reach32) consider(64, 2, 3.8 + 0.51 * per);
+    if (w <= 256 && reach64) consider(64, 4, 5.7 + 0.47 * (per + per % 2));
   }
   return best;
 }
 // fp32: an extent of `valid` rows or columns, padded to 64, 128 or 256 by what the product with the other extent takes
 // (the buffers are padded to 256; bf16 contractions take all of it).
-long f32_extent(long valid, long other, long K, int max_splits) {
+long f32_extent(long valid, long other, long K, int max_splits, long ld = 0) {
   long best = round_up(valid, 256);
-  double us = f32_plan(other, best, K, max_splits).us;
+  double us = f32_plan(other, best, K, max_splits, ld).us;
   for (long pad = 128; pad >= 64; pad /= 2) {
     const long n = round_up(valid, pad);
-    const double t = f32_plan(other, n, K, max_splits).us;
+    const double t = f32_plan(other, n, K, max_splits, ld).us;
     if (t <= us) {
       us = t;
       best = n;
@@ -339,8 +343,8 @@ long window_rows(const rnnlm_config &c, long Mrows) {
   return f32_extent(Mrows, round_up(c.V, PAD_V), c.P > 0 ? c.P : c.H, 1);
 }
 // Columns the contraction over the vocabulary forms: the compressed architecture reads the padding, too.
-long features_formed(const rnnlm_config &c, long Mp, int max_splits) {
-  return c.P > 0 ? round_up(c.P, PAD_H) : f32_extent(c.H, Mp, c.V, max_splits);
+long features_formed(const rnnlm_config &c, long Mp, int max_splits, long ldz) {
+  return c.P > 0 ? round_up(c.P, PAD_H) : f32_extent(c.H, Mp, c.V, max_splits, ldz);
 }
 
 void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, int &KpMax, WsLayout &L) {
@@ -357,7 +361,8 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   if (es == 4) {
     L.partElems = (long)MpMax * Dp;
     for (long M = 64; M <= MpMax; M += M < F32_TRIM_ROWS ? 64 : PAD_M)
-      L.partElems = std::max(L.partElems, (long)f32_plan(M, features_formed(c, M, MAX_SPLITS), c.V, MAX_SPLITS).splits * M * Dp);
+      L.partElems = std::max(
+          L.partElems, f32_plan(M, features_formed(c, M, MAX_SPLITS, MpMax), c.V, MAX_SPLITS, MpMax).splits * M * Dp);
   } else {
     L.partElems = 0;
     for (long M = BIG; M <= MpMax; M += BIG)
@@ -968,8 +973,8 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     T *dP_c = c.P > 0 ? at<T>(h, h->L.dP_c) : nullptr;  // (an operand of the contraction below)
     const long per = (long)Mp * Dp;
     const int max_splits = (int)std::min<long>(MAX_SPLITS, std::max<long>(1, h->L.partElems / per));
-    const long Dn = sizeof(T) == 4 ? features_formed(c, Mp, max_splits) : Dp;
-    const F32Plan plan = sizeof(T) == 4 ? f32_plan(Mp, Dn, c.V, max_splits) : F32Plan{};
+    const long Dn = sizeof(T) == 4 ? features_formed(c, Mp, max_splits, ldz) : Dp;
+    const F32Plan plan = sizeof(T) == 4 ? f32_plan(Mp, Dn, c.V, max_splits, ldz) : F32Plan{};
     int S = sizeof(T) == 4 ? plan.splits : desired_splits(Mp, Dp, Vp / BK);
     if ((long)S * per > h->L.partElems) S = (int)(h->L.partElems / per);
     if (S < 1) S = 1;

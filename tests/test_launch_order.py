@@ -20,7 +20,7 @@ C.CDLL(sys.argv[1], C.RTLD_GLOBAL)
 lib = C.CDLL(sys.argv[2])
 lib.rnnlm_workspace_bytes.restype = C.c_size_t
 call, args = sys.argv[3], eval(sys.argv[4])
-cfg = (C.c_int32 * 9)(*[args[k] for k in ("V", "H", "B", "T_max", "precision")], 0, args.get("K", 0), args.get("rmsprop", 0), 0)
+cfg = (C.c_int32 * 9)(*[args[k] for k in ("V", "H", "B", "T_max", "precision")], 0, args.get("K", 0), args.get("rmsprop", 0), args.get("P", 0))
 at = [1 << 44]
 def dev():
     at[0] += 1 << 40
@@ -28,6 +28,8 @@ def dev():
 class Buffers(C.Structure):
     _fields_ = [(n, C.c_void_p) for n in ("E", "U", "Wo", "b", "h", "ws")] + [("bytes", C.c_size_t), ("A", C.c_void_p), ("C", C.c_void_p)]
 buf = Buffers(dev(), dev(), dev(), dev(), dev(), dev(), lib.rnnlm_workspace_bytes(cfg), None, None)
+if args.get("P"):
+    buf.Wo, buf.A, buf.C = None, dev(), dev()
 h = C.c_void_p()
 assert lib.rnnlm_init(cfg, C.byref(buf), C.byref(h)) == 0
 f, p, x, y, st, T = C.c_float, C.c_void_p, C.c_void_p(dev()), C.c_void_p(dev()), C.c_void_p(int(sys.argv[5])), args["T"]
@@ -124,4 +126,24 @@ def test_rmsprop_steps_leave_the_callers_stream_in_long_windows_only(runtime, tm
 def test_sizes_beyond_32_bit_offsets_are_taken(runtime, tmp_path, V, H, B, T_max, T, precision):
     """Operands whose bytes a contraction kernel's 32-bit offsets do not reach take another kernel."""
     launches, _ = enqueue(runtime, tmp_path, "train", V=V, H=H, B=B, T_max=T_max, T=T, precision=precision)
+    assert sum("gemm" in k for _, k, _ in launches) >= 6
+
+
+@pytest.mark.parametrize("V,H,P,B,T_max,T", [
+    (200, 8, 0, 1, 1 << 24, 1),      # 32 rows of the logits span 2^31 bytes
+    (200, 8, 0, 1, 1 << 24, 3),
+    (256, 64, 0, 32, 1 << 19, 4),
+    (200, 64, 0, 1, 1 << 24, 500),
+    (300, 64, 0, 1, 1 << 24, 2560),
+    (700, 300, 0, 1, 1 << 24, 128),
+    (1604, 400, 0, 3, (1 << 24) // 3, 100000),
+    (2000, 256, 0, 1, 1 << 23, 3000),  # 64 rows
+    (2000, 256, 0, 1, (1 << 23) - 256, 3000),
+    (2000, 256, 100, 1, 1 << 23, 3000),
+    (200, 64, 64, 1, 1 << 24, 3),
+    (700, 300, 300, 1, 1 << 24, 2560),
+])
+def test_the_contraction_over_the_vocabulary_reaches_long_rows_of_logits(runtime, tmp_path, V, H, P, B, T_max, T):
+    """fp32 handles of millions of positions: blocks of 32 or 64 rows of the logits are beyond 32-bit offsets."""
+    launches, _ = enqueue(runtime, tmp_path, "train", V=V, H=H, P=P, B=B, T_max=T_max, T=T, precision=FP32)
     assert sum("gemm" in k for _, k, _ in launches) >= 6
