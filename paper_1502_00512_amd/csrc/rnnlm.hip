@@ -124,11 +124,12 @@ constexpr int BIG = 256;
 
 // fp32 contractions (gemm_split.h): 256x256 output tiles on eight waves, 128x128 on eight that share out the contraction in
 // pairs, 64x64 on four or, where there are few tiles, on eight or sixteen that share it out.  The contraction over the
-// vocabulary (the only one that may be split) takes 256x128 tiles instead of 256x256, which leave registers for the lesser
-// products' own accumulators: 7 % slower, but the errors of a long sum in one accumulator are alike at all positions, and
-// the recurrent gradient, which adds up the positions, was 1.2 times as far from 64 bits as through the fp32 matrix cores
-// (now 0.3).  Contractions of up to 64 terms take 64x64 tiles on the fp32 cores (parts = 0, gemm_dma4.h), which round less
-// there (split, 4..30 terms: 1.3 times as far from 64 bits).
+// vocabulary (ld > 0: row length of its K-major logits) takes 256x128 tiles instead of 256x256, which leave registers for the
+// lesser products' own accumulators: 7 % slower, but with all products in one accumulator its gradients are further from 64
+// bits than through the fp32 matrix cores (input rows, V = 3209, H = 852, 512x32: 1.56 times as far, now 0.74; V = 1200, H =
+// 2000, 256x32: 1.83 and 0.75).
+// Contractions of up to 64 terms take 64x64 tiles on the fp32 cores (parts = 0, gemm_dma4.h), which round less there (split,
+// 4..30 terms: 1.3 times as far from 64 bits); longer ones take them where the estimate is lowest.
 // The tile and the number of splits of the contraction dimension minimise an estimate of the time, fitted to runs of
 // 16..2560 tiles and depths of 32..4096 (both operands K-contiguous, both K-major; us, kb = 32-deep blocks): every full
 // round of 256 tiles 10.5 + 4.45 kb (256x256) and 4.6 + 1.3 kb (128x128: one workgroup per compute unit; a partly filled
@@ -139,8 +140,8 @@ struct F32Plan {
   int tile, parts, splits;
   double us;
 };
-// ld > 0: the contraction over the vocabulary, whose K-major logits have rows of ld values.  A handle of millions of positions
-// takes the forms whose blocks of 16 KS rows the loads' 32-bit offsets still reach (64 x 64 in steps of 16 always).
+// A handle of millions of positions takes the forms whose blocks of 16 KS rows of ld values the loads' 32-bit offsets still
+// reach (64 x 64 in steps of 16 always).
 F32Plan f32_plan(long Mg, long Ng, long K, int max_splits, long ld = 0) {
   const long kb = (K + 31) / 32;
   const bool split = kb > 2;  // shorter sums round less on the fp32 cores
@@ -156,9 +157,8 @@ F32Plan f32_plan(long Mg, long Ng, long K, int max_splits, long ld = 0) {
       const long w = (Mg / rows) * (Ng / cols) * S, rest = w % 256;
       return 2.0 + w / 256 * (fixed + unit * per) + (rest ? fixed + (half + (unit - half) * rest / 256) * per : 0.0);
     };
-    if (split && max_splits == 1 && Mg % 256 == 0 && Ng % 256 == 0) consider(256, 1, whole(256, 256, 10.5, 4.45, 3.2));
-    if (split && reach32 && max_splits > 1 && Mg % 256 == 0 && Ng % 128 == 0)
-      consider(256, 2, whole(256, 128, 7.0, 2.4, 1.75));
+    if (split && ld == 0 && Mg % 256 == 0 && Ng % 256 == 0) consider(256, 1, whole(256, 256, 10.5, 4.45, 3.2));
+    if (split && ld > 0 && reach32 && Mg % 256 == 0 && Ng % 128 == 0) consider(256, 2, whole(256, 128, 7.0, 2.4, 1.75));
     if (split && reach32 && Mg % 128 == 0 && Ng % 128 == 0) consider(128, 2, whole(128, 128, 4.6, 1.3, 1.05));
     const long w = (Mg / 64) * (Ng / 64) * S, share = std::min<long>((w + 255) / 256, 4);
     const double more = std::max(1.0, w / 1024.0);
@@ -195,7 +195,7 @@ long terms(long n) {
 template <int LA, int LB, class Epi>
 hipError_t f32_gemm(hipStream_t st, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
                     const F32Plan &plan, const Epi &epi, int band = 4) {
-  if constexpr (LA == KROW && LB == KROW)
+  if constexpr (LA == KROW && LB == KROW && std::is_same_v<Epi, EpiPartial>)
     if (plan.tile == 256 && plan.parts == 2)
       return launch_gemm_split<256, 128, 4, 2, 1, LA, LB, 2, 1>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
   if (plan.tile == 256)

@@ -2,6 +2,7 @@
 event records and event waits (launch_log.cpp), and the happens-before relation between launches is rebuilt from the log.
 Nothing is computed; device addresses are made up and never followed."""
 import os
+import re
 import subprocess
 import sys
 
@@ -147,3 +148,15 @@ def test_the_contraction_over_the_vocabulary_reaches_long_rows_of_logits(runtime
     """fp32 handles of millions of positions: blocks of 32 or 64 rows of the logits are beyond 32-bit offsets."""
     launches, _ = enqueue(runtime, tmp_path, "train", V=V, H=H, P=P, B=B, T_max=T_max, T=T, precision=FP32)
     assert sum("gemm" in k for _, k, _ in launches) >= 6
+
+
+@pytest.mark.parametrize("V,H,P,B,T_max,T", [
+    (1604, 3659, 0, 234, 29, 29), (2920, 3338, 0, 151, 28, 28), (3209, 852, 0, 512, 44, 32), (38708, 1702, 0, 1024, 256, 256),
+    (1200, 2000, 0, 256, 32, 32), (6000, 1702, 512, 512, 64, 64), (64000, 1024, 0, 128, 10, 10), (100000, 512, 0, 2048, 32, 32),
+])
+def test_long_sums_over_the_vocabulary_keep_their_lesser_products_apart(runtime, tmp_path, V, H, P, B, T_max, T):
+    """The 256 x 256 form adds all six products of an fp32 contraction to one accumulator."""
+    launches, _ = enqueue(runtime, tmp_path, "train", V=V, H=H, P=P, B=B, T_max=T_max, T=T, precision=FP32)
+    # (template arguments: tile, waves, then both operands' layouts, 1 = K-major)
+    over = [k for _, k, _ in launches if re.search(r"gemm_split_kernelI(?:Li\d+E){5}Li1ELi1E.*EpiPartial", k)]
+    assert len(over) == 2 and not any("ILi256ELi256E" in k for k in over), over
