@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import compressed as Cq
 from oracle import oracle as O
 from paper_1502_00512_amd import binding, synth
 
@@ -31,8 +32,9 @@ def test_embedding_update_by_run_length(H, B, T, lengths):
     y = tokens_of(lengths, M, V, 12 + H).reshape(T, B)
     o = O.Model.from_weights(E, U, Wo, b, B)
     d = lambda a: torch.as_tensor(np.ascontiguousarray(a)).cuda()
-    # windows of up to 1024 positions compare ids, the rmsprop call sorts them: the same sums, bit for bit (every
-    # denominator is exactly one there)
+    # windows of up to 1024 positions (the first three shapes) compare ids, the rmsprop call sorts them: the same sums, bit
+    # for bit (every denominator is exactly one there).  The longer ones are sorted in both calls; what compares ids up to
+    # 4096 positions is the compressed architecture below.
     g = binding.Rnnlm(E, U, Wo, b, B, T, binding.RNNLM_FP32)
     s = binding.Rnnlm(E, U, Wo, b, B, T, binding.RNNLM_FP32, rmsprop=True, r_init=1.0)
     g.rnnlm_train_chunk(d(x), d(y), lr)
@@ -63,3 +65,32 @@ def test_noise_contrastive_row_update_by_run_length(H, noise, targets):
     for got, ref, start in ((g.Wo, o.Wo, Wo), (g.b, o.b, b)):
         step, want = got.cpu().numpy().astype(np.float64) - start, ref - start
         assert np.abs(step - want).max() <= 1e-3 * np.abs(want).max() + 1.2e-7 * np.abs(start).max()
+
+
+# P: columns in one, two, three and nine blocks of 256, whole and ragged groups of four; the last window is sorted
+@pytest.mark.parametrize("precision", [binding.RNNLM_FP32, binding.RNNLM_BF16_FP32MASTER])
+@pytest.mark.parametrize("P", [64, 130, 260, 515, 2100])
+@pytest.mark.parametrize("B,T,lengths", [
+    (32, 33, [16, 17, 33, 519, 128]), (64, 64, [4096]), (64, 64, [15, 16, 17, 64, 65, 128, 129, 513, 1500]), (63, 65, [2100, 8, 9]),
+    (64, 65, [16, 17, 513, 64, 65, 1200]),
+])
+def test_tied_matrix_update_by_run_length(B, T, lengths, P, precision):
+    V, H, M, fp32 = 4600, 48, B * T, precision == binding.RNNLM_FP32
+    E, A, U, C_, b = synth.make_compressed_weights(V, H, P, "uniform", 0.2, 3 + P)
+    x = tokens_of(lengths, M, V, 11 + P).reshape(T, B)
+    y = np.full((T, B), V - 1, np.int32)  # (one target: the output-side share of a row is a sum of one sign)
+    g = binding.Rnnlm(E, U, None, b, B, T, precision, A=A, C_=C_)
+    o = Cq.CompressedModel(*(np.asarray(a, np.float64).copy() for a in (E, A, U, C_, b)), np.zeros((B, H)))
+    d = lambda a: torch.as_tensor(np.ascontiguousarray(a)).cuda()
+    ref = Cq.grad_chunk(o, x, y)["gE"]
+    got = g.rnnlm_grad_chunk_compressed(d(x), d(y))["gE"].cpu().numpy().astype(np.float64)
+    # row by row, fp32: a member too few among 4096 is 2.4e-4 of a row, measured 4.4e-6 at most; bf16: operands of the layers
+    # on the way are rounded to 2^-9, P = 2100 measured 3.1e-2 at most
+    off, size = np.linalg.norm(got - ref, axis=1), np.linalg.norm(ref, axis=1)
+    assert (off <= 2e-5 * size if fp32 else off <= 5e-2 * size).all(), (off / size).max()
+    g.rnnlm_train_chunk(d(x), d(y), 0.5)
+    g.rnnlm_check()
+    # the workspace begins with the compute copy of the tied matrix, rows padded to 256 columns
+    Pp, es, dt = -(-P // 256) * 256, 4 if fp32 else 2, torch.float32 if fp32 else torch.bfloat16
+    copy = g.workspace[:V * Pp * es].view(dt).view(V, Pp)
+    assert torch.equal(copy[:, :P], g.E.to(dt)) and not bool(copy[:, P:].any())
