@@ -46,7 +46,9 @@ extern "C" {
 typedef struct rnnlm rnnlm_t; /* opaque host-side handle */
 
 typedef enum {
-  RNNLM_FP32 = 0,            /* fp32 storage, fp32 MFMA contraction */
+  RNNLM_FP32 = 0,            /* fp32 storage, fp32 accumulation; contractions take fp32 operands whole, on the fp32 matrix
+                                cores or as sums of three bf16 parts on the bf16 ones (six of nine products: each product
+                                to about 2^-24 of itself) */
   RNNLM_BF16_FP32MASTER = 1  /* bf16 operands (round-to-nearest-even), fp32 accumulation, fp32 master weights */
 } rnnlm_precision;
 

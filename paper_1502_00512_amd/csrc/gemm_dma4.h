@@ -19,7 +19,8 @@
 // fp32 operands (K blocks of 16 in two steps of 8; ROWK fragments are one 16-byte read as above, KROW fragments four
 // 4-byte reads of 32 consecutive rows, the half-waves reading k and k + 4, whose rows start at the same bank: physical
 // chunk = logical ^ (8 * (k / 4 % 2)) moves one of them to the other 32 banks): 64 x 64 tiles, for the steps of a
-// recurrence outside the persistent kernel and contractions of up to 64 terms; everything else takes gemm_split.h.
+// recurrence outside the persistent kernel, contractions of up to 64 terms, and longer ones of small outputs where the plan
+// (f32_plan) estimates less time than for the forms of gemm_split.h.
 #pragma once
 #include "gemm_dma.h"
 

@@ -4,14 +4,19 @@
 // x = h + m + l with h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), rounded to nearest: both differences are exact and so
 // is l, and |m| <= 2^-8 |h|, |l| <= 2^-17 |h|.  x y = hh' + hm' + mh' + hl' + lh' + mm' + (terms below 2^-24 |x y|); the six
 // products accumulate in fp32, smallest first.  The bf16 rate is sixteen times the fp32 one, so six products take 3/8 of its
-// time.  Distance from 64 bits against the fp32 matrix cores (one window, 45 shapes of V = 1000..60000, H = 64..2000, 3..5751
-// positions): gradients 0.3-0.4 of it in the mean, log-probabilities 0.94; an instruction rounds the sum once per 16 terms
-// instead of once or twice per 2.
+// time.  An operand keeps its 24 bits, a product some 2^-24 of itself, and an instruction rounds the sum once per 16 terms
+// instead of once or twice per 2.  Distance from 64 bits against the fp32 matrix cores, shape by shape (24 windows of V =
+// 1000..64000, H = 64..3659, 6..32768 positions): gradients of U and of the rows of E 0.12 to 0.75, of Wo 0.01 to 0.63; log-
+// probabilities, whose own rounding is most of it, 0.2 to 1.05 (0.96 in the mean; above 1.05 in single windows of 100 and 320
+// positions only).  Subnormal operands keep fewer bits: rows of logit gradients of 8e-39 come out to 1e-4, of 4e-40 to 2e-2,
+// where the fp32 cores give 4e-6 and 1e-6.
 //
 // What bounds it: power, at the large tiles (matrix cores busy 78 % of the cycles, at 1.4 GHz after some milliseconds of it; a
 // conversion that costs one instruction instead of eleven: 3 % faster; another order of the products, no bank conflicts: no
 // change).  64,000 x 1280 outputs, depth 1024 / 1280 x 1024 outputs, depth 64,000 / 64,000 x 1024, depth 1280 with its update,
-// us in a training window: 1231 / 1285 / 1330 on the fp32 cores, now 766 / 790 / 841 (219, 212, 200 TFLOP/s).  Small outputs
+// us in a training window: 1231 / 1285 / 1330 on the fp32 cores, now 766 / 790 / 841 (219, 212, 200 TFLOP/s).  The forward
+// output layer's epilogue (EpiOutFwd) does not fit the registers next to the accumulators: 27 of them spill at 256 x 256 (112
+// bytes of scratch a lane), 4 at 128 x 128, all outside the loop over the blocks.  Small outputs
 // are bound by a workgroup's chain per block (barrier, fragments, products, conversion), which WGK shortens: 256 tiles of
 // 64 x 64, depth 1280: 33 us on the fp32 cores, 37 on four waves, 24 on sixteen.
 //

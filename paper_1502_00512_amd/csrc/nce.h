@@ -149,7 +149,10 @@ __global__ void __launch_bounds__(256) score_candidates_kernel(const T *__restri
 // scores are in registers: dS[row][j] = sigmoid(S + off[j]) * scale in the contraction operand type (0 for padding rows and
 // columns), and, per 32x32 block, the sums of softplus(S + off[j]) over its columns (jpart[column block][row]) and of dS
 // before rounding over its rows (gpart[row block][j]).  V = 64000, H = 1024, 2560 positions, 1024 noise words: the
-// contraction, a pass over its fp32 scores and one more for the column sums took 17 + 15 + 7 us.
+// contraction, a pass over its fp32 scores and one more for the column sums took 17 + 15 + 7 us.  Whole windows with those
+// passes and with this, every tile form (bf16 us): V = 64000, H = 1024, 16x4, 64 words 124 and 116; 128x20, 256 words 170 and
+// 162, 1024 words 193 and 182; 256x32, 2048 words 527 and 459; V = 10000, H = 300, 256x32, 2000 words 362 and 327; V = 20000,
+// H = 2048, 32x20, 500 words 228 and 231; fp32: 394 and 400 at 128x20, 1024 words, 1312 and 1277 at 256x32, 2048 words.
 template <typename T>
 struct EpiNce : EpiZeroInit {
   T *dS;

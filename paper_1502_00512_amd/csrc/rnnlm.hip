@@ -456,7 +456,9 @@ unsigned *p_counter(rnnlm_t *h) { return at<unsigned>(h, h->L.sync); }
 inline unsigned blocks_for(long n, int per) { return (unsigned)((n + per - 1) / per); }
 template <typename T>
 int reduce_splits(hipStream_t st, const float *part, long n, int splits, T *out) {
-  // (786432 entries in 21 parts, shared out: 25 us, 13 expected of whole workgroups)
+  // One after the other and shared out, us: 262144 values, 16 parts 3.4 and 2.8, 24 parts 4.2 and 3.1, 32 parts 5.7 and 3.6, 64
+  // parts 18 and 12; 16384 values, 64 parts 8.1 and 2.8; but 524288 values, 24 parts 8.9 and 13, 64 parts 20 and 32; 2097152
+  // values, 24 parts 30 and 31.  Up to 16 parts the two are within half a microsecond.
   if (splits > 16 && n <= 1 << 18)
     hipLaunchKernelGGL(splitk_reduce_many_kernel<T>, dim3(blocks_for(n / 4, 64)), dim3(256), 0, st, part, n, splits, out);
   else

@@ -50,7 +50,7 @@ def test_fp32_window_of_a_handle_of_millions_of_positions():
 
 
 @pytest.mark.parametrize("V,H,B,T", [
-    (1500, 64, 13, 5),      # output layer of 64 terms: the fp32 matrix cores; 65 positions: a weight update just beyond them
+    (1500, 64, 13, 5),      # output layer of 64 terms and weight update of 65: the fp32 matrix cores (the second by estimate)
     (1500, 65, 8, 8),       # and the other way round
     (600, 200, 64, 30),     # few 64-wide tiles, long sums: the recurrent update on sixteen waves
     (900, 900, 5, 40),      # 64-wide tiles on eight waves, extents padded to 64
@@ -90,8 +90,8 @@ def test_fp32_contractions_of_infinite_and_huge_operands(V, H, B, T):
 @pytest.mark.parametrize("precision", [FP32, BF16])
 @pytest.mark.parametrize("V,H", [(257, 33), (300, 255), (511, 257), (1000, 650), (256, 65), (769, 512)])
 def test_update_epilogue_at_ragged_edges(V, H, precision):
-    """Every master entry is updated (against the oracle), and the compute copies, their padding included, are what a
-    rebuild from the masters gives: the next window's results do not change."""
+    """Every master entry is updated (against the oracle), and the compute copies are what a rebuild from the masters gives:
+    the next window's results do not change.  (Their padding, which meets zeros only, is looked at in test_gpu_bounds.py.)"""
     B, T = 5, 31
     g, o = make_pair(V, H, B, T, precision, seed=V + H, scale=0.1, bias_scale=0.5)
     tok = tokens(V, 2 * B * T + B + 1, 6)
