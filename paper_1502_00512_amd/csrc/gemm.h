@@ -8,6 +8,8 @@
 // fp32 accumulation.  One workgroup owns a BM x BN tile; its WGM x WGN waves own sub-tiles made of
 // 32x32 MFMA blocks.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 namespace rnnlm_dev {
@@ -743,11 +745,14 @@ struct EpiSgd : EpiZeroInit {
     // arithmetic the addresses alone would not fit).  W and out are the same array when training in place: buffer accesses
     // are kept in program order.  The copy in the compute type leaves as packed pairs: neighbouring lanes swap one value so
     // that each lane owns two adjacent columns of one row.
-    // Ragged edges cost no branch: the resources end with row R - 1, and a lane past column C - 1 gets an offset past every
-    // end, so its reads are 0 and its writes are dropped.  The row part is therefore added to the lane's offset: as the
-    // instruction's scalar offset it would not take part in the bounds check.  (The last pair of an odd C includes a padding
-    // column of the copy, whose value is 0 like everything it is formed from.)  Tested entry by entry instead, with one 32 x
-    // 32 block in flight, the edge tiles held up the whole launch: V = 33278, H = 650, 960 positions, 118 us, now 96.
+    // Ragged edges cost no test of an entry: the resources end with row R - 1, and a lane past column C - 1 gets an offset past
+    // every end, so its reads are 0 and its writes are dropped.  The row part is added to the lane's offset: as the
+    // instruction's scalar offset it would not take part in the bounds check.  Large wave tiles that end before row R pass it
+    // so all the same, which needs no check there (V = 64000, H = 1024, 128x20: window 1208 us with the additions everywhere,
+    // 1198 so; on small tiles the second form of the code costs more than the additions, V = 10000, H = 256, fp32, 32x10:
+    // 148.8 us without it, 149.6 with it).  (The last pair of an odd C includes a padding column of the copy, whose value is 0
+    // like everything it is formed from.)  Tested entry by entry instead, with one 32 x 32 block in flight, the edge tiles
+    // held up the whole launch: V = 33278, H = 650, 960 positions, 118 us, now 96.
     if (row0 >= R || col0 >= C) return;
     // (the wave tile's origin is the same for all lanes: say so, or every access becomes a loop over lanes)
     const int urow = __builtin_amdgcn_readfirstlane(row0), ucol = __builtin_amdgcn_readfirstlane(col0);
@@ -791,17 +796,27 @@ struct EpiSgd : EpiZeroInit {
         return col0 + j * 32 + c32 < C ? (unsigned)(((l >> 5) * 4 * ldc + c32) * 4) + j * 128u : PAST;
     };
     const unsigned ldw4 = (unsigned)ldw * 4u, ldcb = (unsigned)ldc * (unsigned)sizeof(T);
-    auto request = [&](int i, float (&w)[TN][16]) {
+    // CHECKED: the row part of an address takes part in the bounds check
+    auto load = [&](auto checked, unsigned vo, unsigned row) {
+      return decltype(checked)::value ? __builtin_amdgcn_raw_buffer_load_b32(rw, vo + row, 0, 0)
+                                      : __builtin_amdgcn_raw_buffer_load_b32(rw, vo, row, 0);
+    };
+    auto store = [&](auto checked, unsigned v, __amdgpu_buffer_rsrc_t rs, unsigned vo, unsigned row) {
+      if constexpr (decltype(checked)::value)
+        __builtin_amdgcn_raw_buffer_store_b32(v, rs, vo + row, 0, 0);
+      else
+        __builtin_amdgcn_raw_buffer_store_b32(v, rs, vo, row, 0);
+    };
+    auto request = [&](auto checked, int i, float (&w)[TN][16]) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const unsigned vo = voff(j);
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          w[j][r] = __builtin_bit_cast(
-              float, __builtin_amdgcn_raw_buffer_load_b32(rw, vo + (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4, 0, 0));
+          w[j][r] = __builtin_bit_cast(float, load(checked, vo, (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4));
       }
     };
-    auto apply = [&](int i, const float (&w)[TN][16]) {
+    auto apply = [&](auto checked, int i, const float (&w)[TN][16]) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         float nv[16];
@@ -809,8 +824,7 @@ struct EpiSgd : EpiZeroInit {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           nv[r] = ((alpha != 0.0f) ? alpha * w[j][r] : 0.0f) - lr * acc[i][j][r];
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, nv[r]), ro,
-                                                vo + (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4, 0, 0);
+          store(checked, __builtin_bit_cast(unsigned, nv[r]), ro, vo, (i * 32 + 8 * (r >> 2) + (r & 3)) * ldw4);
         }
         if (Wc) {
           const unsigned vc = voffc(j);
@@ -828,45 +842,50 @@ struct EpiSgd : EpiZeroInit {
               const unsigned theirs = (unsigned)__builtin_amdgcn_mov_dpp((int)mine, 0xB1, 0xF, 0xF, true);  // lane ^ 1
               const unsigned word = join_pair(mine, theirs, odd);
               const int r0 = 2 * q;
-              __builtin_amdgcn_raw_buffer_store_b32(word, rc, vc + (i * 32 + 8 * (r0 >> 2) + (r0 & 3)) * ldcb, 0, 0);
+              store(checked, word, rc, vc, (i * 32 + 8 * (r0 >> 2) + (r0 & 3)) * ldcb);
             }
           } else {
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, nv[r]), rc,
-                                                    vc + (i * 32 + 8 * (r >> 2) + (r & 3)) * ldcb, 0, 0);
+              store(checked, __builtin_bit_cast(unsigned, nv[r]), rc, vc, (i * 32 + 8 * (r >> 2) + (r & 3)) * ldcb);
           }
         }
       }
     };
-    if (alpha != 0.0f) {
-      static_assert(TM == 1 || TM % 2 == 0, "two row blocks in flight");
-      // (scheduling barriers: left alone, the compiler starts applying the first values after a third of the
-      // requests and issues the rest only when those have arrived, one memory round trip later)
-      float wa[TN][16], wb[TN][16];
-      request(0, wa);
-      if constexpr (TM > 1) request(1, wb);
-      __builtin_amdgcn_sched_barrier(0);
+    auto update = [&](auto checked) {
+      if (alpha != 0.0f) {
+        static_assert(TM == 1 || TM % 2 == 0, "two row blocks in flight");
+        // (scheduling barriers: left alone, the compiler starts applying the first values after a third of the
+        // requests and issues the rest only when those have arrived, one memory round trip later)
+        float wa[TN][16], wb[TN][16];
+        request(checked, 0, wa);
+        if constexpr (TM > 1) request(checked, 1, wb);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < TM; i += 2) {
-        apply(i, wa);
-        __builtin_amdgcn_sched_barrier(0);
-        if (i + 2 < TM) request(i + 2, wa);
-        __builtin_amdgcn_sched_barrier(0);
-        if (i + 1 < TM) apply(i + 1, wb);
-        __builtin_amdgcn_sched_barrier(0);
-        if (i + 3 < TM) request(i + 3, wb);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < TM; i += 2) {
+          apply(checked, i, wa);
+          __builtin_amdgcn_sched_barrier(0);
+          if (i + 2 < TM) request(checked, i + 2, wa);
+          __builtin_amdgcn_sched_barrier(0);
+          if (i + 1 < TM) apply(checked, i + 1, wb);
+          __builtin_amdgcn_sched_barrier(0);
+          if (i + 3 < TM) request(checked, i + 3, wb);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+        float wz[TN][16];
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) wz[j][r] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) apply(checked, i, wz);
       }
-    } else {
-      float wz[TN][16];
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) wz[j][r] = 0.0f;
-#pragma unroll
-      for (int i = 0; i < TM; ++i) apply(i, wz);
+    };
+    if constexpr (TM >= 4) {
+      if (urow + 32 * TM <= R) return update(std::false_type{});
     }
+    update(std::true_type{});
 #endif
   }
 };
