@@ -1126,6 +1126,13 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   const bool early_side = c.P == 0;
   const bool early_rec = early_side && (nce || (long)(Hp / BIG) * (Hp / BIG) < 256);
   if (rec_stream) *rec_stream = early_rec ? es : st;
+  // An event between the fork and the output update's launch (its stage is timed) lets the embedding update start first,
+  // whose workgroups do not fit next to the large update's and keep it from some compute units until they are through.  At
+  // the widest layers those compute units then lack in 49 rounds of tiles (V = 100000, H = 4096, 256x32: update 5.72 ms instead
+  // of 5.28, window 17.6 instead of 17.2), so the stage opens before the fork there.  With few rounds the timed window is
+  // shorter with the embedding update in front (128x20, V = 64000, H = 1024 and V = 100000, H = 2048: 1.2 % each).
+  const bool opened = early_side && !early_rec && !serial;
+  if (opened) StageTimer(h, RNNLM_STAGE_OUT_BWD_W, st, true, false);
   if (early_side) {
     int rc = serial ? RNNLM_OK : side_fork(h, 0, st);
     if (rc) return rc;
@@ -1160,7 +1167,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     // E[v][p] -= lr * sum_m dz[v][m] p[m][p].  bf16 compressed: contracted transposed (tile rows = p, tile columns = v).
     // Everything else in the matrix's own orientation (tile rows = v, tile columns = j), whose update epilogue touches two
     // 128-byte lines per wave instruction instead of 32 (fp32, V = 64000, H = 1024, 1280 positions: 893 -> 841 us).
-    StageTimer tm(h, RNNLM_STAGE_OUT_BWD_W, st);
+    StageTimer tm(h, RNNLM_STAGE_OUT_BWD_W, st, !opened);
     auto aim = [&](auto &epi) {
       epi.W = c.P > 0 ? h->buf.E : h->buf.Wo;
       epi.out = c.P > 0 ? u.E : u.Wo;

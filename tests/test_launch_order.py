@@ -36,6 +36,7 @@ assert lib.rnnlm_init(cfg, C.byref(buf), C.byref(h)) == 0
 f, p, x, y, st, T = C.c_float, C.c_void_p, C.c_void_p(dev()), C.c_void_p(dev()), C.c_void_p(int(sys.argv[5])), args["T"]
 rms = (C.c_void_p * 4)(dev(), dev(), dev(), dev())
 noise, lnq = C.c_void_p(dev()), C.c_void_p(dev())
+lib.rnnlm_profile_enable(h, args.get("profile", 0))
 for _ in range(2):
     if call == "train":
         rc = lib.rnnlm_train_chunk(h, x, y, T, f(0.1), None, None, st)
@@ -160,3 +161,17 @@ def test_long_sums_over_the_vocabulary_keep_their_lesser_products_apart(runtime,
     # (template arguments: tile, waves, then both operands' layouts, 1 = K-major)
     over = [k for _, k, _ in launches if re.search(r"gemm_split_kernelI(?:Li\d+E){5}Li1ELi1E.*EpiPartial", k)]
     assert len(over) == 2 and not any("ILi256ELi256E" in k for k in over), over
+
+
+@pytest.mark.parametrize("V,H,B,T,precision", [(3000, 4096, 256, 8, BF16), (3000, 3841, 64, 20, BF16), (3000, 4000, 64, 3, FP32)])
+def test_timing_the_widest_output_update_delays_it_behind_nothing(runtime, tmp_path, V, H, B, T, precision):
+    """No event lies between the fork of the embedding update and the launch of the large one, which is to come first."""
+    enqueue(runtime, tmp_path, "train", V=V, H=H, B=B, T_max=T, T=T, precision=precision, profile=1 << 7)
+    lines = [l.split() for l in open(tmp_path / "log")]
+    own = [l for l in lines if l[1] == hex(STREAM)]
+    forks = {l[2] for l in lines if l[0] == "W" and l[1] != hex(STREAM)}
+    updates = [i for i, l in enumerate(own) if l[0] == "L" and "gemm" in l[2] and "EpiSgdI" in l[2]]
+    assert len(updates) == 2
+    for i in updates:
+        assert own[i - 1][0] == "R" and own[i - 1][2] in forks  # the fork
+        assert own[i - 2][0] == "R" and own[i + 1][0] == "R"    # the stage's pair around both
