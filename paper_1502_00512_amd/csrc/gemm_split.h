@@ -5,11 +5,10 @@
 // is l, and |m| <= 2^-8 |h|, |l| <= 2^-17 |h|.  x y = hh' + hm' + mh' + hl' + lh' + mm' + (terms below 2^-24 |x y|); the six
 // products accumulate in fp32, smallest first.  The bf16 rate is sixteen times the fp32 one, so six products take 3/8 of its
 // time.  An operand keeps its 24 bits, a product some 2^-24 of itself, and an instruction rounds the sum once per 16 terms
-// instead of once or twice per 2.  Distance from 64 bits against the fp32 matrix cores, shape by shape (24 windows of V =
+// instead of once or twice per 2.  Distance from 64 bits against the fp32 matrix cores, shape by shape (thirty windows of V =
 // 1000..64000, H = 64..3659, 6..32768 positions): gradients of U and of the rows of E 0.12 to 0.75, of Wo 0.01 to 0.63; log-
-// probabilities, whose own rounding is most of it, 0.2 to 1.05 (0.96 in the mean; above 1.05 in single windows of 100 and 320
-// positions only).  Subnormal operands keep fewer bits: rows of logit gradients of 8e-39 come out to 1e-4, of 4e-40 to 2e-2,
-// where the fp32 cores give 4e-6 and 1e-6.
+// probabilities, whose own rounding is most of it, 0.2 to 1.13, below 0.96 in the mean.  Subnormal operands keep fewer bits:
+// rows of logit gradients of 8e-39 come out to 1e-4, of 4e-40 to 2e-2, where the fp32 cores give 4e-6 and 1e-6.
 //
 // What bounds it: power, at the large tiles (matrix cores busy 78 % of the cycles, at 1.4 GHz after some milliseconds of it; a
 // conversion that costs one instruction instead of eleven: 3 % faster; another order of the products, no bank conflicts: no

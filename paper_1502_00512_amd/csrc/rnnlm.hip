@@ -1128,7 +1128,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   if (rec_stream) *rec_stream = early_rec ? es : st;
   // An event between the fork and the output update's launch (its stage is timed) lets the embedding update start first,
   // whose workgroups do not fit next to the large update's and keep it from some compute units until they are through.  At
-  // the widest layers those compute units then lack in 49 rounds of tiles (V = 100000, H = 4096, 256x32: update 5.72 ms instead
+  // the widest layers those compute units then lack in 24 rounds of tiles (V = 100000, H = 4096, 256x32: update 5.72 ms instead
   // of 5.28, window 17.6 instead of 17.2), so the stage opens before the fork there.  With few rounds the timed window is
   // shorter with the embedding update in front (128x20, V = 64000, H = 1024 and V = 100000, H = 2048: 1.2 % each).
   const bool opened = early_side && !early_rec && !serial;
