@@ -461,11 +461,11 @@ template <typename T>
 struct EpiOutFwd : EpiZeroInit {
   const float *b;   // [V]
   T *ZT;            // [Vp][ldz], or nullptr: statistics only
-  float2 *part;     // [Vp / BM][ldz]: one (max, sum exp) per tile row block and position
+  float2 *part;     // [Vp / BM][ldp]: one (max, sum exp) per tile row block and position
   const int *yp;    // [Mp] target id per position, -1 on padding
   float *zy;        // [Mp] target logit
   int V;
-  long ldz;
+  long ldz, ldp;
   template <int BM, int BN>
   static constexpr int lds_bytes() {
     return stage_lds_bytes<T, BM, BN>() > 8 * BN * 8 ? stage_lds_bytes<T, BM, BN>() : 8 * BN * 8;
@@ -567,7 +567,7 @@ struct EpiOutFwd : EpiZeroInit {
         if (q.y > 0.0f) t += q.y * __expf(q.x - nm);
         a = make_float2(nm, t);
       }
-      part[(long)(c.tile_row0 / BM) * ldz + c.tile_col0 + c.tid] = a;
+      part[(long)(c.tile_row0 / BM) * ldp + c.tile_col0 + c.tid] = a;
     }
     if (!ZT) return;  // evaluation: nobody reads the logits, and writing them takes a quarter of the kernel's time
     __syncthreads();

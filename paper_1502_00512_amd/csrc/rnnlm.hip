@@ -211,6 +211,89 @@ hipError_t f32_gemm(hipStream_t st, const void *A, long lda, const void *B, long
   return launch_gemm_dma4<float, 64, 64, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, plan.splits, epi, band);
 }
 
+// bf16 contractions: output tiles of 256x256 (one persistent workgroup of eight waves per compute unit), 128x128 (eight
+// waves, two workgroups per compute unit) or 64x64 (four waves).  The large tiles read an operand least often and win where
+// they fill the chip for some rounds; with fewer, most compute units idle and a lone workgroup is slow (its epilogue alone
+// takes 8-20 us).  The tile minimises an estimate of the time, fitted to runs of 16..20480 tiles and depths of 64..2560
+// (us; w workgroups, K terms each); a hot run of each form at V x M (H = 512) resp. V x H (1024 positions), 256 / 128 / 64:
+//   output layer 10240 x 256: 19.1 / 8.4 / 9.6; 4096 x 1024: 19.8 / 9.0 / 11.6; 10240 x 2560: 43.9 / 44.2 / 56; 32768 x 2560:
+//   117 / 127 / 184;
+//   output update 4096 x 256: 31.4 / 11.1 / 7.7; 10240 x 512: 34.3 / 22.8 / 24.3; 10240 x 1024: 38.8 / 36.2 / 44; 32768 x 1024:
+//   102 / 104 / 139.
+// 128x128 on four waves is slower nearly everywhere (output layer 10240 x 1024: 22.3, on eight 19.5), waves that share out
+// the contraction gain 10-15 % only where 64x64 tiles are few and deep.
+enum Bf16Kind { OUT_FWD, OUT_UPDATE, PLAIN_SUM };  // by epilogue: statistics and logits, weight update, fp32 store
+double bf16_us(Bf16Kind kind, int tile, long Mg, long Ng, long K, int splits = 1) {
+  const double w = (double)(Mg / tile) * (Ng / tile) * splits, k = (double)((K / 64 + splits - 1) / splits * 64);
+  // MB of an update (10 bytes a weight) beyond what the memory-side cache holds
+  const double beyond = std::max(0.0, (double)Mg * Ng * 1e-5 - 170.0);
+  if (tile == 256) {
+    if (kind == PLAIN_SUM) return 6.0 + std::ceil(w / 256) * k * (0.0078 + 0.018 * std::min(1.0, w / 256));
+    const double rounds = std::floor(w / 256), rest = w / 256 - rounds;
+    const bool fwd = kind == OUT_FWD;
+    double us = 1.0 + rounds * (fwd ? 10.9 + 0.024 * k : 24.0 + 0.0265 * k);
+    if (rest > 0) us += fwd ? 10.9 + 0.0155 * k + rest * (1.5 + 0.0045 * k) : 13.5 + 0.0168 * k + rest * rest * (10.5 + 0.0095 * k);
+    return us + (fwd ? 0.0 : std::max(0.03, 0.105 - 4.4e-5 * k) * beyond);
+  }
+  // one workgroup alone; a workgroup's share of the chip's time, where every compute unit has some
+  double alone, share;
+  if (tile == 128) {
+    alone = (kind == OUT_UPDATE ? 5.0 : kind == OUT_FWD ? 4.9 : 4.0) + 0.0053 * k;
+    share = kind == OUT_UPDATE ? 0.0235 + 2.65e-5 * k + 2e-9 * k * k : kind == OUT_FWD ? 0.0095 + 3.38e-5 * k : 0.006 + 2.95e-5 * k;
+  } else {
+    alone = (kind == OUT_UPDATE ? 3.6 : kind == OUT_FWD ? 4.0 : 2.9) + 0.0033 * k;
+    share = kind == OUT_UPDATE ? 0.005 + 1.4e-5 * k : kind == OUT_FWD ? 0.0023 + 1.43e-5 * k : 0.0024 + 1.18e-5 * k;
+  }
+  // per_cu: workgroups a compute unit takes before its matrix cores are busy
+  const double per_cu = tile == 128 ? 1.0 : 4.0, full = 3.0 + 256 * per_cu * share;
+  const double fill = (w <= 256 ? w / 256 : std::ceil(w / 256)) / per_cu;
+  double us;
+  if (fill <= 1.0)
+    us = alone + std::max(0.0, full - alone) * fill * fill;
+  else  // (up to twice that, the fuller compute units take longer than the mean)
+    us = std::max(alone, 3.0 + share * (fill <= 2.0 ? (2 * w + 512 * per_cu) / 3 : w));
+  if (kind == OUT_UPDATE) us += (tile == 128 ? std::min(0.14, 0.08 + 1.2e-4 * k) : std::min(0.12, 0.05 + 3e-4 * k)) * beyond;
+  // long sums whose operands no L2 holds: what all tiles fetch, at what the fabric delivers
+  if (kind == PLAIN_SUM && (double)(Mg + Ng) * K > 4e7) {
+    const double f = 4.0 * K * Mg * Ng / tile / 11e6;
+    us = std::sqrt(std::sqrt(us * us * us * us + f * f * f * f));
+  }
+  return us;
+}
+// Mg a multiple of 256, Ng of 64: the tile that is fastest among those that divide them (window positions and widths of
+// layers are padded to as little as the tile asks for: a window of 77 positions has 128, not 256).  The persistent 256x256
+// forms are kept where the gain would be less than 8 % (update 16 %: it shares the chip with the other stream's work, for
+// which they leave room; V = 40000, H = 500, 120x18, update on 157 x 2 large tiles 539.7 us a window, on 128x128 544.1).
+constexpr double KEEP_LARGE = 0.92, KEEP_LARGE_UPDATE = 0.84;
+int bf16_tile(Bf16Kind kind, long Mg, long Ng, long K, int splits = 1) {
+  int best = 64;
+  double us = bf16_us(kind, 64, Mg, Ng, K, splits);
+  for (int tile : {128, 256}) {
+    if (Mg % tile || Ng % tile) continue;
+    const double t = bf16_us(kind, tile, Mg, Ng, K, splits) *
+                     (tile < 256 ? 1.0 : kind == OUT_UPDATE ? KEEP_LARGE_UPDATE : KEEP_LARGE);
+    if (t <= us) {
+      us = t;
+      best = tile;
+    }
+  }
+  return best;
+}
+// An extent of `valid` rows or columns, padded to 64, 128 or 256 by what the contraction with the other extent takes.
+long bf16_extent(Bf16Kind kind, long valid, long other, long K) {
+  long best = 0;
+  double us = 1e30;
+  for (long pad : {256, 128, 64}) {
+    const long n = round_up(valid, pad);
+    const double t = bf16_us(kind, bf16_tile(kind, other, n, K), other, n, K);
+    if (t < us) {
+      us = t;
+      best = n;
+    }
+  }
+  return best;
+}
+
 // The large bf16 contractions take the direct global->LDS kernels.
 // RING4: the four-stage ring of 32-deep K blocks (deeper prefetch; pays when at least one operand is
 // K-major, whose 32-deep blocks are still made of full cache lines) instead of two stages of 64.
@@ -227,11 +310,21 @@ hipError_t big_gemm(hipStream_t st, const void *A, long lda, const void *B, long
   }
 }
 
+// bf16 contractions on 128x128 or 64x64 tiles: the ring, whose three K blocks in flight are what keeps a lone workgroup's
+// matrix cores fed (register-staged 64x64 tiles took 0.65 us per 64 values of the contraction, the ring 0.4).
+template <int LA, int LB, class Epi>
+hipError_t bf16_small_gemm(hipStream_t st, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
+                           int tile, int splits, const Epi &epi, int band = 4) {
+  if (tile == 128) return launch_gemm_dma4<bf16_t, 128, 128, 4, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
+  return launch_gemm_dma4<bf16_t, 64, 64, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
+}
+
 // The mid-sized contractions (noise-panel products, the layers of the compressed architecture, the recurrent weight
-// gradient): 128x128 output tiles, or 64x64 where those would leave compute units without a workgroup.  bf16 operands
-// take the direct global->LDS kernels (the ring when an operand is K-major or the tile is 64x64: its three K blocks in
-// flight are what keeps a lone workgroup's matrix cores fed; register-staged 64x64 tiles took 0.65 us per 64 values of
-// the contraction, the ring 0.4).
+// gradient): 128x128 or 64x64 output tiles, whichever the estimate favours (128 where it is close: those read less).
+int mid_tile(long Mg, long Ng, long K, int splits) {
+  if (Mg % 128 || Ng % 128) return 64;
+  return bf16_us(PLAIN_SUM, 128, Mg, Ng, K, splits) <= bf16_us(PLAIN_SUM, 64, Mg, Ng, K, splits) ? 128 : 64;
+}
 template <typename T, int LA, int LB, class Epi>
 hipError_t mid_gemm(hipStream_t st, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
                     int splits, const Epi &epi, int band = 4) {
@@ -242,13 +335,9 @@ hipError_t mid_gemm(hipStream_t st, const void *A, long lda, const void *B, long
     F32Plan plan = f32_plan(Mg, Ng, K, 1);
     plan.splits = splits;
     return f32_gemm<LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, plan, epi, band);
-  } else if (fits && (Mg % 128 || Ng % 128 || (Mg / 128) * (Ng / 128) * splits < 256)) {
-    return launch_gemm_dma4<bf16_t, 64, 64, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
-  } else if constexpr (LA == KROW || LB == KROW) {
-    if (fits) return launch_gemm_dma4<bf16_t, 128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
-    return launch_gemm<T, 128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
   } else {
-    if (fits) return launch_gemm_dma<128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
+    if (fits) return bf16_small_gemm<LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, mid_tile(Mg, Ng, K, splits), splits, epi, band);
+    if (Mg % 128 || Ng % 128) return launch_gemm<T, 64, 64, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
     return launch_gemm<T, 128, 128, 2, 2, LA, LB>(st, A, lda, B, ldb, Mg, Ng, K, splits, epi, band);
   }
 }
@@ -290,6 +379,36 @@ int desired_splits(long Mp, long Hp, long kBlocks) {
     }
   }
   return (int)best;
+}
+
+// Tile and splits of the bf16 contraction over the vocabulary: 256x256 tiles with the splits above, or smaller ones, where
+// few splits fill the chip and the pass over the parts is short, by the same estimate.  Window positions and features are
+// taken as 256-multiples by the large tiles; `feats` as the small ones take them.  (V = 10000, H = 512, 256 positions: 16
+// parts on 256x256 tiles 18.3 us and a pass of 5.4, now 7.2 and 4.8.)
+struct SumPlan {
+  int tile, splits;
+  long feats;
+};
+SumPlan bf16_sum_plan(long Mp, long D, long K, bool padded_feats) {
+  const long Dp = round_up(D, PAD_H), kBlocks = K / 64;
+  SumPlan best = {64, 1, padded_feats ? Dp : round_up(D, 64)};
+  double us = 1e30;
+  auto consider = [&](int tile, int S, long feats) {
+    const double t = bf16_us(PLAIN_SUM, tile, Mp, feats, K, S) * (tile == 256 ? KEEP_LARGE : 1.0) + (S > 1 ? 5.0 + (S + 1) * (double)Mp * Dp * 4.0 / 7e6 : 0.0);
+    if (t >= us) return;
+    us = t;
+    best = {tile, S, feats};
+  };
+  if (Mp % 256 == 0) consider(256, desired_splits(Mp, Dp, kBlocks), Dp);
+  for (int tile : {128, 64}) {
+    if (Mp % tile) continue;
+    const long feats = padded_feats ? Dp : round_up(D, tile), tiles = (Mp / tile) * (feats / tile);
+    for (long S = 1; S <= std::min<long>(kBlocks, BF16_SPLITS) && (S == 1 || tiles * S <= 1024); ++S) {
+      const long per = (kBlocks + S - 1) / S;
+      if ((kBlocks + per - 1) / per == S) consider(tile, (int)S, feats);  // (else the last ones would be empty)
+    }
+  }
+  return best;
 }
 
 // A wave's share of the matrix has to fit its registers: four waves and 32 units per workgroup up to 1024 units, eight
@@ -339,7 +458,9 @@ StepPlan step_plan(const rnnlm_config &c, int Bp, int Hp) {
 // 256-row tiles: the padding is below 2 % there.
 constexpr long F32_TRIM_ROWS = 16384;
 long window_rows(const rnnlm_config &c, long Mrows) {
-  if (c.precision != RNNLM_FP32 || Mrows > F32_TRIM_ROWS) return round_up(Mrows, PAD_M);
+  if (c.precision != RNNLM_FP32)
+    return bf16_extent(OUT_FWD, Mrows, round_up(c.V, PAD_V), terms<bf16_t>(c.P > 0 ? c.P : c.H));
+  if (Mrows > F32_TRIM_ROWS) return round_up(Mrows, PAD_M);
   return f32_extent(Mrows, round_up(c.V, PAD_V), c.P > 0 ? c.P : c.H, 1);
 }
 // Columns the contraction over the vocabulary forms: the compressed architecture reads the padding, too.
@@ -357,16 +478,19 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   const RecurrentPlan plan = recurrent_plan(c);
   Bp = plan.nwg == 0 && Hp >= 2048 && round_up(c.B, PAD_B) % 256 == 0 ? (int)round_up(c.B, PAD_B) : c.B;
   MpMax = (int)round_up((long)c.T_max * Bp, PAD_M);
-  const int nPart = Vp / (es == 4 ? 64 : BIG);  // one softmax-statistics partial per tile row block (fp32: of the smallest tile)
+  // softmax statistics: a partial per tile row block and position (fp32: of the smallest tile)
+  long statElems = (long)(Vp / 64) * MpMax;
   if (es == 4) {
     L.partElems = (long)MpMax * Dp;
     for (long M = 64; M <= MpMax; M += M < F32_TRIM_ROWS ? 64 : PAD_M)
       L.partElems = std::max(
           L.partElems, f32_plan(M, features_formed(c, M, MAX_SPLITS, MpMax), c.V, MAX_SPLITS, MpMax).splits * M * Dp);
   } else {
-    L.partElems = 0;
-    for (long M = BIG; M <= MpMax; M += BIG)
-      L.partElems = std::max(L.partElems, (long)desired_splits(M, Dp, Vp / 64) * M * Dp);
+    L.partElems = statElems = 0;
+    for (long M = 64; M <= MpMax; M += 64) {
+      L.partElems = std::max(L.partElems, bf16_sum_plan(M, Pp > 0 ? c.P : c.H, Vp, Pp > 0).splits * M * Dp);
+      statElems = std::max(statElems, Vp / bf16_tile(OUT_FWD, Vp, M, terms<bf16_t>(Pp > 0 ? c.P : c.H)) * M);
+    }
   }
   const StepPlan step = step_plan(c, Bp, Hp);
   if (plan.nwg == 0) L.partElems = std::max(L.partElems, (long)step.splits * step.rows * Hp);
@@ -386,7 +510,7 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   L.dHs32 = take((size_t)MpMax * Hp * 4);
   L.dA32 = take((size_t)MpMax * Hp * 4);
   L.part32 = take((size_t)L.partElems * 4);
-  L.stat = take((size_t)nPart * MpMax * 8);
+  L.stat = take((size_t)statElems * 8);
   L.lse = take((size_t)MpMax * 4);
   L.zy = take((size_t)MpMax * 4);
   L.logp_int = take((size_t)MpMax * 4);
@@ -766,7 +890,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     feat = at<T>(h, h->L.P_c);
   }
   if (!with_output) return RNNLM_OK;  // the scoring calls only wanted the layer above the states
-  int nPart = Vp / BIG;
+  int nPart;
   {
     StageTimer tm(h, RNNLM_STAGE_OUT_FWD, st);
     EpiOutFwd<T> epi;
@@ -777,12 +901,20 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     epi.zy = zy;
     epi.V = c.V;
     epi.ldz = ldz;
+    epi.ldp = Mp;
     if constexpr (sizeof(T) == 2) {
+      const int tile = bf16_tile(OUT_FWD, Vp, Mp, terms<T>(h->D));
+      nPart = Vp / tile;
       // thousands of short tiles: one persistent workgroup per compute unit walks them, in bands of 8 vocabulary
       // row panels (the 32 tiles an XCD works on at a time then share 8 row panels and 4 position panels in its L2:
       // measured best of 1..16 on all three large configurations)
-      HIP_TRY((launch_gemm_dma<BIG, BIG, 4, 2, ROWK, ROWK, true>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp,
-                                                                    Mp, terms<T>(h->D), 1, epi, 8)));
+      if (tile == BIG) {
+        HIP_TRY((launch_gemm_dma<BIG, BIG, 4, 2, ROWK, ROWK, true>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp,
+                                                                   terms<T>(h->D), 1, epi, 8)));
+      } else {
+        HIP_TRY((bf16_small_gemm<ROWK, ROWK>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp, terms<T>(h->D), tile, 1,
+                                             epi, 8)));
+      }
     } else {
       const F32Plan plan = f32_plan(Vp, Mp, h->D, 1);
       HIP_TRY((f32_gemm<ROWK, ROWK>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp, round_up(h->D, 32), plan, epi, 8)));
@@ -791,7 +923,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
   }
   StageTimer tm(h, RNNLM_STAGE_STATS, st);
   hipLaunchKernelGGL(merge_stats_kernel, dim3(blocks_for(Mrows, MERGE_M)), dim3(1024), 0, st, at<float2>(h, h->L.stat),
-                     nPart, ldz, Tn, c.B, Bp, zy, lse, at<float>(h, h->L.logp_int), logp_out,
+                     nPart, Mp, Tn, c.B, Bp, zy, lse, at<float>(h, h->L.logp_int), logp_out,
                      wsum ? p_counter(h) + sync_word(0, 0) : nullptr, wsum ? *wsum : WindowSum{});
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
@@ -943,7 +1075,6 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   const int Mrows = Tn * Bp;
   const int Mp = (int)window_rows(h->cfg, Mrows);
   const long ldz = h->MpMax, rowTerms = terms<T>(Mrows);
-  constexpr int BK = Elem<T>::BK;
   T *Hs_c = at<T>(h, h->L.Hs_c);
   T *ZT = at<T>(h, h->L.ZT);
   T *Wo_c = at<T>(h, h->L.Wo_c);
@@ -977,7 +1108,8 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     const int max_splits = (int)std::min<long>(MAX_SPLITS, std::max<long>(1, h->L.partElems / per));
     const long Dn = sizeof(T) == 4 ? features_formed(c, Mp, max_splits, ldz) : Dp;
     const F32Plan plan = sizeof(T) == 4 ? f32_plan(Mp, Dn, c.V, max_splits, ldz) : F32Plan{};
-    int S = sizeof(T) == 4 ? plan.splits : desired_splits(Mp, Dp, Vp / BK);
+    const SumPlan sum = sizeof(T) == 2 ? bf16_sum_plan(Mp, h->D, Vp, c.P > 0) : SumPlan{};
+    int S = sizeof(T) == 4 ? plan.splits : sum.splits;
     if ((long)S * per > h->L.partElems) S = (int)(h->L.partElems / per);
     if (S < 1) S = 1;
     EpiPartial epi;
@@ -991,8 +1123,10 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
       StageTimer tm(h, RNNLM_STAGE_OUT_BWD_H, st);
       if constexpr (sizeof(T) == 4) {
         HIP_TRY((f32_gemm<KROW, KROW>(st, ZT, ldz, Wo_c, Dp, Mp, Dn, round_up(c.V, 32), plan, epi)));
-      } else {
+      } else if (sum.tile == BIG) {
         HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(st, ZT, ldz, Wo_c, Dp, Mp, Dp, Vp, S, epi)));
+      } else {
+        HIP_TRY((bf16_small_gemm<KROW, KROW>(st, ZT, ldz, Wo_c, Dp, Mp, sum.feats, Vp, sum.tile, S, epi)));
       }
     }
     if (S > 1 || (c.P > 0 && sizeof(T) == 2)) {
@@ -1109,7 +1243,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
       if constexpr (sizeof(T) == 2)
         HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, rowTerms, 1, epi)));
     } else {
-      const long n = sizeof(T) == 4 ? round_up(c.H, 64) : Hp;  // (the epilogue writes valid entries only)
+      const long n = round_up(c.H, 64);  // (the epilogue writes valid entries only)
       HIP_TRY((mid_gemm<T, KROW, KROW>(rs, Hs_c, Hp, dA_c, Hp, n, n, rowTerms, 1, epi)));
     }
   }
@@ -1192,6 +1326,10 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
       } else {
         HIP_TRY((launch_gemm<T, 64, 64, 2, 2, ROWK, KROW>(st, ZT, ldz, feat, h->Dp, Vp, Dn, K, 1, epi, -4)));
       }
+    } else if (const long Dn = bf16_extent(OUT_UPDATE, h->D, Vp, rowTerms);
+               bf16_tile(OUT_UPDATE, Vp, Dn, rowTerms) != BIG) {
+      HIP_TRY((bf16_small_gemm<ROWK, KROW>(st, ZT, ldz, feat, h->Dp, Vp, Dn, rowTerms, bf16_tile(OUT_UPDATE, Vp, Dn, rowTerms), 1,
+                                           epi, -4)));
     } else if (c.P == 0) {
       // Tiles are walked in bands of 4 (wide matrices: 8) tile columns, so that the 32 tiles an XCD works on at a time
       // share few operand panels in its L2 (8 x 4 or 4 x 8 instead of 2 x 16: 4 % faster on the widest configuration).
