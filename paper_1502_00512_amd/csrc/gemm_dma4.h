@@ -167,29 +167,24 @@ constexpr int dma4_stage_bytes() {
 // work items id, id + grid, ... (the grid is a multiple of 8, so a workgroup stays on the XCD whose chunk of
 // tiles it walks); the first three K blocks of the next tile are requested before the current tile's epilogue
 // starts, so the next main loop finds them in LDS instead of waiting a memory round trip per tile.
-template <typename T, int BM, int BN, int WGM, int WGN, int LA, int LB, class Epi, bool PERSIST = false>
-__global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShape g, const Epi epi) {
+// The work items first, first + stride, .. of a contraction, by one workgroup with four stages of LDS.
 #if defined(__HIP_DEVICE_COMPILE__)
+template <typename T, int BM, int BN, int WGM, int WGN, int LA, int LB, class Epi, bool PERSIST>
+__device__ inline void gemm_dma4_items(const GemmShape &g, const Epi &epi, int first, int stride, char *const stage0,
+                                       char *const stage1, char *const stage2, char *const stage3) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int ES = sizeof(T);
   constexpr int BK = 64 / ES;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int TM = WTM / 32, TN = WTN / 32;
-  constexpr int SBYTES = dma4_stage_bytes<BM, BN, Epi>();
-  __shared__ __attribute__((aligned(1024))) char stage0[SBYTES];
-  __shared__ __attribute__((aligned(1024))) char stage1[SBYTES];
-  __shared__ __attribute__((aligned(1024))) char stage2[SBYTES];
-  __shared__ __attribute__((aligned(1024))) char stage3[SBYTES];
-
   static_assert(!PERSIST || Epi::template lds_bytes<BM, BN>() == 0, "the next tile's blocks land while the epilogue runs");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WGM, wn = wave / WGM;
   const int nwork = g.perXcd * NUM_XCD;
-  const int stride = PERSIST ? (int)gridDim.x : nwork;
   DmaLoader32<T, BM, LA, NT> la;
   DmaLoader32<T, BN, LB, NT> lb;
   bool prefetched = false;  // the loaders are set up for this tile and its first three blocks are in flight
-  for (int wid = blockIdx.x; wid < nwork; wid += stride) {
+  for (int wid = first; wid < nwork; wid += stride) {
   int tile_m, tile_n, split;
   if (!map_workgroup(g, wid, split, tile_m, tile_n)) continue;  // uniform for the workgroup (never after a prefetch)
   // g.kBlocks counts blocks of 128 bytes; this kernel walks blocks of 64
@@ -316,6 +311,19 @@ __global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShap
   ctx.split = this_split;
   epi.template run<BM, BN, TM, TN, NT>(acc, ctx);
   }
+}
+#endif  // __HIP_DEVICE_COMPILE__
+
+template <typename T, int BM, int BN, int WGM, int WGN, int LA, int LB, class Epi, bool PERSIST = false>
+__global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma4_kernel(const GemmShape g, const Epi epi) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int SBYTES = dma4_stage_bytes<BM, BN, Epi>();
+  __shared__ __attribute__((aligned(1024))) char stage0[SBYTES];
+  __shared__ __attribute__((aligned(1024))) char stage1[SBYTES];
+  __shared__ __attribute__((aligned(1024))) char stage2[SBYTES];
+  __shared__ __attribute__((aligned(1024))) char stage3[SBYTES];
+  gemm_dma4_items<T, BM, BN, WGM, WGN, LA, LB, Epi, PERSIST>(
+      g, epi, blockIdx.x, PERSIST ? (int)gridDim.x : g.perXcd * NUM_XCD, stage0, stage1, stage2, stage3);
 #endif  // __HIP_DEVICE_COMPILE__
 }
 
@@ -327,13 +335,11 @@ inline bool dma4_reaches(int layout, long ld, int rows, long K) {
   return (layout == ROWK ? rows : ES == 4 ? 64 / ES : K) * ld * ES < (1L << 31);
 }
 
-template <typename T, int BM, int BN, int WGM, int WGN, int LA, int LB, bool PERSIST = false, class Epi>
-inline hipError_t launch_gemm_dma4(hipStream_t stream, const void *A, long lda, const void *B, long ldb, long Mg,
-                                   long Ng, long K, int splits, const Epi &epi, int band = 4) {
+template <typename T, int BM, int BN, int LA, int LB>
+inline hipError_t dma4_shape(GemmShape &g, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
+                             int splits, int band) {
   constexpr int ES = sizeof(T), BK = 128 / ES;  // splits are made of blocks of 128 bytes, as in launch_gemm_dma
   if (Mg <= 0 || Ng <= 0 || K < 0 || Mg % BM || Ng % BN || K % BK || splits < 1) return hipErrorInvalidValue;
-  static_assert(4 * dma4_stage_bytes<BM, BN, Epi>() <= 160 * 1024, "tile does not fit the 160 KB of LDS");
-  GemmShape g;
   g.A = A;
   g.B = B;
   g.lda = lda;
@@ -351,6 +357,16 @@ inline hipError_t launch_gemm_dma4(hipStream_t stream, const void *A, long lda, 
   g.perXcd = (int)((total + NUM_XCD - 1) / NUM_XCD);
   g.bandOverN = band < 0;
   g.band = band < 0 ? -band : band;
+  return hipSuccess;
+}
+
+template <typename T, int BM, int BN, int WGM, int WGN, int LA, int LB, bool PERSIST = false, class Epi>
+inline hipError_t launch_gemm_dma4(hipStream_t stream, const void *A, long lda, const void *B, long ldb, long Mg,
+                                   long Ng, long K, int splits, const Epi &epi, int band = 4) {
+  static_assert(4 * dma4_stage_bytes<BM, BN, Epi>() <= 160 * 1024, "tile does not fit the 160 KB of LDS");
+  GemmShape g;
+  const hipError_t e = dma4_shape<T, BM, BN, LA, LB>(g, A, lda, B, ldb, Mg, Ng, K, splits, band);
+  if (e != hipSuccess) return e;
   unsigned grid = (unsigned)(g.perXcd * NUM_XCD);
   if (PERSIST && grid > 256u) grid = 256u;  // one workgroup per compute unit
   hipLaunchKernelGGL((gemm_dma4_kernel<T, BM, BN, WGM, WGN, LA, LB, Epi, PERSIST>), dim3(grid), dim3(WGM * WGN * 64), 0,

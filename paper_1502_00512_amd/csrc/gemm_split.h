@@ -160,9 +160,9 @@ constexpr int split_lds_bytes() {
 
 // KS = steps of 16 values of k per block; WGK = groups of WGM x WGN waves that share out the steps of a block (their sums
 // are added at the end, in order); PF = blocks in registers ahead of the two in LDS.
-template <int BM, int BN, int WGM, int WGN, int WGK, int LA, int LB, int KS, int PF, class Epi>
-__global__ void __launch_bounds__(WGM *WGN *WGK * 64, (BM == 64 ? 4 : 2)) gemm_split_kernel(const GemmShape g, const Epi epi) {
 #if defined(__HIP_DEVICE_COMPILE__)
+template <int BM, int BN, int WGM, int WGN, int WGK, int LA, int LB, int KS, int PF, class Epi>
+__device__ inline void gemm_split_item(const GemmShape &g, const Epi &epi, int item, char *const smem) {
   constexpr int NT = WGM * WGN * WGK * 64;
   constexpr int BK = 16 * KS, KSW = KS / WGK;
   static_assert(KS % WGK == 0 && (32 % BK == 0 || BK % 32 == 0), "");
@@ -171,12 +171,11 @@ __global__ void __launch_bounds__(WGM *WGN *WGK * 64, (BM == 64 ? 4 : 2)) gemm_s
   using LoadA = SplitLoader<BM, LA, NT, KS>;
   using LoadB = SplitLoader<BN, LB, NT, KS>;
   constexpr int STAGE = LoadA::BYTES + LoadB::BYTES;
-  __shared__ __attribute__((aligned(1024))) char smem[split_lds_bytes<BM, BN, KS, Epi>()];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WGM, wn = wave / WGM % WGN, wk = wave / (WGM * WGN);
   int tile_m, tile_n, split;
-  if (!map_workgroup(g, blockIdx.x, split, tile_m, tile_n)) return;  // uniform for the workgroup
+  if (!map_workgroup(g, item, split, tile_m, tile_n)) return;  // uniform for the workgroup
   const int kb0 = split * g.kBlocksPerSplit, nk = min((split + 1) * g.kBlocksPerSplit, g.kBlocks) - kb0;
 
   f32x16_t acc[TM][TN];
@@ -291,7 +290,7 @@ __global__ void __launch_bounds__(WGM *WGN *WGK * 64, (BM == 64 ? 4 : 2)) gemm_s
       for (int j = 0; j < TN; ++j) acc[i][j] += corr[i][j];
   const bool again = __syncthreads_or(__builtin_bit_cast(unsigned, big) >= SPLIT_MAX);
   if constexpr (WGK > 1) {
-    static_assert(WGM * WGN * (WGK - 1) * TM * TN * 4096 <= sizeof(smem), "");
+    static_assert(WGM * WGN * (WGK - 1) * TM * TN * 4096 <= split_lds_bytes<BM, BN, KS, Epi>(), "");
     float *part = reinterpret_cast<float *>(smem) + (long)(wave % (WGM * WGN)) * (TM * TN * 1024);
     auto at = [&](int i, int j, int r) { return part + ((i * TN + j) * 16 + r) * 64 + lane; };
     if (wk > 0) {
@@ -349,18 +348,24 @@ __global__ void __launch_bounds__(WGM *WGN *WGK * 64, (BM == 64 ? 4 : 2)) gemm_s
   ctx.tid = tid;
   ctx.split = split;
   epi.template run<BM, BN, TM, TN, WGM * WGN * 64>(acc, ctx);
+}
+#endif
+
+template <int BM, int BN, int WGM, int WGN, int WGK, int LA, int LB, int KS, int PF, class Epi>
+__global__ void __launch_bounds__(WGM *WGN *WGK * 64, (BM == 64 ? 4 : 2)) gemm_split_kernel(const GemmShape g, const Epi epi) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __shared__ __attribute__((aligned(1024))) char smem[split_lds_bytes<BM, BN, KS, Epi>()];
+  gemm_split_item<BM, BN, WGM, WGN, WGK, LA, LB, KS, PF, Epi>(g, epi, blockIdx.x, smem);
 #endif
 }
 
 // The 32-bit byte offsets of the loads cover a tile's rows (ROWK), or a block's rows of k (KROW).
 inline bool split_reaches(int layout, long ld, int rows, int bk) { return (layout == ROWK ? rows : bk) * ld * 4 < (1L << 31); }
 
-template <int BM, int BN, int WGM, int WGN, int WGK, int LA, int LB, int KS, int PF, class Epi>
-inline hipError_t launch_gemm_split(hipStream_t stream, const void *A, long lda, const void *B, long ldb, long Mg, long Ng,
-                                    long K, int splits, const Epi &epi, int band = 4) {
+template <int BM, int BN, int LA, int LB, int KS>
+inline hipError_t split_shape(GemmShape &g, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
+                              int splits, int band) {
   if (Mg <= 0 || Ng <= 0 || K < 0 || Mg % BM || Ng % BN || K % 32 || splits < 1) return hipErrorInvalidValue;
-  static_assert(split_lds_bytes<BM, BN, KS, Epi>() <= 160 * 1024, "tile does not fit the 160 KB of LDS");
-  GemmShape g;
   g.A = A;
   g.B = B;
   g.lda = lda;
@@ -379,6 +384,16 @@ inline hipError_t launch_gemm_split(hipStream_t stream, const void *A, long lda,
   g.perXcd = (int)((total + NUM_XCD - 1) / NUM_XCD);
   g.bandOverN = band < 0;
   g.band = band < 0 ? -band : band;
+  return hipSuccess;
+}
+
+template <int BM, int BN, int WGM, int WGN, int WGK, int LA, int LB, int KS, int PF, class Epi>
+inline hipError_t launch_gemm_split(hipStream_t stream, const void *A, long lda, const void *B, long ldb, long Mg, long Ng,
+                                    long K, int splits, const Epi &epi, int band = 4) {
+  static_assert(split_lds_bytes<BM, BN, KS, Epi>() <= 160 * 1024, "tile does not fit the 160 KB of LDS");
+  GemmShape g;
+  const hipError_t e = split_shape<BM, BN, LA, LB, KS>(g, A, lda, B, ldb, Mg, Ng, K, splits, band);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((gemm_split_kernel<BM, BN, WGM, WGN, WGK, LA, LB, KS, PF, Epi>), dim3((unsigned)(g.perXcd * NUM_XCD)),
                      dim3(WGM * WGN * WGK * 64), 0, stream, g, epi);
   return hipGetLastError();

@@ -706,64 +706,75 @@ __global__ void __launch_bounds__(64 * RUN_WAVES) scatter_runs_kernel(const floa
 // power of two) times slices of the run's members; the sums are the same tree as a sorted window's.  P = 512, 2560
 // positions: 35 -> 21 us.
 constexpr int SCAN_MAX = 4096;
-template <bool ALIGNED, typename T>
-__global__ void __launch_bounds__(64 * RUN_WAVES) scatter_scan_kernel(const float *__restrict__ dA, int Hp, int H, int B,
-                                                                      int Bp, const int32_t *__restrict__ xp,
-                                                                      const float *__restrict__ E,
-                                                                      float *__restrict__ out, float alpha, float lr,
-                                                                      T *__restrict__ Ec, int ldc, int M, int blocks) {
-  constexpr int THREADS = 64 * RUN_WAVES, KEYS = SCAN_MAX / THREADS;  // keys per thread: threadIdx.x + THREADS k
-  __shared__ unsigned short members[SCAN_MAX];
-  __shared__ f32x4_t shared[2 * RUN_WAVES][64];  // (RUN_WAVES - each) * blocks rows are in use
-  __shared__ unsigned long long found[KEYS * RUN_WAVES];  // group of 64 positions -> which of them
-  __shared__ int before[KEYS * RUN_WAVES], total;
-  static_assert(KEYS * RUN_WAVES == 64, "one lane per group");
-  auto row_of = [&](int m) { return (m / B) * Bp + m % B; };
+template <typename T>
+struct ScanUpdate {
+  const float *dA;
+  int Hp, H, B, Bp;
+  const int32_t *xp;
+  const float *E;
+  float *out;
+  float alpha, lr;
+  T *Ec;
+  int ldc, M, blocks;
+};
+struct ScanShared {
+  f32x4_t sums[2 * RUN_WAVES][64];  // (RUN_WAVES - each) * blocks rows are in use
+  unsigned long long found[64];     // group of 64 positions -> which of them
+  int before[64], total;
+  unsigned short members[SCAN_MAX];
+};
+// By a workgroup of WAVES waves; g: its position, y: its group of column blocks.
+template <int WAVES, bool ALIGNED, typename T>
+__device__ inline void scatter_scan(const ScanUpdate<T> &p, ScanShared &sh, int g, int y) {
+  constexpr int THREADS = 64 * WAVES, KEYS = SCAN_MAX / THREADS;  // keys per thread: threadIdx.x + THREADS k
+  static_assert(KEYS * WAVES == 64 && RUN_WAVES % WAVES == 0, "one lane per group");
+  const int H = p.H, M = p.M, blocks = p.blocks;
+  auto row_of = [&](int m) { return (m / p.B) * p.Bp + m % p.B; };
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int g = blockIdx.x, w = xp[row_of(g)];
+  const int w = p.xp[row_of(g)];
   int key[KEYS];
 #pragma unroll
-  for (int k = 0; k < KEYS; ++k) key[k] = threadIdx.x + THREADS * k < M ? xp[row_of(threadIdx.x + THREADS * k)] : -1;
+  for (int k = 0; k < KEYS; ++k) key[k] = threadIdx.x + THREADS * k < M ? p.xp[row_of(threadIdx.x + THREADS * k)] : -1;
   unsigned mine = 0;
 #pragma unroll
   for (int k = 0; k < KEYS; ++k) {
     const unsigned long long b = __ballot(key[k] == w);
-    if (lane == 0) found[k * RUN_WAVES + wave] = b;
+    if (lane == 0) sh.found[k * WAVES + wave] = b;
     mine |= (unsigned)(key[k] == w) << k;
   }
   __syncthreads();
   if (wave == 0) {  // members before each group of 64 positions
-    const int n = __popcll(found[lane]);
+    const int n = __popcll(sh.found[lane]);
     int incl = n;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const int up = __shfl_up(incl, o, 64);
       if (lane >= o) incl += up;
     }
-    before[lane] = incl - n;
-    if (lane == 63) total = incl;
+    sh.before[lane] = incl - n;
+    if (lane == 63) sh.total = incl;
   }
   __syncthreads();
-  auto rank = [&](int m) { return before[m >> 6] + __popcll(found[m >> 6] & ((1ull << (m & 63)) - 1)); };
+  auto rank = [&](int m) { return sh.before[m >> 6] + __popcll(sh.found[m >> 6] & ((1ull << (m & 63)) - 1)); };
   if (rank(g) != 0) return;  // an earlier position starts this run
   for (; mine; mine &= mine - 1) {
     const int m = threadIdx.x + THREADS * (__ffs(mine) - 1);
-    members[rank(m)] = (unsigned short)m;
+    sh.members[rank(m)] = (unsigned short)m;
   }
   __syncthreads();
-  const int slices = RUN_WAVES / blocks, slice = wave / blocks, cb = wave % blocks;
+  const int slices = WAVES / blocks, slice = wave / blocks, cb = wave % blocks;
   const int each = RUN_WAVES / slices;  // slices of the members a wave takes
-  const int n = __builtin_amdgcn_readfirstlane(total);
-  const int col = (blockIdx.y * blocks + cb) * RUN_COLS + lane * 4;
+  const int n = __builtin_amdgcn_readfirstlane(sh.total);
+  const int col = (y * blocks + cb) * RUN_COLS + lane * 4;
   f32x4_t old = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (slice == 0 && alpha != 0.0f) old = load_row4<ALIGNED>(E + (long)w * H, col, H) * alpha;
+  if (slice == 0 && p.alpha != 0.0f) old = load_row4<ALIGNED>(p.E + (long)w * H, col, H) * p.alpha;
   auto sum = [&](int s0, int s1) {
     RunSum s;
-    if (col < Hp)
+    if (col < p.Hp)
       s.take(s0, s1,
              [&](int i) {
                return *reinterpret_cast<const f32x4_t *>(
-                   dA + (long)row_of(__builtin_amdgcn_readfirstlane(members[i])) * Hp + col);
+                   p.dA + (long)row_of(__builtin_amdgcn_readfirstlane(sh.members[i])) * p.Hp + col);
              },
              [](int, f32x4_t v, f32x4_t &acc) { acc += v; });
     return s.total();
@@ -778,15 +789,20 @@ __global__ void __launch_bounds__(64 * RUN_WAVES) scatter_scan_kernel(const floa
       const int q = slice * each + j, s0 = min(q * per, n);
       const f32x4_t v = sum(s0, min(s0 + per, n));
       if (slice != 0)
-        shared[(q - each) * blocks + cb][lane] = v;
+        sh.sums[(q - each) * blocks + cb][lane] = v;
       else
         tot = j == 0 ? v : tot + v;
     }
     __syncthreads();
     if (slice != 0) return;
-    for (int q = each; q < RUN_WAVES; ++q) tot += shared[(q - each) * blocks + cb][lane];
+    for (int q = each; q < RUN_WAVES; ++q) tot += sh.sums[(q - each) * blocks + cb][lane];
   }
-  store_row4<ALIGNED>(old - lr * tot, col, H, out + (long)w * H, Ec ? Ec + (long)w * ldc : nullptr);
+  store_row4<ALIGNED>(old - p.lr * tot, col, H, p.out + (long)w * H, p.Ec ? p.Ec + (long)w * p.ldc : nullptr);
+}
+template <bool ALIGNED, typename T>
+__global__ void __launch_bounds__(64 * RUN_WAVES) scatter_scan_kernel(const ScanUpdate<T> p) {
+  __shared__ ScanShared sh;
+  scatter_scan<RUN_WAVES, ALIGNED>(p, sh, blockIdx.x, blockIdx.y);
 }
 
 // 8-bit row-wise quantisation (Sec. 5.4 quantises all the weights; the scheme is a reading): one workgroup

@@ -21,6 +21,7 @@
 #include "gemm_split.h"
 #include "rnn_persistent.h"
 #include "rnn_resident.h"
+#include "update.h"
 
 using namespace rnnlm_dev;
 
@@ -142,9 +143,10 @@ struct F32Plan {
 };
 // A handle of millions of positions takes the forms whose blocks of 16 KS rows of ld values the loads' 32-bit offsets still
 // reach (64 x 64 in steps of 16 always).
+constexpr long F32_SHORT = 64;  // terms up to which a sum rounds less on the fp32 cores
 F32Plan f32_plan(long Mg, long Ng, long K, int max_splits, long ld = 0) {
   const long kb = (K + 31) / 32;
-  const bool split = kb > 2;  // shorter sums round less on the fp32 cores
+  const bool split = K > F32_SHORT;
   const bool reach32 = split_reaches(KROW, ld, 0, 32), reach64 = split_reaches(KROW, ld, 0, 64);
   F32Plan best = {64, 0, 1, 1e30};
   for (int S = 1; S <= max_splits && S <= kb; ++S) {
@@ -1064,6 +1066,59 @@ int nce_update(rnnlm_t *h, int Tn, const NceCall &n, const UpdateTargets &u, hip
   return RNNLM_OK;
 }
 
+// Fills in the contractions of a window's updates in one launch; the tile, or 0 where they take launches of their own: where
+// the output update's tiles are large, or an operand is beyond the loads' offsets.
+template <typename T>
+int window_update_shape(rnnlm_t *h, int Mrows, const T *ZT, const T *Hs_c, const T *dA_c, WindowUpdate<T> &w) {
+  const rnnlm_config &c = h->cfg;
+  const int Hp = h->Hp, Vp = h->Vp;
+  const long ldz = h->MpMax, K = terms<T>(Mrows);
+  const T *Hs1 = Hs_c + (long)h->Bp * Hp;
+  int tile;
+  hipError_t e = hipErrorInvalidValue;
+  if constexpr (sizeof(T) == 4) {
+    const long Dn = f32_extent(c.H, Vp, Mrows, 1), Hn = round_up(c.H, 64);
+    tile = f32_plan(Vp, Dn, Mrows, 1).tile;
+    if (tile == 64 && Mrows <= F32_SHORT) {
+      e = dma4_shape<T, 64, 64, ROWK, KROW>(w.out_g, ZT, ldz, Hs1, Hp, Vp, Dn, K, 1, -4);
+      if (e == hipSuccess) e = dma4_shape<T, 64, 64, KROW, KROW>(w.rec_g, Hs_c, Hp, dA_c, Hp, Hn, Hn, K, 1, 4);
+    } else if (tile == 64) {
+      e = split_shape<64, 64, ROWK, KROW, 1>(w.out_g, ZT, ldz, Hs1, Hp, Vp, Dn, K, 1, -4);
+      if (e == hipSuccess) e = split_shape<64, 64, KROW, KROW, 1>(w.rec_g, Hs_c, Hp, dA_c, Hp, Hn, Hn, K, 1, 4);
+    }
+  } else {
+    const long Dn = bf16_extent(OUT_UPDATE, c.H, Vp, K), Hn = round_up(c.H, 128);
+    tile = bf16_tile(OUT_UPDATE, Vp, Dn, K);
+    if (tile == 64) {
+      e = dma4_shape<T, 64, 64, ROWK, KROW>(w.out_g, ZT, ldz, Hs1, Hp, Vp, Dn, K, 1, -4);
+      if (e == hipSuccess) e = dma4_shape<T, 64, 64, KROW, KROW>(w.rec_g, Hs_c, Hp, dA_c, Hp, round_up(c.H, 64), round_up(c.H, 64), K, 1, 4);
+    } else if (tile == 128) {
+      e = dma4_shape<T, 128, 128, ROWK, KROW>(w.out_g, ZT, ldz, Hs1, Hp, Vp, Dn, K, 1, -4);
+      if (e == hipSuccess) e = dma4_shape<T, 128, 128, KROW, KROW>(w.rec_g, Hs_c, Hp, dA_c, Hp, Hn, Hn, K, 1, 4);
+    }
+  }
+  return e == hipSuccess ? tile : 0;
+}
+template <typename T>
+int launch_window_update(WindowUpdate<T> &w, int tile, int Mrows, int W, hipStream_t st) {
+  w.nRec = w.rec_g.perXcd * NUM_XCD;
+  w.nOut = w.out_g.perXcd * NUM_XCD;
+  const dim3 grid(w.nRec + w.nOut + w.scan.M * blocks_for(W, w.scan.blocks * RUN_COLS)), threads(tile * 4);
+  const bool aligned = W % 4 == 0;
+  if constexpr (sizeof(T) == 4) {
+    if (Mrows <= F32_SHORT)
+      hipLaunchKernelGGL((aligned ? window_update_kernel<T, 64, 0, true> : window_update_kernel<T, 64, 0, false>), grid, threads, 0, st, w);
+    else
+      hipLaunchKernelGGL((aligned ? window_update_kernel<T, 64, 1, true> : window_update_kernel<T, 64, 1, false>), grid, threads, 0, st, w);
+  } else if (tile == 64) {
+    hipLaunchKernelGGL((aligned ? window_update_kernel<T, 64, 0, true> : window_update_kernel<T, 64, 0, false>), grid, threads, 0, st, w);
+  } else {
+    hipLaunchKernelGGL((aligned ? window_update_kernel<T, 128, 0, true> : window_update_kernel<T, 128, 0, false>), grid, threads, 0, st, w);
+  }
+  HIP_TRY(hipGetLastError());
+  return RNNLM_OK;
+}
+
 // Backward half of a window + fused updates.  Everything it starts is ordered before whatever comes next on st.
 // rec_stream (may be nullptr) receives the stream whose next launch is ordered behind the recurrent update: work on the
 // other stream is not.
@@ -1192,6 +1247,49 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     HIP_TRY(hipGetLastError());
   }
 
+  auto scan_update = [&](const float *rows, const float *src, float alpha, T *copy, int waves) {
+    ScanUpdate<T> s = {rows, h->Dp, h->D, c.B, Bp, xp, src, u.E, alpha, u.lr, copy, h->Dp, Tn * c.B, 1};
+    while (s.blocks < waves && s.blocks * RUN_COLS < h->D) s.blocks *= 2;  // 256-column blocks a workgroup has waves for
+    return s;
+  };
+  auto recurrent_epilogue = [&]() {
+    EpiSgdT<T> epi;
+    epi.W = h->buf.U;
+    epi.out = u.U;
+    epi.Wc = u.refresh_copies ? U_c : nullptr;
+    epi.WcT = u.refresh_copies ? at<T>(h, h->L.UT_c) : nullptr;  // the backward pass reads the transposed copy
+    epi.ldw = c.H;
+    epi.ldc = Hp;
+    epi.R = c.H;
+    epi.C = c.H;
+    epi.alpha = u.alpha;
+    epi.lr = u.lr;
+    return epi;
+  };
+  auto aim = [&](auto &epi) {  // at the output layer's matrix
+    epi.W = c.P > 0 ? h->buf.E : h->buf.Wo;
+    epi.out = c.P > 0 ? u.E : u.Wo;
+    epi.Wc = u.refresh_copies ? Wo_c : nullptr;
+    epi.ldw = h->D;
+    epi.ldc = h->Dp;
+    epi.R = c.V;
+    epi.C = h->D;
+    epi.alpha = u.alpha;
+    epi.lr = u.lr;
+  };
+  const bool big_rec = sizeof(T) == 2 && (long)(Hp / BIG) * (Hp / BIG) >= 64;  // the recurrent update fills the chip
+  if (!nce && c.P == 0 && !big_rec && scan_ids(h, Tn, u)) {
+    WindowUpdate<T> w;
+    const int tile = window_update_shape<T>(h, Mrows, ZT, Hs_c, dA_c, w);
+    if (tile > 0) {
+      StageTimer tm(h, RNNLM_STAGE_OUT_BWD_W, st);
+      aim(w.out);
+      w.rec = recurrent_epilogue();
+      w.scan = scan_update(dA32, h->buf.E, u.alpha, nullptr, tile / 16);
+      if (rec_stream) *rec_stream = st;
+      return launch_window_update<T>(w, tile, Mrows, h->D, st);
+    }
+  }
   const bool serial = !nce && scan_ids(h, Tn, u) && short_output_update(h, Tn);
   hipStream_t es = serial ? st : h->side;
   // E[w] -= lr * sum_{m: x[m] = w} dA[m]: on the side stream, behind the sort helpers already queued there (joined at
@@ -1210,11 +1308,9 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     const bool scan = scan_ids(h, Tn, u);
     const dim3 threads(64 * RUN_WAVES);
     if (scan) {
-      int blocks = 1;  // 256-column blocks a workgroup has waves for
-      while (blocks < RUN_WAVES && blocks * RUN_COLS < W) blocks *= 2;
+      const ScanUpdate<T> su = scan_update(rows, src, e_alpha, Ec, RUN_WAVES);
       hipLaunchKernelGGL((W % 4 == 0 ? scatter_scan_kernel<true, T> : scatter_scan_kernel<false, T>),
-                         dim3(Tn * c.B, blocks_for(W, blocks * RUN_COLS)), threads, 0, es, rows, Wp, W, c.B, Bp, xp, src, u.E,
-                         e_alpha, u.lr, Ec, Wp, Tn * c.B, blocks);
+                         dim3(su.M, blocks_for(W, su.blocks * RUN_COLS)), threads, 0, es, su);
     } else {
       hipLaunchKernelGGL((W % 4 == 0 ? scatter_runs_kernel<true, T> : scatter_runs_kernel<false, T>),
                          dim3(blocks_for(Tn * c.B, RUN_WAVES), blocks_for(W, RUN_COLS)), threads, 0, es, rows, Wp, W, c.B, Bp,
@@ -1228,18 +1324,8 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   auto recurrent_update = [&](hipStream_t rs) -> int {
   {
     StageTimer tm(h, RNNLM_STAGE_REC_W, rs);
-    EpiSgdT<T> epi;
-    epi.W = h->buf.U;
-    epi.out = u.U;
-    epi.Wc = u.refresh_copies ? U_c : nullptr;
-    epi.WcT = u.refresh_copies ? at<T>(h, h->L.UT_c) : nullptr;  // the backward pass reads the transposed copy
-    epi.ldw = c.H;
-    epi.ldc = Hp;
-    epi.R = c.H;
-    epi.C = c.H;
-    epi.alpha = u.alpha;
-    epi.lr = u.lr;
-    if (sizeof(T) == 2 && (long)(Hp / BIG) * (Hp / BIG) >= 64) {
+    const EpiSgdT<T> epi = recurrent_epilogue();
+    if (big_rec) {
       if constexpr (sizeof(T) == 2)
         HIP_TRY((big_gemm<2, 4, KROW, KROW, true>(rs, Hs_c, Hp, dA_c, Hp, Hp, Hp, rowTerms, 1, epi)));
     } else {
@@ -1281,38 +1367,12 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     int rc = nce_update<T>(h, Tn, *nce, u, st);
     if (rc) return rc;
   } else {
-    if (c.P > 0) {
-      // C[p][j] -= lr * sum_m dp[m][p] h[m][j], contracted transposed (tile rows = j, tile columns = p)
-      StageTimer tm(h, RNNLM_STAGE_PROJ, st);
-      EpiSgdT<T> epi;
-      epi.W = h->buf.C;
-      epi.out = u.C;
-      epi.Wc = u.refresh_copies ? at<T>(h, h->L.C_c) : nullptr;
-      epi.ldw = c.H;
-      epi.ldc = Hp;
-      epi.R = c.P;
-      epi.C = c.H;
-      epi.alpha = u.alpha;
-      epi.lr = u.lr;
-      HIP_TRY((mid_gemm<T, KROW, KROW>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.dP_c), h->Pp, Hp, h->Pp, rowTerms, 1, epi)));
-    }
     {
     // Wo[v][j] -= lr * sum_m dz[v][m] Hs[m][j]; compressed architecture: the output-side update of the tied matrix,
     // E[v][p] -= lr * sum_m dz[v][m] p[m][p].  bf16 compressed: contracted transposed (tile rows = p, tile columns = v).
     // Everything else in the matrix's own orientation (tile rows = v, tile columns = j), whose update epilogue touches two
     // 128-byte lines per wave instruction instead of 32 (fp32, V = 64000, H = 1024, 1280 positions: 893 -> 841 us).
     StageTimer tm(h, RNNLM_STAGE_OUT_BWD_W, st, !opened);
-    auto aim = [&](auto &epi) {
-      epi.W = c.P > 0 ? h->buf.E : h->buf.Wo;
-      epi.out = c.P > 0 ? u.E : u.Wo;
-      epi.Wc = u.refresh_copies ? Wo_c : nullptr;
-      epi.ldw = h->D;
-      epi.ldc = h->Dp;
-      epi.R = c.V;
-      epi.C = h->D;
-      epi.alpha = u.alpha;
-      epi.lr = u.lr;
-    };
     const T *feat = c.P > 0 ? at<T>(h, h->L.P_c) : Hs_c + (long)Bp * Hp;
     EpiSgd<T> epi;
     aim(epi);
@@ -1367,23 +1427,59 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     rc = embedding_update();
     if (rc) return rc;
   }
+  bool rec_done = early_rec;
   if (c.P > 0) {
-    // A[i][p] -= lr * sum_m da[m][i] x[m][p], contracted transposed (tile rows = p, tile columns = i)
     StageTimer tm(h, RNNLM_STAGE_PROJ, st);
-    EpiSgdT<T> epi;
-    epi.W = h->buf.A;
-    epi.out = u.A;
-    epi.Wc = u.refresh_copies ? at<T>(h, h->L.A_c) : nullptr;
-    epi.ldw = c.P;
-    epi.ldc = h->Pp;
-    epi.R = c.H;
-    epi.C = c.P;
-    epi.alpha = u.alpha;
-    epi.lr = u.lr;
-    HIP_TRY((mid_gemm<T, KROW, KROW>(st, at<T>(h, h->L.Xp_c), h->Pp, dA_c, Hp, h->Pp, Hp, rowTerms, 1, epi)));
+    // C[p][j] -= lr * sum_m dp[m][p] h[m][j], contracted transposed (tile rows = j, tile columns = p)
+    EpiSgdT<T> ec;
+    ec.W = h->buf.C;
+    ec.out = u.C;
+    ec.Wc = u.refresh_copies ? at<T>(h, h->L.C_c) : nullptr;
+    ec.ldw = c.H;
+    ec.ldc = Hp;
+    ec.R = c.P;
+    ec.C = c.H;
+    ec.alpha = u.alpha;
+    ec.lr = u.lr;
+    // A[i][p] -= lr * sum_m da[m][i] x[m][p], contracted transposed (tile rows = p, tile columns = i)
+    EpiSgdT<T> ea;
+    ea.W = h->buf.A;
+    ea.out = u.A;
+    ea.Wc = u.refresh_copies ? at<T>(h, h->L.A_c) : nullptr;
+    ea.ldw = c.P;
+    ea.ldc = h->Pp;
+    ea.R = c.H;
+    ea.C = c.P;
+    ea.alpha = u.alpha;
+    ea.lr = u.lr;
+    const T *Hs1 = Hs_c + (long)Bp * Hp, *dP_c = at<T>(h, h->L.dP_c), *Xp_c = at<T>(h, h->L.Xp_c);
+    bool grouped = false;
+    if constexpr (sizeof(T) == 2) {
+      // (epilogues write valid entries only: extents are padded to whole tiles, no further)
+      const long Hn = round_up(c.H, 64), Pn = round_up(c.P, 64);
+      UpdateGroup<EpiSgdT<T>> group;
+      grouped = dma4_shape<T, 64, 64, KROW, KROW>(group.g[0], Hs1, Hp, dP_c, h->Pp, Hn, Pn, rowTerms, 1, 4) == hipSuccess &&
+                dma4_shape<T, 64, 64, KROW, KROW>(group.g[1], Xp_c, h->Pp, dA_c, Hp, Pn, Hn, rowTerms, 1, 4) == hipSuccess &&
+                dma4_shape<T, 64, 64, KROW, KROW>(group.g[2], Hs_c, Hp, dA_c, Hp, Hn, Hn, rowTerms, 1, 4) == hipSuccess;
+      if (grouped) {
+        group.epi[0] = ec;
+        group.epi[1] = ea;
+        group.epi[2] = recurrent_epilogue();
+        group.first[0] = 0;
+        for (int q = 0; q < GROUP_MAX; ++q) group.first[q + 1] = group.first[q] + group.g[q].perXcd * NUM_XCD;
+        rec_done = !big_rec;
+        hipLaunchKernelGGL((update_group_kernel<KROW, KROW, EpiSgdT<T>>), dim3(group.first[rec_done ? 3 : 2]), dim3(256), 0, st,
+                           group);
+        HIP_TRY(hipGetLastError());
+      }
+    }
+    if (!grouped) {
+      HIP_TRY((mid_gemm<T, KROW, KROW>(st, Hs1, Hp, dP_c, h->Pp, Hp, h->Pp, rowTerms, 1, ec)));
+      HIP_TRY((mid_gemm<T, KROW, KROW>(st, Xp_c, h->Pp, dA_c, Hp, h->Pp, Hp, rowTerms, 1, ea)));
+    }
   }
 
-  if (!early_rec) {
+  if (!rec_done) {
     int rc = recurrent_update(st);
     if (rc) return rc;
   }

@@ -1,5 +1,5 @@
 """bf16 contractions on 256 x 256, 128 x 128 and 64 x 64 output tiles: windows at the edges of the tiles, where an estimate of
-the time chooses between them and pads positions and units to as little as the tile asks for."""
+the time chooses between them and pads positions and units to as little as the tile asks for; windows whose updates share a launch."""
 import numpy as np
 import pytest
 
@@ -34,3 +34,31 @@ def test_bf16_window_against_oracle(V, H, B, T):
         for key in ("logp", "gE", "gU", "gWo", "gb"):
             a = got[key].cpu().numpy().astype(np.float64)
             assert np.abs(a - ref[key]).max() <= 2e-2 * np.abs(ref[key]).max(), key
+
+
+@pytest.mark.parametrize("precision", [binding.RNNLM_FP32, binding.RNNLM_BF16_FP32MASTER])
+@pytest.mark.parametrize("V,H,B,T", [
+    (40, 300, 64, 16),    # 1024 positions, runs of equal ids beyond what one wave sums, two column blocks
+    (30, 1100, 5, 13),    # 65 positions, more column blocks than a workgroup has waves
+    (5000, 70, 8, 8),     # 64 positions: the last window on the fp32 cores; ragged rows
+    (20000, 130, 3, 50),  # 128 x 128 tiles
+    (700, 64, 1, 1),
+])
+def test_updates_in_one_launch(V, H, B, T, precision):
+    E, U, Wo, b = synth.make_weights(V, H, "uniform", 0.1, 5 + V)
+    tok = synth.zipf_tokens(B * T + B + 1, V, 1.05, 3)
+    g = binding.Rnnlm(E, U, Wo, b, B, T, precision)
+    o = O.Model.from_weights(E, U, Wo, b, B)
+    x, y = O.stream_chunk(tok, B, T, 0)
+    before = {n: getattr(o, n).copy() for n in ("E", "U", "Wo", "b")}
+    g.rnnlm_train_chunk(torch.as_tensor(x).cuda(), torch.as_tensor(y).cuda(), 0.5)
+    O.train_chunk(o, x, y, 0.5)
+    g.rnnlm_check()
+    # the suite's bounds for gradients, on what the step moved: 1e-3 of each tensor's largest entry in fp32, 2e-2 in bf16;
+    # the weights themselves are kept in fp32 (half an ulp of weights up to 0.6: 3e-8)
+    tol = 1e-3 if precision == binding.RNNLM_FP32 else 2e-2
+    for name, old in before.items():
+        got, ref = getattr(g, name).cpu().numpy().astype(np.float64), getattr(o, name)
+        assert np.abs(got - ref).max() <= tol * np.abs(ref - old).max() + 6e-8, name
+    untouched = np.setdiff1d(np.arange(V), x)
+    assert np.array_equal(g.E.cpu().numpy()[untouched], E[untouched])
