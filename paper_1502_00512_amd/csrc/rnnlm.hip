@@ -21,6 +21,7 @@
 #include "gemm_split.h"
 #include "rnn_persistent.h"
 #include "rnn_resident.h"
+#include "rnn_step.h"
 #include "update.h"
 
 using namespace rnnlm_dev;
@@ -433,7 +434,7 @@ RecurrentPlan recurrent_plan(const rnnlm_config &c) {
   return p;
 }
 
-// Per-step recurrent path for shapes the persistent kernel does not cover: the step's contraction is split over its
+// Per-step recurrent path for shapes neither the persistent kernel nor a step in one launch covers: the step's contraction is split over its
 // contraction dimension, then one pass sums the parts and applies the elementwise part.  Whole blocks of 256 streams of a
 // wide layer: 256 x 128 tiles (fp32: 256 x 64, register-staged), one workgroup per compute unit.  Everything else: 64 x 64
 // tiles of the ring, up to eight splits and two workgroups per compute unit: the step is bound by the latency of a
@@ -718,6 +719,40 @@ int launch_rnn_resident(rnnlm_t *h, int Tn, bool advance_state, hipStream_t st) 
   return RNNLM_OK;
 }
 
+// One step in one launch (rnn_step.h): where its workgroups, with up to 64 streams each, are at most one per compute unit.
+// Blocks of 16 streams a workgroup takes: as few as that allows (more streams read the matrix less often, fewer load faster).
+// us a window of 16 positions, V = 2000, two launches a step and one: bf16 H = 2816, 1 stream 434 and 248, 16 530 and 326, 64
+// 618 and 467; H = 4000, 16 streams 648 and 446, 64 741 and 607; fp32 H = 1300, 16 streams 417 and 241, 128 866 and 678; H =
+// 2816, 16 streams 793 and 421, 64 1020 and 909.  Beyond: bf16 H = 4000, 128 streams 898 and 933, fp32 H = 2816, 1536 and 1645.
+int step_groups(const rnnlm_config &c, int blocks) { return (int)((c.H + 15) / 16 * ((c.B + 16L * blocks - 1) / (16 * blocks))); }
+bool step_in_one(const rnnlm_config &c) { return c.H <= 4096 && c.B <= 4096 && step_groups(c, 4) <= 256; }
+int step_blocks(const rnnlm_config &c) { return c.B <= 16 ? 1 : step_groups(c, 2) <= 256 ? 2 : 4; }
+template <typename T, bool BACKWARD>
+int launch_rnn_step(rnnlm_t *h, int t, bool contract, float *h_state, hipStream_t st) {
+  const rnnlm_config &c = h->cfg;
+  const long slot = (long)h->Bp * h->Hp;
+  T *Hs = at<T>(h, h->L.Hs_c) + (t + 1) * slot, *dA = at<T>(h, h->L.dA_c) + t * slot;
+  RnnStepArgs a;
+  a.W = BACKWARD ? at<T>(h, h->L.UT_c) : at<T>(h, h->L.U_c);
+  a.state = BACKWARD ? dA + slot : Hs - slot;
+  a.X = (BACKWARD ? at<float>(h, h->L.dHs32) : at<float>(h, h->L.X32)) + t * slot;
+  a.h = Hs;
+  a.out = BACKWARD ? dA : Hs;
+  a.out32 = at<float>(h, h->L.dA32) + t * slot;
+  a.h_state = h_state;
+  a.B = c.B;
+  a.H = c.H;
+  a.Hp = h->Hp;
+  a.pieces = contract ? (int)(terms<T>(c.H) * (long)sizeof(T) / 128) : 0;
+  const int rt = step_blocks(c);
+  hipLaunchKernelGGL((rt == 1   ? rnn_step_kernel<T, 1, BACKWARD>
+                      : rt == 2 ? rnn_step_kernel<T, 2, BACKWARD>
+                                : rnn_step_kernel<T, 4, BACKWARD>),
+                     dim3(blocks_for(c.H, 16), blocks_for(c.B, 16 * rt)), dim3(512), 0, st, a);
+  HIP_TRY(hipGetLastError());
+  return RNNLM_OK;
+}
+
 struct UpdateTargets {
   // where each fused update writes: training -> the masters (alpha 1, lr), gradient export -> caller
   // buffers (alpha 0, lr -1, no compute-copy refresh, no state advance)
@@ -860,6 +895,12 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
   } else
   for (int t = 0; t < Tn; ++t) {
     StageTimer tm(h, (t == 0 || t == Tn - 1) ? RNNLM_STAGE_RNN_FWD : -1, st, t == 0, t == Tn - 1);
+    float *const h_state = (advance_state && t == Tn - 1) ? h->buf.h_state : nullptr;
+    if (step_in_one(c)) {
+      int rc = launch_rnn_step<T, false>(h, t, true, h_state, st);
+      if (rc) return rc;
+      continue;
+    }
     const T *A_ = Hs_c + (long)t * Bp * Hp;
     const T *B_ = at<T>(h, h->L.U_c);
     const StepPlan p = step_plan(c, Bp, Hp);
@@ -877,7 +918,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     }
     hipLaunchKernelGGL(rnn_step_fwd_kernel<T>, dim3(blocks_for(per / 4, 256)), dim3(256), 0, st,
                        at<float>(h, h->L.part32), p.rows * Hp, p.splits, X32 + (long)t * Bp * Hp, c.B, c.H, Hp, per / 4,
-                       Hs_c + (long)(t + 1) * Bp * Hp, (advance_state && t == Tn - 1) ? h->buf.h_state : nullptr);
+                       Hs_c + (long)(t + 1) * Bp * Hp, h_state);
     HIP_TRY(hipGetLastError());
   }
   if (!with_output && !(need_feat && c.P > 0)) return RNNLM_OK;  // the noise-contrastive calls score the hidden states themselves
@@ -1223,6 +1264,11 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   for (int t = Tn - 1; t >= 0; --t) {
     StageTimer tm(h, (t == 0 || t == Tn - 1) ? RNNLM_STAGE_RNN_BWD : -1, st, t == Tn - 1, t == 0);
     const bool contract = t < Tn - 1;  // nothing flows into the window's last position
+    if (step_in_one(c)) {
+      int rc = launch_rnn_step<T, true>(h, t, contract, nullptr, st);
+      if (rc) return rc;
+      continue;
+    }
     const T *A_ = dA_c + (long)(t + 1) * Bp * Hp;
     const StepPlan p = step_plan(c, Bp, Hp);
     const long per = (long)Bp * Hp, at_t = (long)t * per, K = terms<T>(c.H);

@@ -40,6 +40,30 @@ def test_fp32_against_oracle(V, H, B, T):
     g.rnnlm_check()
 
 
+# steps in one launch of their own: one, two and four blocks of 16 streams a workgroup, the last one partly filled, units
+# and pieces of the contraction that are no multiple of a workgroup's; and past them, two launches a step
+@pytest.mark.parametrize("H,B,T,precision", [
+    (1025, 16, 3, FP32), (1100, 17, 2, FP32), (1500, 33, 2, FP32), (1290, 100, 3, FP32), (1600, 200, 2, FP32),
+    (2049, 1, 4, BF16), (2064, 16, 3, BF16), (2300, 31, 2, BF16), (2500, 63, 3, BF16), (2060, 65, 2, BF16), (2500, 130, 2, BF16),
+])
+def test_wide_layers_step_by_step(H, B, T, precision):
+    V = 300
+    g, o = make_pair(V, H, B, T, precision, seed=H + B, scale=0.03, bias_scale=0.5)
+    tok = tokens(V, 2 * B * T + B + 1, 6)
+    x, y = O.stream_chunk(tok, B, T, 0)
+    g.rnnlm_forward_logprob(dev(x), dev(y))
+    O.forward_logprob(o, x, y)
+    # the bounds of the suite: fp32 2e-5 on states; bf16 states, of at most 1, to a few roundings of 2^-9
+    assert np.abs(g.h_state.cpu().numpy() - o.h).max() < (2e-5 if precision == FP32 else 2e-2)
+    x, y = O.stream_chunk(tok, B, T, 1)
+    r = g.rnnlm_grad_chunk(dev(x), dev(y))
+    ref = O.grad_chunk(o, x, y)
+    for k in ("gE", "gU", "gWo", "gb"):
+        a = r[k].cpu().numpy().astype(np.float64)
+        assert np.abs(a - ref[k]).max() <= (1e-3 if precision == FP32 else 2e-2) * np.abs(ref[k]).max(), k
+    g.rnnlm_check()
+
+
 @pytest.mark.parametrize("H,B,few", [(40, 256, 3), (200, 100, 1), (650, 250, 7), (1024, 129, 16), (1100, 256, 5), (2000, 120, 9)])
 def test_bf16_exchange_and_group_size(H, B, few):
     V, T = 500, 5
