@@ -193,8 +193,6 @@ __device__ inline void gemm_dma4_items(const GemmShape &g, const Epi &epi, int f
   const int nk = kb1 - kb0;
 
   f32x16_t acc[TM][TN];
-  epi.template init<TM, TN>(acc, tile_m * BM + wm * WTM, tile_n * BN + wn * WTN, lane, split);
-
   if (!prefetched) {
     la.init(static_cast<const char *>(g.A), g.bytesA, g.lda * ES, (long)tile_m * BM, (long)kb0 * BK, tid);
     lb.init(static_cast<const char *>(g.B), g.bytesB, g.ldb * ES, (long)tile_n * BN, (long)kb0 * BK, tid);
@@ -256,12 +254,14 @@ __device__ inline void gemm_dma4_items(const GemmShape &g, const Epi &epi, int f
     mfmas(1);
   };
 
+  if (nk > 0 && !prefetched) {
+    fetch(stage0, 0);
+    fetch(stage1, 1);
+    fetch(stage2, 2);
+  }
+  // (behind the first loads: what it loads itself arrives with them)
+  epi.template init<TM, TN>(acc, tile_m * BM + wm * WTM, tile_n * BN + wn * WTN, lane, split);
   if (nk > 0) {
-    if (!prefetched) {
-      fetch(stage0, 0);
-      fetch(stage1, 1);
-      fetch(stage2, 2);
-    }
     __builtin_amdgcn_s_waitcnt(WAIT_TWO_BLOCKS);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);

@@ -24,6 +24,27 @@ __device__ inline float logisticf_(float d) {
   return (d >= 0.0f) ? 1.0f / (1.0f + e) : e / (1.0f + e);
 }
 
+// Both at once, as the elementwise pass over all scores wants them: the exponent's rounding error taken along, divisions by
+// the hardware reciprocal and a correction by the remainder, ln(1 + e) = 2 artanh(e / (2 + e)) by the series in the
+// argument's square (to t^4; coefficients through the Chebyshev nodes of [0, 1/9], 4e-9 relative).  Some 30 instructions
+// instead of 80, which bound the pass (2560 positions, 1024 noise words, 160 workgroups: contraction and pass 28 us, without
+// the pass 12; window 224 and 213, with the target words' share formed in the next contraction).  Relative error against 64
+// bits, root mean square over scores of -30..30, with the exponential and the reciprocal an ulp off at random, before and now:
+// logistic 2.3e-7 and 0.6e-7, softplus 2.3e-7 and 0.6e-7.
+__device__ inline void noise_terms(float d, float &logistic, float &softplus) {
+  const float a = -fabsf(d), x = a * 1.44269502f;
+  float lo = fmaf(a, 1.92596303e-8f, fmaf(a, 1.44269502f, -x));  // what the product lost
+  lo = a > -128.0f ? lo : 0.0f;                                  // (an infinite score has no remainder)
+  float e = __builtin_amdgcn_exp2f(x);
+  e = fmaf(e * lo, 0.693147181f, e);
+  const float d1 = 1.0f + e, n1 = d >= 0.0f ? 1.0f : e, q1 = __builtin_amdgcn_rcpf(d1), r1 = n1 * q1;
+  logistic = fmaf(fmaf(-d1, r1, n1), q1, r1);
+  const float d2 = 2.0f + e, q2 = __builtin_amdgcn_rcpf(d2), r2 = e * q2;
+  const float s = fmaf(fmaf(-r2, e - (d2 - 2.0f), fmaf(-d2, r2, e)), q2, r2), t = s * s;
+  const float p = fmaf(fmaf(fmaf(0.14078889f, t, 0.13982579f), t, 0.20012298f), t, 0.33333161f);
+  softplus = fmaxf(d, 0.0f) + fmaf((s + s) * t, p, s + s);
+}
+
 // Dot product of two compute-type rows of n values (n a multiple of 16 / sizeof(T)), one wave: 16-byte loads, per-lane
 // sums, then a butterfly.  Every lane returns the sum.
 template <typename T>
@@ -153,6 +174,18 @@ __global__ void __launch_bounds__(256) score_candidates_kernel(const T *__restri
 // passes and with this, every tile form (bf16 us): V = 64000, H = 1024, 16x4, 64 words 124 and 116; 128x20, 256 words 170 and
 // 162, 1024 words 193 and 182; 256x32, 2048 words 527 and 459; V = 10000, H = 300, 256x32, 2000 words 362 and 327; V = 20000,
 // H = 2048, 32x20, 500 words 228 and 231; fp32: 394 and 400 at 128x20, 1024 words, 1312 and 1277 at 256x32, 2048 words.
+// The value of lane ^ MASK (inside a half-wave), without an address register.
+template <int MASK>
+__device__ inline int swap_lanes(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (MASK == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);   // quad_perm 1, 0, 3, 2
+  if constexpr (MASK == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);   // quad_perm 2, 3, 0, 1
+  if constexpr (MASK == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);  // a row of 16 rotated by 8
+  return __builtin_amdgcn_ds_swizzle(v, (MASK << 10) | 0x1F);
+#else
+  return v;
+#endif
+}
 template <typename T>
 struct EpiNce : EpiZeroInit {
   T *dS;
@@ -178,29 +211,50 @@ struct EpiNce : EpiZeroInit {
         const int col0 = c.tile_col0 + c.wcol + j * 32, col = col0 + (c.lane & 31);
         const float o = off[col];
         const unsigned live = col < K ? valid : 0u;
-        float cost[16], gsum = 0.0f;
+        float cost[16], grad[16], gsum = 0.0f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const float d = acc[i][j][r] + o;
           const bool on = (live >> r) & 1u;
-          const float g = on ? logisticf_(d) * scale : 0.0f;
-          cost[r] = on ? softplusf_(d) : 0.0f;
-          gsum += g;
-          dS[(long)(row0 + RNNLM_ACC_ROW(r, c.lane)) * ld + col] = from_f32<T>(g);
+          float g, s;
+          noise_terms(acc[i][j][r] + o, g, s);
+          grad[r] = on ? g * scale : 0.0f;
+          cost[r] = on ? s : 0.0f;
+          gsum += grad[r];
+        }
+        if constexpr (sizeof(T) == 2) {  // neighbouring lanes swap one value: each owns two adjacent columns of one row
+          typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+          const bool odd = c.lane & 1;
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            bf16x2_t h;
+            h[0] = (bf16_t)grad[2 * q];
+            h[1] = (bf16_t)grad[2 * q + 1];
+            const unsigned mine = __builtin_bit_cast(unsigned, h);
+            const unsigned theirs = (unsigned)swap_lanes<1>((int)mine);
+            const long row = row0 + RNNLM_ACC_ROW(2 * q, c.lane) + (odd ? 1 : 0);
+            *reinterpret_cast<unsigned *>(dS + row * ld + (col & ~1)) = join_pair(mine, theirs, odd);
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dS[(long)(row0 + RNNLM_ACC_ROW(r, c.lane)) * ld + col] = from_f32<T>(grad[r]);
         }
         gsum += __shfl_xor(gsum, 32, 64);
         if (c.lane < 32) gpart[(long)(row0 >> 5) * ld + col] = gsum;
         // sums over the 32 lanes of a row: at each exchange a lane keeps half of its rows and gives the other half away
-#pragma unroll
-        for (int n = 8; n > 0; n >>= 1) {
+        auto halve = [&](auto n_) {
+          constexpr int n = decltype(n_)::value;
           const bool upper = c.lane & (2 * n);
 #pragma unroll
           for (int k = 0; k < n; ++k) {
             const float give = upper ? cost[k] : cost[k + n];
-            cost[k] = (upper ? cost[k + n] : cost[k]) + __shfl_xor(give, 2 * n, 64);
+            cost[k] = (upper ? cost[k + n] : cost[k]) + __int_as_float(swap_lanes<2 * n>(__float_as_int(give)));
           }
-        }
-        cost[0] += __shfl_xor(cost[0], 1, 64);
+        };
+        halve(std::integral_constant<int, 8>());
+        halve(std::integral_constant<int, 4>());
+        halve(std::integral_constant<int, 2>());
+        halve(std::integral_constant<int, 1>());
+        cost[0] += __int_as_float(swap_lanes<1>(__float_as_int(cost[0])));
         const int r = (c.lane & 31) >> 1;  // the row this lane has kept
         if (!(c.lane & 1)) jpart[(long)(col0 >> 5) * Mp + row0 + RNNLM_ACC_ROW(r, c.lane)] = cost[0];
       }
@@ -260,20 +314,28 @@ __global__ void __launch_bounds__(1024) nce_merge_kernel(const float *__restrict
   window_sum(w, M, [&](int m) { return __hip_atomic_load(J_int + m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); });
 }
 
-// dHs[row][:] += ct[row] * Wo_c[y_row][:]: the target word's share of what the output layer sends back.
+// Epilogue of dHs = dS . Wn + ct * Wo[target]: the accumulators start at the target word's share of what the output layer
+// sends back, gathered while the first blocks of the contraction are on their way.  (As a pass over dHs of its own, 7 us and a launch at
+// 2560 positions; gathered in the epilogue, a dependent load per row, 4 us more than the pass.)
 template <typename T>
-__global__ void __launch_bounds__(256) nce_target_dhs_kernel(const T *__restrict__ Wo_c, int Hp,
-                                                             const int32_t *__restrict__ yp,
-                                                             const float *__restrict__ ct,
-                                                             float *__restrict__ dHs) {
-  const int row = blockIdx.x;
-  const int y = yp[row];
-  if (y < 0) return;
-  const float c = ct[row];
-  const T *w = Wo_c + (long)y * Hp;
-  float *d = dHs + (long)row * Hp;
-  for (int col = threadIdx.x; col < Hp; col += 256) d[col] = fmaf(c, to_f32(w[col]), d[col]);
-}
+struct EpiNceDhs : EpiPartial {
+  const T *Wo_c;
+  const int *yp;  // [Mp] target id per position, -1 on padding
+  const float *ct;
+  template <int TM, int TN>
+  __device__ inline void init(f32x16_t (&acc)[TM][TN], int row0, int col0, int lane, int) const {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = row0 + i * 32 + RNNLM_ACC_ROW(r, lane), y = yp[row];
+        const float c = y >= 0 ? ct[row] : 0.0f;
+        const T *const w = Wo_c + (long)max(y, 0) * ld + col0 + (lane & 31);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j][r] = c * to_f32(w[j * 32]);
+      }
+  }
+};
 
 // Update of the touched rows of Wo, atomic-free and order-fixed:
 //   out[w][:] = alpha*Wo[w][:] - lr * ( sum_{noise entries e of w} G[e][:] + sum_{target entries} ct*Hs[row][:] )

@@ -1054,15 +1054,15 @@ int nce_backward_h(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
   const int Kp = (int)round_up(n.K, 256);
   float *dHs32 = at<float>(h, h->L.dHs32);
   StageTimer tm(h, RNNLM_STAGE_NCE_BWD_H, st);
-  EpiPartial epi;
+  EpiNceDhs<T> epi;
   epi.part = dHs32;
   epi.ld = Hp;
   epi.split_stride = 0;
+  epi.Wo_c = at<T>(h, h->L.Wo_c);
+  epi.yp = at<int32_t>(h, h->L.yp);
+  epi.ct = at<float>(h, h->L.nct);
   HIP_TRY((mid_gemm<T, ROWK, KROW>(st, at<T>(h, h->L.dS_c), Kp, at<T>(h, h->L.Wn_c), Hp, Mp, Hp, terms<T>(n.K),
                                       1, epi)));
-  hipLaunchKernelGGL(nce_target_dhs_kernel<T>, dim3(Mrows), dim3(256), 0, st, at<T>(h, h->L.Wo_c), Hp,
-                     at<int32_t>(h, h->L.yp), at<float>(h, h->L.nct), dHs32);
-  HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
 
