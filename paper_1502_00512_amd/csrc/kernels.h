@@ -258,19 +258,22 @@ struct WindowSum {
 };
 template <class Load>
 __device__ inline void window_sum(const WindowSum &w, int n, Load &&load) {
-  __shared__ double sh[1024];
+  __shared__ double sh[16];
   if (w.counters)
     for (int i = threadIdx.x; i < SYNC_WORDS; i += 1024) w.counters[i] = 0u;
   double a = 0.0;
   for (int i = threadIdx.x; i < n; i += 1024) a += (double)load(i);
-  sh[threadIdx.x] = a;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
   __syncthreads();
-  for (int k = 512; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
-    __syncthreads();
+  if (threadIdx.x < 16) {
+    a = sh[threadIdx.x];
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
   }
   if (threadIdx.x == 0) {
-    const double s = sh[0];
+    const double s = a;
     if (w.out) *w.out = s;
     if (w.running) *w.running += s;
     if (!(s == s) || s - s != 0.0) w.flags[1] = 1;
@@ -430,7 +433,16 @@ __global__ void splitk_reduce_kernel(const float *__restrict__ part, long n, int
   const long i = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (i >= n) return;
   f32x4_t a = *reinterpret_cast<const f32x4_t *>(part + i);
-  for (int s = 1; s < splits; ++s) a += *reinterpret_cast<const f32x4_t *>(part + s * n + i);
+  constexpr int FLIGHT = 5;
+  for (int s = 1; s < splits; s += FLIGHT) {  // (loads left in the loop one by one would wait for one another)
+    f32x4_t v[FLIGHT];
+#pragma unroll
+    for (int q = 0; q < FLIGHT; ++q)
+      if (s + q < splits) v[q] = *reinterpret_cast<const f32x4_t *>(part + (s + q) * n + i);
+#pragma unroll
+    for (int q = 0; q < FLIGHT; ++q)
+      if (s + q < splits) a += v[q];
+  }
   store_sum4(out + i, a);
 }
 
