@@ -1669,6 +1669,60 @@ int rms_apply_nce(rnnlm_t *h, int Tn, int K, const rnnlm_rmsprop_state &state, f
   HIP_TRY(hipGetLastError());
   return overlap ? side_join(h, 0, st) : RNNLM_OK;
 }
+// Evaluation of a whole text: windows follow one another in each stream, and a forward pass writes no logits, so the space
+// of the logits holds the positions of many windows and the handle runs them as one.  What that saves, per window: the
+// launches between two recurrences and their start (some 20 us), and a last, partly empty round of tiles (V = 64000, H = 1024,
+// 64x20, eight windows: 1250 tiles each on 256 compute units, 10000 together).  The layout is the handle's own again when
+// this goes out of scope.
+struct LongWindows {
+  rnnlm_t *h;
+  const WsLayout L;
+  const int MpMax;
+  long windows = 1;  // how many windows of T positions a call takes
+  LongWindows(rnnlm_t *h_, int T, long most) : h(h_), L(h_->L), MpMax(h_->MpMax) {
+    // (the other recurrent forms leave padding to what the workspace is initialised with)
+    if (!persistent_ok(h)) return;
+    const long per = (long)T * h->cfg.B;
+    long W = std::min(most, std::max(1L, std::min((1L << 24) / per, 4096L / T)));
+    while (W > 1 && !carve(W * T, most % W * T)) W = W > 2 ? W * 7 / 8 : 1;
+    windows = W;
+    if (W == 1) {
+      h->L = L;
+      h->MpMax = MpMax;
+    }
+  }
+  ~LongWindows() {
+    h->L = L;
+    h->MpMax = MpMax;
+  }
+  // T positions a stream, and `last` in the call for what is left over
+  bool carve(long T, long last) {
+    const rnnlm_config &c = h->cfg;
+    const size_t es = c.precision == RNNLM_FP32 ? 4 : 2;
+    const long Mmax = round_up(T * h->Bp, PAD_M);
+    auto stats = [&](long M) {
+      const long Mp = window_rows(c, M);
+      const int tile = es == 4 ? f32_plan(h->Vp, Mp, h->D, 1).tile : bf16_tile(OUT_FWD, h->Vp, Mp, terms<bf16_t>(h->D));
+      return (size_t)(h->Vp / tile) * Mp * 8;
+    };
+    size_t o = L.ZT;
+    auto take = [&](size_t &at, size_t bytes) {
+      at = o;
+      o = align256(o + bytes);
+    };
+    WsLayout &n = h->L;
+    take(n.Hs_c, (size_t)(Mmax + h->Bp + 64) * h->Hp * es);
+    take(n.X32, (size_t)Mmax * h->Hp * 4);
+    take(n.stat, std::max(stats(T * h->Bp), last > 0 ? stats(last * h->Bp) : 0));
+    for (size_t *at : {&n.lse, &n.zy, &n.logp_int, &n.xp, &n.yp, &n.xtmp, &n.ytmp}) take(*at, (size_t)Mmax * 4);
+    if (c.P > 0) {
+      take(n.Xp_c, (size_t)Mmax * h->Pp * es);
+      take(n.P_c, (size_t)Mmax * h->Pp * es);
+    }
+    h->MpMax = (int)Mmax;
+    return o <= L.dA_c;  // (what follows the logits in the workspace)
+  }
+};
 }  // namespace
 
 extern "C" {
@@ -1981,15 +2035,26 @@ int rnnlm_perplexity(rnnlm_t *h, const int32_t *tok, int64_t N, int32_t T, doubl
   int rc = rnnlm_reset_state(h, stream);
   if (rc) return rc;
   hipLaunchKernelGGL(fill_kernel<double>, dim3(1), dim3(64), 0, st, p_running(h), 1L, 0.0);
-  int32_t *xt = at<int32_t>(h, h->L.xtmp), *yt = at<int32_t>(h, h->L.ytmp);
-  for (long k = 0; k < nchunks; ++k) {
-    hipLaunchKernelGGL(stream_chunk_kernel, dim3(blocks_for((long)T * B, 256)), dim3(256), 0, st, tok, L, k, T, B, xt,
-                       yt);
-    const WindowSum ws = {nullptr, p_running(h), p_flags(h), nullptr};
-    rc = (h->cfg.precision == RNNLM_FP32)
-             ? forward_window<float>(h, xt, yt, T, nullptr, true, true, st, false, false, false, &ws)
-             : forward_window<bf16_t>(h, xt, yt, T, nullptr, true, true, st, false, false, false, &ws);
-    if (rc) return rc;
+  {
+    const LongWindows many(h, T, nchunks);
+    int32_t *xt = at<int32_t>(h, h->L.xtmp), *yt = at<int32_t>(h, h->L.ytmp);
+    for (long k = 0; k < nchunks; k += many.windows) {
+      const int Tn = (int)std::min(many.windows, nchunks - k) * T;
+      hipLaunchKernelGGL(stream_chunk_kernel, dim3(blocks_for((long)Tn * B, 256)), dim3(256), 0, st, tok + k * T, L, 0L, Tn, B,
+                         xt, yt);
+      const long M = (long)Tn * h->Bp, pad = (window_rows(h->cfg, M) - M) * h->Hp;
+      if (many.windows > 1 && pad > 0) {  // what was there may be anything: rows of states past the positions are operands
+        const size_t es = h->cfg.precision == RNNLM_FP32 ? 4 : 2;
+        const long n = pad * (long)es / 4;
+        hipLaunchKernelGGL(fill_kernel<uint32_t>, dim3(std::min<long>(blocks_for(n, 256), 1024)), dim3(256), 0, st,
+                           reinterpret_cast<uint32_t *>(h->ws + h->L.Hs_c + (M + h->Bp) * h->Hp * es), n, 0u);
+      }
+      const WindowSum ws = {nullptr, p_running(h), p_flags(h), nullptr};
+      rc = (h->cfg.precision == RNNLM_FP32)
+               ? forward_window<float>(h, xt, yt, Tn, nullptr, true, true, st, false, false, false, &ws)
+               : forward_window<bf16_t>(h, xt, yt, Tn, nullptr, true, true, st, false, false, false, &ws);
+      if (rc) return rc;
+    }
   }
   HIP_TRY(hipGetLastError());
   double total = 0.0;

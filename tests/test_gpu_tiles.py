@@ -62,3 +62,41 @@ def test_updates_in_one_launch(V, H, B, T, precision):
         assert np.abs(got - ref).max() <= tol * np.abs(ref - old).max() + 6e-8, name
     untouched = np.setdiff1d(np.arange(V), x)
     assert np.array_equal(g.E.cpu().numpy()[untouched], E[untouched])
+
+
+@pytest.mark.parametrize("precision", [binding.RNNLM_FP32, binding.RNNLM_BF16_FP32MASTER])
+@pytest.mark.parametrize("V,H,P,B,T,windows", [
+    (3000, 64, 0, 4, 5, 101),     # many windows a pass, one left over
+    (3000, 64, 0, 3, 7, 2),
+    (9000, 300, 0, 20, 10, 17),
+    (2000, 200, 100, 6, 9, 40),   # compressed architecture
+    (300, 500, 0, 9, 4, 5),       # the logits' space holds hardly more than a window
+    (3000, 1100, 0, 2, 3, 4),     # fp32: one window at a time
+])
+def test_perplexity_of_long_texts(V, H, P, B, T, windows, precision):
+    rng = np.random.default_rng(V + H)
+    w = lambda *s: rng.uniform(-0.1, 0.1, s).astype(np.float32)
+    args = [w(V, P or H), w(H, H), None if P else w(V, H), w(V)]
+    more = dict(A=w(H, P), C_=w(P, H)) if P else {}
+    tok = synth.zipf_tokens(windows * B * T + B + 1, V, 1.05, 3)
+    a = binding.Rnnlm(*args, B, T, precision, **more)
+    b = binding.Rnnlm(*args, B, T, precision, **more)
+    dtok = torch.as_tensor(tok).cuda()
+    for _ in range(2):
+        ppl, scored = a.rnnlm_perplexity(dtok, T)
+        # the same windows one call at a time: other tiles, so other orders of the sums
+        b.rnnlm_reset_state()
+        total = 0.0
+        for k in range(windows):
+            total += b.rnnlm_forward_logprob(*b.rnnlm_stream_chunk(dtok, k, T)).double().sum().item()
+        assert scored == windows * B * T
+        rel = 1e-5 if precision == binding.RNNLM_FP32 else 1e-3
+        assert abs(ppl - np.exp(-total / scored)) <= rel * ppl
+        assert (a.h_state - b.h_state).abs().max().item() <= (1e-5 if precision == binding.RNNLM_FP32 else 1e-2)
+        # and the workspace is as it was: the next windows' training is the same
+        a.h_state.copy_(b.h_state)
+        for k in range(2):
+            for m in (a, b):
+                m.rnnlm_train_chunk(*m.rnnlm_stream_chunk(dtok, k, T), 0.1)
+        assert torch.equal(a.E, b.E) and torch.equal(a.U, b.U) and torch.equal(a.b, b.b)
+    a.rnnlm_check()
