@@ -466,6 +466,7 @@ struct EpiOutFwd : EpiZeroInit {
   float *zy;        // [Mp] target logit
   int V;
   long ldz, ldp;
+  int v0 = 0;       // word of row 0 (what b, ZT and part are aimed at), V counted from there
   template <int BM, int BN>
   static constexpr int lds_bytes() {
     return stage_lds_bytes<T, BM, BN>() > 8 * BN * 8 ? stage_lds_bytes<T, BM, BN>() : 8 * BN * 8;
@@ -496,7 +497,7 @@ struct EpiOutFwd : EpiZeroInit {
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int m = col0 + j * 32 + (lane & 31);
-      const int target = yp[m];
+      const int target = yp[m] - v0;
       float mx = -INFINITY;
       float sum = 0.0f;
       if (interior) {

@@ -139,16 +139,13 @@ constexpr int dma_stage_bytes() {
 // PERSIST: the grid is one workgroup per compute unit and each walks the work items id, id + grid, ... (the
 // grid is a multiple of 8, so a workgroup stays on the XCD whose chunk of tiles it walks): the next tile's
 // first loads are issued while the previous tile's stores drain, and no workgroup is relaunched per tile.
-template <int BM, int BN, int WGM, int WGN, int LA, int LB, class Epi, bool PERSIST = false>
-__global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma_kernel(const GemmShape g, const Epi epi) {
 #if defined(__HIP_DEVICE_COMPILE__)
+template <int BM, int BN, int WGM, int WGN, int LA, int LB, class Epi, bool PERSIST>
+__device__ inline void gemm_dma_items(const GemmShape &g, const Epi &epi, char *const stage0, char *const stage1) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int BK = 64;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int TM = WTM / 32, TN = WTN / 32;
-  constexpr int SBYTES = dma_stage_bytes<BM, BN, Epi>();
-  __shared__ __attribute__((aligned(1024))) char stage0[SBYTES];
-  __shared__ __attribute__((aligned(1024))) char stage1[SBYTES];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WGM, wn = wave / WGM;
@@ -263,16 +260,24 @@ __global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma_kernel(const GemmShape
     __builtin_amdgcn_s_barrier();
   }
   }
+}
+#endif  // __HIP_DEVICE_COMPILE__
+
+template <int BM, int BN, int WGM, int WGN, int LA, int LB, class Epi, bool PERSIST = false>
+__global__ void __launch_bounds__(WGM *WGN * 64) gemm_dma_kernel(const GemmShape g, const Epi epi) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int SBYTES = dma_stage_bytes<BM, BN, Epi>();
+  __shared__ __attribute__((aligned(1024))) char stage0[SBYTES];
+  __shared__ __attribute__((aligned(1024))) char stage1[SBYTES];
+  gemm_dma_items<BM, BN, WGM, WGN, LA, LB, Epi, PERSIST>(g, epi, stage0, stage1);
 #endif  // __HIP_DEVICE_COMPILE__
 }
 
-template <int BM, int BN, int WGM, int WGN, int LA, int LB, bool PERSIST = false, class Epi>
-inline hipError_t launch_gemm_dma(hipStream_t stream, const void *A, long lda, const void *B, long ldb, long Mg,
-                                  long Ng, long K, int splits, const Epi &epi, int band = 4) {
+template <int BM, int BN, int LA, int LB>
+inline hipError_t dma_shape(GemmShape &g, const void *A, long lda, const void *B, long ldb, long Mg, long Ng, long K,
+                            int splits, int band) {
   constexpr int BK = 64;
   if (Mg <= 0 || Ng <= 0 || K < 0 || Mg % BM || Ng % BN || K % BK || splits < 1) return hipErrorInvalidValue;
-  static_assert(2 * dma_stage_bytes<BM, BN, Epi>() <= 160 * 1024, "tile does not fit the 160 KB of LDS");
-  GemmShape g;
   g.A = A;
   g.B = B;
   g.lda = lda;
@@ -293,6 +298,16 @@ inline hipError_t launch_gemm_dma(hipStream_t stream, const void *A, long lda, c
   g.perXcd = (int)((total + NUM_XCD - 1) / NUM_XCD);
   g.bandOverN = band < 0;
   g.band = band < 0 ? -band : band;
+  return hipSuccess;
+}
+
+template <int BM, int BN, int WGM, int WGN, int LA, int LB, bool PERSIST = false, class Epi>
+inline hipError_t launch_gemm_dma(hipStream_t stream, const void *A, long lda, const void *B, long ldb, long Mg,
+                                  long Ng, long K, int splits, const Epi &epi, int band = 4) {
+  static_assert(2 * dma_stage_bytes<BM, BN, Epi>() <= 160 * 1024, "tile does not fit the 160 KB of LDS");
+  GemmShape g;
+  const hipError_t e = dma_shape<BM, BN, LA, LB>(g, A, lda, B, ldb, Mg, Ng, K, splits, band);
+  if (e != hipSuccess) return e;
   unsigned grid = (unsigned)(g.perXcd * NUM_XCD);
   if (PERSIST && grid > 256u) grid = 256u;  // one workgroup per compute unit
   hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, WGM, WGN, LA, LB, Epi, PERSIST>), dim3(grid), dim3(WGM * WGN * 64), 0,

@@ -19,6 +19,7 @@
 #include "rmsprop.h"
 #include "gemm_ring64.h"
 #include "gemm_split.h"
+#include "gemm_tail.h"
 #include "rnn_persistent.h"
 #include "rnn_resident.h"
 #include "rnn_step.h"
@@ -52,6 +53,18 @@ struct EventPair {
   int stage;
 };
 
+// How a window of so many positions runs: rows the contractions walk, and the bf16 contraction over the vocabulary.  Worked
+// out when the length of the window changes (10 us of estimates).
+struct SumPlan {
+  int tile, splits;
+  long feats;
+  double us;
+};
+struct WindowPlan {
+  long Mrows = -1, Mp = 0;
+  SumPlan sum = {};
+};
+
 struct rnnlm {
   rnnlm_config cfg;
   rnnlm_buffers buf;
@@ -60,6 +73,7 @@ struct rnnlm {
   int D, Dp;  // width of the output layer's input: H / Hp, or P / Pp for the compressed architecture
   int KpMax;  // K_max rounded up to the tile size (0: no noise-contrastive workspace)
   RecurrentPlan plan;
+  WindowPlan window;
   WsLayout L;
   char *ws;
   // stage timing (host-side only)
@@ -226,7 +240,7 @@ hipError_t f32_gemm(hipStream_t st, const void *A, long lda, const void *B, long
 // 128x128 on four waves is slower nearly everywhere (output layer 10240 x 1024: 22.3, on eight 19.5), waves that share out
 // the contraction gain 10-15 % only where 64x64 tiles are few and deep.
 enum Bf16Kind { OUT_FWD, OUT_UPDATE, PLAIN_SUM };  // by epilogue: statistics and logits, weight update, fp32 store
-double bf16_us(Bf16Kind kind, int tile, long Mg, long Ng, long K, int splits = 1) {
+double bf16_all_us(Bf16Kind kind, int tile, long Mg, long Ng, long K, int splits = 1) {
   const double w = (double)(Mg / tile) * (Ng / tile) * splits, k = (double)((K / 64 + splits - 1) / splits * 64);
   // MB of an update (10 bytes a weight) beyond what the memory-side cache holds
   const double beyond = std::max(0.0, (double)Mg * Ng * 1e-5 - 170.0);
@@ -263,11 +277,31 @@ double bf16_us(Bf16Kind kind, int tile, long Mg, long Ng, long K, int splits = 1
   }
   return us;
 }
+// Rows of the output layer that 256x256 tiles take (gemm_tail.h): whole rounds of them where the rest is faster on 128x128 by
+// a good part of a round, or all (V = 10000, P = 512, 128x20, 1.56 rounds, whose rest is as long on small tiles: output layer
+// 49.7 and 52.4 us).
+long large_rows(long Mg, long Ng, long K, double *us = nullptr) {
+  const double all = Mg % 256 || Ng % 256 ? 0.0 : bf16_all_us(OUT_FWD, 256, Mg, Ng, K);
+  if (us) *us = all;
+  if (Mg % 256 || Ng % 256) return Mg;  // (no large tiles)
+  const long cols = Ng / 256, rounds = Mg / 256 * cols / 256, rows = rounds * 256 / cols * 256;
+  if (rounds == 0 || rows >= Mg) return Mg;
+  const double mixed = bf16_all_us(OUT_FWD, 256, rows, Ng, K) + bf16_all_us(OUT_FWD, 128, Mg - rows, Ng, K) - 3.0;
+  if (mixed >= 0.85 * all && all - mixed < 8.0) return Mg;
+  if (us) *us = mixed;
+  return rows;
+}
+double bf16_us(Bf16Kind kind, int tile, long Mg, long Ng, long K, int splits = 1) {
+  if (tile != 256 || kind != OUT_FWD) return bf16_all_us(kind, tile, Mg, Ng, K, splits);
+  double us;
+  large_rows(Mg, Ng, K, &us);
+  return us;
+}
 // Mg a multiple of 256, Ng of 64: the tile that is fastest among those that divide them (window positions and widths of
 // layers are padded to as little as the tile asks for: a window of 77 positions has 128, not 256).  The persistent 256x256
-// forms are kept where the gain would be less than 8 % (update 16 %: it shares the chip with the other stream's work, for
+// forms are kept where the gain would be small (update 16 %: it shares the chip with the other stream's work, for
 // which they leave room; V = 40000, H = 500, 120x18, update on 157 x 2 large tiles 539.7 us a window, on 128x128 544.1).
-constexpr double KEEP_LARGE = 0.92, KEEP_LARGE_UPDATE = 0.84;
+constexpr double KEEP_LARGE = 0.95, KEEP_LARGE_SUM = 0.92, KEEP_LARGE_UPDATE = 0.84;
 int bf16_tile(Bf16Kind kind, long Mg, long Ng, long K, int splits = 1) {
   int best = 64;
   double us = bf16_us(kind, 64, Mg, Ng, K, splits);
@@ -281,6 +315,13 @@ int bf16_tile(Bf16Kind kind, long Mg, long Ng, long K, int splits = 1) {
     }
   }
   return best;
+}
+// Softmax statistics of the output layer: a partial per tile row block and position.
+long stat_parts(long Vp, long Mp, long K) {
+  const int tile = bf16_tile(OUT_FWD, Vp, Mp, K);
+  if (tile < 256) return Vp / tile;
+  const long rows = large_rows(Vp, Mp, K);
+  return rows / 256 + (Vp - rows) / 128;
 }
 // An extent of `valid` rows or columns, padded to 64, 128 or 256 by what the contraction with the other extent takes.
 long bf16_extent(Bf16Kind kind, long valid, long other, long K) {
@@ -388,19 +429,12 @@ int desired_splits(long Mp, long Hp, long kBlocks) {
 // few splits fill the chip and the pass over the parts is short, by the same estimate.  Window positions and features are
 // taken as 256-multiples by the large tiles; `feats` as the small ones take them.  (V = 10000, H = 512, 256 positions: 16
 // parts on 256x256 tiles 18.3 us and a pass of 5.4, now 7.2 and 4.8.)
-struct SumPlan {
-  int tile, splits;
-  long feats;
-};
 SumPlan bf16_sum_plan(long Mp, long D, long K, bool padded_feats) {
   const long Dp = round_up(D, PAD_H), kBlocks = K / 64;
-  SumPlan best = {64, 1, padded_feats ? Dp : round_up(D, 64)};
-  double us = 1e30;
+  SumPlan best = {64, 1, padded_feats ? Dp : round_up(D, 64), 1e30};
   auto consider = [&](int tile, int S, long feats) {
-    const double t = bf16_us(PLAIN_SUM, tile, Mp, feats, K, S) * (tile == 256 ? KEEP_LARGE : 1.0) + (S > 1 ? 5.0 + (S + 1) * (double)Mp * Dp * 4.0 / 7e6 : 0.0);
-    if (t >= us) return;
-    us = t;
-    best = {tile, S, feats};
+    const double t = bf16_us(PLAIN_SUM, tile, Mp, feats, K, S) * (tile == 256 ? KEEP_LARGE_SUM : 1.0) + (S > 1 ? 5.0 + (S + 1) * (double)Mp * Dp * 4.0 / 7e6 : 0.0);
+    if (t < best.us) best = {tile, S, feats, t};
   };
   if (Mp % 256 == 0) consider(256, desired_splits(Mp, Dp, kBlocks), Dp);
   for (int tile : {128, 64}) {
@@ -457,13 +491,27 @@ StepPlan step_plan(const rnnlm_config &c, int Bp, int Hp) {
   return {false, (int)std::min({std::max<long>(1, 512 / tiles), 8L, kBlocks}), rows};
 }
 
-// Rows the contractions of a window of Mrows positions walk (MpMax is a multiple of 256).  Long fp32 windows keep whole
-// 256-row tiles: the padding is below 2 % there.
-constexpr long F32_TRIM_ROWS = 16384;
+// Rows the contractions of a window of Mrows positions walk (MpMax is a multiple of 256).  Long windows keep whole 256-row
+// tiles: the padding is below 2 % there.
+constexpr long TRIM_ROWS = 16384;
 long window_rows(const rnnlm_config &c, long Mrows) {
-  if (c.precision != RNNLM_FP32)
-    return bf16_extent(OUT_FWD, Mrows, round_up(c.V, PAD_V), terms<bf16_t>(c.P > 0 ? c.P : c.H));
-  if (Mrows > F32_TRIM_ROWS) return round_up(Mrows, PAD_M);
+  if (Mrows > TRIM_ROWS) return round_up(Mrows, PAD_M);
+  if (c.precision != RNNLM_FP32) {
+    // what the output layer, the pass over the logits and the contraction over the vocabulary take of them
+    const long Vp = round_up(c.V, PAD_V), D = c.P > 0 ? c.P : c.H, K = terms<bf16_t>(D);
+    long best = 0;
+    double us = 1e30;
+    for (long pad : {256, 128, 64}) {
+      const long n = round_up(Mrows, pad);
+      const double t = bf16_us(OUT_FWD, bf16_tile(OUT_FWD, Vp, n, K), Vp, n, K) + 0.75e-6 * n * Vp +
+                       bf16_sum_plan(n, D, Vp, c.P > 0).us;
+      if (t < us) {
+        us = t;
+        best = n;
+      }
+    }
+    return best;
+  }
   return f32_extent(Mrows, round_up(c.V, PAD_V), c.P > 0 ? c.P : c.H, 1);
 }
 // Columns the contraction over the vocabulary forms: the compressed architecture reads the padding, too.
@@ -485,14 +533,14 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   long statElems = (long)(Vp / 64) * MpMax;
   if (es == 4) {
     L.partElems = (long)MpMax * Dp;
-    for (long M = 64; M <= MpMax; M += M < F32_TRIM_ROWS ? 64 : PAD_M)
+    for (long M = 64; M <= MpMax; M += M < TRIM_ROWS ? 64 : PAD_M)
       L.partElems = std::max(
           L.partElems, f32_plan(M, features_formed(c, M, MAX_SPLITS, MpMax), c.V, MAX_SPLITS, MpMax).splits * M * Dp);
   } else {
     L.partElems = statElems = 0;
-    for (long M = 64; M <= MpMax; M += 64) {
+    for (long M = 64; M <= MpMax; M += M < TRIM_ROWS ? 64 : PAD_M) {
       L.partElems = std::max(L.partElems, bf16_sum_plan(M, Pp > 0 ? c.P : c.H, Vp, Pp > 0).splits * M * Dp);
-      statElems = std::max(statElems, Vp / bf16_tile(OUT_FWD, Vp, M, terms<bf16_t>(Pp > 0 ? c.P : c.H)) * M);
+      statElems = std::max(statElems, stat_parts(Vp, M, terms<bf16_t>(Pp > 0 ? c.P : c.H)) * M);
     }
   }
   const StepPlan step = step_plan(c, Bp, Hp);
@@ -567,6 +615,16 @@ void make_layout(const rnnlm_config &c, int &Hp, int &Vp, int &Bp, int &MpMax, i
   L.ring = take(plan.nwg > 0 ? 2 * align256(plan.ring_bytes((int)es)) : 0);  // forward, backward
   L.scalars = take(256);  // [0]: int nseg, [4]: int nseg of the noise-contrastive update list, [8..19]: int flags[3], [32]: double sum, [40]: double running
   L.total = o;
+}
+
+const WindowPlan &window_plan(rnnlm_t *h, long Mrows) {
+  WindowPlan &p = h->window;
+  if (p.Mrows != Mrows) {
+    p.Mp = window_rows(h->cfg, Mrows);
+    if (h->cfg.precision != RNNLM_FP32) p.sum = bf16_sum_plan(p.Mp, h->D, h->Vp, h->cfg.P > 0);
+    p.Mrows = Mrows;
+  }
+  return p;
 }
 
 template <typename P>
@@ -801,9 +859,9 @@ bool scan_ids(const rnnlm_t *h, int Tn, const UpdateTargets &u) {
 // stream: fp32 V = 1000, H = 64, 4x8 92 and 67 us; bf16 V = 3000, H = 256, 16x8 111 and 106, 32x30 164 and 170.  Beyond the
 // line fp32 still gains (V = 10000, H = 256, 32x10 165 and 146; V = 10000, H = 512, 32x30 476 and 469; V = 20000, H = 1024,
 // 32x30 1269 and 1273), bf16 below some 500 positions (V = 30000, H = 256, 16x8 148 and 140; 32x30 227 and 231).
-bool short_output_update(const rnnlm_t *h, int Tn) {
+bool short_output_update(rnnlm_t *h, int Tn) {
   const double n = (double)h->Vp * h->Dp, rate = h->cfg.precision == RNNLM_FP32 ? 1e8 : 6e8;  // per us
-  return 2.0 * n * window_rows(h->cfg, (long)Tn * h->Bp) / rate + 8.0 * n / 4e6 < 15.0;
+  return 2.0 * n * window_plan(h, (long)Tn * h->Bp).Mp / rate + 8.0 * n / 4e6 < 15.0;
 }
 
 // train: a backward pass follows.  sort_inputs: its embedding update wants the input ids sorted: started on the side
@@ -815,7 +873,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp, Vp = h->Vp;
   const int Mrows = Tn * Bp;
-  const int Mp = (int)window_rows(h->cfg, Mrows);
+  const int Mp = (int)window_plan(h, Mrows).Mp;
   const long ldz = h->MpMax;
   T *Hs_c = at<T>(h, h->L.Hs_c);
   float *X32 = at<float>(h, h->L.X32);
@@ -947,13 +1005,23 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     epi.ldp = Mp;
     if constexpr (sizeof(T) == 2) {
       const int tile = bf16_tile(OUT_FWD, Vp, Mp, terms<T>(h->D));
-      nPart = Vp / tile;
+      const long rows = large_rows(Vp, Mp, terms<T>(h->D));
+      nPart = (int)stat_parts(Vp, Mp, terms<T>(h->D));
       // thousands of short tiles: one persistent workgroup per compute unit walks them, in bands of 8 vocabulary
       // row panels (the 32 tiles an XCD works on at a time then share 8 row panels and 4 position panels in its L2:
       // measured best of 1..16 on all three large configurations)
-      if (tile == BIG) {
+      if (tile == BIG && rows == Vp) {
         HIP_TRY((launch_gemm_dma<BIG, BIG, 4, 2, ROWK, ROWK, true>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp,
                                                                    terms<T>(h->D), 1, epi, 8)));
+      } else if (tile == BIG) {
+        EpiOutFwd<T> tail = epi;
+        tail.b += rows;
+        if (tail.ZT) tail.ZT += rows * ldz;
+        tail.part += rows / BIG * epi.ldp;
+        tail.V -= (int)rows;
+        tail.v0 = (int)rows;
+        HIP_TRY((launch_gemm_tail<4, 2, ROWK>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp, terms<T>(h->D), rows, epi,
+                                              tail, 8)));
       } else {
         HIP_TRY((bf16_small_gemm<ROWK, ROWK>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp, terms<T>(h->D), tile, 1,
                                              epi, 8)));
@@ -999,7 +1067,7 @@ template <typename T>
 int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, const WindowSum *wsum, hipStream_t st) {
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp;
-  const int Mrows = Tn * Bp, Mp = (int)window_rows(h->cfg, Mrows), M = Tn * c.B;
+  const int Mrows = Tn * Bp, Mp = (int)window_plan(h, Mrows).Mp, M = Tn * c.B;
   const int K = n.K, Kp = (int)round_up(K, 256);
   T *Hs1 = at<T>(h, h->L.Hs_c) + (long)Bp * Hp;
   T *Wn = at<T>(h, h->L.Wn_c);
@@ -1050,7 +1118,7 @@ int nce_forward(rnnlm_t *h, int Tn, const NceCall &n, const WindowSum *wsum, hip
 template <typename T>
 int nce_backward_h(rnnlm_t *h, int Tn, const NceCall &n, hipStream_t st) {
   const int Hp = h->Hp, Bp = h->Bp;
-  const int Mrows = Tn * Bp, Mp = (int)window_rows(h->cfg, Mrows);
+  const int Mrows = Tn * Bp, Mp = (int)window_plan(h, Mrows).Mp;
   const int Kp = (int)round_up(n.K, 256);
   float *dHs32 = at<float>(h, h->L.dHs32);
   StageTimer tm(h, RNNLM_STAGE_NCE_BWD_H, st);
@@ -1169,7 +1237,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp, Vp = h->Vp;
   const int Mrows = Tn * Bp;
-  const int Mp = (int)window_rows(h->cfg, Mrows);
+  const int Mp = (int)window_plan(h, Mrows).Mp;
   const long ldz = h->MpMax, rowTerms = terms<T>(Mrows);
   T *Hs_c = at<T>(h, h->L.Hs_c);
   T *ZT = at<T>(h, h->L.ZT);
@@ -1204,7 +1272,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     const int max_splits = (int)std::min<long>(MAX_SPLITS, std::max<long>(1, h->L.partElems / per));
     const long Dn = sizeof(T) == 4 ? features_formed(c, Mp, max_splits, ldz) : Dp;
     const F32Plan plan = sizeof(T) == 4 ? f32_plan(Mp, Dn, c.V, max_splits, ldz) : F32Plan{};
-    const SumPlan sum = sizeof(T) == 2 ? bf16_sum_plan(Mp, h->D, Vp, c.P > 0) : SumPlan{};
+    const SumPlan sum = window_plan(h, Mrows).sum;
     int S = sizeof(T) == 4 ? plan.splits : sum.splits;
     if ((long)S * per > h->L.partElems) S = (int)(h->L.partElems / per);
     if (S < 1) S = 1;
@@ -1609,7 +1677,7 @@ bool window_args_ok(rnnlm_t *h, const int32_t *x, const int32_t *y, int T) {
 // = 1000, H = 64, one position 160 and 138 us, 1024 positions 167 and 157, 2048 positions 175 and 180 (V = 20000, H = 1024,
 // 128 positions, not short: 229 and 232); noise-contrastive, V = 10000, H = 512, 256 positions 213 and 182, V = 64000,
 // H = 1024, 1280 positions 205 and 187, 2560 positions 249 and 253.
-bool rms_overlaps(const rnnlm_t *h, int Tn, bool nce) {
+bool rms_overlaps(rnnlm_t *h, int Tn, bool nce) {
   return (long)Tn * h->cfg.B > 1024 || !(nce || short_output_update(h, Tn));
 }
 int rms_decay(rnnlm_t *h, float *r0, float *r1, float *r2, float rho, bool overlap, hipStream_t st) {
@@ -1702,8 +1770,8 @@ struct LongWindows {
     const long Mmax = round_up(T * h->Bp, PAD_M);
     auto stats = [&](long M) {
       const long Mp = window_rows(c, M);
-      const int tile = es == 4 ? f32_plan(h->Vp, Mp, h->D, 1).tile : bf16_tile(OUT_FWD, h->Vp, Mp, terms<bf16_t>(h->D));
-      return (size_t)(h->Vp / tile) * Mp * 8;
+      const long parts = es == 4 ? h->Vp / f32_plan(h->Vp, Mp, h->D, 1).tile : stat_parts(h->Vp, Mp, terms<bf16_t>(h->D));
+      return (size_t)parts * Mp * 8;
     };
     size_t o = L.ZT;
     auto take = [&](size_t &at, size_t bytes) {
@@ -2042,7 +2110,7 @@ int rnnlm_perplexity(rnnlm_t *h, const int32_t *tok, int64_t N, int32_t T, doubl
       const int Tn = (int)std::min(many.windows, nchunks - k) * T;
       hipLaunchKernelGGL(stream_chunk_kernel, dim3(blocks_for((long)Tn * B, 256)), dim3(256), 0, st, tok + k * T, L, 0L, Tn, B,
                          xt, yt);
-      const long M = (long)Tn * h->Bp, pad = (window_rows(h->cfg, M) - M) * h->Hp;
+      const long M = (long)Tn * h->Bp, pad = (window_plan(h, M).Mp - M) * h->Hp;
       if (many.windows > 1 && pad > 0) {  // what was there may be anything: rows of states past the positions are operands
         const size_t es = h->cfg.precision == RNNLM_FP32 ? 4 : 2;
         const long n = pad * (long)es / 4;
