@@ -14,22 +14,30 @@
 
 namespace rnnlm_dev {
 
+//
+// The same contraction by itself (STEP_STORE, STEP_STORE32): the inserted layers of the compressed architecture over the few
+// positions of a scored text (P = 512, H = 1024, 20 positions: 5.2 and 7.2 us on 64x64 tiles, whose workgroups walk 16 and 32
+// blocks one after the other; scoring call 43.0 and 37.6).
+enum : int { STEP_FORWARD, STEP_BACKWARD, STEP_STORE, STEP_STORE32 };
+
 struct RnnStepArgs {
   const void *W;      // forward: U_c [Hp][Hp]; backward: UT_c [Hp][Hp] (row n holds the k-contiguous operand)
-  const void *state;  // rows [B][Hp] that are contracted: previous states, or the gradients of the next position
+  const void *state;  // rows [B][lds] that are contracted: previous states, or the gradients of the next position
   const float *X;     // forward: additive input; backward: gradient from the output layer; [B][Hp]
   const void *h;      // backward: states of the position [B][Hp]
   void *out;          // compute type [B][Hp]: new states, or gradients
   float *out32;       // backward: gradients in fp32
   float *h_state;     // forward: [B][H] or nullptr
-  int B, H, Hp;
+  int B, H, Hp;       // rows, units, row length of what is written
+  int lds;            // row length of the operands (Hp, where they are states)
   int pieces;         // 128-byte pieces of a row that are contracted (0: nothing flows in)
 };
 
-template <typename T, int RT, bool BACKWARD>
+template <typename T, int RT, int MODE>
 __global__ void __launch_bounds__(512) rnn_step_kernel(const RnnStepArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int ES = sizeof(T), NWAVE = 8;
+  constexpr bool BACKWARD = MODE == STEP_BACKWARD, STORE = MODE == STEP_STORE || MODE == STEP_STORE32;
   constexpr int DEPTH = RT == 1 ? 4 : RT == 2 ? 3 : 2;   // pieces of a wave in flight (what the LDS holds)
   constexpr int PIECE = 2048, SLOT = (1 + RT) * PIECE;   // 16 rows x 128 bytes; matrix, then RT row blocks of states
   constexpr int LOADS = 2 * (1 + RT);                    // a piece is two kilobyte loads
@@ -45,7 +53,7 @@ __global__ void __launch_bounds__(512) rnn_step_kernel(const RnnStepArgs a) {
   f32x4_t x = {0.0f, 0.0f, 0.0f, 0.0f};
   typedef T tv_t __attribute__((ext_vector_type(4)));
   tv_t hv = {};
-  if (mine) {
+  if (mine && !STORE) {
     x = *reinterpret_cast<const f32x4_t *>(a.X + (long)erow * Hp + ecol);
     if (BACKWARD) hv = *reinterpret_cast<const tv_t *>(static_cast<const T *>(a.h) + (long)erow * Hp + ecol);
   }
@@ -69,7 +77,7 @@ __global__ void __launch_bounds__(512) rnn_step_kernel(const RnnStepArgs a) {
       r[3] = 0x00020000;
       return r;
     };
-    const long ld = (long)Hp * ES;
+    const long ld = (long)a.lds * ES;
     const i32x4_t rw = resource(static_cast<const char *>(a.W) + unit0 * ld, 16 * ld);
     const i32x4_t rs = resource(static_cast<const char *>(a.state) + row0 * ld, (a.B - row0) * ld);
     int off[1 + RT][2];
@@ -149,13 +157,13 @@ __global__ void __launch_bounds__(512) rnn_step_kernel(const RnnStepArgs a) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float h = BACKWARD ? to_f32(hv[e]) : 0.0f;
-    o[e] = BACKWARD ? (x[e] + s[e]) * h * (1.0f - h) : sigmoidf_(s[e] + x[e]);
+    o[e] = STORE ? s[e] : BACKWARD ? (x[e] + s[e]) * h * (1.0f - h) : sigmoidf_(s[e] + x[e]);
     if (ecol + e >= a.H) o[e] = 0.0f;
     oc[e] = from_f32<T>(o[e]);
   }
-  *reinterpret_cast<tv_t *>(static_cast<T *>(a.out) + (long)erow * Hp + ecol) = oc;
-  if (BACKWARD) *reinterpret_cast<f32x4_t *>(a.out32 + (long)erow * Hp + ecol) = o;
-  if (!BACKWARD && a.h_state)
+  if (MODE != STEP_STORE32) *reinterpret_cast<tv_t *>(static_cast<T *>(a.out) + (long)erow * Hp + ecol) = oc;
+  if (BACKWARD || MODE == STEP_STORE32) *reinterpret_cast<f32x4_t *>(a.out32 + (long)erow * Hp + ecol) = o;
+  if (MODE == STEP_FORWARD && a.h_state)
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (ecol + e < a.H) a.h_state[(long)erow * a.H + ecol + e] = o[e];

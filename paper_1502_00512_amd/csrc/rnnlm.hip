@@ -785,6 +785,31 @@ int launch_rnn_resident(rnnlm_t *h, int Tn, bool advance_state, hipStream_t st) 
 int step_groups(const rnnlm_config &c, int blocks) { return (int)((c.H + 15) / 16 * ((c.B + 16L * blocks - 1) / (16 * blocks))); }
 bool step_in_one(const rnnlm_config &c) { return c.H <= 4096 && c.B <= 4096 && step_groups(c, 4) <= 256; }
 int step_blocks(const rnnlm_config &c) { return c.B <= 16 ? 1 : step_groups(c, 2) <= 256 ? 2 : 4; }
+template <typename T, int MODE>
+void launch_step_kernel(const RnnStepArgs &a, int rt, hipStream_t st) {
+  hipLaunchKernelGGL((rt == 1   ? rnn_step_kernel<T, 1, MODE>
+                      : rt == 2 ? rnn_step_kernel<T, 2, MODE>
+                                : rnn_step_kernel<T, 4, MODE>),
+                     dim3(blocks_for(a.H, 16), blocks_for(a.B, 16 * rt)), dim3(512), 0, st, a);
+}
+// out = rows . W^T for a few rows (row lengths ldo and ldk; `units` columns of out, `terms_` values of a row).
+constexpr int FEW_ROWS = 64;
+template <int MODE>
+int few_rows(const bf16_t *rows, const bf16_t *W, long ldk, long terms_, void *out, long ldo, int n, int units, hipStream_t st) {
+  RnnStepArgs a = {};
+  a.W = W;
+  a.state = rows;
+  a.out = out;
+  a.out32 = static_cast<float *>(out);
+  a.B = n;
+  a.H = units;
+  a.Hp = (int)ldo;
+  a.lds = (int)ldk;
+  a.pieces = (int)(terms_ * 2 / 128);
+  launch_step_kernel<bf16_t, MODE>(a, n <= 16 ? 1 : n <= 32 ? 2 : 4, st);
+  HIP_TRY(hipGetLastError());
+  return RNNLM_OK;
+}
 template <typename T, bool BACKWARD>
 int launch_rnn_step(rnnlm_t *h, int t, bool contract, float *h_state, hipStream_t st) {
   const rnnlm_config &c = h->cfg;
@@ -800,13 +825,9 @@ int launch_rnn_step(rnnlm_t *h, int t, bool contract, float *h_state, hipStream_
   a.h_state = h_state;
   a.B = c.B;
   a.H = c.H;
-  a.Hp = h->Hp;
+  a.Hp = a.lds = h->Hp;
   a.pieces = contract ? (int)(terms<T>(c.H) * (long)sizeof(T) / 128) : 0;
-  const int rt = step_blocks(c);
-  hipLaunchKernelGGL((rt == 1   ? rnn_step_kernel<T, 1, BACKWARD>
-                      : rt == 2 ? rnn_step_kernel<T, 2, BACKWARD>
-                                : rnn_step_kernel<T, 4, BACKWARD>),
-                     dim3(blocks_for(c.H, 16), blocks_for(c.B, 16 * rt)), dim3(512), 0, st, a);
+  launch_step_kernel<T, BACKWARD ? STEP_BACKWARD : STEP_FORWARD>(a, step_blocks(c), st);
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
 }
@@ -931,15 +952,24 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     }
   }
 
+  // (training windows contract over the padded rows of what the layers give as well; fp32 keeps its split operands, which
+  // round less than the fp32 cores)
+  const bool few = sizeof(T) == 2 && !train && Mrows <= FEW_ROWS;
   if (c.P > 0) {
     // layer below the state: X[m][i] = sum_p x_m[p] A[i][p], the additive input of every recurrent step
     StageTimer tm(h, RNNLM_STAGE_PROJ, st);
-    EpiPartial epi;
-    epi.part = X32;
-    epi.ld = Hp;
-    epi.split_stride = 0;
-    HIP_TRY((mid_gemm<T, ROWK, ROWK>(st, at<T>(h, h->L.Xp_c), h->Pp, at<T>(h, h->L.A_c), h->Pp, Mp, Hp, terms<T>(c.P), 1,
-                                      epi)));
+    if (few) {
+      int rc = few_rows<STEP_STORE32>(at<bf16_t>(h, h->L.Xp_c), at<bf16_t>(h, h->L.A_c), h->Pp, terms<bf16_t>(c.P), X32, Hp, Mrows,
+                                      c.H, st);
+      if (rc) return rc;
+    } else {
+      EpiPartial epi;
+      epi.part = X32;
+      epi.ld = Hp;
+      epi.split_stride = 0;
+      HIP_TRY((mid_gemm<T, ROWK, ROWK>(st, at<T>(h, h->L.Xp_c), h->Pp, at<T>(h, h->L.A_c), h->Pp, Mp, Hp, terms<T>(c.P), 1,
+                                        epi)));
+    }
   }
 
   if (persistent_ok(h)) {
@@ -983,11 +1013,16 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
   const T *feat = Hs_c + (long)Bp * Hp;  // what the output layer reads: the states, or the layer above them
   if (c.P > 0) {
     StageTimer tm(h, RNNLM_STAGE_PROJ, st);
-    EpiStore<T> epi;
-    epi.outc = at<T>(h, h->L.P_c);
-    epi.ld = h->Pp;
-    HIP_TRY((mid_gemm<T, ROWK, ROWK>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.C_c), Hp, Mp,
-                                                        h->Pp, terms<T>(c.H), 1, epi)));
+    if (few) {
+      int rc = few_rows<STEP_STORE>(at<bf16_t>(h, h->L.Hs_c) + (long)Bp * Hp, at<bf16_t>(h, h->L.C_c), Hp, terms<bf16_t>(c.H),
+                                    at<bf16_t>(h, h->L.P_c), h->Pp, Mrows, c.P, st);
+      if (rc) return rc;
+    } else {
+      EpiStore<T> epi;
+      epi.outc = at<T>(h, h->L.P_c);
+      epi.ld = h->Pp;
+      HIP_TRY((mid_gemm<T, ROWK, ROWK>(st, Hs_c + (long)Bp * Hp, Hp, at<T>(h, h->L.C_c), Hp, Mp, h->Pp, terms<T>(c.H), 1, epi)));
+    }
     feat = at<T>(h, h->L.P_c);
   }
   if (!with_output) return RNNLM_OK;  // the scoring calls only wanted the layer above the states

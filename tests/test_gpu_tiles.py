@@ -100,3 +100,19 @@ def test_perplexity_of_long_texts(V, H, P, B, T, windows, precision):
                 m.rnnlm_train_chunk(*m.rnnlm_stream_chunk(dtok, k, T), 0.1)
         assert torch.equal(a.E, b.E) and torch.equal(a.U, b.U) and torch.equal(a.b, b.b)
     a.rnnlm_check()
+
+
+# the inserted layers over few positions, one, two and four blocks of 16, against the same layers over the padded window
+# (a window of gradients, which keeps the log-probabilities)
+@pytest.mark.parametrize("V,H,P,B,T", [(500, 100, 70, 1, 1), (900, 256, 64, 2, 8), (2000, 1000, 500, 1, 20), (700, 333, 130, 9, 7)])
+def test_inserted_layers_over_few_positions(V, H, P, B, T):
+    rng = np.random.default_rng(V)
+    w = lambda *s: rng.uniform(-0.2, 0.2, s).astype(np.float32)
+    g = binding.Rnnlm(w(V, P), w(H, H), None, w(V), B, T, binding.RNNLM_BF16_FP32MASTER, A=w(H, P), C_=w(P, H))
+    x = torch.as_tensor(rng.integers(0, V, (T, B)).astype(np.int32)).cuda()
+    y = torch.as_tensor(rng.integers(0, V, (T, B)).astype(np.int32)).cuda()
+    ref = g.rnnlm_grad_chunk_compressed(x, y)["logp"]  # (the state is left as it was)
+    got = g.rnnlm_forward_logprob(x, y)
+    # sums in another order before two roundings to 8 bits: a few of them, 2^-9 each, on logits of the order of 1
+    assert (got - ref).abs().max().item() <= 2e-2
+    g.rnnlm_check()
