@@ -62,6 +62,7 @@ struct SumPlan {
 };
 struct WindowPlan {
   long Mrows = -1, Mp = 0;
+  int parts = 0;  // softmax statistics of a position
   SumPlan sum = {};
 };
 
@@ -621,11 +622,18 @@ const WindowPlan &window_plan(rnnlm_t *h, long Mrows) {
   WindowPlan &p = h->window;
   if (p.Mrows != Mrows) {
     p.Mp = window_rows(h->cfg, Mrows);
-    if (h->cfg.precision != RNNLM_FP32) p.sum = bf16_sum_plan(p.Mp, h->D, h->Vp, h->cfg.P > 0);
+    if (h->cfg.precision != RNNLM_FP32) {
+      p.sum = bf16_sum_plan(p.Mp, h->D, h->Vp, h->cfg.P > 0);
+      p.parts = (int)stat_parts(h->Vp, p.Mp, terms<bf16_t>(h->D));
+    } else {
+      p.parts = h->Vp / f32_plan(h->Vp, p.Mp, h->D, 1).tile;
+    }
     p.Mrows = Mrows;
   }
   return p;
 }
+// The softmax-gradient pass merges the statistics of a training window itself.
+bool merged_in_pass(const WindowPlan &p) { return p.Mp <= SHORT_POSITIONS && p.parts * p.Mp <= SHORT_STATS; }
 
 template <typename P>
 P *at(rnnlm_t *h, size_t off) {
@@ -1026,7 +1034,6 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     feat = at<T>(h, h->L.P_c);
   }
   if (!with_output) return RNNLM_OK;  // the scoring calls only wanted the layer above the states
-  int nPart;
   {
     StageTimer tm(h, RNNLM_STAGE_OUT_FWD, st);
     EpiOutFwd<T> epi;
@@ -1041,7 +1048,6 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     if constexpr (sizeof(T) == 2) {
       const int tile = bf16_tile(OUT_FWD, Vp, Mp, terms<T>(h->D));
       const long rows = large_rows(Vp, Mp, terms<T>(h->D));
-      nPart = (int)stat_parts(Vp, Mp, terms<T>(h->D));
       // thousands of short tiles: one persistent workgroup per compute unit walks them, in bands of 8 vocabulary
       // row panels (the 32 tiles an XCD works on at a time then share 8 row panels and 4 position panels in its L2:
       // measured best of 1..16 on all three large configurations)
@@ -1064,12 +1070,12 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
     } else {
       const F32Plan plan = f32_plan(Vp, Mp, h->D, 1);
       HIP_TRY((f32_gemm<ROWK, ROWK>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp, round_up(h->D, 32), plan, epi, 8)));
-      nPart = Vp / plan.tile;
     }
   }
+  if (train && merged_in_pass(window_plan(h, Mrows))) return RNNLM_OK;
   StageTimer tm(h, RNNLM_STAGE_STATS, st);
   hipLaunchKernelGGL(merge_stats_kernel, dim3(blocks_for(Mrows, MERGE_M)), dim3(1024), 0, st, at<float2>(h, h->L.stat),
-                     nPart, Mp, Tn, c.B, Bp, zy, lse, at<float>(h, h->L.logp_int), logp_out,
+                     window_plan(h, Mrows).parts, Mp, Tn, c.B, Bp, zy, lse, at<float>(h, h->L.logp_int), logp_out,
                      wsum ? p_counter(h) + sync_word(0, 0) : nullptr, wsum ? *wsum : WindowSum{});
   HIP_TRY(hipGetLastError());
   return RNNLM_OK;
@@ -1267,8 +1273,8 @@ int launch_window_update(WindowUpdate<T> &w, int tile, int Mrows, int W, hipStre
 // rec_stream (may be nullptr) receives the stream whose next launch is ordered behind the recurrent update: work on the
 // other stream is not.
 template <typename T>
-int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *nce, hipStream_t st,
-                    hipStream_t *rec_stream = nullptr) {
+int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *nce, hipStream_t st, hipStream_t *rec_stream,
+                    float *logp_out, const WindowSum &wsum) {
   const rnnlm_config &c = h->cfg;
   const int Hp = h->Hp, Bp = h->Bp, Vp = h->Vp;
   const int Mrows = Tn * Bp;
@@ -1293,8 +1299,12 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   // fused softmax gradient + bias update, in place on the vocabulary-major logits
   {
     StageTimer tm(h, RNNLM_STAGE_SOFTMAX_GRAD, st);
-    hipLaunchKernelGGL(softmax_grad_kernel<T>, dim3(Vp / 16), dim3(256), 0, st, ZT, ldz, Mp, c.V, Vp,
-                       at<float>(h, h->L.lse), yp, 1.0f / (float)(Tn * c.B), h->buf.b, u.b, u.alpha, u.lr);
+    const WindowPlan &wp = window_plan(h, Mrows);
+    const StatsMerge merge = {at<float2>(h, h->L.stat), wp.parts, Tn, c.B, Bp, at<float>(h, h->L.zy), at<float>(h, h->L.logp_int),
+                              logp_out, wsum};
+    hipLaunchKernelGGL((merged_in_pass(wp) ? softmax_grad_kernel<T, true> : softmax_grad_kernel<T, false>), dim3(Vp / 16),
+                       dim3(256), 0, st, ZT, ldz, Mp, c.V, Vp, at<float>(h, h->L.lse), yp, 1.0f / (float)(Tn * c.B), h->buf.b, u.b,
+                       u.alpha, u.lr, merge);
     HIP_TRY(hipGetLastError());
   }
 
@@ -1649,7 +1659,7 @@ int window_call(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float *l
     rc = nce_forward<T>(h, Tn, *nce, want_sum ? &ws : nullptr, st);
     if (rc) return rc;
   }
-  if (u) rc = backward_window<T>(h, Tn, *u, nce, st, rec_stream);
+  if (u) rc = backward_window<T>(h, Tn, *u, nce, st, rec_stream, logp, ws);
   return rc;
 }
 
