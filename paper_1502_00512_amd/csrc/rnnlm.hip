@@ -883,6 +883,7 @@ bool scan_ids(const rnnlm_t *h, int Tn, const UpdateTargets &u) {
   return u.e_compact_ld == 0 && (long)Tn * h->cfg.B <= (h->cfg.P > 0 ? SCAN_MAX : 1024);
 }
 
+// (Plain windows whose updates share a launch, update.h, need no second stream.)
 // Where the output weight update is over before a second stream is tied in and out (four events: 20-30 us of host time
 // and of latency between the streams), the small updates stay on the caller's stream.  With and without the second
 // stream: fp32 V = 1000, H = 64, 4x8 92 and 67 us; bf16 V = 3000, H = 256, 16x8 111 and 106, 32x30 164 and 170.  Beyond the
@@ -1528,7 +1529,8 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
   } else {
     {
     // Wo[v][j] -= lr * sum_m dz[v][m] Hs[m][j]; compressed architecture: the output-side update of the tied matrix,
-    // E[v][p] -= lr * sum_m dz[v][m] p[m][p].  bf16 compressed: contracted transposed (tile rows = p, tile columns = v).
+    // E[v][p] -= lr * sum_m dz[v][m] p[m][p].  bf16 compressed on large tiles: contracted transposed (tile rows = p, tile
+    // columns = v).
     // Everything else in the matrix's own orientation (tile rows = v, tile columns = j), whose update epilogue touches two
     // 128-byte lines per wave instruction instead of 32 (fp32, V = 64000, H = 1024, 1280 positions: 893 -> 841 us).
     StageTimer tm(h, RNNLM_STAGE_OUT_BWD_W, st, !opened);
