@@ -17,7 +17,8 @@ namespace rnnlm_dev {
 //
 // The same contraction by itself (STEP_STORE, STEP_STORE32): the inserted layers of the compressed architecture over the few
 // positions of a scored text (P = 512, H = 1024, 20 positions: 5.2 and 7.2 us on 64x64 tiles, whose workgroups walk 16 and 32
-// blocks one after the other; scoring call 43.0 and 37.6).
+// blocks one after the other; scoring call 43.0 and 37.6).  It writes whole rows: columns past the units become zeros, which
+// the contractions that follow read.
 enum : int { STEP_FORWARD, STEP_BACKWARD, STEP_STORE, STEP_STORE32 };
 
 struct RnnStepArgs {
@@ -59,7 +60,8 @@ __global__ void __launch_bounds__(512) rnn_step_kernel(const RnnStepArgs a) {
   }
 
   // this wave's pieces: first .. first + n - 1
-  const int base = a.pieces / NWAVE, more = a.pieces % NWAVE;
+  const int pieces = unit0 < a.H ? a.pieces : 0;  // (columns past the units: zeros)
+  const int base = pieces / NWAVE, more = pieces % NWAVE;
   const int n = base + (wave < more), first = wave * base + min(wave, more);
   f32x4_t acc[RT][2];
 #pragma unroll

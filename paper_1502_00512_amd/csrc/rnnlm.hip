@@ -798,9 +798,10 @@ void launch_step_kernel(const RnnStepArgs &a, int rt, hipStream_t st) {
   hipLaunchKernelGGL((rt == 1   ? rnn_step_kernel<T, 1, MODE>
                       : rt == 2 ? rnn_step_kernel<T, 2, MODE>
                                 : rnn_step_kernel<T, 4, MODE>),
-                     dim3(blocks_for(a.H, 16), blocks_for(a.B, 16 * rt)), dim3(512), 0, st, a);
+                     dim3(blocks_for(MODE == STEP_STORE || MODE == STEP_STORE32 ? a.Hp : a.H, 16), blocks_for(a.B, 16 * rt)),
+                     dim3(512), 0, st, a);
 }
-// out = rows . W^T for a few rows (row lengths ldo and ldk; `units` columns of out, `terms_` values of a row).
+// out = rows . W^T for a few rows (row lengths ldo and ldk; `units` columns of out and zeros up to ldo, `terms_` values of a row).
 constexpr int FEW_ROWS = 64;
 template <int MODE>
 int few_rows(const bf16_t *rows, const bf16_t *W, long ldk, long terms_, void *out, long ldo, int n, int units, hipStream_t st) {

@@ -116,3 +116,45 @@ def test_inserted_layers_over_few_positions(V, H, P, B, T):
     # sums in another order before two roundings to 8 bits: a few of them, 2^-9 each, on logits of the order of 1
     assert (got - ref).abs().max().item() <= 2e-2
     g.rnnlm_check()
+
+
+def compressed(V, H, P, B, T):
+    rng = np.random.default_rng(V + P)
+    w = lambda *s: rng.uniform(-0.2, 0.2, s).astype(np.float32)
+    return binding.Rnnlm(w(V, P), w(H, H), None, w(V), B, T, binding.RNNLM_BF16_FP32MASTER, A=w(H, P), C_=w(P, H))
+
+
+# P: the output layer reads the layer above the state in whole blocks of 64 units, the scores in blocks of 256
+@pytest.mark.parametrize("V,H,P,B,T", [(10000, 256, 100, 1, 20), (3000, 300, 70, 3, 7), (5000, 512, 257, 2, 10)])
+def test_a_short_text_after_a_long_one(V, H, P, B, T):
+    """What a long text leaves in the workspace has no part in a text of up to 64 positions."""
+    tok = torch.as_tensor(synth.zipf_tokens(20 * B * T + B + 1, V, 1.05, 11)).cuda()
+    short = tok[:3 * B * T + B + 1].contiguous()
+    g, fresh = compressed(V, H, P, B, T), compressed(V, H, P, B, T)
+    for _ in range(2):
+        g.rnnlm_perplexity(tok, T)
+        assert g.rnnlm_perplexity(short, T) == fresh.rnnlm_perplexity(short, T)
+        assert torch.equal(g.h_state, fresh.h_state)
+
+
+@pytest.mark.parametrize("V,H,P,B,T", [(900, 256, 64, 2, 8), (2000, 300, 100, 1, 20), (700, 333, 257, 9, 7)])
+def test_scores_after_a_window_that_diverged(V, H, P, B, T):
+    """A window that is not finite leaves nothing behind once the weights and the state are finite again."""
+    tok = synth.zipf_tokens(2 * B * T + B + 1, V, 1.05, 5)
+    x, y = (torch.as_tensor(a).cuda() for a in O.stream_chunk(tok, B, T, 0))
+    g, fresh = compressed(V, H, P, B, T), compressed(V, H, P, B, T)
+    g.U[0, 0] = float("nan")
+    g.rnnlm_sync_compute_copies()
+    g.rnnlm_train_chunk(x, y, 0.1)
+    with pytest.raises(binding.RnnlmError) as e:
+        g.rnnlm_check()
+    assert e.value.status == -3  # RNNLM_ERR_NONFINITE
+    for name in ("E", "U", "A", "C", "b", "h_state"):
+        getattr(g, name).copy_(getattr(fresh, name))
+    g.rnnlm_sync_compute_copies()
+    cand = torch.as_tensor(np.random.default_rng(3).integers(0, V, (T, B, 10)).astype(np.int32)).cuda()
+    for call in (lambda m: m.rnnlm_forward_score(x, y), lambda m: m.rnnlm_forward_score_shortlist(x, cand),
+                 lambda m: m.rnnlm_forward_logprob(x, y)):
+        a, b = call(g), call(fresh)
+        assert torch.isfinite(b).all() and torch.equal(a, b)
+    g.rnnlm_check()
