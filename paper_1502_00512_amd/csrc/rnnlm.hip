@@ -286,7 +286,7 @@ long large_rows(long Mg, long Ng, long K, double *us = nullptr) {
   if (us) *us = all;
   if (Mg % 256 || Ng % 256) return Mg;  // (no large tiles)
   const long cols = Ng / 256, rounds = Mg / 256 * cols / 256, rows = rounds * 256 / cols * 256;
-  if (rounds == 0 || rows >= Mg) return Mg;
+  if (rows == 0 || rows >= Mg) return Mg;  // (0: the whole rounds do not fill a row of tiles)
   const double mixed = bf16_all_us(OUT_FWD, 256, rows, Ng, K) + bf16_all_us(OUT_FWD, 128, Mg - rows, Ng, K) - 3.0;
   if (mixed >= 0.85 * all && all - mixed < 8.0) return Mg;
   if (us) *us = mixed;

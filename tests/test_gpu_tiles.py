@@ -20,6 +20,7 @@ binding = pytest.importorskip("paper_1502_00512_amd.binding")
     (9000, 384, 32, 8),   # 256 positions exactly
     (700, 500, 96, 20),   # few words, long window: many positions per tile of words
     (12000, 300, 60, 16), # 128 x 128 tiles, units past a multiple of 256
+    (200, 64, 1024, 70),  # 71680 positions over one row of output tiles
 ])
 def test_bf16_window_against_oracle(V, H, B, T):
     E, U, Wo, b = synth.make_weights(V, H, "normal", 0.05, 911 + V)

@@ -44,6 +44,10 @@ for _ in range(2):
         rc = lib.rnnlm_train_chunk_rmsprop(h, x, y, T, f(0.1), f(0.9), f(1e-6), rms, None, None, st)
     elif call == "nce_rmsprop":
         rc = lib.rnnlm_nce_train_chunk_rmsprop(h, x, y, T, noise, args["K"], lnq, f(7.0), f(0.1), f(0.9), f(1e-6), rms, None, None, st)
+    elif call == "logprob":
+        rc = lib.rnnlm_forward_logprob(h, x, y, T, p(dev()), st)
+    elif call == "perplexity":
+        rc = lib.rnnlm_perplexity(h, x, C.c_int64(args["N"]), T, C.byref(C.c_double()), None, st)
     assert rc == 0, rc
 """
 
@@ -149,6 +153,17 @@ def test_the_contraction_over_the_vocabulary_reaches_long_rows_of_logits(runtime
     """fp32 handles of millions of positions: blocks of 32 or 64 rows of the logits are beyond 32-bit offsets."""
     launches, _ = enqueue(runtime, tmp_path, "train", V=V, H=H, P=P, B=B, T_max=T_max, T=T, precision=FP32)
     assert sum("gemm" in k for _, k, _ in launches) >= 6
+
+
+@pytest.mark.parametrize("call", ["train", "logprob", "perplexity"])
+@pytest.mark.parametrize("V,H,P,B,T_max,T", [
+    (256, 64, 0, 1024, 70, 70), (2, 72, 0, 1869, 46, 46), (200, 300, 0, 257, 256, 256), (256, 512, 0, 2048, 33, 33),
+    (22, 90, 0, 288, 1000, 300), (127, 100, 40, 2300, 100, 100), (256, 64, 0, 1024, 64, 64),
+])
+def test_long_windows_over_few_words_are_taken(runtime, tmp_path, call, V, H, P, B, T_max, T):
+    """bf16, one row of 256 x 256 output tiles and more than a round of them, whole rounds or not."""
+    launches, _ = enqueue(runtime, tmp_path, call, V=V, H=H, P=P, B=B, T_max=T_max, T=T, precision=BF16, N=3 * B * T + B + 1)
+    assert sum("EpiOutFwd" in k for _, k, _ in launches) >= 2
 
 
 @pytest.mark.parametrize("V,H,P,B,T_max,T", [
