@@ -304,8 +304,13 @@ int rnnlm_set_recurrent_exchange(rnnlm_t *h, int32_t mode);
 int rnnlm_measure_peaks(rnnlm_t *h, double *mfma_bf16_random_tflops, double *mfma_bf16_constant_tflops,
                         double *copy_gbs, void *stream);
 
-/* Stage timing with HIP events on the call's stream (for benchmarks; off by default).  Stages of a
- * window, in the order of the kernel sequence: */
+/* Stage timing with HIP events on the call's stream (for benchmarks; off by default).  Some windows run several
+ * stages in one launch: the three updates of a short one, the statistics of a very short one with the softmax
+ * gradient, the recurrent update of the compressed architecture (bf16) with those of the inserted layers.  While one
+ * of the stages that share a launch is timed, each takes a launch of its own, and the window is longer by that.
+ * (Statistics by themselves are added up in another order: the last bits of a very short window may differ.)
+ * rnnlm_perplexity runs as many windows of a text together as the workspace holds: one execution of each stage.
+ * Stages of a window, in the order of the kernel sequence: */
 typedef enum {
   RNNLM_STAGE_PREP = 0,         /* token check, state load, embedding gather */
   RNNLM_STAGE_RNN_FWD = 1,      /* T recurrent forward steps */
@@ -319,8 +324,8 @@ typedef enum {
   RNNLM_STAGE_EMB = 9,          /* sort/segments + segmented embedding update */
   RNNLM_STAGE_REDUCE = 10,      /* fixed-order sum of the split-K partials of stage 5 */
   /* noise-contrastive calls: stages 2-5 and 7 are replaced by */
-  RNNLM_STAGE_NCE_SCORE = 11,   /* noise-row gather, score contraction, target scores */
-  RNNLM_STAGE_NCE_GRAD = 12,    /* elementwise pass: coefficients, losses, bias-gradient column sums */
+  RNNLM_STAGE_NCE_SCORE = 11,   /* noise-row gather, score contraction (+ fused coefficients and losses), target scores */
+  RNNLM_STAGE_NCE_GRAD = 12,    /* sums over the blocks of scores: losses, bias gradients; target coefficients */
   RNNLM_STAGE_NCE_BWD_H = 13,   /* gradient w.r.t. the hidden states (contraction over the noise words + targets) */
   RNNLM_STAGE_NCE_BWD_W = 14,   /* noise-row weight gradient contraction */
   RNNLM_STAGE_NCE_UPDATE = 15,  /* sort/segments of the touched words + row and bias updates */

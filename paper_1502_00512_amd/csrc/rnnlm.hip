@@ -131,6 +131,12 @@ struct StageTimer {
     if (p && close_) (void)hipEventRecord(p->stop, st);
   }
 };
+// Stages that would share a launch take launches of their own while one of them is timed.
+bool timed(const rnnlm *h, std::initializer_list<int> stages) {
+  for (int s : stages)
+    if (h->prof_mask & (1u << s)) return true;
+  return false;
+}
 }  // namespace
 
 namespace {
@@ -633,7 +639,9 @@ const WindowPlan &window_plan(rnnlm_t *h, long Mrows) {
   return p;
 }
 // The softmax-gradient pass merges the statistics of a training window itself.
-bool merged_in_pass(const WindowPlan &p) { return p.Mp <= SHORT_POSITIONS && p.parts * p.Mp <= SHORT_STATS; }
+bool merged_in_pass(const rnnlm_t *h, const WindowPlan &p) {
+  return p.Mp <= SHORT_POSITIONS && p.parts * p.Mp <= SHORT_STATS && !timed(h, {RNNLM_STAGE_STATS, RNNLM_STAGE_SOFTMAX_GRAD});
+}
 
 template <typename P>
 P *at(rnnlm_t *h, size_t off) {
@@ -1074,7 +1082,7 @@ int forward_window(rnnlm_t *h, const int32_t *x, const int32_t *y, int Tn, float
       HIP_TRY((f32_gemm<ROWK, ROWK>(st, at<T>(h, h->L.Wo_c), h->Dp, feat, h->Dp, Vp, Mp, round_up(h->D, 32), plan, epi, 8)));
     }
   }
-  if (train && merged_in_pass(window_plan(h, Mrows))) return RNNLM_OK;
+  if (train && merged_in_pass(h, window_plan(h, Mrows))) return RNNLM_OK;
   StageTimer tm(h, RNNLM_STAGE_STATS, st);
   hipLaunchKernelGGL(merge_stats_kernel, dim3(blocks_for(Mrows, MERGE_M)), dim3(1024), 0, st, at<float2>(h, h->L.stat),
                      window_plan(h, Mrows).parts, Mp, Tn, c.B, Bp, zy, lse, at<float>(h, h->L.logp_int), logp_out,
@@ -1252,23 +1260,42 @@ int window_update_shape(rnnlm_t *h, int Mrows, const T *ZT, const T *Hs_c, const
   return e == hipSuccess ? tile : 0;
 }
 template <typename T>
-int launch_window_update(WindowUpdate<T> &w, int tile, int Mrows, int W, hipStream_t st) {
-  w.nRec = w.rec_g.perXcd * NUM_XCD;
-  w.nOut = w.out_g.perXcd * NUM_XCD;
-  const dim3 grid(w.nRec + w.nOut + w.scan.M * blocks_for(W, w.scan.blocks * RUN_COLS)), threads(tile * 4);
+int launch_window_update(rnnlm_t *h, WindowUpdate<T> &w, int tile, int Mrows, hipStream_t st) {
+  const int W = h->D;
   const bool aligned = W % 4 == 0;
-  if constexpr (sizeof(T) == 4) {
-    if (Mrows <= F32_SHORT)
+  auto launch = [&](int rec, int out, int scan) -> int {  // workgroups of each update
+    w.nRec = rec;
+    w.nOut = out;
+    const dim3 grid(rec + out + scan), threads(tile * 4);
+    if constexpr (sizeof(T) == 4) {
+      if (Mrows <= F32_SHORT)
+        hipLaunchKernelGGL((aligned ? window_update_kernel<T, 64, 0, true> : window_update_kernel<T, 64, 0, false>), grid, threads, 0, st, w);
+      else
+        hipLaunchKernelGGL((aligned ? window_update_kernel<T, 64, 1, true> : window_update_kernel<T, 64, 1, false>), grid, threads, 0, st, w);
+    } else if (tile == 64) {
       hipLaunchKernelGGL((aligned ? window_update_kernel<T, 64, 0, true> : window_update_kernel<T, 64, 0, false>), grid, threads, 0, st, w);
-    else
-      hipLaunchKernelGGL((aligned ? window_update_kernel<T, 64, 1, true> : window_update_kernel<T, 64, 1, false>), grid, threads, 0, st, w);
-  } else if (tile == 64) {
-    hipLaunchKernelGGL((aligned ? window_update_kernel<T, 64, 0, true> : window_update_kernel<T, 64, 0, false>), grid, threads, 0, st, w);
-  } else {
-    hipLaunchKernelGGL((aligned ? window_update_kernel<T, 128, 0, true> : window_update_kernel<T, 128, 0, false>), grid, threads, 0, st, w);
+    } else {
+      hipLaunchKernelGGL((aligned ? window_update_kernel<T, 128, 0, true> : window_update_kernel<T, 128, 0, false>), grid, threads, 0, st, w);
+    }
+    HIP_TRY(hipGetLastError());
+    return RNNLM_OK;
+  };
+  const int rec = w.rec_g.perXcd * NUM_XCD, out = w.out_g.perXcd * NUM_XCD;
+  const int scan = w.scan.M * (int)blocks_for(W, w.scan.blocks * RUN_COLS);
+  if (!timed(h, {RNNLM_STAGE_OUT_BWD_W, RNNLM_STAGE_REC_W, RNNLM_STAGE_EMB})) return launch(rec, out, scan);
+  int rc;
+  {
+    StageTimer tm(h, RNNLM_STAGE_EMB, st);
+    rc = launch(0, 0, scan);
   }
-  HIP_TRY(hipGetLastError());
-  return RNNLM_OK;
+  if (rc) return rc;
+  {
+    StageTimer tm(h, RNNLM_STAGE_REC_W, st);
+    rc = launch(rec, 0, 0);
+  }
+  if (rc) return rc;
+  StageTimer tm(h, RNNLM_STAGE_OUT_BWD_W, st);
+  return launch(0, out, 0);
 }
 
 // Backward half of a window + fused updates.  Everything it starts is ordered before whatever comes next on st.
@@ -1304,7 +1331,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     const WindowPlan &wp = window_plan(h, Mrows);
     const StatsMerge merge = {at<float2>(h, h->L.stat), wp.parts, Tn, c.B, Bp, at<float>(h, h->L.zy), at<float>(h, h->L.logp_int),
                               logp_out, wsum};
-    hipLaunchKernelGGL((merged_in_pass(wp) ? softmax_grad_kernel<T, true> : softmax_grad_kernel<T, false>), dim3(Vp / 16),
+    hipLaunchKernelGGL((merged_in_pass(h, wp) ? softmax_grad_kernel<T, true> : softmax_grad_kernel<T, false>), dim3(Vp / 16),
                        dim3(256), 0, st, ZT, ldz, Mp, c.V, Vp, at<float>(h, h->L.lse), yp, 1.0f / (float)(Tn * c.B), h->buf.b, u.b,
                        u.alpha, u.lr, merge);
     HIP_TRY(hipGetLastError());
@@ -1443,12 +1470,11 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
     WindowUpdate<T> w;
     const int tile = window_update_shape<T>(h, Mrows, ZT, Hs_c, dA_c, w);
     if (tile > 0) {
-      StageTimer tm(h, RNNLM_STAGE_OUT_BWD_W, st);
       aim(w.out);
       w.rec = recurrent_epilogue();
       w.scan = scan_update(dA32, h->buf.E, u.alpha, nullptr, tile / 16);
       if (rec_stream) *rec_stream = st;
-      return launch_window_update<T>(w, tile, Mrows, h->D, st);
+      return launch_window_update<T>(h, w, tile, Mrows, st);
     }
   }
   const bool serial = !nce && scan_ids(h, Tn, u) && short_output_update(h, Tn);
@@ -1629,7 +1655,7 @@ int backward_window(rnnlm_t *h, int Tn, const UpdateTargets &u, const NceCall *n
         group.epi[2] = recurrent_epilogue();
         group.first[0] = 0;
         for (int q = 0; q < GROUP_MAX; ++q) group.first[q + 1] = group.first[q] + group.g[q].perXcd * NUM_XCD;
-        rec_done = !big_rec;
+        rec_done = !big_rec && !timed(h, {RNNLM_STAGE_PROJ, RNNLM_STAGE_REC_W});
         hipLaunchKernelGGL((update_group_kernel<KROW, KROW, EpiSgdT<T>>), dim3(group.first[rec_done ? 3 : 2]), dim3(256), 0, st,
                            group);
         HIP_TRY(hipGetLastError());

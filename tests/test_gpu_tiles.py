@@ -65,6 +65,37 @@ def test_updates_in_one_launch(V, H, B, T, precision):
     assert np.array_equal(g.E.cpu().numpy()[untouched], E[untouched])
 
 
+
+@pytest.mark.parametrize("precision", [binding.RNNLM_FP32, binding.RNNLM_BF16_FP32MASTER])
+@pytest.mark.parametrize("V,H,P,B,T", [(1000, 64, 0, 4, 8), (30, 1100, 0, 5, 13), (20000, 130, 0, 3, 50), (5000, 70, 0, 40, 16),
+                                       (3000, 300, 100, 16, 9)])
+def test_timed_stages_of_short_windows(V, H, P, B, T, precision):
+    """Every stage of a window is executed once and takes time, and the window's results are those of an untimed one."""
+    rng = np.random.default_rng(V)
+    w = lambda *s: rng.uniform(-0.1, 0.1, s).astype(np.float32)
+    args, more = [w(V, P or H), w(H, H), None if P else w(V, H), w(V)], dict(A=w(H, P), C_=w(P, H)) if P else {}
+    f, g = binding.Rnnlm(*args, B, T, precision, **more), binding.Rnnlm(*args, B, T, precision, **more)
+    x, y = (torch.as_tensor(a).cuda() for a in O.stream_chunk(synth.zipf_tokens(B * T + B + 1, V, 1.05, 3), B, T, 0))
+    f.rnnlm_train_chunk(x, y, 0.5)
+    g.rnnlm_profile_enable((1 << len(binding.STAGES)) - 1)
+    g.rnnlm_train_chunk(x, y, 0.5)
+    for name in ("stats", "softmax_grad", "out_bwd_w", "rec_w", "emb"):
+        ms, executions = g.rnnlm_profile_read(binding.STAGES.index(name))
+        assert executions == 1 and ms > 0, name
+    g.rnnlm_profile_enable(0)
+    old = dict(E=args[0], U=args[1], b=args[3], **(dict(A=more["A"], C=more["C_"]) if P else dict(Wo=args[2])))
+    for name, before in old.items():
+        a, b = getattr(g, name), getattr(f, name)
+        # equal but for the order in which a very short window's statistics are added up: log-sums a few ulps of 2^-24 apart,
+        # of 10 at most, and in bf16 gradients that then round to the other side here and there (2^-9 of an entry; the
+        # weights are kept in fp32, half an ulp of values up to 0.6)
+        tol = 1e-5 if precision == binding.RNNLM_FP32 else 4e-3
+        moved = (b - torch.as_tensor(before).cuda()).abs().max().item()
+        assert (a - b).abs().max().item() <= tol * moved + 6e-8, name
+    f.rnnlm_check()
+    g.rnnlm_check()
+
+
 @pytest.mark.parametrize("precision", [binding.RNNLM_FP32, binding.RNNLM_BF16_FP32MASTER])
 @pytest.mark.parametrize("V,H,P,B,T,windows", [
     (3000, 64, 0, 4, 5, 101),     # many windows a pass, one left over

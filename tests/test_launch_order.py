@@ -190,3 +190,59 @@ def test_timing_the_widest_output_update_delays_it_behind_nothing(runtime, tmp_p
     for i in updates:
         assert own[i - 1][0] == "R" and own[i - 1][2] in forks  # the fork
         assert own[i - 2][0] == "R" and own[i + 1][0] == "R"    # the stage's pair around both
+
+
+def timed_launches(runtime, tmp_path, stage, **args):
+    """Kernels between the two events of every execution of a stage of two training calls, and all kernels."""
+    launches, _ = enqueue(runtime, tmp_path, "train", profile=1 << stage, **args)
+    lines = [l.split() for l in open(tmp_path / "log")]
+    ordering = {l[2] for l in lines if l[0] == "W"}
+    pairs, is_open = [], {}
+    for op, stream, what, *_ in lines:
+        if op == "L":
+            for inside in is_open.values():
+                inside.append(what)
+        elif op == "R" and what not in ordering:
+            if stream in is_open:
+                pairs.append(is_open.pop(stream))
+            else:
+                is_open[stream] = []
+    assert not is_open
+    return pairs, [k for _, k, _ in launches]
+
+
+STATS, SOFTMAX_GRAD, OUT_BWD_W, REC_W, EMB, PROJ = 3, 4, 7, 8, 9, 17
+
+
+@pytest.mark.parametrize("V,H,B,T,precision", [(1000, 64, 4, 8, FP32), (5000, 70, 8, 9, FP32), (1000, 65, 5, 13, BF16),
+                                               (20000, 130, 3, 50, BF16), (3000, 300, 60, 16, BF16)])
+@pytest.mark.parametrize("stage", [OUT_BWD_W, REC_W, EMB])
+def test_a_timed_update_of_a_short_window_is_a_launch_of_its_own(runtime, tmp_path, stage, V, H, B, T, precision):
+    pairs, kernels = timed_launches(runtime, tmp_path, stage, V=V, H=H, B=B, T_max=T, T=T, precision=precision)
+    assert [["window_update" in k for k in pair] for pair in pairs] == [[True], [True]]
+    assert sum("window_update" in k for k in kernels) == 6  # three updates, two calls
+    untimed, _ = enqueue(runtime, tmp_path, "train", V=V, H=H, B=B, T_max=T, T=T, precision=precision)
+    assert sum("window_update" in k for _, k, _ in untimed) == 2
+
+
+@pytest.mark.parametrize("precision", [FP32, BF16])
+@pytest.mark.parametrize("stage,kernel", [(STATS, "merge_stats"), (SOFTMAX_GRAD, "softmax_grad")])
+def test_timed_statistics_of_a_very_short_window_are_a_launch_of_their_own(runtime, tmp_path, precision, stage, kernel):
+    args = dict(V=1000, H=64, B=4, T_max=8, T=8, precision=precision)
+    pairs, kernels = timed_launches(runtime, tmp_path, stage, **args)
+    assert [[kernel in k for k in pair] for pair in pairs] == [[True], [True]]
+    assert sum("merge_stats" in k for k in kernels) == 2
+    untimed, _ = enqueue(runtime, tmp_path, "train", **args)
+    assert not any("merge_stats" in k for _, k, _ in untimed)
+
+
+@pytest.mark.parametrize("stage", [REC_W, PROJ])
+def test_a_timed_recurrent_update_of_the_compressed_architecture_is_a_launch_of_its_own(runtime, tmp_path, stage):
+    args = dict(V=3000, H=300, P=100, B=16, T_max=9, T=9, precision=BF16)
+    pairs, kernels = timed_launches(runtime, tmp_path, stage, **args)
+    recurrent = [k for k in kernels if "gemm" in k and "EpiSgdT" in k]
+    assert len(recurrent) == 2 and sum("update_group" in k for k in kernels) == 2
+    inside = [k for pair in pairs for k in pair]
+    assert (inside == recurrent) if stage == REC_W else not set(inside) & set(recurrent)
+    untimed, _ = enqueue(runtime, tmp_path, "train", **args)
+    assert not any("gemm" in k and "EpiSgdT" in k for _, k, _ in untimed)
