@@ -42,6 +42,7 @@ __global__ void __launch_bounds__(512) rnn_step_kernel(const RnnStepArgs a) {
   constexpr int DEPTH = RT == 1 ? 4 : RT == 2 ? 3 : 2;   // pieces of a wave in flight (what the LDS holds)
   constexpr int PIECE = 2048, SLOT = (1 + RT) * PIECE;   // 16 rows x 128 bytes; matrix, then RT row blocks of states
   constexpr int LOADS = 2 * (1 + RT);                    // a piece is two kilobyte loads
+  static_assert(DEPTH >= 2 && DEPTH <= 4 && (DEPTH - 1) * LOADS <= 63, "the counted waits below");  // 12, 12 and 10 loads
   static_assert(NWAVE * RT * 1024 <= NWAVE * DEPTH * SLOT, "the partial tiles reuse the ring");
   __shared__ __attribute__((aligned(1024))) char lds[NWAVE * DEPTH * SLOT];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -118,8 +119,10 @@ __global__ void __launch_bounds__(512) rnn_step_kernel(const RnnStepArgs a) {
       const int behind = min(n - 1 - p, DEPTH - 1);
       if (behind == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       else if (behind == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
-      else if (behind == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LOADS) : "memory");
-      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * LOADS) : "memory");  // (24 at most, where DEPTH is 4)
+      else if constexpr (DEPTH > 2) {
+        if (behind == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LOADS) : "memory");
+        else if constexpr (DEPTH > 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * LOADS) : "memory");
+      }
       const char *const at = ring + slot * SLOT;
       const int g = lane >> 4;
       u32x4_t w[2], f[RT][2];
