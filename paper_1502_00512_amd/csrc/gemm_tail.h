@@ -2,9 +2,10 @@
 //
 // One persistent workgroup per compute unit walks the large tiles, and a last round that only some compute units have a tile
 // for takes nearly as long as a full one.  So the large tiles take as many rows of the output as fill whole rounds, and the
-// same workgroups then share out the remaining rows in tiles of a quarter the size.  us a window, before and after: V =
-// 33278, H = 650, 100x9 (520 tiles are 2.03 rounds) 330 and 324; V = 100000, H = 2048, 128x20 (15.3) 3137 and 3084; V = 40000,
-// H = 500, 120x18 (5.5) 530 and 522; eight evaluated windows of V = 64000, H = 1024, 64x20 (39.06) 1430 and 1391.
+// same workgroups then share out the remaining rows in tiles of a quarter the size.  us a window, all rows on large tiles and
+// this: V = 33278, H = 650, 100x9 (520 tiles are 2.03 rounds) 331 and 327; V = 100000, H = 2048, 128x20 (15.3) 3146 and 3130,
+// hardly more than two runs differ; V = 40000, H = 500, 120x18 (5.5) 507 and 507; eight evaluated windows of V = 64000, H =
+// 1024, 64x20 (39.06) 1333 and 1293.
 // (The output update's rest on small tiles: V = 33278, H = 650, 1.5 rounds, 331 and 348; V = 30000, H = 1500, 2.8 rounds, 618 and
 // 628; nowhere more than a hundredth faster: its epilogue's memory traffic is what a full round waits for.)
 #pragma once

@@ -26,9 +26,9 @@ __device__ inline float logisticf_(float d) {
 
 // Both at once, as the elementwise pass over all scores wants them: the exponent's rounding error taken along, divisions by
 // the hardware reciprocal and a correction by the remainder, ln(1 + e) = 2 artanh(e / (2 + e)) by the series in the
-// argument's square (to t^4; coefficients through the Chebyshev nodes of [0, 1/9], 4e-9 relative).  Some 30 instructions
+// argument's square (to t^4; coefficients through the Chebyshev nodes of [0, 1/9], 8e-9 relative).  Some 30 instructions
 // instead of 80, which bound the pass (2560 positions, 1024 noise words, 160 workgroups: contraction and pass 28 us, without
-// the pass 12; window 224 and 213, with the target words' share formed in the next contraction).  Relative error against 64
+// the pass 12; window with rmsprop 224 and 214, with the target words' share formed in the next contraction).  Relative error against 64
 // bits, root mean square over scores of -30..30, with the exponential and the reciprocal an ulp off at random, before and now:
 // logistic 2.3e-7 and 0.6e-7, softplus 2.3e-7 and 0.6e-7.
 __device__ inline void noise_terms(float d, float &logistic, float &softplus) {
@@ -166,14 +166,6 @@ __global__ void __launch_bounds__(256) score_candidates_kernel(const T *__restri
   if (lane == 0) out[item] = acc + b[w] - shift;
 }
 
-// Epilogue of the score contraction S = Hs . Wn^T (rows: padded positions, columns: noise slots), elementwise while the
-// scores are in registers: dS[row][j] = sigmoid(S + off[j]) * scale in the contraction operand type (0 for padding rows and
-// columns), and, per 32x32 block, the sums of softplus(S + off[j]) over its columns (jpart[column block][row]) and of dS
-// before rounding over its rows (gpart[row block][j]).  V = 64000, H = 1024, 2560 positions, 1024 noise words: the
-// contraction, a pass over its fp32 scores and one more for the column sums took 17 + 15 + 7 us.  Whole windows with those
-// passes and with this, every tile form (bf16 us): V = 64000, H = 1024, 16x4, 64 words 124 and 116; 128x20, 256 words 170 and
-// 162, 1024 words 193 and 182; 256x32, 2048 words 527 and 459; V = 10000, H = 300, 256x32, 2000 words 362 and 327; V = 20000,
-// H = 2048, 32x20, 500 words 228 and 231; fp32: 394 and 400 at 128x20, 1024 words, 1312 and 1277 at 256x32, 2048 words.
 // The value of lane ^ MASK (inside a half-wave), without an address register.
 template <int MASK>
 __device__ inline int swap_lanes(int v) {
@@ -186,6 +178,15 @@ __device__ inline int swap_lanes(int v) {
   return v;
 #endif
 }
+
+// Epilogue of the score contraction S = Hs . Wn^T (rows: padded positions, columns: noise slots), elementwise while the
+// scores are in registers: dS[row][j] = sigmoid(S + off[j]) * scale in the contraction operand type (0 for padding rows and
+// columns), and, per 32x32 block, the sums of softplus(S + off[j]) over its columns (jpart[column block][row]) and of dS
+// before rounding over its rows (gpart[row block][j]).  V = 64000, H = 1024, 2560 positions, 1024 noise words: the
+// contraction, a pass over its fp32 scores and one more for the column sums took 17 + 15 + 7 us.  Whole windows with those
+// passes and with this, every tile form (bf16 us): V = 64000, H = 1024, 16x4, 64 words 124 and 116; 128x20, 256 words 170 and
+// 162, 1024 words 193 and 182; 256x32, 2048 words 527 and 459; V = 10000, H = 300, 256x32, 2000 words 362 and 327; V = 20000,
+// H = 2048, 32x20, 500 words 228 and 231; fp32: 394 and 400 at 128x20, 1024 words, 1312 and 1277 at 256x32, 2048 words.
 template <typename T>
 struct EpiNce : EpiZeroInit {
   T *dS;

@@ -195,7 +195,7 @@ F32Plan f32_plan(long Mg, long Ng, long K, int max_splits, long ld = 0) {
   return best;
 }
 // fp32: an extent of `valid` rows or columns, padded to 64, 128 or 256 by what the product with the other extent takes
-// (the buffers are padded to 256; bf16 contractions take all of it).
+// (the buffers are padded to 256).
 long f32_extent(long valid, long other, long K, int max_splits, long ld = 0) {
   long best = round_up(valid, 256);
   double us = f32_plan(other, best, K, max_splits, ld).us;
@@ -244,6 +244,8 @@ hipError_t f32_gemm(hipStream_t st, const void *A, long lda, const void *B, long
 //   117 / 127 / 184;
 //   output update 4096 x 256: 31.4 / 11.1 / 7.7; 10240 x 512: 34.3 / 22.8 / 24.3; 10240 x 1024: 38.8 / 36.2 / 44; 32768 x 1024:
 //   102 / 104 / 139.
+// Windows whose operands are not in the caches take longer than a hot run (V = 33278, H = 650, 900 positions: the output layer,
+// put at 62, takes 78).
 // 128x128 on four waves is slower nearly everywhere (output layer 10240 x 1024: 22.3, on eight 19.5), waves that share out
 // the contraction gain 10-15 % only where 64x64 tiles are few and deep.
 enum Bf16Kind { OUT_FWD, OUT_UPDATE, PLAIN_SUM };  // by epilogue: statistics and logits, weight update, fp32 store
